@@ -13,7 +13,6 @@
 
 #include "../../include/dpllm.h"
 #include "aux_kernels.hpp"
-#include "gemv_kernels.hpp"
 #include "gemv_lane.hpp"
 #include "layout.hpp"
 #include "selector_kernels.hpp"
@@ -66,11 +65,6 @@ struct Linear {
   int part_k() const {   // the bitwidth the work of a step launch is cut for: the larger one of the pair of target 0
     return active >= 0 ? sel[active].h : L.p;
   }
-  bool streaming() const {   // every bitwidth its selectors can ask for has a decode scheme in the streaming kernel
-    for (const Pair& s : sel)
-      if (s.set && (s.l < kFastKMin || s.h > kFastKMax)) return false;
-    return true;
-  }
 };
 
 // A decode step is cut into phases: maximal runs of consecutive linears none of which reads or overwrites
@@ -84,12 +78,10 @@ struct Phase {
   int gemv_first = 0, gemv_count = 0;   // slice of the device GEMV job table (streaming kernel, one launch)
   int blocks = 0;                       // workgroups of that launch
   int block_first = 0;                  // slice of the device workgroup-to-job table
-  std::vector<int> plain;               // linears served by the plain kernel, one launch each
   bool estimators = true;               // under some target a job of the selector launch has an estimator (else the launch is skipped)
-  bool decide = false;                  // a linear of the selector launch is served by the plain kernel, which reads its
-                                        // bitwidth from k_dev: the decisions of this launch are taken by a launch of their own
+  int groups = 1;                       // column groups per wavefront of that launch (see gemv_narrow)
 };
-constexpr int kLanePoolRows = 8192;     // row blocks x splits of the column-split launches that may be in flight
+constexpr int kMaxGroups = 8;           // column groups per wavefront, at most
 constexpr size_t kSelOneSlots = (size_t)kSelMaxChunks * kSelMaxRank;
 
 struct StepPlan {
@@ -106,7 +98,6 @@ struct StepPlan {
 struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
-  size_t lane_ws = 0, lane_cnt = 0;          // column-split pool: kLanePoolRows x 64 fp32, kLanePoolRows counters
   size_t est_ws = 0;                         // dpllm_estimate: kSelOneSlots fp64
   size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
@@ -188,12 +179,10 @@ Workspace carve_workspace(const dpllm_model* m) {
     const size_t rg = (size_t)std::max(1, lin.max_rowgroups());
     parts += rg * kSelMaxChunks + 1;
     slots += rg * kSelPartRows * kSelMaxChunks;
-    blocks += (size_t)lin.L.nrq * 8;
+    blocks += (size_t)lin.L.nrq * kMaxGroups;
   }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
-  w.lane_ws = take(sizeof(float) * 64 * kLanePoolRows);
-  w.lane_cnt = take(sizeof(uint32_t) * kLanePoolRows);
   w.est_ws = take(sizeof(double) * kSelOneSlots);
   w.target = take(sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
@@ -257,17 +246,14 @@ GemvJob make_gemv_job(const Linear& lin, int k, const int32_t* k_dev, const void
   j.has_fin = 0;
   j.fin = SelFinish{};
   j.plane_stride_u4 = (uint32_t)(lin.L.plane_bytes / 16);
-  for (int kk = kFastKMin; kk <= kFastKMax; ++kk)
-    j.lut_off[kk - kFastKMin] = (kk >= lin.L.kmin && kk <= lin.L.p) ? (uint32_t)lin.L.lut_offset[kk] : 0u;
+  for (int kk = 1; kk <= kKMax; ++kk)
+    j.lut_off[kk - 1] = (kk >= lin.L.kmin && kk <= lin.L.p) ? (uint32_t)lin.L.lut_offset[kk] : 0u;
   j.k = k;
   j.kmin = lin.L.kmin; j.p = lin.L.p;
   j.out = lin.L.out; j.ncw = lin.L.ncw; j.nrq = lin.L.nrq; j.ncc = lin.L.ncc;
   j.nblocks = lin.L.nrq;
   j.block_start = 0;
   j.nsamples = 1;
-  j.nsplit = 1;
-  j.ws = nullptr;
-  j.cnt = nullptr;
   return j;
 }
 
@@ -280,7 +266,6 @@ constexpr long kLaneGroupBytes = 1048576;
 // GEMV launches below this many workgroups take their selectors' decisions themselves; larger ones get a launch
 // of its own for the decisions (measured on a 7B step of 3094 workgroups: 509 against 514 us)
 constexpr int kFoldMaxBlocks = 1536;
-constexpr int kLaneSplitBlocks = 256;   // a launch that splits columns aims at one workgroup per compute unit
 int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long group_bytes = kLaneGroupBytes) {
   const long bytes_per_block = 64L * L.in * k / 8;
   long r = std::min<long>(16, std::max<long>(1, group_bytes / std::max<long>(1, bytes_per_block)));
@@ -288,70 +273,50 @@ int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long 
   return (int)r;
 }
 
-// Launches with fewer workgroups than compute units (a workgroup is tied to 64 rows): the workgroups that share
-// a block of rows.  Measured on 4096 .. 28672 rows x 4096 .. 14336 columns: splitting pays only below about one
-// workgroup per compute unit (64 blocks of rows: 23 -> 12 us at 14336 columns) and costs above it (172 blocks:
-// 9 -> 12 us), since every split builds the tables again and runs fewer tiles per wavefront.
-// workgroups = those of the whole launch before splitting; rows = blocks of rows x samples per pass x groups of
-// the job; pool = what is left of the partial-sum pool.
-int pick_lane_split(const LinearLayout& L, long workgroups, long rows, long pool) {
-  long s = std::min<long>(8, kLaneSplitBlocks / std::max<long>(1, workgroups));
-  s = std::min<long>(s, L.ncc / kLaneWaves);   // at least one tile per wavefront
-  while (s > 1 && rows * s > pool) --s;
-  return (int)std::max<long>(1, s);
+// Column groups per wavefront (rows per workgroup = 64 / groups) of a launch whose linears have `blocks64` blocks of 64
+// rows in all (times the passes of a batch), the shortest row ncc column tiles: the most that leave at most one
+// workgroup per compute unit.  Measured, us per launch in a graph, one linear at k = 4 with 1 / 2 / 4 / 8 groups: 4096 x
+// 4096 8.5 / 6.7 / 5.5 / 8.4, 4096 x 11008 18.0 / 12.0 / 9.2 / 12.7, 8192 x 8192 14.8 / 11.3 / 14.2 / 18.5, 11008 x 4096
+// 9.7 / 12.3 / 12.5 / 21.2, 192 x 28672 38.0 / 20.1 / 12.3 / 9.8.  Eight groups only where every wavefront gets a step
+// (1024 x 4096: 3.9 us with four, 4.1 with eight), and not for a batch (registers).
+int pick_groups(long blocks64, int ncc, int nb) {
+  int g = 1;
+  while (g < 4 && blocks64 * g * 2 <= 256) g *= 2;
+  if (g == 4 && nb == 1 && blocks64 * 8 <= 256 && ncc >= 8 * kLaneWaves) g = 8;
+  return g;
 }
 
-template <int B>
-void launch_plain_t(const GemvArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL(gemv_plain_kernel<B>, dim3((a.out + 15) / 16), dim3(256), 0, st, a);
-}
-
-int launch_plain(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
-  GemvArgs a;
-  a.arena = lin.arena;
-  a.plane_bytes = lin.L.plane_bytes;
-  for (int kk = 0; kk <= 8; ++kk) a.lut_off[kk] = (kk >= lin.L.kmin && kk <= lin.L.p) ? (uint32_t)lin.L.lut_offset[kk] : 0u;
-  a.k = k;
-  a.k_dev = k_dev;
-  a.kmin = lin.L.kmin; a.p = lin.L.p;
-  a.x = (const uint16_t*)x;
-  a.y = (uint16_t*)y;
-  a.out = lin.L.out; a.in = lin.L.in; a.ncw = lin.L.ncw; a.ncc = lin.L.ncc;
-  switch (B) {
-    case 1: launch_plain_t<1>(a, st); break;
-    case 2: launch_plain_t<2>(a, st); break;
-    case 3: launch_plain_t<3>(a, st); break;
-    case 4: launch_plain_t<4>(a, st); break;
-    case 5: launch_plain_t<5>(a, st); break;
-    case 6: launch_plain_t<6>(a, st); break;
-    case 7: launch_plain_t<7>(a, st); break;
-    case 8: launch_plain_t<8>(a, st); break;
-    default: return fail(m, DPLLM_ESHAPE, "batch %d outside [1, %d]", B, DPLLM_MAX_BATCH);
+void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const GemvJob* jobs, const int32_t* block_jobs, int njobs,
+                 const GemvJob& one, const SelParams* params, const int32_t* target, int n) {
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, jobs, block_jobs, njobs, one, params, target, n); };
+  if (nb == 1) {
+    switch (groups) {
+      case 1: go(gemv_lane_kernel<1, 1>); break;
+      case 2: go(gemv_lane_kernel<1, 2>); break;
+      case 4: go(gemv_lane_kernel<1, 4>); break;
+      default: go(gemv_lane_kernel<1, 8>); break;
+    }
+  } else {
+    switch (groups) {
+      case 1: go(gemv_lane_kernel<4, 1>); break;
+      case 2: go(gemv_lane_kernel<4, 2>); break;
+      default: go(gemv_lane_kernel<4, 4>); break;
+    }
   }
-  HIP_TRY(m, hipGetLastError());
-  return DPLLM_OK;
 }
 
 // one linear, B right-hand sides: a batch runs in groups of four samples that share one pass over the planes
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
-  const bool streaming = k_dev ? lin.L.kmin >= kFastKMin : (k >= kFastKMin && k <= kFastKMax);
-  if (!streaming) return launch_plain(m, lin, k, k_dev, x, y, B, st);
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
-  const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
-  j.nblocks = (lin.L.nrq + rpb - 1) / rpb;
-  const long groups = B > 1 ? (B + 3) / 4 : 1, per_pass = B > 1 ? 4 : 1;
-  if (m->ws.base) {   // without a workspace there is no pool for partial sums: no column split
-    j.nsplit = pick_lane_split(lin.L, j.nblocks * groups, (long)lin.L.nrq * per_pass * groups, kLanePoolRows);
-    j.nblocks *= j.nsplit;
-    j.ws = m->ws.at<float>(m->ws.lane_ws);
-    j.cnt = m->ws.at<uint32_t>(m->ws.lane_cnt);
+  const int passes = B > 1 ? (B + 3) / 4 : 1;
+  const int groups = pick_groups((long)lin.L.nrq * passes, lin.L.ncc, B > 1 ? 4 : 1);
+  if (groups > 1) {
+    j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
+  } else {
+    const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
+    j.nblocks = (lin.L.nrq + rpb - 1) / rpb;
   }
-  if (B > 1)
-    hipLaunchKernelGGL((gemv_lane_kernel<4>), dim3(j.nblocks * (unsigned)groups), dim3(kLaneThreads), 0, st, (const GemvJob*)nullptr,
-                       (const int32_t*)nullptr, B, j, (const SelParams*)nullptr, (const int32_t*)nullptr, 0);
-  else
-    hipLaunchKernelGGL((gemv_lane_kernel<1>), dim3(j.nblocks), dim3(kLaneThreads), 0, st, (const GemvJob*)nullptr,
-                       (const int32_t*)nullptr, 1, j, (const SelParams*)nullptr, (const int32_t*)nullptr, 0);
+  launch_lane(groups, B > 1 ? 4 : 1, (unsigned)(j.nblocks * passes), st, nullptr, nullptr, B, j, nullptr, nullptr, 0);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }
@@ -463,7 +428,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
   }
   std::vector<int> sel_job_of(n, -1);   // index of every linear's selector job (it sits in its own phase or an earlier one)
   for (size_t pi = 0; pi < bounds.size(); ++pi) {
-    long pool_used = 0;   // phases follow one another on the stream: each may use the whole partial-sum pool
     const int id = bounds[pi].first, end = bounds[pi].second;
     Phase ph;
     ph.sel_first = (int)sel_jobs.size();
@@ -480,7 +444,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
       sj.ws = W.at<double>(W.sel_ws) + ws_slots;
       ws_slots += (size_t)sj.ws_rows * sj.nchunks;
       sel_job_of[j] = (int)sel_jobs.size();
-      if (!lin.streaming()) ph.decide = true;
       sel_jobs.push_back(sj);
     }
     // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
@@ -503,8 +466,10 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     ph.gemv_first = (int)gemv_jobs.size();
     ph.block_first = (int)block_jobs.size();
     long total_rq = 0, lane_groups = 0;
-    for (int j = id; j < end; ++j)
-      if (m->linears[j].streaming()) total_rq += m->linears[j].L.nrq;
+    for (int j = id; j < end; ++j) total_rq += m->linears[j].L.nrq;
+    int min_ncc = m->linears[id].L.ncc;
+    for (int j = id; j < end; ++j) min_ncc = std::min(min_ncc, m->linears[j].L.ncc);
+    ph.groups = pick_groups(total_rq, min_ncc, 1);
     // The chip runs 512 workgroups at a time.  A launch of a few such rounds loses the unfilled part of its last
     // round (2.7 rounds cost 3): the work per workgroup is scaled, between half and one and a half times the
     // usual megabyte, to the value with the smallest estimate of rounds x (start-up + work of a workgroup).
@@ -516,7 +481,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         long groups = 0;
         for (int j = id; j < end; ++j) {
           const Linear& lin = m->linears[j];
-          if (!lin.streaming()) continue;
           const int rpb = pick_blocks_per_group(lin.L, lin.part_k(), total_rq, gb);
           groups += (lin.L.nrq + rpb - 1) / rpb;
         }
@@ -530,7 +494,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
       long acc = 0;
       for (int j = end - 1; j >= id; --j) {
         const Linear& lin = m->linears[j];
-        if (!lin.streaming()) continue;
         bytes_after[j - id] = acc;
         acc += (long)lin.L.nrq * 64 * lin.L.in * lin.part_k() / 8;
       }
@@ -542,21 +505,13 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     int blocks = 0;
     for (int j = id; j < end; ++j) {
       const Linear& lin = m->linears[j];
-      if (!lin.streaming()) { ph.plain.push_back(j); continue; }
       GemvJob gj = make_gemv_job(lin, 0, k_dev + j, xs[j], ys[j]);
       gj.has_fin = 1;
       gj.fin = sel_finish_of(sel_jobs[sel_job_of[j]]);
       long group_bytes = base_bytes;
       if (taper && bytes_after[j - id] < 512 * base_bytes) group_bytes /= 2;
       const int rpb = pick_blocks_per_group(lin.L, lin.part_k(), total_rq, group_bytes);
-      gj.nblocks = (lin.L.nrq + rpb - 1) / rpb;
-      gj.nsplit = pick_lane_split(lin.L, lane_groups, lin.L.nrq, kLanePoolRows - pool_used);
-      if (gj.nsplit > 1) {
-        gj.nblocks *= gj.nsplit;
-        gj.ws = W.at<float>(W.lane_ws) + pool_used * 64;
-        gj.cnt = W.at<uint32_t>(W.lane_cnt) + pool_used;
-        pool_used += (long)lin.L.nrq * gj.nsplit;
-      }
+      gj.nblocks = ph.groups > 1 ? (lin.L.out + 64 / ph.groups - 1) / (64 / ph.groups) : (lin.L.nrq + rpb - 1) / rpb;
       gj.block_start = blocks;
       blocks += gj.nblocks;
       block_jobs.insert(block_jobs.end(), gj.nblocks, (int32_t)(gemv_jobs.size() - ph.gemv_first));
@@ -666,10 +621,8 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   w.base = (char*)ws_dev;
   w.bytes = bytes;
   hipStream_t st = (hipStream_t)stream;
-  // counters and the target word start at zero; everything else is written before it is read
-  struct { size_t off, words; } zero[] = {{w.lane_cnt, (size_t)kLanePoolRows}, {w.target, 1}};
-  for (const auto& z : zero)
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, 0u);
+  // the target word starts at zero; everything else is written before it is read
+  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, w.at<uint32_t>(w.target), (size_t)1, 0u);
   HIP_TRY(m, hipGetLastError());
   m->ws = w;
   m->params_dirty = true;
@@ -942,7 +895,7 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   const int32_t* d_target = W.at<int32_t>(W.target);
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
   for (const Phase& ph : P.phases) {
-    const bool fold = both && !ph.decide && ph.blocks < kFoldMaxBlocks;
+    const bool fold = both && ph.blocks < kFoldMaxBlocks;
     if ((parts & DPLLM_STEP_SELECT) && ph.sel_count > 0) {
       const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
       if (ph.estimators)
@@ -950,21 +903,14 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
                            (const SelPart*)(W.at<SelPart>(W.sel_parts) + ph.part_first),
                            (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), d_params, d_target, n, none, pnone);
       // Whole step: the GEMV workgroups take the decisions of their linears themselves (one launch fewer per
-      // dependency level).  Selectors alone, a linear on the plain kernel, or a GEMV launch of so many workgroups
-      // that repeating the decision in each of them costs more than a launch: a launch that finishes every job of
+      // dependency level).  Selectors alone, or a GEMV launch of so many workgroups that repeating the decision in each of them costs more than a launch: a launch that finishes every job of
       // this selector launch.
       if (!fold)
         hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, d_params, d_target, n, none, pnone);
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
-    if (ph.gemv_count > 0)
-      hipLaunchKernelGGL((gemv_lane_kernel<1>), dim3(ph.blocks), dim3(kLaneThreads), 0, st,
-                         (const GemvJob*)(W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first), (const int32_t*)(W.at<int32_t>(W.block_jobs) + ph.block_first),
-                         ph.gemv_count, gnone, fold ? d_params : (const SelParams*)nullptr, d_target, n);
-    for (int j : ph.plain) {
-      int rc = launch_plain(m, m->linears[j], 0, k_dev + j, xs[j], ys[j], 1, st);
-      if (rc != DPLLM_OK) return rc;
-    }
+    launch_lane(ph.groups, 1, (unsigned)ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
+                ph.gemv_count, gnone, fold ? d_params : nullptr, d_target, n);
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;

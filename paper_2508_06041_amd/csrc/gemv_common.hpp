@@ -25,7 +25,7 @@ typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
-constexpr int kFastKMin = 3, kFastKMax = 8;   // bitwidths the streaming kernel serves; others take the plain kernel
+constexpr int kKMax = 8;   // bitwidths 1 .. 8
 
 struct GemvJob {
   const char* arena;          // device planes start here; plane b at + b * plane_stride_u4 * 16 bytes
@@ -38,20 +38,14 @@ struct GemvJob {
   int32_t has_fin;
   SelFinish fin;
   uint32_t plane_stride_u4;
-  uint32_t lut_off[kFastKMax - kFastKMin + 1];  // byte offset of the k-bit table inside the arena, k = 3..8
+  uint32_t lut_off[kKMax];    // [k - 1]: byte offset of the k-bit table inside the arena, k = kmin..p
   int32_t k;                  // the bitwidth when k_dev == nullptr
   int32_t kmin, p;            // bitwidths the linear serves: a value read from k_dev outside them is not served
   int32_t out, ncw;           // rows; 32-column words per row
   int32_t nrq, ncc;           // blocks of 64 rows; 128-column tiles per row
-  int32_t nblocks;            // workgroups of this job; workgroup b streams row blocks b / nsplit, + nblocks / nsplit, ...
+  int32_t nblocks;            // workgroups of this job; workgroup b serves row blocks b, b + nblocks, ...
   int32_t block_start;        // index of this job's first workgroup inside a multi-job grid
   int32_t nsamples;           // right-hand sides served together (1..NB): sample s reads x + s * in, writes y + s * out
-  // column split: nsplit workgroups share every block of rows, each taking 1 / nsplit of its column tiles
-  // (nblocks counts all of them).  Their fp32 partial sums meet in ws ([row block][sample][split][64 rows]);
-  // cnt ([row block][sample], zero between launches) tells the last one to arrive, which adds them up.
-  int32_t nsplit;
-  float* ws;
-  uint32_t* cnt;
 };
 
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }

@@ -26,13 +26,15 @@
 // Each lane accumulates its own row: no cross-lane reduction.  A workgroup is eight wavefronts that split the
 // columns of the same 64 rows and share the tables; their eight partial sums per row meet in LDS.
 //
-//   k = 3, 4 : two weights per lookup, tables of 64 / 256 fp16 pairs per row (16 / 64 KiB per workgroup)
+//   k <= 4   : two weights per lookup, tables of 64 / 256 fp16 pairs per row (16 / 64 KiB per workgroup); k = 1, 2 are
+//              k = 3 without the planes that are not read
 //   k >= 5   : one weight per lookup (table of 2^k entries per row, 8 .. 64 KiB), two results packed into one
 //              register of the B operand
-// One kernel serves every bitwidth from 3 to 8: a workgroup reads the bitwidth of its job (a value, or the word a
-// selector wrote in device memory) and branches to the code of that bitwidth.  Every branch stays below 128 vector
-// registers and the workgroup's LDS is sized for the largest tables (64 KiB), so two workgroups share a compute
-// unit whatever the bitwidth; which bitwidth runs is never a matter for the host.
+// One kernel serves every bitwidth from 1 to 8: a workgroup reads the bitwidth of its job (a value, or the word a
+// selector wrote in device memory) and branches to the code of that bitwidth.  Every branch of the kernel for large
+// launches (G = 1) stays below 128 vector registers and the workgroup's LDS is sized for the largest tables (64 KiB), so
+// two workgroups share a compute unit whatever the bitwidth; which bitwidth runs is never a matter for the host.
+// Small launches give a workgroup 64 / G rows, G = 2, 4, 8 (gemv_narrow).
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -50,9 +52,12 @@ constexpr int kLaneThreads = 64 * kLaneWaves;
 template <int K>
 struct LaneDecode {
   static constexpr bool pair = K <= 4;                        // two weights per lookup
-  static constexpr int entries = pair ? (1 << (2 * K)) : (1 << K);
-  static constexpr int table_bytes = entries * 256;           // 64 rows interleaved, 4 bytes per row and entry
+  static constexpr int entries = K <= 3 ? 64 : K == 4 ? 256 : (1 << K);
+  static constexpr int table_bytes = entries * 256;           // 64 lanes interleaved, 4 bytes per lane and entry
   static constexpr int share = entries / kLaneWaves;          // entries a wavefront builds per row block
+  // k <= 3: the bits of an entry number that carry a code; the byte of a merged word holds [a2 a1 a0 b2 b1 b0 . .]
+  // above two bits of other weights, and with k < 3 planes the low bits of a and b are not there
+  static constexpr uint32_t pair_mask = K == 3 ? 0x3fu : K == 2 ? 0x36u : 0x24u;
   // single-weight schemes: the byte of column `col` is its code; which of the eight merged words, which byte
   static constexpr int d = 8 - K;
   __host__ __device__ static constexpr int top(int col) { return (col_to_pos(col) + d) & 31; }
@@ -63,21 +68,25 @@ struct LaneDecode {
 constexpr int kLaneRedBytes = kLaneWaves * 64 * 4;            // the partial sums of the eight wavefronts, per sample
 constexpr int kLaneKeepTiles = 4;                             // a wavefront with so few tiles per row block keeps their activations in LDS
 constexpr int kLaneTableBytes = 65536;                        // the largest tables: k = 4 (pairs) and k = 8
-static_assert(LaneDecode<3>::table_bytes <= kLaneTableBytes && LaneDecode<4>::table_bytes <= kLaneTableBytes &&
+static_assert(LaneDecode<2>::table_bytes <= kLaneTableBytes && LaneDecode<3>::table_bytes <= kLaneTableBytes && LaneDecode<4>::table_bytes <= kLaneTableBytes &&
               LaneDecode<5>::table_bytes <= kLaneTableBytes && LaneDecode<6>::table_bytes <= kLaneTableBytes &&
               LaneDecode<7>::table_bytes <= kLaneTableBytes && LaneDecode<8>::table_bytes <= kLaneTableBytes, "tables fit");
-// NB right-hand sides per pass (1 or 4).  Per wavefront: a 256-byte slot for the parked activations of a tile per
-// sample; with one sample, four more for the tiles it keeps across row blocks.
-template <int NB>
-__host__ __device__ constexpr int lane_x_bytes() { return NB == 1 ? 256 + kLaneKeepTiles * 256 : NB * 256; }
-// tables, partial sums, activation slots.  Two things borrow space from the partial sums while these are not in
-// use (between the barrier that opens a row block and the stores that close it): the 256 bytes a wavefront needs
-// to re-pair the activations at k = 4 (its own partial sums of sample 0), and the word of the column-split
-// hand-over (the first word; written after every reader of the partial sums has passed a barrier).  With four
-// samples the total is exactly half of a compute unit's LDS.
-template <int NB>
-__host__ __device__ constexpr int lane_lds_bytes() { return kLaneTableBytes + NB * kLaneRedBytes + kLaneWaves * lane_x_bytes<NB>(); }
-static_assert(lane_lds_bytes<4>() <= 81920 && lane_lds_bytes<1>() <= 81920, "two workgroups per compute unit");
+// G column groups per wavefront (see below); bytes from one group's parked activations to the next: 64 more than a
+// tile's 256, so that the groups' reads of the same word fall on different banks
+constexpr int kLaneGroupStride = 320;
+// NB right-hand sides per pass (1 or 4).  Per wavefront: a slot for the parked activations of its tiles (G of them)
+// per sample; with one sample and one group, four more for the tiles it keeps across row blocks.
+template <int NB, int G>
+__host__ __device__ constexpr int lane_x_bytes() {
+  return G > 1 ? NB * G * kLaneGroupStride : NB == 1 ? 256 + kLaneKeepTiles * 256 : NB * 256;
+}
+// tables, partial sums, activation slots.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
+// activations are borrowed from the partial sums, which are not in use between the barrier that opens a row block
+// and the stores that close it (its own partial sums of sample 0).
+template <int NB, int G>
+__host__ __device__ constexpr int lane_lds_bytes() { return kLaneTableBytes + NB * kLaneRedBytes + kLaneWaves * lane_x_bytes<NB, G>(); }
+static_assert(lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920 && lane_lds_bytes<1, 2>() <= 81920 &&
+              lane_lds_bytes<1, 4>() <= 81920, "two workgroups per compute unit");
 
 // x pair held by lane Q of the quad, times the looked-up pair, added to acc
 template <int Q>
@@ -93,12 +102,14 @@ typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 // acc[i] += sum_n x(lane 4 Q + i)[n] * w[n]: x = four fp16 (what this lane holds matters to the lanes whose Q is
-// this lane's quad), w = the four weights {w0.lo, w0.hi, w1.lo, w1.hi} of this lane's row
-template <int Q>
+// this lane's quad), w = the four weights {w0.lo, w0.hi, w1.lo, w1.hi} of this lane's row.  With G groups Q counts
+// the quads of the lane's own group: 16 / G of them share an operand.
+template <int Q, int G>
 __device__ __forceinline__ void mfma_chunk(f32x4& acc, uint64_t x, uint32_t w0, uint32_t w1) {
-  static_assert(Q >= 0 && Q < 16, "quad of the wavefront");
+  static_assert(Q >= 0 && Q < 16 / G, "quad of the group");
+  constexpr int cbsz = G == 1 ? 4 : G == 2 ? 3 : G == 4 ? 2 : 1;
   const uint64_t w = (uint64_t)w0 | ((uint64_t)w1 << 32);
-  acc = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, x), __builtin_bit_cast(f16x4, w), acc, 4, Q, 0);
+  acc = __builtin_amdgcn_mfma_f32_4x4x4f16(__builtin_bit_cast(f16x4, x), __builtin_bit_cast(f16x4, w), acc, cbsz, Q, 0);
 }
 
 // The lane's partial sums.  One sample: four fp32 sums that take turns.  Four samples: two sets of four (sum i
@@ -200,10 +211,14 @@ __device__ __forceinline__ void lane_park_x(uint32_t x, int lane, char* scratch,
 // ---- entry words of one 32-column word -----------------------------------------------------------------------
 // k = 3: four words of four bytes (8 a + b) + 64 (two bits of other weights, cleared when the address is formed),
 // the pairs (2i, 2i+1), i = 4 jj + n (word 3 is left rotated by one byte: its pair n sits in byte n + 1)
-__device__ __forceinline__ void lane_entries3(uint32_t w0, uint32_t w1, uint32_t w2, uint32_t (&T)[4], const MergeMasks<3>& M) {
+// k = 1, 2: the same words without the planes that are not read (the bits in their places are cleared too)
+template <int K>
+__device__ __forceinline__ void lane_entries3(const uint32_t (&w)[K], uint32_t (&T)[4], const MergeMasks<3>& M) {
 #pragma unroll
   for (int jj = 0; jj < 4; ++jj) {
-    const uint32_t o = bfi_v(M.m[2 * jj], w0, bfi_v(M.m[2 * jj + 1], w1, w2));
+    uint32_t o = w[0];
+    if constexpr (K == 2) o = bfi_v(M.m[2 * jj], w[0], w[1]);
+    if constexpr (K == 3) o = bfi_v(M.m[2 * jj], w[0], bfi_v(M.m[2 * jj + 1], w[1], w[2]));
     T[jj] = jj == 3 ? o : __builtin_rotateright32(o, 2 * jj + 2);   // jj = 3: a whole byte, taken care of by the byte index
   }
 }
@@ -254,16 +269,6 @@ __device__ __forceinline__ void lane_consume_pairs(const uint32_t (&v)[8], const
   dot2_quad<JA>(acc[0], x.x, v[0]);
 }
 
-// Four samples: the eight lookups of entry words JA, JA + 1 of word j (JO = j mod 2) are the chunks 8 JO + 2 JA .. + 3 of the
-// tile's half j / 2, whose activations x holds.
-template <int JA, int JO>
-__device__ __forceinline__ void lane_consume_pairs(const uint32_t (&v)[8], uint64_t x, f32x4 (&acc)[2]) {
-  mfma_chunk<8 * JO + 2 * JA + 3>(acc[1], x, v[6], v[7]);
-  mfma_chunk<8 * JO + 2 * JA + 2>(acc[0], x, v[4], v[5]);
-  mfma_chunk<8 * JO + 2 * JA + 1>(acc[1], x, v[2], v[3]);
-  mfma_chunk<8 * JO + 2 * JA + 0>(acc[0], x, v[0], v[1]);
-}
-
 // single-weight schemes: the eight lookups of columns 8 JJ .. 8 JJ + 7
 template <int K, int JJ>
 __device__ __forceinline__ void lane_issue_singles(const uint32_t (&R)[8], uint32_t lanecol, const char* lds, uint32_t (&v)[8]) {
@@ -288,67 +293,88 @@ __device__ __forceinline__ void lane_consume_singles(const uint32_t (&v)[8], con
   dot2_quad<JJ>(acc[0], x.x, v[0] | (v[1] << 16));
 }
 
-// four samples: columns 8 JJ .. + 7 of word j (JO = j mod 2) are the chunks 8 JO + 2 JJ, + 1
-template <int JJ, int JO>
-__device__ __forceinline__ void lane_consume_singles(const uint32_t (&v)[8], uint64_t x, f32x4 (&acc)[2]) {
-  mfma_chunk<8 * JO + 2 * JJ + 1>(acc[1], x, v[4] | (v[5] << 16), v[6] | (v[7] << 16));
-  mfma_chunk<8 * JO + 2 * JJ + 0>(acc[0], x, v[0] | (v[1] << 16), v[2] | (v[3] << 16));
-}
+// k = 1, 2 use the masks of k = 3
+template <int K>
+using LaneMasks = MergeMasks<(K < 3 ? 3 : K)>;
 
 // k = 5, 6: the merge tree with its masks in vector registers (full-rate instructions); k = 7, 8 have no registers
 // to spare for fifteen masks at two workgroups per compute unit and keep them in the instructions
 template <int K>
-__device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32_t (&R)[8], const MergeMasks<K>& M) {
+__device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32_t (&R)[8], const LaneMasks<K>& M) {
   if constexpr (K <= 6) merge_byte_fields_v<K, LaneDecode<K>::d>(w, R, M);
   else merge_byte_fields<K, LaneDecode<K>::d>(w, R);
 }
 
 // ---- one tile -------------------------------------------------------------------------------------------------
 // Lookups run in chunks of eight; the next chunk's lookups are issued before the current chunk's multiply-adds.
-// xmine: where this lane finds its part of the tile's parked activations.  One sample: the 16 bytes of its quad
-// lane in word 0 (slot + 16 * (lane mod 4)), those of word j 64 j bytes on.  Four samples: its chunk of the tile's
-// first half (its sample's slot + 8 * (lane / 4)), that of the second half 128 bytes on.
-template <int K, int NB>
+// xmine: where this lane finds its part of its tile's parked activations.  One sample: the 16 bytes of its quad
+// lane in word 0 (slot + 16 * (lane mod 4)), those of word j 64 j bytes on.  Four samples: chunk n of the tile's 32
+// (four activations, 8 n bytes into the sample's slot) sits in lane quad n mod P of the group, P = 16 / G quads per
+// group, as its operand n / P.
+template <int NB, int G>
 struct LaneX;
-template <int K>
-struct LaneX<K, 1> {
+template <int G>
+struct LaneX<1, G> {
   u32x4 q[4];   // q[j][m] = pair 4 (lane mod 4) + m of word j
   __device__ __forceinline__ void load(const char* xmine) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64);
   }
 };
-template <int K>
-struct LaneX<K, 4> {
-  uint64_t a[2];   // a[h] = chunk 16 h + lane / 4 of the tile, of sample lane mod 4
+template <int G>
+struct LaneX<4, G> {
+  static constexpr int P = 16 / G;
+  uint64_t a[2 * G];   // a[h] = chunk P h + (lane / 4) mod P of the tile, of sample lane mod 4
   __device__ __forceinline__ void load(const char* xmine) {
-    a[0] = *reinterpret_cast<const uint64_t*>(xmine);
-    a[1] = *reinterpret_cast<const uint64_t*>(xmine + 128);
+#pragma unroll
+    for (int h = 0; h < 2 * G; ++h) a[h] = *reinterpret_cast<const uint64_t*>(xmine + h * P * 8);
   }
 };
+// chunk C of the tile for four samples; chunks take turns in the two accumulator sets
+template <int C, int G>
+__device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<4, G>& x, LaneAcc<4>& acc) {
+  mfma_chunk<C % LaneX<4, G>::P, G>(acc.v[C & 1], x.a[C / LaneX<4, G>::P], w0, w1);
+}
 
-template <int JA, int J, int K>
-__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<K, 1>& x, LaneAcc<1>& acc) {
+// the eight lookups of entry words JA, JA + 1 of word J: chunks 8 J + 2 JA .. + 3
+template <int JA, int J, int G>
+__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
   lane_consume_pairs<JA>(v, x.q[J], acc.v);
 }
-template <int JA, int J, int K>
-__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<K, 4>& x, LaneAcc<4>& acc) {
-  lane_consume_pairs<JA, J & 1>(v, x.a[J >> 1], acc.v);
+template <int JA, int J, int G>
+__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<4, G>& x, LaneAcc<4>& acc) {
+  lane_mac_chunk<8 * J + 2 * JA + 3>(v[6], v[7], x, acc);
+  lane_mac_chunk<8 * J + 2 * JA + 2>(v[4], v[5], x, acc);
+  lane_mac_chunk<8 * J + 2 * JA + 1>(v[2], v[3], x, acc);
+  lane_mac_chunk<8 * J + 2 * JA + 0>(v[0], v[1], x, acc);
 }
-template <int JJ, int J, int K>
-__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<K, 1>& x, LaneAcc<1>& acc) {
+// the lookups of columns 8 JJ .. + 7 of word J: chunks 8 J + 2 JJ, + 1
+template <int JJ, int J, int G>
+__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
   lane_consume_singles<JJ>(v, x.q[J], acc.v);
 }
-template <int JJ, int J, int K>
-__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<K, 4>& x, LaneAcc<4>& acc) {
-  lane_consume_singles<JJ, J & 1>(v, x.a[J >> 1], acc.v);
+template <int JJ, int J, int G>
+__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<4, G>& x, LaneAcc<4>& acc) {
+  lane_mac_chunk<8 * J + 2 * JJ + 1>(v[4] | (v[5] << 16), v[6] | (v[7] << 16), x, acc);
+  lane_mac_chunk<8 * J + 2 * JJ + 0>(v[0] | (v[1] << 16), v[2] | (v[3] << 16), x, acc);
 }
 
-template <int K, int NB>
-__device__ __forceinline__ void lane_compute(const LaneTile<K, NB>& t, uint32_t lanecol, const char* lds, const char* xmine,
-                                             LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const MergeMasks<K>& M) {
+// words: how many of the lane's four words lie inside the row, ragged: not all four in every lane (wave-uniform).  The
+// activations of the others are zero, but their codes are zero too, and an infinite centroid of that code would make
+// 0 x inf; k <= 2 clears what those lookups return.
+template <int K, int NB, int G>
+__device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lanecol, const char* lds, const char* xmine,
+                                             LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const LaneMasks<K>& M, int words, bool ragged) {
+  auto clear = [&](uint32_t (&v)[8], int j) {
+    if constexpr (K <= 2) {
+      if (ragged) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) v[i] = j < words ? v[i] : 0u;
+      }
+    }
+  };
   uint32_t va[8], vb[8];
-  LaneX<K, NB> x;
+  LaneX<NB, G> x;
   x.load(xmine);
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
@@ -358,22 +384,23 @@ __device__ __forceinline__ void lane_compute(const LaneTile<K, NB>& t, uint32_t 
     uint32_t T[4][4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      if constexpr (K == 3) {
-        lane_entries3(t.w[0][j], t.w[1][j], t.w[2][j], T[j], M);
-      } else {
-        const uint32_t w[4] = {t.w[0][j], t.w[1][j], t.w[2][j], t.w[3][j]};
-        merge_nibble_pairs_v(w, T[j], M);
-      }
+      uint32_t w[K];
+#pragma unroll
+      for (int b = 0; b < K; ++b) w[b] = tw[b][j];
+      if constexpr (K <= 3) lane_entries3<K>(w, T[j], M);
+      else merge_nibble_pairs_v(w, T[j], M);
     }
-    lane_issue_pairs<0, K == 3>(T[0], lanecol, lds, va, addr, mask);
+    lane_issue_pairs<0, K <= 3>(T[0], lanecol, lds, va, addr, mask);
     auto word = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      lane_issue_pairs<2, K == 3>(T[j], lanecol, lds, vb, addr, mask);
+      lane_issue_pairs<2, K <= 3>(T[j], lanecol, lds, vb, addr, mask);
       sched_fence();
+      clear(va, j);
       lane_mac_pairs<0, j>(va, x, acc);
       sched_fence();
-      if constexpr (j + 1 < 4) lane_issue_pairs<0, K == 3>(T[j + 1], lanecol, lds, va, addr, mask);
+      if constexpr (j + 1 < 4) lane_issue_pairs<0, K <= 3>(T[j + 1], lanecol, lds, va, addr, mask);
       sched_fence();
+      clear(vb, j);
       lane_mac_pairs<2, j>(vb, x, acc);
       sched_fence();
     };
@@ -383,7 +410,7 @@ __device__ __forceinline__ void lane_compute(const LaneTile<K, NB>& t, uint32_t 
     {
       uint32_t w[K];
 #pragma unroll
-      for (int b = 0; b < K; ++b) w[b] = t.w[b][0];
+      for (int b = 0; b < K; ++b) w[b] = tw[b][0];
       lane_merge_fields<K>(w, R[0], M);
     }
     lane_issue_singles<K, 0>(R[0], lanecol, lds, va);
@@ -392,7 +419,7 @@ __device__ __forceinline__ void lane_compute(const LaneTile<K, NB>& t, uint32_t 
       if constexpr (j + 1 < 4) {
         uint32_t w[K];
 #pragma unroll
-        for (int b = 0; b < K; ++b) w[b] = t.w[b][j + 1];
+        for (int b = 0; b < K; ++b) w[b] = tw[b][j + 1];
         lane_merge_fields<K>(w, R[(j + 1) & 1], M);
       }
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
@@ -418,16 +445,16 @@ __device__ __forceinline__ void lane_compute(const LaneTile<K, NB>& t, uint32_t 
 
 // ---- tables -------------------------------------------------------------------------------------------------
 // The lane's row of the k-bit table (the part this wavefront builds entries from), fetched one row block ahead.
-//   k = 3: the whole row (8 fp16); k = 4: the whole row (16 fp16); k >= 5: entries [share * wave, + share)
+//   k <= 4: the whole row (2^k fp16); k >= 5: entries [share * wave, + share)
 template <int K>
 struct LaneLut {
-  static constexpr int kDwords = K == 3 ? 4 : K == 4 ? 8 : LaneDecode<K>::share / 2;
+  static constexpr int kDwords = K <= 4 ? (1 << K) / 2 : LaneDecode<K>::share / 2;
   uint32_t v[kDwords];
 };
 
 template <int K>
-__device__ __forceinline__ void lane_fetch_lut(LaneLut<K>& L, const DPLLM_GLOBAL uint16_t* lut_base, int rb, int lane, int wave) {
-  const DPLLM_GLOBAL uint32_t* row = reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(lut_base + (((size_t)rb * 64 + lane) << K));
+__device__ __forceinline__ void lane_fetch_lut(LaneLut<K>& L, const DPLLM_GLOBAL uint16_t* lut_base, int row_number, int wave) {
+  const DPLLM_GLOBAL uint32_t* row = reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(lut_base + ((size_t)row_number << K));
   const DPLLM_GLOBAL uint32_t* src = K <= 4 ? row : row + wave * LaneLut<K>::kDwords;
   if constexpr (LaneLut<K>::kDwords >= 4) {
 #pragma unroll
@@ -446,7 +473,18 @@ __device__ __forceinline__ uint32_t half_of(uint32_t d, int h) { return h ? d >>
 
 template <int K>
 __device__ __forceinline__ void lane_build_table(const LaneLut<K>& L, int wave, uint32_t lanecol, char* lds) {
-  if constexpr (K == 3) {
+  if constexpr (K <= 2) {
+    // wavefront w < 2^k writes the entries (a = w, b): (LUT[a], LUT[b])
+    if (wave < (1 << K)) {
+      const uint32_t la = half_of(K == 2 && wave >= 2 ? L.v[LaneLut<K>::kDwords - 1] : L.v[0], wave & 1);
+#pragma unroll
+      for (int b = 0; b < (1 << K); ++b) {
+        const uint32_t hb = (b & 1) ? (L.v[b >> 1] & 0xffff0000u) : (L.v[b >> 1] << 16);
+        const uint32_t entry = (uint32_t)wave << (6 - K) | (uint32_t)b << (3 - K);
+        *reinterpret_cast<uint32_t*>(lds + entry * 256 + lanecol) = la | hb;
+      }
+    }
+  } else if constexpr (K == 3) {
     // wavefront w writes the entries (a = w, b = 0..7): (LUT[a], LUT[b])
     const uint32_t lw = wave < 2 ? L.v[0] : wave < 4 ? L.v[1] : wave < 6 ? L.v[2] : L.v[3];
     const uint32_t la = half_of(lw, wave & 1);
@@ -494,25 +532,21 @@ __device__ __forceinline__ void lane_group_barrier() {
 // requests in flight.
 constexpr int kLaneDepth = 2;
 
-// One workgroup: row blocks block, block + step, ... of a job (step = nblocks / nsplit); it is number `split` of
-// the nsplit workgroups that share these row blocks, and its wavefront w takes slice v = 8 split + w of the
-// 8 nsplit slices of the column tiles, [v ncc / (8 nsplit), (v + 1) ncc / (8 nsplit)), in every row block.  Tile
-// loads run kLaneDepth - 1 tiles ahead, also across row blocks; past the end of the run the ring is refilled with
-// dummy loads (see lane_load_tile).
+// One workgroup: row blocks block, block + nblocks, ... of a job; its wavefront w takes the column tiles
+// [w ncc / 8, (w + 1) ncc / 8) in every row block.  Tile loads run kLaneDepth - 1 tiles ahead, also across row
+// blocks; past the end of the run the ring is refilled with dummy loads (see lane_load_tile).
 template <int K, int NB>
-__device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, int block, int split, int tid, char* lds) {
+__device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
   constexpr int table_bytes = kLaneTableBytes;
   constexpr int D = kLaneDepth;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint32_t lanecol = (uint32_t)lane * 4;  // the lane's column of the interleaved tables
   float* red = reinterpret_cast<float*>(lds + table_bytes);
-  char* ready = lds + table_bytes + NB * kLaneRedBytes + wave * lane_x_bytes<NB>();   // + 256 b: the parked tile of sample b
+  char* ready = lds + table_bytes + NB * kLaneRedBytes + wave * lane_x_bytes<NB, 1>();   // + 256 b: the parked tile of sample b
   char* repair = reinterpret_cast<char*>(red) + wave * 256;   // k = 4: room to re-pair a tile's activations (see lane_lds_bytes)
-  const int nsplit = job.nsplit;
-  const int slice = split * kLaneWaves + wave, nslices = nsplit * kLaneWaves;
-  const int c0 = slice * job.ncc / nslices, c1 = (slice + 1) * job.ncc / nslices;
+  const int c0 = wave * job.ncc / kLaneWaves, c1 = (wave + 1) * job.ncc / kLaneWaves;
   const int nrb = job.nrq;                     // row blocks of the job
-  const int step = job.nblocks / nsplit;
+  const int step = job.nblocks;
   const DPLLM_GLOBAL uint16_t* lut_base = as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off));
   const bool idle = c0 >= c1;                  // fewer tiles than wavefronts: this one only helps with the tables
   // the table rows of the next row block travel one block ahead, except at k >= 7, where their 8 - 16 registers
@@ -539,7 +573,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
         lane_park_x<K>(lane_mask_x(job, cc, lane, lane_load_x(job, cc, lane)), lane, repair, kept + (cc - c0) * 256);
     }
   }
-  if constexpr (kLutAhead) lane_fetch_lut<K>(L, lut_base, block, lane, wave);
+  if constexpr (kLutAhead) lane_fetch_lut<K>(L, lut_base, block * 64 + lane, wave);
   int lrb = block, lcc = c0;                   // load cursor
   bool more = true;                            // the load cursor is still inside the run
   auto load_next = [&](LaneTile<K, NB>& t) {
@@ -560,16 +594,16 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   }
   LaneAcc<NB> acc;
   acc.zero();
-  MergeMasks<K> M;
+  LaneMasks<K> M;
   if constexpr (K <= 6) M.init();
-  uint32_t addr[8], mask = 0x3fu;              // k = 3: address registers of the lookups (see lane_issue_pairs)
+  uint32_t addr[8], mask = LaneDecode<K>::pair ? LaneDecode<K>::pair_mask : 0;   // k <= 3: address registers of the lookups (see lane_issue_pairs)
 #pragma unroll
   for (int i = 0; i < 8; ++i) addr[i] = lanecol;
   int rb = block, cc = c0;                     // compute cursor
   auto open_block = [&]() {
-    if constexpr (!kLutAhead) lane_fetch_lut<K>(L, lut_base, rb, lane, wave);
+    if constexpr (!kLutAhead) lane_fetch_lut<K>(L, lut_base, rb * 64 + lane, wave);
     lane_build_table<K>(L, wave, lanecol, lds);
-    if constexpr (kLutAhead) lane_fetch_lut<K>(L, lut_base, rb + step < nrb ? rb + step : rb, lane, wave);
+    if constexpr (kLutAhead) lane_fetch_lut<K>(L, lut_base, (rb + step < nrb ? rb + step : rb) * 64 + lane, wave);
     lane_group_barrier();
   };
   auto close_block = [&]() {
@@ -583,43 +617,8 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
 #pragma unroll
       for (int w = 0; w < kLaneWaves; ++w) s += red[(wave * kLaneWaves + w) * 64 + lane];
     }
-    bool last = true;
-    if (nsplit > 1) {
-      // Column split: every workgroup of the row block leaves its sums in the pool, then takes a ticket; the
-      // holder of the last ticket finds all of them, adds them in the order of the splits (so the result does
-      // not depend on who arrives last) and leaves the counter at zero again.  Ordering: plain stores ->
-      // workgroup barrier -> thread 0: release fence at agent scope, ticket (agent-scope read-modify-write),
-      // acquire fence at agent scope when the ticket is the last -> workgroup barrier -> plain loads.  The
-      // release fence writes the sums back to where every die sees them before the ticket is taken; the acquire
-      // fence drops what this die may still cache of the pool before the sums are read.
-      DPLLM_GLOBAL float* part = as_global(job.ws) + (size_t)(rb * NB + wave) * nsplit * 64 + lane;
-      DPLLM_GLOBAL uint32_t* ticket = as_global(job.cnt) + rb * NB;
-      uint32_t* flag = reinterpret_cast<uint32_t*>(red);   // free by now: the sums above were read before the next barrier
-      if (storer) part[split * 64] = s;
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      if (tid == 0) {
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-        const uint32_t old = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        const bool mine = old == (uint32_t)(nsplit - 1);
-        if (mine) {
-          __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-          __hip_atomic_store(ticket, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-        *flag = mine;
-      }
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
-      __builtin_amdgcn_s_barrier();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
-      last = *flag != 0;
-      if (storer && last) {
-        s = 0.f;
-        for (int i = 0; i < nsplit; ++i) s += part[i * 64];
-      }
-    }
     const int o = rb * 64 + lane;
-    if (storer && last && o < job.out) as_global(job.y)[(size_t)wave * job.out + o] = __builtin_bit_cast(uint16_t, (_Float16)s);
+    if (storer && o < job.out) as_global(job.y)[(size_t)wave * job.out + o] = __builtin_bit_cast(uint16_t, (_Float16)s);
   };
   open_block();
   if (idle) {
@@ -640,7 +639,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
         for (int b = 0; b < NB; ++b) lane_park_x<K>(lane_mask_x(job, cc, lane, ring[s].x[b]), lane, repair, ready + b * 256);
         xready = ready;
       }
-      lane_compute<K, NB>(ring[s], lanecol, lds, xready + xlane, acc, addr, mask, M);
+      lane_compute<K, NB, 1>(ring[s].w, lanecol, lds, xready + xlane, acc, addr, mask, M, job.ncw - cc * 4, cc * 4 + 4 > job.ncw);
       if (++cc >= c1) {
         close_block();
         rb += step;
@@ -652,33 +651,208 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   }
 }
 
+// Launches that would leave the chip idle with 64 rows per workgroup (a 4096-row linear has 64 such blocks for 256
+// compute units): a workgroup takes a block of 64 / G rows, and each of its wavefronts G neighbouring column tiles of
+// them at a time: lane l works on row l mod (64 / G) of the block and on the tile of group l / (64 / G).  Every lane
+// still has a column of its own in the interleaved tables (the G lanes of a row hold G copies of its table), so the
+// lookups stay free of bank conflicts and the decode is the same code.  The sums of a row meet inside the workgroup:
+// nothing is handed over between workgroups (sharing 64 rows between workgroups that split the columns, with a
+// device-scope release, ticket and acquire at the end, cost 2 - 3 us of 10).
+// What bounds it is one chain of latencies, not bandwidth: 4096 x 4096 at k = 4 on 256 workgroups, us after the first
+// workgroup's entry: table rows here 1.4 - 1.7, tables built 2.0, first tile here 2.5, its 128 columns decoded 3.4,
+// stored 4.2; another 1.3 around the kernel.  So the loads are asked for in the order they are needed, the activations
+// are parked while the rest is on its way, and one workgroup per compute unit may use all its registers.
+// us per launch, columns split between workgroups -> now: 4096 x 4096 k = 4 10.9 -> 5.5, k = 8 14.6 -> 8.5; 4096 x 11008
+// k = 3 12.2 -> 7.9; 1024 x 4096 k = 3 7.3 -> 3.9.
+template <int K, int NB, int G>
+struct NarrowTile {
+  u32x4 w[K];
+  uint32_t x[NB][G];   // the lane's G dwords of the G tiles' activations: dwords G lane .. + G - 1
+};
+
+template <int N>
+__device__ __forceinline__ void load_dwords(uint32_t (&v)[N], const DPLLM_GLOBAL uint32_t* p) {
+  if constexpr (N == 2) {
+    const u32x2 q = *reinterpret_cast<const DPLLM_GLOBAL u32x2*>(p);
+    v[0] = q.x; v[1] = q.y;
+  } else {
+#pragma unroll
+    for (int i = 0; i < N; i += 4) {
+      const u32x4 q = *reinterpret_cast<const DPLLM_GLOBAL u32x4*>(p + i);
+      v[i] = q.x; v[i + 1] = q.y; v[i + 2] = q.z; v[i + 3] = q.w;
+    }
+  }
+}
+
+// the planes of the lane's tile (number `tile`, clamped to the row); real as in lane_load_tile
+template <int K, int NB, int G>
+__device__ __forceinline__ void narrow_load_planes(NarrowTile<K, NB, G>& t, const GemvJob& job, const DPLLM_GLOBAL u32x4* rows, int tile, bool real) {
+  const DPLLM_GLOBAL u32x4* p = real ? rows + (size_t)min(tile, job.ncc - 1) * 64 : as_global(reinterpret_cast<const u32x4*>(job.x));
+  const size_t stride = real ? (size_t)job.plane_stride_u4 : 0;
+#pragma unroll
+  for (int b = 0; b < K; ++b) t.w[b] = load_stream(p + (size_t)b * stride);
+}
+
+// the lane's part of the activations of step sc (G tiles).  A lane's 4 G bytes are 2 G columns; rows are whole
+// 32-column words, so they are all inside the row or all past it.
+template <int K, int NB, int G>
+__device__ __forceinline__ void narrow_load_x(NarrowTile<K, NB, G>& t, const GemvJob& job, int sc, int lane) {
+  const int c = min(sc * G * 128 + lane * 2 * G, job.ncw * 32 - 2 * G);
+#pragma unroll
+  for (int b = 0; b < NB; ++b) {
+    const uint16_t* xs = job.x + (size_t)(NB == 1 ? 0 : min(b, job.nsamples - 1)) * job.ncw * 32;
+    load_dwords<G>(t.x[b], reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(as_global(xs) + c));
+  }
+}
+
+// The sum over the G lanes of a row (64 / G lanes apart), in every one of them.  The swaps exchange two registers,
+// so the value goes in twice, in registers of its own (the copy is opaque: left to itself the compiler hands the
+// instruction one register twice, which then holds what it held).
+template <int G>
+__device__ __forceinline__ float sum_groups(float s) {
+  if constexpr (G >= 8) s += __shfl_xor(s, 8, 64);
+  auto copy = [](float v) { uint32_t r; asm("v_mov_b32 %0, %1" : "=v"(r) : "v"(v)); return r; };
+  if constexpr (G >= 4) {
+    const auto q = __builtin_amdgcn_permlane16_swap(__builtin_bit_cast(uint32_t, s), copy(s), false, false);
+    s = __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]);
+  }
+  const auto q = __builtin_amdgcn_permlane32_swap(__builtin_bit_cast(uint32_t, s), copy(s), false, false);
+  return __builtin_bit_cast(float, (uint32_t)q[0]) + __builtin_bit_cast(float, (uint32_t)q[1]);
+}
+
+// parks the G tiles' activations of one sample (see lane_park_x): group g's at ready + kLaneGroupStride g
+template <int K, int G>
+__device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside, int lane, char* ready) {
+  constexpr int per = 64 / G;   // lanes that hold one tile's dwords
+  char* mine = ready + (lane / per) * kLaneGroupStride + (lane % per) * 4 * G;
+#pragma unroll
+  for (int i = 0; i < G; ++i) *reinterpret_cast<uint32_t*>(mine + 4 * i) = inside ? x[i] : 0u;
+  lds_order();
+  if constexpr (K == 4) {       // re-paired in place: everything is read before anything is written
+    const int j = lane >> 4, q = (lane >> 2) & 3, m = lane & 3, mr = (m + 3) & 3;
+    const int ca = q == 0 ? 17 + 2 * m : q == 1 ? 8 + 2 * m : q == 2 ? 25 + 2 * m : 2 * m;
+    const int cb = q == 0 ? 1 + 2 * m : q == 1 ? 24 + 2 * mr : q == 2 ? 9 + 2 * m : 16 + 2 * mr;
+    uint32_t v[G];
+#pragma unroll
+    for (int g = 0; g < G; ++g) {
+      const uint32_t lo = *reinterpret_cast<const uint16_t*>(ready + g * kLaneGroupStride + (j * 32 + ca) * 2);
+      const uint32_t hi = *reinterpret_cast<const uint16_t*>(ready + g * kLaneGroupStride + (j * 32 + cb) * 2);
+      v[g] = lo | (hi << 16);
+    }
+    lds_order();
+#pragma unroll
+    for (int g = 0; g < G; ++g) *reinterpret_cast<uint32_t*>(ready + g * kLaneGroupStride + lane * 4) = v[g];
+    lds_order();
+  }
+}
+
+// one workgroup: block number `block` of 64 / G rows
+template <int K, int NB, int G>
+__device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
+  constexpr int D = kLaneDepth;
+  constexpr int rows = 64 / G;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int row = block * rows + lane % rows, group = lane / rows;
+  const uint32_t lanecol = (uint32_t)lane * 4;
+  float* red = reinterpret_cast<float*>(lds + kLaneTableBytes);
+  char* ready = lds + kLaneTableBytes + NB * kLaneRedBytes + wave * lane_x_bytes<NB, G>();   // sample b: + G * kLaneGroupStride * b
+  const int xlane = group * kLaneGroupStride +
+                    (NB == 1 ? (lane & 3) * 16 : (lane & 3) * G * kLaneGroupStride + ((lane >> 2) % (16 / G)) * 8);
+  const int nsc = (job.ncc + G - 1) / G;
+  const int c0 = wave * nsc / kLaneWaves, c1 = (wave + 1) * nsc / kLaneWaves;
+  const DPLLM_GLOBAL u32x4* plane_rows = as_global(reinterpret_cast<const u32x4*>(job.arena)) + (size_t)(row / 64) * job.ncc * 64 + row % 64;
+  // first the activations of the first step (hot in L2: parked while the rest is on its way), then the table rows and
+  // the planes of the first D steps
+  LaneLut<K> L;
+  NarrowTile<K, NB, G> ring[D];
+  const bool some = c0 < c1;                   // fewer steps than wavefronts: some only help with the tables
+  auto inside = [&](int sc) { return sc * G * 128 + lane * 2 * G < job.ncw * 32; };
+  if (some) narrow_load_x<K, NB, G>(ring[0], job, c0, lane);
+  lane_fetch_lut<K>(L, as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off)), row, wave);
+  if (some) {
+    narrow_load_planes<K, NB, G>(ring[0], job, plane_rows, c0 * G + group, true);
+#pragma unroll
+    for (int i = 1; i < D; ++i) {
+      narrow_load_x<K, NB, G>(ring[i], job, c0 + i, lane);
+      narrow_load_planes<K, NB, G>(ring[i], job, plane_rows, (c0 + i) * G + group, c0 + i < c1);
+    }
+    sched_fence();
+#pragma unroll
+    for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[0].x[b], inside(c0), lane, ready + b * G * kLaneGroupStride);
+  }
+  LaneAcc<NB> acc;
+  acc.zero();
+  float done[NB];   // the sums before the last step, where lanes may be without a tile
+#pragma unroll
+  for (int b = 0; b < NB; ++b) done[b] = 0.f;
+  LaneMasks<K> M;
+  if constexpr (K <= 6) M.init();
+  uint32_t addr[8], mask = LaneDecode<K>::pair ? LaneDecode<K>::pair_mask : 0;   // k <= 3 (see lane_issue_pairs)
+#pragma unroll
+  for (int i = 0; i < 8; ++i) addr[i] = lanecol;
+  lane_build_table<K>(L, wave, lanecol, lds);
+  lane_group_barrier();
+  for (int cc = c0; cc < c1;) {
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      if (cc != c0) {
+#pragma unroll
+        for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[s].x[b], inside(cc), lane, ready + b * G * kLaneGroupStride);
+      }
+#pragma unroll
+      for (int b = 0; b < NB; ++b) done[b] = acc.sum(b);
+      lane_compute<K, NB, G>(ring[s].w, lanecol, lds, ready + xlane, acc, addr, mask, M, job.ncw - (cc * G + group) * 4,
+                             (cc + 1) * G * 4 > job.ncw);
+      if (++cc >= c1) break;
+      narrow_load_x<K, NB, G>(ring[s], job, cc + D - 1, lane);
+      narrow_load_planes<K, NB, G>(ring[s], job, plane_rows, (cc + D - 1) * G + group, cc + D - 1 < c1);
+    }
+  }
+  // the last step may have fewer than G tiles: a lane without one (it decoded another tile) drops what it added there
+  const bool whole = (c1 - 1) * G + group < job.ncc;
+#pragma unroll
+  for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
+  lane_group_barrier();
+  if (wave < NB && (NB == 1 || wave < job.nsamples)) {   // wavefront b stores sample b
+    float s = 0.f;
+#pragma unroll
+    for (int w = 0; w < kLaneWaves; ++w) s += red[(wave * kLaneWaves + w) * 64 + lane];
+    s = sum_groups<G>(s);
+    if (group == 0 && row < job.out) as_global(job.y)[(size_t)wave * job.out + row] = __builtin_bit_cast(uint16_t, (_Float16)s);
+  }
+}
+
 // The bitwidth of the job: its own value, the word a selector left in device memory, or the decision taken here
 // from the partial results of an earlier selector launch (every workgroup of the job repeats the same fixed-order
 // sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
 // linear does not serve (outside [max(kmin, 3), p]) is not served: the workgroup returns and y keeps what it held.
-template <int NB>
+template <int NB, int G>
 __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* params,
                                                 const int32_t* target, int n_linears) {   // params == nullptr: no decisions here
-  const int first = block == 0;
-  const int split = block % job.nsplit;
-  block /= job.nsplit;
-  if (block >= job.nrq) return;
+  if (block * (64 / G) >= job.out) return;   // (no row of the job is this workgroup's)
   int k = job.k;
   if (job.has_fin && params != nullptr) {
     k = selector_finish(job.fin, params + (size_t)(*target) * n_linears + job.fin.linear, tid, kLaneThreads,
-                        reinterpret_cast<double*>(lds), first);   // the tables are not built yet
+                        reinterpret_cast<double*>(lds), block == 0);   // the tables are not built yet
     k = __builtin_amdgcn_readfirstlane(k);
   } else if (job.k_dev != nullptr) {
     k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
   }
-  if (k < max(job.kmin, kFastKMin) || k > min(job.p, kFastKMax)) return;
+  if (k < job.kmin || k > job.p) return;
+  auto run = [&](auto kc) {
+    constexpr int K = decltype(kc)::value;
+    if constexpr (G == 1) gemv_lane<K, NB>(job, job.lut_off[K - 1], block, tid, lds);
+    else gemv_narrow<K, NB, G>(job, job.lut_off[K - 1], block, tid, lds);
+  };
   switch (k) {   // (the table offsets are taken by constant index: a run-time index would put the job record in scratch memory)
-    case 3: gemv_lane<3, NB>(job, job.lut_off[0], block, split, tid, lds); break;
-    case 4: gemv_lane<4, NB>(job, job.lut_off[1], block, split, tid, lds); break;
-    case 5: gemv_lane<5, NB>(job, job.lut_off[2], block, split, tid, lds); break;
-    case 6: gemv_lane<6, NB>(job, job.lut_off[3], block, split, tid, lds); break;
-    case 7: gemv_lane<7, NB>(job, job.lut_off[4], block, split, tid, lds); break;
-    default: gemv_lane<8, NB>(job, job.lut_off[5], block, split, tid, lds); break;
+    case 1: run(std::integral_constant<int, 1>{}); break;
+    case 2: run(std::integral_constant<int, 2>{}); break;
+    case 3: run(std::integral_constant<int, 3>{}); break;
+    case 4: run(std::integral_constant<int, 4>{}); break;
+    case 5: run(std::integral_constant<int, 5>{}); break;
+    case 6: run(std::integral_constant<int, 6>{}); break;
+    case 7: run(std::integral_constant<int, 7>{}); break;
+    default: run(std::integral_constant<int, 8>{}); break;
   }
 }
 
@@ -686,11 +860,11 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
 // the planes (group g reads x + g * NB * in and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) *
 // nblocks) serve it); else (NB = 1) block b belongs to job block_jobs[b] of the table.  params / target /
 // n_linears: the table of selector parameters, for jobs that take their decision here.
-template <int NB>
-__global__ void __launch_bounds__(kLaneThreads) gemv_lane_kernel(const GemvJob* __restrict__ jobs, const int32_t* __restrict__ block_jobs,
+template <int NB, int G>
+__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const GemvJob* __restrict__ jobs, const int32_t* __restrict__ block_jobs,
                                                                  int njobs, GemvJob one, const SelParams* __restrict__ params,
                                                                  const int32_t* __restrict__ target, int n_linears) {
-  __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB>()];
+  __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB, G>()];
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
   if (jobs == nullptr) {
@@ -698,15 +872,13 @@ __global__ void __launch_bounds__(kLaneThreads) gemv_lane_kernel(const GemvJob* 
     one.x += (size_t)group * NB * one.ncw * 32;
     one.y += (size_t)group * NB * one.out;
     one.nsamples = min(NB, njobs - group * NB);
-    one.ws += (size_t)group * one.nrq * NB * one.nsplit * 64;
-    one.cnt += (size_t)group * one.nrq * NB;
-    gemv_lane_block<NB>(one, blockIdx.x - group * one.nblocks, threadIdx.x, lds, params, target, n_linears);
+    gemv_lane_block<NB, G>(one, blockIdx.x - group * one.nblocks, threadIdx.x, lds, params, target, n_linears);
     return;
   }
   if constexpr (NB == 1) {
     const int b = blockIdx.x;
     GemvJob job = jobs[block_jobs[b]];
-    gemv_lane_block<1>(job, b - job.block_start, threadIdx.x, lds, params, target, n_linears);
+    gemv_lane_block<1, G>(job, b - job.block_start, threadIdx.x, lds, params, target, n_linears);
   }
 }
 
