@@ -14,8 +14,8 @@
  *     or aborts.  dpllm_last_error() gives the text of the last failure on a model.
  *   - "host" / "device" on a pointer says where the memory lives.  The caller owns all
  *     device memory: the weight arenas, G, x, y, k, e, and one workspace per model
- *     (partial results of the selectors and of column-split GEMV launches, arrival
- *     counters, job and parameter tables: a few MiB, see dpllm_workspace_bytes) that it
+ *     (partial results of the selectors, job, task and parameter tables: some MiB, see
+ *     dpllm_workspace_bytes) that it
  *     hands over with dpllm_set_workspace.  Everything is borrowed until the model is
  *     destroyed (a linear's memory: until it is loaded again).  No call allocates device
  *     memory, except dpllm_load_linear from host pointers (a staging buffer it frees
@@ -99,9 +99,8 @@ int dpllm_load_linear(dpllm_model* m, int id, int out, int in, int p, int kmin,
 int dpllm_workspace_bytes(const dpllm_model* m, size_t* bytes);
 
 /* Hands the model its workspace: ws_dev (device, caller-owned, 256-byte aligned, >= dpllm_workspace_bytes), which
- * the model uses until it is destroyed or given another.  Enqueues the clearing of its counters on `stream`.
- * dpllm_estimate, dpllm_decode_step(_parts) and dpllm_set_target need a workspace; dpllm_gemv runs without one
- * (it then never splits the columns of a linear over several workgroups).
+ * the model uses until it is destroyed or given another.  Enqueues the clearing of its target word on `stream`.
+ * dpllm_estimate, dpllm_decode_step(_parts) and dpllm_set_target need a workspace; dpllm_gemv runs without one.
  * Errors: EINVAL, ESTATE (too small), EHIP. */
 int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream);
 
@@ -131,7 +130,7 @@ int dpllm_set_active_pair(dpllm_model* m, int id, int l, int h);
  * for t runs as under target 0.  Errors: EINVAL, ESTATE (pair not set). */
 int dpllm_set_target_entry(dpllm_model* m, int target, int id, int l, int h, float T);
 
-/* Switches the whole model to `target` with one word written on the device, enqueued on `stream`: the steps
+/* Switches the whole model to `target` with one small kernel enqueued on `stream`: the steps
  * enqueued behind it (also replays of graphs captured earlier, and it can be captured itself) run every linear
  * under that target's pair and threshold.  No launch plan is rebuilt and nothing is synchronised.
  * Errors: EINVAL, ESTATE (no workspace), EHIP. */

@@ -70,7 +70,7 @@ struct Linear {
 // A decode step is cut into phases: maximal runs of consecutive linears none of which reads or overwrites
 // what an earlier linear of the run writes.  Inside a phase all selectors run in one launch and all GEMVs
 // in another; phases run one after the other on the stream, so the result equals running the linears strictly
-// in order.
+// in order.  Small GEMV launches run the selectors themselves (fused).
 struct Phase {
   int sel_first = 0, sel_count = 0;     // slice of the device selector job table
   int part_first = 0, part_count = 0;   // slice of the device selector part table
@@ -80,6 +80,8 @@ struct Phase {
   int block_first = 0;                  // slice of the device workgroup-to-job table
   bool estimators = true;               // under some target a job of the selector launch has an estimator (else the launch is skipped)
   int groups = 1;                       // column groups per wavefront of that launch (see gemv_narrow)
+  bool fused = false;                   // a whole step runs the selectors inside the GEMV launch
+  int task_first = 0, task_count = 0;   // slice of the device table of selector tasks
 };
 constexpr int kMaxGroups = 8;           // column groups per wavefront, at most
 constexpr size_t kSelOneSlots = (size_t)kSelMaxChunks * kSelMaxRank;
@@ -92,6 +94,8 @@ struct StepPlan {
   int32_t* k_dev = nullptr;
   float* e_dev = nullptr;
   std::vector<Phase> phases;
+  size_t slots = 0;      // partial dot products of all selectors; emptied at the start of a whole step if
+  bool fused = false;    //   any of its phases runs selectors inside its GEMV launch
 };
 
 // The caller's workspace, carved once by dpllm_set_workspace.  Offsets in bytes, every region 256-byte aligned.
@@ -99,8 +103,10 @@ struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
   size_t est_ws = 0;                         // dpllm_estimate: kSelOneSlots fp64
-  size_t target = 0;                         // the number of the active target
+  size_t target = 0;                         // the number of the active target, the number of selector tasks
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
+  size_t sel_active = 0;                     // SelParams [n]: the row of the active target
+  size_t sel_tasks = 0, sel_tasks_cap = 0;   // SelTask [cap]
   size_t sel_jobs = 0, sel_members = 0;      // SelJob [n], int32 [n]
   size_t sel_parts = 0, sel_parts_cap = 0;   // SelPart [cap]
   size_t sel_ws = 0, sel_ws_cap = 0;         // fp64 [cap]
@@ -127,6 +133,8 @@ struct dpllm_model {
   std::vector<GemvJob> h_gemv_jobs;
   std::vector<int32_t> h_block_jobs;
   std::vector<SelParams> h_params;
+  std::vector<SelTask> h_sel_tasks;
+  int32_t h_ntasks = 0;
   int device = 0;
 };
 
@@ -169,23 +177,30 @@ Linear* get_linear(dpllm_model* m, int id, int* rc) {
 }
 
 // ---- workspace ------------------------------------------------------------------------------------------------
+// slices of a row of G, at most
+int sel_slices(int in) { return (in + kSelTaskCols - 1) / kSelTaskCols; }
+
 // Sized for any launch plan over the linears as they stand (shapes, pairs): the caps are upper bounds.
 Workspace carve_workspace(const dpllm_model* m) {
   Workspace w;
   const size_t n = m->linears.size();
-  size_t parts = 0, slots = 0, blocks = 0;
+  size_t parts = 0, slots = 0, blocks = 0, tasks = 0;
   for (const Linear& lin : m->linears) {
     if (!lin.loaded) continue;
     const size_t rg = (size_t)std::max(1, lin.max_rowgroups());
     parts += rg * kSelMaxChunks + 1;
-    slots += rg * kSelPartRows * kSelMaxChunks;
+    slots += rg * kSelPartRows * std::max(kSelMaxChunks, kSelCopies * sel_slices(lin.L.in));
+    tasks += rg * kSelPartRows * sel_slices(lin.L.in);
     blocks += (size_t)lin.L.nrq * kMaxGroups;
   }
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
   w.est_ws = take(sizeof(double) * kSelOneSlots);
-  w.target = take(sizeof(int32_t));
+  w.target = take(2 * sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
+  w.sel_active = take(sizeof(SelParams) * n);
+  w.sel_tasks_cap = tasks;
+  w.sel_tasks = take(sizeof(SelTask) * tasks);
   w.sel_jobs = take(sizeof(SelJob) * n);
   w.sel_members = take(sizeof(int32_t) * n);
   w.sel_parts_cap = parts;
@@ -205,7 +220,6 @@ SelParams make_params(const Pair& s, float T) {
   P.G = s.G;
   P.T = T; P.alpha = s.alpha; P.beta = s.beta;
   P.r = s.r; P.l = s.l; P.h = s.h; P.kind = s.kind;
-  P.pad = 0;
   return P;
 }
 
@@ -263,9 +277,10 @@ GemvJob make_gemv_job(const Linear& lin, int k, const int32_t* k_dev, const void
 // end of the launch (measured on the 7B step: 0.25 MiB 496 us, 0.375 MiB 480, 0.75 MiB 471, 1 MiB 468, 2 MiB
 // 477, 4 MiB 546); and a launch wants at least a few workgroups per compute unit.
 constexpr long kLaneGroupBytes = 1048576;
-// GEMV launches below this many workgroups take their selectors' decisions themselves; larger ones get a launch
-// of its own for the decisions (measured on a 7B step of 3094 workgroups: 509 against 514 us)
-constexpr int kFoldMaxBlocks = 1536;
+// GEMV launches below this many workgroups run their selectors themselves; larger ones get launches of their own for
+// the selectors and the decisions (repeating the decision in each of 3094 workgroups: 514 against 509 us for a 7B step)
+constexpr int kFusedMaxBlocks = 1536;
+constexpr int kSelPolls = 64;   // polls of about a microsecond before a workgroup computes missing products itself
 int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long group_bytes = kLaneGroupBytes) {
   const long bytes_per_block = 64L * L.in * k / 8;
   long r = std::min<long>(16, std::max<long>(1, group_bytes / std::max<long>(1, bytes_per_block)));
@@ -286,9 +301,8 @@ int pick_groups(long blocks64, int ncc, int nb) {
   return g;
 }
 
-void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const GemvJob* jobs, const int32_t* block_jobs, int njobs,
-                 const GemvJob& one, const SelParams* params, const int32_t* target, int n) {
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, jobs, block_jobs, njobs, one, params, target, n); };
+void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const GemvJob& one, int nrhs) {
+  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, one, nrhs); };
   if (nb == 1) {
     switch (groups) {
       case 1: go(gemv_lane_kernel<1, 1>); break;
@@ -305,6 +319,21 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
   }
 }
 
+// fewer workgroups than compute units: more of them help with the selectors
+void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, const int32_t* block_jobs, const SelParams* active,
+                 const SelTask* tasks, int ntasks) {
+  const unsigned grid = (unsigned)std::max(blocks, std::min(ntasks, kSelTaskGroups));
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLaneThreads), 0, st, tasks, jobs, block_jobs, active, ntasks, kSelTaskGroups, blocks, kSelPolls);
+  };
+  switch (groups) {
+    case 1: go(gemv_step_kernel<1>); break;
+    case 2: go(gemv_step_kernel<2>); break;
+    case 4: go(gemv_step_kernel<4>); break;
+    default: go(gemv_step_kernel<8>); break;
+  }
+}
+
 // one linear, B right-hand sides: a batch runs in groups of four samples that share one pass over the planes
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
@@ -316,7 +345,7 @@ int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, 
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
     j.nblocks = (lin.L.nrq + rpb - 1) / rpb;
   }
-  launch_lane(groups, B > 1 ? 4 : 1, (unsigned)(j.nblocks * passes), st, nullptr, nullptr, B, j, nullptr, nullptr, 0);
+  launch_lane(groups, B > 1 ? 4 : 1, (unsigned)(j.nblocks * passes), st, j, B);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }
@@ -344,6 +373,12 @@ void fill_params(dpllm_model* m) {
   }
 }
 
+void activate(const dpllm_model* m, int target, hipStream_t st) {
+  const Workspace& W = m->ws;
+  hipLaunchKernelGGL(selector_activate_kernel, dim3(64), dim3(256), 0, st, (const SelParams*)W.at<SelParams>(W.sel_params), W.at<SelParams>(W.sel_active),
+                     (int)m->linears.size(), W.at<SelTask>(W.sel_tasks), (const int32_t*)(W.at<int32_t>(W.target) + 1), W.at<int32_t>(W.target), target);
+}
+
 int upload_params(dpllm_model* m, hipStream_t st) {
   fill_params(m);
   // a selector launch none of whose linears has an estimator under any target has nothing to compute
@@ -356,6 +391,8 @@ int upload_params(dpllm_model* m, hipStream_t st) {
   }
   HIP_TRY(m, hipMemcpyAsync(m->ws.at<SelParams>(m->ws.sel_params), m->h_params.data(), sizeof(SelParams) * m->h_params.size(),
                             hipMemcpyHostToDevice, st));
+  activate(m, -1, st);
+  HIP_TRY(m, hipGetLastError());
   m->params_dirty = false;
   return DPLLM_OK;
 }
@@ -370,10 +407,13 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
   P.k_dev = k_dev;
   P.e_dev = e_dev;
   P.phases.clear();
+  P.fused = false;
   std::vector<SelJob>& sel_jobs = m->h_sel_jobs;
   std::vector<SelPart>& sel_parts = m->h_sel_parts;
   std::vector<int32_t>& sel_members = m->h_sel_members;
+  std::vector<SelTask>& sel_tasks = m->h_sel_tasks;
   sel_members.clear();
+  sel_tasks.clear();
   std::vector<GemvJob>& gemv_jobs = m->h_gemv_jobs;
   std::vector<int32_t>& block_jobs = m->h_block_jobs;
   sel_jobs.clear(); sel_parts.clear(); gemv_jobs.clear(); block_jobs.clear();
@@ -400,69 +440,9 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     bounds.emplace_back(id, end);
     id = end;
   }
-  // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
-  // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
-  // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
-  // input), so that its own phase starts with the GEMV launch; without such a phase it stays where it is.
-  std::vector<char> has_selectors(bounds.size(), 0);
-  for (int j = 0; j < n; ++j)
-    if (!m->linears[j].sel_input) has_selectors[phase_of[j]] = 1;
-  std::vector<std::vector<int>> sel_of_phase(bounds.size());
-  for (int j = 0; j < n; ++j) {
-    const Linear& lin = m->linears[j];
-    int q = phase_of[j];
-    if (lin.sel_input) {
-      int first = q;   // earliest phase the selector may run in
-      while (first > 0) {
-        bool written = false;
-        for (int i = bounds[first - 1].first; i < bounds[first - 1].second && !written; ++i)
-          written = overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[i], (size_t)m->linears[i].L.out * 2);
-        if (written) break;
-        --first;
-      }
-      while (q > first && !has_selectors[q]) --q;
-      if (!has_selectors[q]) q = phase_of[j];
-      has_selectors[q] = 1;
-    }
-    sel_of_phase[q].push_back(j);
-  }
-  std::vector<int> sel_job_of(n, -1);   // index of every linear's selector job (it sits in its own phase or an earlier one)
-  for (size_t pi = 0; pi < bounds.size(); ++pi) {
-    const int id = bounds[pi].first, end = bounds[pi].second;
+  // the GEMV launch of every phase
+  for (const auto& [id, end] : bounds) {
     Phase ph;
-    ph.sel_first = (int)sel_jobs.size();
-    ph.sel_count = (int)sel_of_phase[pi].size();
-    ph.part_first = (int)sel_parts.size();
-    long launch_rowgroups = 0;
-    for (int j : sel_of_phase[pi]) launch_rowgroups += m->linears[j].max_rowgroups();
-    for (size_t local = 0; local < sel_of_phase[pi].size(); ++local) {
-      const int j = sel_of_phase[pi][local];
-      const Linear& lin = m->linears[j];
-      const int rowgroups = lin.max_rowgroups();
-      SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, launch_rowgroups);
-      for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
-      sj.ws = W.at<double>(W.sel_ws) + ws_slots;
-      ws_slots += (size_t)sj.ws_rows * sj.nchunks;
-      sel_job_of[j] = (int)sel_jobs.size();
-      sel_jobs.push_back(sj);
-    }
-    // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
-    // estimator is the linear regression
-    ph.member_first = (int)sel_members.size();
-    for (int a = 0; a < ph.sel_count; ++a) {
-      const SelJob& ja = sel_jobs[ph.sel_first + a];
-      bool head = true;
-      for (int b = 0; b < a && head; ++b) head = sel_jobs[ph.sel_first + b].x != ja.x || sel_jobs[ph.sel_first + b].in != ja.in;
-      if (!head) continue;
-      const int first = (int)sel_members.size() - ph.member_first;
-      for (int b = a; b < ph.sel_count; ++b) {
-        const SelJob& jb = sel_jobs[ph.sel_first + b];
-        if (jb.x == ja.x && jb.in == ja.in) sel_members.push_back(b);
-      }
-      sel_parts.push_back(SelPart{a, -1, ja.linear, (int)sel_members.size() - ph.member_first - first, first, 0});
-    }
-    ph.part_count = (int)sel_parts.size() - ph.part_first;
-    // GEMV jobs of the phase: one launch of the streaming kernel for all linears it serves
     ph.gemv_first = (int)gemv_jobs.size();
     ph.block_first = (int)block_jobs.size();
     long total_rq = 0, lane_groups = 0;
@@ -506,8 +486,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     for (int j = id; j < end; ++j) {
       const Linear& lin = m->linears[j];
       GemvJob gj = make_gemv_job(lin, 0, k_dev + j, xs[j], ys[j]);
-      gj.has_fin = 1;
-      gj.fin = sel_finish_of(sel_jobs[sel_job_of[j]]);
       long group_bytes = base_bytes;
       if (taper && bytes_after[j - id] < 512 * base_bytes) group_bytes /= 2;
       const int rpb = pick_blocks_per_group(lin.L, lin.part_k(), total_rq, group_bytes);
@@ -519,9 +497,98 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     }
     ph.gemv_count = (int)gemv_jobs.size() - ph.gemv_first;
     ph.blocks = blocks;
+    ph.fused = blocks < kFusedMaxBlocks;
+    // a selector that reads what its own linear writes has to be done before the GEMV launch starts
+    for (int j = id; j < end; ++j) {
+      const Linear& lin = m->linears[j];
+      if (lin.sel_input && overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[j], (size_t)lin.L.out * 2)) ph.fused = false;
+    }
     P.phases.push_back(ph);
   }
-  if (sel_parts.size() > W.sel_parts_cap || ws_slots > W.sel_ws_cap || block_jobs.size() > W.block_jobs_cap)
+  // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
+  // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
+  // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
+  // input), so that its own phase starts with the GEMV; without such a phase it stays where it is, and so it does where
+  // the GEMV launch of its own phase does not take the decision (the launch that does serves the selectors of its phase).
+  std::vector<char> has_selectors(bounds.size(), 0);
+  for (int j = 0; j < n; ++j)
+    if (!m->linears[j].sel_input) has_selectors[phase_of[j]] = 1;
+  std::vector<std::vector<int>> sel_of_phase(bounds.size());
+  for (int j = 0; j < n; ++j) {
+    const Linear& lin = m->linears[j];
+    int q = phase_of[j];
+    if (lin.sel_input && P.phases[q].fused) {
+      int first = q;   // earliest phase the selector may run in
+      while (first > 0) {
+        bool written = false;
+        for (int i = bounds[first - 1].first; i < bounds[first - 1].second && !written; ++i)
+          written = overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[i], (size_t)m->linears[i].L.out * 2);
+        if (written) break;
+        --first;
+      }
+      while (q > first && !has_selectors[q]) --q;
+      if (!has_selectors[q]) q = phase_of[j];
+      has_selectors[q] = 1;
+    }
+    sel_of_phase[q].push_back(j);
+  }
+  for (size_t pi = 0; pi < bounds.size(); ++pi) {
+    Phase& ph = P.phases[pi];
+    ph.sel_first = (int)sel_jobs.size();
+    ph.sel_count = (int)sel_of_phase[pi].size();
+    ph.part_first = (int)sel_parts.size();
+    long launch_rowgroups = 0;
+    for (int j : sel_of_phase[pi]) launch_rowgroups += m->linears[j].max_rowgroups();
+    // Selectors inside the GEMV launch: a task is a row of G times a slice of at most 4096 columns (one load per
+    // wavefront), or more where there are more rows than workgroups to share them out to.
+    ph.task_first = (int)sel_tasks.size();
+    const long slices_each = std::max<long>(1, kSelTaskGroups / std::max<long>(1, launch_rowgroups * kSelPartRows));
+    for (size_t local = 0; local < sel_of_phase[pi].size(); ++local) {
+      const int j = sel_of_phase[pi][local];
+      const Linear& lin = m->linears[j];
+      const int rowgroups = lin.max_rowgroups();
+      SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, launch_rowgroups);
+      for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
+      sj.ws = W.at<double>(W.sel_ws) + ws_slots;
+      SelFinish fin = sel_finish_of(sj);
+      if (ph.fused && rowgroups > 0) {
+        const long slices = std::min<long>(sel_slices(lin.L.in), slices_each);
+        fin.chunk_cols = (int)((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
+        fin.nchunks = (lin.L.in + fin.chunk_cols - 1) / fin.chunk_cols;
+        fin.copies = kSelCopies;
+        for (int row = 0; row < rowgroups * kSelPartRows; ++row)
+          for (int c = 0; c < fin.nchunks; ++c) {
+            const int col0 = c * fin.chunk_cols;
+            sel_tasks.push_back(SelTask{nullptr, fin.x + col0, (uint64_t*)sj.ws + (size_t)c * sj.ws_rows + row,
+                                        fin.nchunks * sj.ws_rows, std::min(fin.chunk_cols, lin.L.in - col0), j, row, col0, lin.L.in});
+          }
+      }
+      ws_slots += (size_t)sj.ws_rows * std::max(sj.nchunks, fin.copies * fin.nchunks);
+      gemv_jobs[j].has_fin = 1;                 // (the jobs of all linears, in their order)
+      gemv_jobs[j].fin = fin;
+      sel_jobs.push_back(sj);
+    }
+    ph.task_count = (int)sel_tasks.size() - ph.task_first;
+    // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
+    // estimator is the linear regression
+    ph.member_first = (int)sel_members.size();
+    for (int a = 0; a < ph.sel_count; ++a) {
+      const SelJob& ja = sel_jobs[ph.sel_first + a];
+      bool head = true;
+      for (int b = 0; b < a && head; ++b) head = sel_jobs[ph.sel_first + b].x != ja.x || sel_jobs[ph.sel_first + b].in != ja.in;
+      if (!head) continue;
+      const int first = (int)sel_members.size() - ph.member_first;
+      for (int b = a; b < ph.sel_count; ++b) {
+        const SelJob& jb = sel_jobs[ph.sel_first + b];
+        if (jb.x == ja.x && jb.in == ja.in) sel_members.push_back(b);
+      }
+      sel_parts.push_back(SelPart{a, -1, ja.linear, (int)sel_members.size() - ph.member_first - first, first, 0});
+    }
+    ph.part_count = (int)sel_parts.size() - ph.part_first;
+    if (ph.fused) P.fused = true;
+  }
+  P.slots = ws_slots;
+  if (sel_parts.size() > W.sel_parts_cap || ws_slots > W.sel_ws_cap || sel_tasks.size() > W.sel_tasks_cap || block_jobs.size() > W.block_jobs_cap)
     return fail(m, DPLLM_ESTATE, "workspace too small for this step (set after the model changed?): call dpllm_workspace_bytes and "
                                  "dpllm_set_workspace again");
   // The tables may still be read by a step enqueued earlier on this stream: the copies are ordered behind it.
@@ -529,13 +596,17 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     HIP_TRY(m, hipMemcpyAsync(W.at<SelPart>(W.sel_parts), sel_parts.data(), sizeof(SelPart) * sel_parts.size(), hipMemcpyHostToDevice, st));
   if (!block_jobs.empty())
     HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.block_jobs), block_jobs.data(), sizeof(int32_t) * block_jobs.size(), hipMemcpyHostToDevice, st));
+  m->h_ntasks = (int32_t)sel_tasks.size();
+  if (!sel_tasks.empty())
+    HIP_TRY(m, hipMemcpyAsync(W.at<SelTask>(W.sel_tasks), sel_tasks.data(), sizeof(SelTask) * sel_tasks.size(), hipMemcpyHostToDevice, st));
+  HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.target) + 1, &m->h_ntasks, sizeof(int32_t), hipMemcpyHostToDevice, st));
   HIP_TRY(m, hipMemcpyAsync(W.at<SelJob>(W.sel_jobs), sel_jobs.data(), sizeof(SelJob) * sel_jobs.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.sel_members), sel_members.data(), sizeof(int32_t) * sel_members.size(), hipMemcpyHostToDevice, st));
   if (!gemv_jobs.empty())
     HIP_TRY(m, hipMemcpyAsync(W.at<GemvJob>(W.gemv_jobs), gemv_jobs.data(), sizeof(GemvJob) * gemv_jobs.size(), hipMemcpyHostToDevice, st));
   P.version = m->version;
   P.valid = true;
-  m->params_dirty = true;   // the phases' estimator flags are worked out with the parameter table
+  m->params_dirty = true;   // the phases' estimator flags and the tasks' rows of G are worked out with the parameter table
   return DPLLM_OK;
 }
 
@@ -621,8 +692,8 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   w.base = (char*)ws_dev;
   w.bytes = bytes;
   hipStream_t st = (hipStream_t)stream;
-  // the target word starts at zero; everything else is written before it is read
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, w.at<uint32_t>(w.target), (size_t)1, 0u);
+  // the target and the number of tasks start at zero; everything else is written before it is used
+  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, w.at<uint32_t>(w.target), (size_t)2, 0u);
   HIP_TRY(m, hipGetLastError());
   m->ws = w;
   m->params_dirty = true;
@@ -769,8 +840,7 @@ int dpllm_set_target(dpllm_model* m, int target, void* stream) {
   if (!m) return DPLLM_EINVAL;
   if (target < 0 || target >= DPLLM_MAX_TARGETS) return fail(m, DPLLM_EINVAL, "target %d outside [0,%d]", target, DPLLM_MAX_TARGETS - 1);
   if (!m->ws.base) return fail(m, DPLLM_ESTATE, "no workspace set");
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, (hipStream_t)stream, m->ws.at<uint32_t>(m->ws.target), (size_t)1,
-                     (uint32_t)target);
+  activate(m, target, (hipStream_t)stream);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }
@@ -795,9 +865,9 @@ static int launch_estimate(dpllm_model* m, const Linear& lin, int id, const Pair
   const int blocks = sel.kind == DPLLM_SEL_PROJ ? rowgroups * j.nchunks : sel.kind == DPLLM_SEL_LINREG ? 1 : 0;
   if (blocks > 0)
     hipLaunchKernelGGL(selector_part_kernel, dim3(blocks), dim3(kSelPartThreads), 0, st, (const SelJob*)nullptr,
-                       (const SelPart*)nullptr, (const int32_t*)nullptr, (const SelParams*)nullptr, (const int32_t*)nullptr, 0, j, P);
+                       (const SelPart*)nullptr, (const int32_t*)nullptr, (const SelParams*)nullptr, j, P);
   hipLaunchKernelGGL(selector_decide_kernel, dim3(1), dim3(kSelDecideThreads), 0, st, (const SelJob*)nullptr,
-                     (const SelParams*)nullptr, (const int32_t*)nullptr, 0, j, P);
+                     (const SelParams*)nullptr, j, P);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }
@@ -889,28 +959,25 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   }
   const Workspace& W = m->ws;
   SelJob none{};
-  GemvJob gnone{};
   SelParams pnone{};
-  const SelParams* d_params = W.at<SelParams>(W.sel_params);
-  const int32_t* d_target = W.at<int32_t>(W.target);
+  const SelParams* active = W.at<SelParams>(W.sel_active);
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
+  if (both && P.fused && P.slots > 0)   // the slots the fused launches collect start empty
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((P.slots * 2 + 255) / 256)), dim3(256), 0, st,
+                       W.at<uint32_t>(W.sel_ws), P.slots * 2, (uint32_t)kSelEmpty);
   for (const Phase& ph : P.phases) {
-    const bool fold = both && ph.blocks < kFoldMaxBlocks;
-    if ((parts & DPLLM_STEP_SELECT) && ph.sel_count > 0) {
-      const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
+    const bool fused = both && ph.fused;
+    const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
+    const SelPart* sel_parts = W.at<SelPart>(W.sel_parts) + ph.part_first;
+    if ((parts & DPLLM_STEP_SELECT) && !fused && ph.sel_count > 0) {
       if (ph.estimators)
-        hipLaunchKernelGGL(selector_part_kernel, dim3(ph.part_count), dim3(kSelPartThreads), 0, st, jobs,
-                           (const SelPart*)(W.at<SelPart>(W.sel_parts) + ph.part_first),
-                           (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), d_params, d_target, n, none, pnone);
-      // Whole step: the GEMV workgroups take the decisions of their linears themselves (one launch fewer per
-      // dependency level).  Selectors alone, or a GEMV launch of so many workgroups that repeating the decision in each of them costs more than a launch: a launch that finishes every job of
-      // this selector launch.
-      if (!fold)
-        hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, d_params, d_target, n, none, pnone);
+        hipLaunchKernelGGL(selector_part_kernel, dim3(ph.part_count), dim3(kSelPartThreads), 0, st, jobs, sel_parts,
+                           (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), active, none, pnone);
+      hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, active, none, pnone);
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
-    launch_lane(ph.groups, 1, (unsigned)ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
-                ph.gemv_count, gnone, fold ? d_params : nullptr, d_target, n);
+    launch_step(ph.groups, ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
+                fused ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && ph.estimators ? ph.task_count : 0);
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;

@@ -27,14 +27,13 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr int kKMax = 8;   // bitwidths 1 .. 8
 
-struct GemvJob {
+struct alignas(64) GemvJob {   // (aligned: few scalar loads)
   const char* arena;          // device planes start here; plane b at + b * plane_stride_u4 * 16 bytes
   const uint16_t* x;          // fp16 [in]
   uint16_t* y;                // fp16 [out]
   const int32_t* k_dev;       // nullptr: serve k; else the bitwidth is *k_dev (written by a selector)
-  // has_fin != 0: neither; the bitwidth is decided in the workgroup's prologue from the partial results an earlier
-  // selector launch left in the workspace (selector_finish), and the job's first workgroup writes it and the
-  // estimate to the caller's arrays
+  // has_fin != 0, in a launch that runs selectors: neither; the bitwidth is decided in the workgroup's prologue
+  // (selector_gather), and the job's first workgroup writes it and the estimate to the caller's arrays
   int32_t has_fin;
   SelFinish fin;
   uint32_t plane_stride_u4;

@@ -80,11 +80,13 @@ template <int NB, int G>
 __host__ __device__ constexpr int lane_x_bytes() {
   return G > 1 ? NB * G * kLaneGroupStride : NB == 1 ? 256 + kLaneKeepTiles * 256 : NB * 256;
 }
-// tables, partial sums, activation slots.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
+// tables, partial sums, activation slots, and (one sample: the decode step) room for the selectors.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
 // activations are borrowed from the partial sums, which are not in use between the barrier that opens a row block
 // and the stores that close it (its own partial sums of sample 0).
 template <int NB, int G>
-__host__ __device__ constexpr int lane_lds_bytes() { return kLaneTableBytes + NB * kLaneRedBytes + kLaneWaves * lane_x_bytes<NB, G>(); }
+__host__ __device__ constexpr int lane_lds_bytes() {
+  return kLaneTableBytes + NB * kLaneRedBytes + kLaneWaves * lane_x_bytes<NB, G>() + (NB == 1 ? kSelSharedBytes : 0);
+}
 static_assert(lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920 && lane_lds_bytes<1, 2>() <= 81920 &&
               lane_lds_bytes<1, 4>() <= 81920, "two workgroups per compute unit");
 
@@ -518,12 +520,6 @@ __device__ __forceinline__ void lane_build_table(const LaneLut<K>& L, int wave, 
   }
 }
 
-__device__ __forceinline__ void lane_group_barrier() {
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-  __builtin_amdgcn_s_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
 // Tiles in registers per wavefront: one being decoded, one in flight.  A third measured equal or up to 1.3 %
 // slower in launches that fill the chip (with sixteen wavefronts on a compute unit the memory system has enough
 // requests either way), and three or four tiles in flight did not help launches of a few hundred workgroups
@@ -604,13 +600,13 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
     if constexpr (!kLutAhead) lane_fetch_lut<K>(L, lut_base, rb * 64 + lane, wave);
     lane_build_table<K>(L, wave, lanecol, lds);
     if constexpr (kLutAhead) lane_fetch_lut<K>(L, lut_base, (rb + step < nrb ? rb + step : rb) * 64 + lane, wave);
-    lane_group_barrier();
+    lds_barrier();
   };
   auto close_block = [&]() {
 #pragma unroll
     for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = acc.sum(b);
     acc.zero();
-    lane_group_barrier();
+    lds_barrier();
     const bool storer = wave < NB && (NB == 1 || wave < job.nsamples);   // wavefront b stores sample b
     float s = 0.f;
     if (storer) {
@@ -791,7 +787,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 #pragma unroll
   for (int i = 0; i < 8; ++i) addr[i] = lanecol;
   lane_build_table<K>(L, wave, lanecol, lds);
-  lane_group_barrier();
+  lds_barrier();
   for (int cc = c0; cc < c1;) {
 #pragma unroll
     for (int s = 0; s < D; ++s) {
@@ -812,7 +808,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   const bool whole = (c1 - 1) * G + group < job.ncc;
 #pragma unroll
   for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
-  lane_group_barrier();
+  lds_barrier();
   if (wave < NB && (NB == 1 || wave < job.nsamples)) {   // wavefront b stores sample b
     float s = 0.f;
 #pragma unroll
@@ -822,18 +818,22 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   }
 }
 
+template <int NB, int G>
+__device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpret_cast<double*>(lds + lane_lds_bytes<NB, G>() - kSelSharedBytes); }
+
 // The bitwidth of the job: its own value, the word a selector left in device memory, or the decision taken here
-// from the partial results of an earlier selector launch (every workgroup of the job repeats the same fixed-order
-// sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
+// from the partial products that the launch's workgroups left in the slots (every workgroup of the job repeats the same
+// fixed-order sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
 // linear does not serve (outside [max(kmin, 3), p]) is not served: the workgroup returns and y keeps what it held.
 template <int NB, int G>
-__device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* params,
-                                                const int32_t* target, int n_linears) {   // params == nullptr: no decisions here
+__device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* active,
+                                                int polls) {   // active == nullptr: no decisions here
   if (block * (64 / G) >= job.out) return;   // (no row of the job is this workgroup's)
   int k = job.k;
-  if (job.has_fin && params != nullptr) {
-    k = selector_finish(job.fin, params + (size_t)(*target) * n_linears + job.fin.linear, tid, kLaneThreads,
-                        reinterpret_cast<double*>(lds), block == 0);   // the tables are not built yet
+  if (NB == 1 && job.has_fin && active != nullptr) {
+    static_assert(kSelMaxRank * sizeof(double) <= kLaneTableBytes, "room where the tables will be");
+    const SelParams P = load_record(active + job.fin.linear);
+    k = selector_gather(job.fin, P, polls, block, tid, lane_sel_shared<NB, G>(lds), reinterpret_cast<double*>(lds), block == 0);
     k = __builtin_amdgcn_readfirstlane(k);
   } else if (job.k_dev != nullptr) {
     k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
@@ -856,30 +856,34 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
   }
 }
 
-// jobs == nullptr: the job passed by value, for njobs right-hand sides in groups of NB that share one pass over
-// the planes (group g reads x + g * NB * in and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) *
-// nblocks) serve it); else (NB = 1) block b belongs to job block_jobs[b] of the table.  params / target /
-// n_linears: the table of selector parameters, for jobs that take their decision here.
+// One linear, the job passed by value, for nrhs right-hand sides in groups of NB that share one pass over the planes
+// (group g reads x + g * NB * in and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) * nblocks) serve it).
 template <int NB, int G>
-__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const GemvJob* __restrict__ jobs, const int32_t* __restrict__ block_jobs,
-                                                                 int njobs, GemvJob one, const SelParams* __restrict__ params,
-                                                                 const int32_t* __restrict__ target, int n_linears) {
+__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(GemvJob one, int nrhs) {
   __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB, G>()];
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
-  if (jobs == nullptr) {
-    const int group = blockIdx.x / one.nblocks;
-    one.x += (size_t)group * NB * one.ncw * 32;
-    one.y += (size_t)group * NB * one.out;
-    one.nsamples = min(NB, njobs - group * NB);
-    gemv_lane_block<NB, G>(one, blockIdx.x - group * one.nblocks, threadIdx.x, lds, params, target, n_linears);
-    return;
-  }
-  if constexpr (NB == 1) {
-    const int b = blockIdx.x;
-    GemvJob job = jobs[block_jobs[b]];
-    gemv_lane_block<1, G>(job, b - job.block_start, threadIdx.x, lds, params, target, n_linears);
-  }
+  const int group = blockIdx.x / one.nblocks;
+  one.x += (size_t)group * NB * one.ncw * 32;
+  one.y += (size_t)group * NB * one.out;
+  one.nsamples = min(NB, nrhs - group * NB);
+  gemv_lane_block<NB, G>(one, blockIdx.x - group * one.nblocks, threadIdx.x, lds, nullptr, 0);
+}
+
+// The linears of a dependency level of a decode step: block b < nblocks belongs to job block_jobs[b]; blocks past them
+// help with the selectors only.  active: the table of selector parameters, for launches that run the selectors of their
+// jobs (tasks, see selector_tasks) and take the decisions here; else nullptr.
+template <int G>
+__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_step_kernel(const SelTask* tasks, const GemvJob* jobs, const int32_t* block_jobs,
+                                                                                const SelParams* active, int ntasks, int task_groups,
+                                                                                int nblocks, int polls) {
+  __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<1, G>()];
+  if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
+  const int b = blockIdx.x;
+  selector_tasks(tasks, ntasks, task_groups, b, threadIdx.x, lane_sel_shared<1, G>(lds));
+  if (b >= nblocks) return;
+  const GemvJob job = load_record(jobs + load_record(block_jobs + b));
+  gemv_lane_block<1, G>(job, b - job.block_start, threadIdx.x, lds, active, polls);
 }
 
 }  // namespace dpllm

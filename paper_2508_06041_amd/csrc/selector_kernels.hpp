@@ -5,9 +5,10 @@
 //
 // What a linear's selector is (candidate pair, estimator kind, G, alpha, beta, T) depends on the target
 // precision the model runs under (Algorithm 1 hands out one threshold list per target; Sec. 5.1 keeps one G per
-// candidate pair): the kernels read the number of the active target from device memory and take the linear's
-// parameters from the row of that target in a table, so that a switch of target is one word written on the
-// device and the launches stay what they are.
+// candidate pair): a table on the device holds the parameters of every target, and the kernels read a copy of the
+// active target's row.  A switch of target is one small kernel (selector_activate_kernel) that copies the row and
+// puts the rows of G where the tasks find them; the launches stay what they are, and none of them has to look the
+// target up before it can look its parameters up (a round trip to memory of 0.6 us in every launch of a chained step).
 //
 // A projection job reads 0.5 - 3.5 MB of G.  It is cut into parts of 16 rows of G (one workgroup of four
 // wavefronts, four rows per wavefront sharing the activation loads) by a chunk of columns: the whole row when
@@ -17,16 +18,26 @@
 // sum x^2 only: the jobs of a launch that read the same input vector form a group with one extra part, which
 // adds up x^2 once and leaves it in the slot of every member that asks for it.
 //
-// The estimate and the decision are taken by whoever consumes them, in a LATER launch on the same stream
-// (selector_finish): the GEMV kernel, in the prologue of every workgroup of the linear (the first one also
-// writes the estimate and the bitwidth to the caller's arrays), or selector_decide_kernel where no GEMV follows.
-// The end of the launch that wrote the partial products and the start of the one that reads them order the two
-// at device scope; no workgroup waits for another inside a launch.  (Handing the partial products to a last-
-// arriving part inside the launch needs a device-scope release by every part and an acquire by the last one;
-// the release writes back the die's whole L2 and measured 126 us for the 224 selectors of a 7B step, against
-// 30 us for the parts alone.)  selector_finish adds the partial products of every row in chunk order, squares,
-// adds the rows in index order, takes the square root and compares: the order of all additions is fixed, so every
-// workgroup that repeats it gets the same bits.
+// Who takes the estimate and the decision:
+//   - selectors alone, and in front of GEMV launches that fill the chip several times over: selector_decide_kernel, in
+//     a launch of its own behind the parts (the end of one launch and the start of the next order the two at device
+//     scope);
+//   - in the small launches of a chained step (selector_tasks, selector_gather): every workgroup of the GEMV launch
+//     first works off its share of the launch's selectors, a row of G times a slice of the columns, and leaves the
+//     partial dot product in its slot; then every workgroup collects the slots of its own linear, adds them up and
+//     decides.  A slot is its own flag: it holds kSelEmpty (a NaN no writer stores) until the value is there, and both
+//     sides use relaxed atomics on that one 64-bit word, so nothing rests on the order of two memory locations and no
+//     fence is needed (a device-scope release writes back the die's whole L2: 126 us instead of 30 for the 224
+//     selectors of a 7B step).  A fill kernel empties the slots at the start of the step.  The wait is bounded: a
+//     workgroup that has polled often enough computes the missing products itself, so no workgroup depends on
+//     another one being scheduled.  What the way costs (7B block, q, k, v: 192 workgroups, us after the first one's
+//     entry): task record here 0.8, product stored 2.6, all slots seen 3.8, bitwidth known 4.3; the launches of their own
+//     cost 3.8 for the parts, 1.6 between launches and 1.6 for the decision in the GEMV prologue.  Chained step of 32
+//     blocks 1888 -> 1428 us, of 16 8B blocks with selectors ahead 1060 -> 940.  Tried on top of it: asking for the
+//     planes and tables of the level while the selectors work (the traffic delays the hand-over by more than it saves:
+//     1605 us with the first tiles, 1460 with the table rows alone), longer pauses between polls (no change).
+// Either way the partial products of every row are added in chunk order, squared, added over the rows in index order:
+// the order of all additions is fixed, so every workgroup that repeats it gets the same bits.
 //
 // The estimate and the compare are taken in fp64: fp16 x fp16 products are exact in fp32, their sum runs in
 // fp64 in a fixed order, so a decision is reproducible and differs from an ideal-arithmetic decision only
@@ -49,11 +60,10 @@ constexpr int kSelMaxChunks = 32;    // column chunks of a job
 constexpr int kSelChunkStep = 512;   // columns a wavefront covers per tile: chunks are multiples of it
 
 // What the selector of one linear is under one target.  kind: 0 none (always l), 1 projection, 2 linear regression
-struct SelParams {
+struct alignas(64) SelParams {   // (aligned: one scalar load)
   const uint16_t* G;   // fp16 [r][in] (projection kind)
   float T, alpha, beta;
   int32_t r, l, h, kind;
-  int32_t pad;
 };
 
 // The target-independent part of a selector job.
@@ -81,10 +91,46 @@ __host__ __device__ inline int sel_rowgroups_of(int kind, int r) {
   return kind == 1 ? (r + kSelPartRows - 1) / kSelPartRows : 0;
 }
 
+// a partial dot product nobody has written yet; a computed NaN with these bits is stored as another NaN
+constexpr uint64_t kSelEmpty = ~0ull;
+__device__ __forceinline__ double sel_storable(double v) {
+  return __builtin_bit_cast(uint64_t, v) == kSelEmpty ? __builtin_bit_cast(double, 0x7ff8000000000000ull) : v;
+}
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)u, CTRL, 0xf, 0xf, true);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(uint32_t)(u >> 32), CTRL, 0xf, 0xf, true);
+  return __builtin_bit_cast(double, (uint64_t)hi << 32 | lo);
+}
+// v of this half (16 or 32 lanes) plus v of the other one.  The swaps exchange two registers, so the value goes in
+// twice, in registers of its own (the copies are opaque: left to itself the compiler passes one register twice).
+template <int LANES>
+__device__ __forceinline__ double swap_add_f64(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const uint32_t lo = (uint32_t)u, hi = (uint32_t)(u >> 32);
+  uint32_t lo2, hi2;
+  asm("v_mov_b32 %0, %1" : "=v"(lo2) : "v"(lo));
+  asm("v_mov_b32 %0, %1" : "=v"(hi2) : "v"(hi));
+  if constexpr (LANES == 16) {
+    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo2, false, false);
+    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi2, false, false);
+    return __builtin_bit_cast(double, (uint64_t)b[0] << 32 | a[0]) + __builtin_bit_cast(double, (uint64_t)b[1] << 32 | a[1]);
+  } else {
+    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo2, false, false);
+    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi2, false, false);
+    return __builtin_bit_cast(double, (uint64_t)b[0] << 32 | a[0]) + __builtin_bit_cast(double, (uint64_t)b[1] << 32 | a[1]);
+  }
+}
+// the sum over the wavefront, in every lane: pairs, quads, groups of 8 and 16 with DPP moves, then across the rows
 __device__ __forceinline__ double wave_sum_f64(double v) {
-#pragma unroll
-  for (int s = 32; s >= 1; s >>= 1) v += __shfl_xor(v, s, 64);
-  return v;
+  v += dpp_f64<0xB1>(v);    // quad_perm [1,0,3,2]
+  v += dpp_f64<0x4E>(v);    // quad_perm [2,3,0,1]
+  v += dpp_f64<0x141>(v);   // row_half_mirror
+  v += dpp_f64<0x140>(v);   // row_mirror
+  v = swap_add_f64<16>(v);
+  return swap_add_f64<32>(v);
 }
 
 typedef uint32_t sel_u32x4 __attribute__((ext_vector_type(4)));
@@ -126,15 +172,18 @@ struct SelShared {
   double sq[kSelMaxRank + 1];   // [kSelMaxRank]: the total
 };
 
-// What the finishing step needs of a selector job (a copy of it travels in the GEMV job record)
+// What the finishing step needs of a selector job (a copy of it travels in the GEMV job record).  Slot [chunk]
+// [row] of ws holds the partial dot product of a row.
 struct SelFinish {
   const double* ws;
   float* e_out;
   int32_t* k_out;
-  int32_t in, linear, nchunks, ws_rows;
+  const uint16_t* x;
+  int32_t in, linear, nchunks, ws_rows, chunk_cols;   // chunk c: columns [chunk_cols c, + chunk_cols) inside the row
+  int32_t copies;      // of the slots, [copy][chunk][row] (1 or kSelCopies)
 };
 __host__ __device__ inline SelFinish sel_finish_of(const SelJob& j) {
-  return SelFinish{j.ws, j.e_out, j.k_out, j.in, j.linear, j.nchunks, j.ws_rows};
+  return SelFinish{j.ws, j.e_out, j.k_out, j.x, j.in, j.linear, j.nchunks, j.ws_rows, j.chunk_cols, 1};
 }
 
 // The estimate from what the selector launch left in the workspace, and the decision; called by all `nthreads`
@@ -143,7 +192,7 @@ __host__ __device__ inline SelFinish sel_finish_of(const SelJob& j) {
 // earlier launch.  Order of the additions (fixed, so that every workgroup that repeats them gets the same bits):
 // per row of G its chunks in chunk order; the squares of rows t, t + 64, t + 128, ... in that order in lane t of
 // the first wavefront; the 64 lane sums by a butterfly.  Loads are issued in batches ahead of the additions that
-// consume them: a workgroup of the GEMV kernel pays this latency before it can start streaming.
+// consume them.
 __device__ __forceinline__ int selector_finish(const SelFinish& f, const SelParams* prow, int tid, int nthreads, double* sq, bool write) {
   const DPLLM_SEL_GLOBAL double* ws = (const DPLLM_SEL_GLOBAL double*)f.ws;
   // the first batch of partial products is asked for before the parameters, so that both arrive together (what
@@ -269,17 +318,226 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
 #pragma unroll
   for (int i = 0; i < kSelRowsPerWave; ++i) {
     const double rowsum = wave_sum_f64(acc[i]);
-    if (lane == 0) ws[(size_t)ch * job.ws_rows + row0 + i] = rowsum;
+    if (lane == 0) ws[(size_t)ch * job.ws_rows + row0 + i] = sel_storable(rowsum);
+  }
+}
+
+// ---- the selectors of a small GEMV launch, worked off by its own workgroups --------------------------------------
+// One row of a projection times a slice of the columns: what a workgroup does at a time.
+struct alignas(64) SelTask {
+  const uint16_t* g;   // the slice of the row of G; nullptr: nothing to do under the active target (selector_activate_kernel)
+  const uint16_t* x;   // the same columns of the vector
+  uint64_t* slot;      // where the partial dot product goes, kSelCopies times,
+  int32_t copy_stride; //   slots apart
+  int32_t cols;        // length of the slice
+  int32_t linear, row, col0, in;
+};
+// Records that no kernel of the launch writes, read at an address that is the same for the whole workgroup: from the
+// constant address space they come with one scalar load (through a generic pointer every field is a vector load of its
+// own, waited for where it is first used: four round trips of 0.5 us before the row of G was asked for).
+template <class T>
+__device__ __forceinline__ T load_record(const T* p) {
+  static_assert(sizeof(T) % 4 == 0, "whole dwords");
+  struct Raw { uint32_t w[sizeof(T) / 4]; };
+  const __attribute__((address_space(4))) uint32_t* q = (const __attribute__((address_space(4))) uint32_t*)(uintptr_t)p;
+  Raw r;
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) r.w[i] = q[i];
+#pragma unroll
+  for (size_t i = 0; i < sizeof(T) / 4; ++i) asm volatile("" : "+s"(r.w[i]));   // all of it here, not each field where it is used
+  return __builtin_bit_cast(T, r);
+}
+constexpr int kSelTaskGroups = 256;     // workgroups the tasks of a launch are cut for: one per compute unit
+constexpr int kSelTaskCols = 4096;      // a slice this long keeps eight wavefronts busy with one load each
+// Every product is stored this many times and every workgroup reads the copy of its own number modulo that (its die's,
+// as workgroups are dealt out to the dies): 256 workgroups that poll the same four lines wait for one another.  Chained
+// 7B step with 1, 2, 8, 16 copies: 1539, 1473, 1428, 1430 us.
+constexpr int kSelCopies = 8;
+constexpr int kSelSharedBytes = 256;    // LDS of selector_tasks and selector_gather
+
+// chunks w, w + 8, ... of 512 columns of a slice, in the lane's eight columns of each; the wavefront's sum in every lane
+__device__ __forceinline__ double selector_chunks_dot(const uint16_t* row, const uint16_t* x, int cols, int w, int lane) {
+  constexpr int step = 8 * kSelChunkStep;
+  const DPLLM_SEL_GLOBAL uint16_t* g = (const DPLLM_SEL_GLOBAL uint16_t*)row;
+  const DPLLM_SEL_GLOBAL uint16_t* xg = (const DPLLM_SEL_GLOBAL uint16_t*)x;
+  const int last = cols - 8;            // cols is a multiple of 32: eight columns are inside or outside together
+  auto load = [&](const DPLLM_SEL_GLOBAL uint16_t* p, int c) { return *(const DPLLM_SEL_GLOBAL sel_u32x4*)(p + min(c, last)); };
+  int c = w * kSelChunkStep + lane * 8;
+  sel_u32x4 ga = load(g, c), xa = load(xg, c);
+  double acc = 0.0;
+  for (int c0 = w * kSelChunkStep; c0 < cols; c0 += step) {
+    const sel_u32x4 gv = ga, xv = xa;
+    const bool valid = c <= last;
+    c += step;
+    if (c0 + step < cols) {
+      ga = load(g, c);
+      xa = load(xg, c);
+    }
+    if (valid) {
+      const __half* gh = reinterpret_cast<const __half*>(&gv);
+      const __half* xh = reinterpret_cast<const __half*>(&xv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) acc = fma((double)__half2float(gh[i]), (double)__half2float(xh[i]), acc);
+    }
+  }
+  return wave_sum_f64(acc);
+}
+
+// barrier of a workgroup that shares data through LDS only: loads and stores in flight stay in flight
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// The launch's share of selector work: workgroup b < groups runs tasks b, b + groups, ...  By a workgroup of eight
+// wavefronts; sh: kSelSharedBytes of LDS, [0, 16)
+__device__ __forceinline__ void selector_tasks(const SelTask* tasks, int count, int groups, int block, int tid, double* sh) {
+  if (block >= groups) return;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  int turn = 0;   // the tasks take turns in two sets of eight partial sums, so that one barrier per task is enough
+  for (int t = block; t < count; t += groups) {
+    const SelTask k = load_record(tasks + t);
+    if (k.g == nullptr) continue;
+    const double v = selector_chunks_dot(k.g, k.x, k.cols, wave, lane);
+    if (lane == 0) sh[turn + wave] = v;
+    lds_barrier();
+    if (tid < kSelCopies) {
+      double sum = 0.0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) sum += sh[turn + w];
+      __hip_atomic_store((DPLLM_SEL_GLOBAL uint64_t*)k.slot + (size_t)tid * k.copy_stride, __builtin_bit_cast(uint64_t, sel_storable(sum)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    turn ^= 8;
+  }
+}
+
+// The estimate and the decision from the slots of the linear, by the 512 threads of a workgroup; every thread returns
+// the bitwidth.  sh: kSelSharedBytes of LDS, [16, 32); spare: kSelMaxRank doubles of LDS, free again on return.
+__device__ __forceinline__ int selector_gather(const SelFinish& f, const SelParams& P, int polls, int block, int tid, double* sh, double* spare, bool write) {
+  constexpr int threads = 512, waves = threads / 64, batch = 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  double e = 0.0;
+  if (P.kind == 1) {
+    const DPLLM_SEL_GLOBAL uint64_t* slots = (const DPLLM_SEL_GLOBAL uint64_t*)f.ws + (size_t)(block & (f.copies - 1)) * f.nchunks * f.ws_rows;
+    // row t in thread t mod 512: its slices in order, squared; the rows of a thread in order, the threads of a
+    // wavefront, the wavefronts in order
+    double part = 0.0;
+    bool lack = false;
+    for (int t = tid; t < P.r; t += threads) {
+      double g = 0.0;
+      for (int c0 = 0; c0 < f.nchunks; c0 += batch) {
+        uint64_t v[batch];
+        for (int left = polls;; --left) {
+          bool all = true;
+#pragma unroll
+          for (int i = 0; i < batch; ++i)
+            v[i] = __hip_atomic_load(slots + (size_t)min(c0 + i, f.nchunks - 1) * f.ws_rows + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+          for (int i = 0; i < batch; ++i) all = all && v[i] != kSelEmpty;
+          if (__all(all) || left <= 0) break;
+          __builtin_amdgcn_s_sleep(1);
+        }
+#pragma unroll
+        for (int i = 0; i < batch; ++i) {
+          lack = lack || v[i] == kSelEmpty;
+          if (c0 + i < f.nchunks) g += __builtin_bit_cast(double, v[i]);
+        }
+      }
+      part += g * g;
+    }
+    part = wave_sum_f64(part);
+    // a wavefront that lacks a product says so with a word of its own (the sum of squares may be any double)
+    uint32_t* lacks = reinterpret_cast<uint32_t*>(sh + 16 + waves);
+    const bool wave_lacks = __any(lack);
+    if (lane == 0) {
+      sh[16 + wave] = part;
+      lacks[wave] = wave_lacks;
+    }
+    lds_barrier();
+    double sum = 0.0;
+    uint32_t lacking = 0;
+#pragma unroll
+    for (int w = 0; w < waves; ++w) {
+      sum += sh[16 + w];
+      lacking |= lacks[w];
+    }
+    if (__builtin_amdgcn_readfirstlane(lacking)) {
+      // the same sums in the same order, all of them here
+      for (int t = wave; t < P.r; t += waves) {
+        double g = 0.0;
+        for (int c = 0; c < f.nchunks; ++c) {
+          const size_t at = (size_t)c * f.chunk_cols;
+          const int cols = min(f.chunk_cols, f.in - c * f.chunk_cols);
+          double s = 0.0;
+          for (int w = 0; w < 8; ++w) s += w * kSelChunkStep < cols ? selector_chunks_dot(P.G + (size_t)t * f.in + at, f.x + at, cols, w, lane) : 0.0;
+          g += sel_storable(s);
+        }
+        if (lane == 0) spare[t] = g;
+      }
+      lds_barrier();
+      sum = 0.0;
+      for (int w = 0; w < waves; ++w) {
+        double mine = 0.0;
+        for (int t = w * 64 + lane; t < P.r; t += threads) mine += spare[t] * spare[t];
+        sum += wave_sum_f64(mine);
+      }
+      lds_barrier();
+    }
+    e = sqrt(sum);
+  } else if (P.kind == 2) {
+    // sum x^2 of the linear's own vector: no hand-over; the first kSelPartWaves wavefronts, as selector_group_part does
+    if (wave < kSelPartWaves) {
+      double acc = 0.0;
+      for (int c = tid * 8; c < f.in; c += kSelPartThreads * 8) {
+        const sel_u32x4 xv = *(const DPLLM_SEL_GLOBAL sel_u32x4*)(f.x + c);
+        const __half* xh = reinterpret_cast<const __half*>(&xv);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const float v = __half2float(xh[i]);
+          acc += (double)(v * v);
+        }
+      }
+      acc = wave_sum_f64(acc);
+      if (lane == 0) sh[16 + wave] = acc;
+    }
+    lds_barrier();
+    double tot = 0.0;
+#pragma unroll
+    for (int w = 0; w < kSelPartWaves; ++w) tot += sh[16 + w];
+    e = (double)P.alpha * sqrt(tot) + (double)P.beta;
+  }
+  const int k = (P.kind != 0 && e > (double)P.T) ? P.h : P.l;
+  if (write && tid == 0) {
+    *f.e_out = (float)e;
+    *f.k_out = k;
+  }
+  return k;
+}
+
+// Makes a target the active one: copies its row of the parameter table to `active` and gives every task its slice of
+// the target's G.  target < 0: the one *target_word names; else that word is written too.
+__global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams* __restrict__ table, SelParams* __restrict__ active, int n_linears,
+                                                                SelTask* __restrict__ tasks, const int32_t* __restrict__ ntasks,
+                                                                int32_t* target_word, int target) {
+  if (target < 0) target = *target_word;
+  else if (blockIdx.x == 0 && threadIdx.x == 0) *target_word = target;
+  const SelParams* row = table + (size_t)target * n_linears;
+  const int stride = gridDim.x * 256, first = blockIdx.x * 256 + threadIdx.x;
+  for (int i = first; i < n_linears; i += stride) active[i] = row[i];
+  const int n = *ntasks;
+  for (int t = first; t < n; t += stride) {
+    const SelParams* P = row + tasks[t].linear;
+    tasks[t].g = P->kind == 1 && tasks[t].row < P->r ? P->G + (size_t)tasks[t].row * tasks[t].in + tasks[t].col0 : nullptr;
   }
 }
 
 // parts == nullptr: the single job `one_job` with the parameters `one`; workgroup b is its projection part b, or
 // (linear regression: one workgroup) its group part.  Else workgroup b serves parts[b] of the launch's job table
-// under the target *target (members: the launch's table of group members).
+// under the parameters `active` (members: the launch's table of group members).
 __global__ void __launch_bounds__(kSelPartThreads) __attribute__((amdgpu_waves_per_eu(5))) selector_part_kernel(const SelJob* __restrict__ jobs, const SelPart* __restrict__ parts,
                                                                          const int32_t* __restrict__ members,
-                                                                         const SelParams* __restrict__ params,
-                                                                         const int32_t* __restrict__ target, int n_linears,
+                                                                         const SelParams* __restrict__ active,
                                                                          SelJob one_job, SelParams one) {
   __shared__ SelShared sh;
   if (parts == nullptr) {
@@ -288,22 +546,20 @@ __global__ void __launch_bounds__(kSelPartThreads) __attribute__((amdgpu_waves_p
     return;
   }
   const SelPart p = parts[blockIdx.x];
-  const SelParams* row = params + (size_t)(*target) * n_linears;
   if (p.part < 0) {
-    selector_group_part(jobs, members + p.first, p.count, row, one_job, one, threadIdx.x, sh);
+    selector_group_part(jobs, members + p.first, p.count, active, one_job, one, threadIdx.x, sh);
   } else {
-    const SelParams P = row[p.linear];
+    const SelParams P = active[p.linear];
     const SelJob job = jobs[p.job];
     selector_proj_part(job, P, p.part, threadIdx.x);
   }
 }
 
 // The estimates and decisions of a selector launch, where no GEMV launch follows that takes them itself:
-// workgroup b finishes jobs[b] under the target *target (jobs == nullptr: the single job `one_job` with the
+// workgroup b finishes jobs[b] under the parameters `active` (jobs == nullptr: the single job `one_job` with the
 // parameters `one`).  Launched after selector_part_kernel on the same stream.
 constexpr int kSelDecideThreads = 128;
-__global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(const SelJob* __restrict__ jobs, const SelParams* __restrict__ params,
-                                                                            const int32_t* __restrict__ target, int n_linears,
+__global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(const SelJob* __restrict__ jobs, const SelParams* __restrict__ active,
                                                                             SelJob one_job, SelParams one) {
   __shared__ SelShared sh;
   if (jobs == nullptr) {
@@ -311,7 +567,7 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
     return;
   }
   const SelJob job = jobs[blockIdx.x];
-  selector_finish(sel_finish_of(job), params + (size_t)(*target) * n_linears + job.linear, threadIdx.x, kSelDecideThreads, sh.sq, true);
+  selector_finish(sel_finish_of(job), active + job.linear, threadIdx.x, kSelDecideThreads, sh.sq, true);
 }
 
 }  // namespace dpllm

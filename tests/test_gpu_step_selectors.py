@@ -1,0 +1,104 @@
+"""GPU tests of the selectors that run inside the GEMV launch of a small dependency level: rows of G dealt out to the
+launch's workgroups in slices of 4096 columns, partial products handed over through slots of the workspace, the decision
+taken by every workgroup from the slots of its own linear."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dp():
+    import paper_2508_06041_amd as dp
+    assert torch.cuda.is_available()
+    return dp
+
+
+def _lone_linear(dp, in_, r, seed, out=70):
+    lin = synth.make_linear(out, in_, 4, 3, seed=seed)
+    model = dp.Model(1)
+    planes, luts = synth.planes_np(lin["planes"]), {k: synth.lut_np(v) for k, v in lin["luts"].items()}
+    model.dpllm_load_linear(0, planes, luts, 3)
+    G = (torch.randn(r, in_, generator=torch.Generator().manual_seed(seed)) / math.sqrt(r)).half()
+    return model, planes, luts, G
+
+
+# ranks around the 16 rows of a row group, the 256 workgroups the tasks are dealt out to and the 512 threads that collect
+# them; rows below one chunk of 512 columns, of one slice (4096) exactly, and with a ragged last chunk or slice
+@pytest.mark.parametrize("in_,r", [(32, 3), (1056, 17), (4096, 64), (4128, 16), (11008, 64), (16416, 40), (4096, 300), (8224, 1024)])
+def test_step_selectors_match_oracle(dp, in_, r):
+    model, planes, luts, G = _lone_linear(dp, in_, r, seed=in_ + r)
+    xs = synth.make_x(in_, 4, seed=r)
+    est = [oracle.estimate(synth.lut_np(G), synth.lut_np(x)) for x in xs]
+    T = synth.nudge_threshold(float(np.median(est)), torch.tensor(est))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=T)
+    x_dev = torch.zeros(in_, dtype=torch.float16, device="cuda")
+    y = torch.zeros(planes.shape[1], dtype=torch.float16, device="cuda")
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    for x, e_ref in zip(xs, est):       # another vector every time: a slot left over from the step before would show
+        x_dev.copy_(x)
+        model.dpllm_decode_step([x_dev], [y], k_dev, e_dev)
+        assert math.isclose(float(e_dev), e_ref, rel_tol=3e-7)
+        k = oracle.decide(e_ref, T, 3, 4)
+        assert int(k_dev) == k
+        ref = oracle.gemv(planes, k, luts[k], synth.lut_np(x))
+        assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
+    model.close()
+
+
+@pytest.mark.parametrize("in_,r", [(1056, 17), (8224, 64), (4096, 600)])
+def test_step_takes_products_nobody_delivers_itself(dp, in_, r):
+    """A graph captured while no linear has an estimator holds launches that run no selectors.  Replayed after the pair in
+    use has changed to one with a projection, every workgroup finds its slots empty, stops polling and computes the
+    products itself: same bits as an eager step, whose workgroups share the work."""
+    model, planes, luts, G = _lone_linear(dp, in_, r, seed=in_ * 3 + r)
+    x = synth.make_x(in_, 1, seed=r)[0].cuda()
+    e_ref = oracle.estimate(synth.lut_np(G), synth.lut_np(x))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(1.1 * e_ref)))
+    model.dpllm_set_selector(0, 4, 4, dp.DPLLM_SEL_NONE)
+    y = torch.zeros(planes.shape[1], dtype=torch.float16, device="cuda")
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    xp, yp = model.pointers([x]), model.pointers([y])
+    model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+    torch.cuda.synchronize()
+    assert int(k_dev) == 4
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+    model.dpllm_set_active_pair(0, 3, 4)
+    model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+    torch.cuda.synchronize()
+    want = (k_dev.clone(), e_dev.clone(), y.clone())
+    assert int(k_dev) == 3 and math.isclose(float(e_dev), e_ref, rel_tol=3e-7)
+    for _ in range(3):
+        y.zero_(), k_dev.zero_(), e_dev.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(k_dev, want[0]) and torch.equal(e_dev, want[1]) and torch.equal(y, want[2])
+    model.close()
+
+
+def test_selector_on_the_buffer_its_own_linear_writes(dp):
+    """A selector input that is the linear's own output buffer: the estimate comes from what the buffer held before the
+    GEMV wrote it, so the selectors of such a level are done before its GEMV launch starts."""
+    model, planes, luts, G = _lone_linear(dp, 256, 32, seed=91, out=256)
+    x = synth.make_x(256, 1, seed=92)[0].cuda()
+    before = synth.make_x(256, 1, seed=93)[0].cuda()
+    e_ref = oracle.estimate(synth.lut_np(G), synth.lut_np(before))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.9 * e_ref)))
+    y = torch.zeros(256, dtype=torch.float16, device="cuda")
+    model.dpllm_set_selector_input(0, y)
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    for _ in range(3):
+        y.copy_(before)
+        model.dpllm_decode_step([x], [y], k_dev, e_dev)
+        assert math.isclose(float(e_dev), e_ref, rel_tol=3e-7) and int(k_dev) == 4
+        ref = oracle.gemv(planes, 4, luts[4], synth.lut_np(x))
+        assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
+    model.close()
