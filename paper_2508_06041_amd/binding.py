@@ -69,13 +69,15 @@ lib = _load()
 
 
 def _stream():
-    return C.c_void_p(torch.cuda.current_stream().cuda_stream)
+    """The current stream's handle.  torch.cuda.current_stream() builds a Stream object for it (2.9 us of a call of
+    7.1 us, of which the library takes 3.3); the raw lookup takes 0.2 us but wants an initialised device."""
+    if not torch.cuda.is_initialized():
+        torch.cuda.init()
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def _ptr(t):
-    if t is None:
-        return None
-    return C.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _check(model, rc):
