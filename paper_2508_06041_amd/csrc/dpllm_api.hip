@@ -310,12 +310,14 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
       case 4: go(gemv_lane_kernel<1, 4>); break;
       default: go(gemv_lane_kernel<1, 8>); break;
     }
-  } else {
+  } else if (nb == 4) {
     switch (groups) {
       case 1: go(gemv_lane_kernel<4, 1>); break;
       case 2: go(gemv_lane_kernel<4, 2>); break;
       default: go(gemv_lane_kernel<4, 4>); break;
     }
+  } else {
+    go(gemv_lane_kernel<8, 1>);
   }
 }
 
@@ -334,18 +336,22 @@ void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, co
   }
 }
 
-// one linear, B right-hand sides: a batch runs in groups of four samples that share one pass over the planes
+// One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
+// more workgroups than there are compute units; below that the second pass runs beside the first one.  us per call of
+// B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 10.5, k = 6 23.1 / 17.5, 11008 x 4096 k = 8 27.5 / 18.5, 28672 x
+// 8192 k = 5 64.1 / 40.8 (B = 4: 35.3); 4096 x 14336 k = 3 12.8 / 13.8, 4096 x 4096 k = 4 8.2 / 8.9.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
-  const int passes = B > 1 ? (B + 3) / 4 : 1;
-  const int groups = pick_groups((long)lin.L.nrq * passes, lin.L.ncc, B > 1 ? 4 : 1);
+  const int nb = B == 1 ? 1 : B <= 4 || lin.L.nrq <= 128 ? 4 : 8;
+  const int passes = (B + nb - 1) / nb;
+  const int groups = nb == 8 ? 1 : pick_groups((long)lin.L.nrq * passes, lin.L.ncc, nb);
   if (groups > 1) {
     j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   } else {
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
     j.nblocks = (lin.L.nrq + rpb - 1) / rpb;
   }
-  launch_lane(groups, B > 1 ? 4 : 1, (unsigned)(j.nblocks * passes), st, j, B);
+  launch_lane(groups, nb, (unsigned)(j.nblocks * passes), st, j, B);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }

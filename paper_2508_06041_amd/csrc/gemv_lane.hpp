@@ -19,10 +19,11 @@
 // pipe instead: v_mfma_f32_4x4x4_16b_f16 works on 16 blocks of four lanes; with the A operand of one block
 // broadcast to all blocks (cbsz = 4, abid = Q) lane L gets
 //     acc[i] += sum_n A(lane 4 Q + i)[n] * B(lane L)[n],  n = 0 .. 3,  i = 0 .. 3.
+// (Five to eight right-hand sides: two matrix instructions per looked-up chunk, each with its four samples.)
 // B = four looked-up weights of the lane's own row; A = the four activations that go with them, held by the
 // lanes of quad Q: lane 4 Q + i holds sample i's chunk, acc[i] is sample i's sum.  Quad Q of the wavefront holds
 // chunks Q and 16 + Q of the tile's 32 chunks of four activations, so 4 registers carry a tile's activations and
-// every lookup serves four samples: up to four right-hand sides share a pass at the cost of one.
+// every lookup serves four (eight) samples: up to eight right-hand sides share a pass over the planes.
 // Each lane accumulates its own row: no cross-lane reduction.  A workgroup is eight wavefronts that split the
 // columns of the same 64 rows and share the tables; their eight partial sums per row meet in LDS.
 //
@@ -74,7 +75,7 @@ static_assert(LaneDecode<2>::table_bytes <= kLaneTableBytes && LaneDecode<3>::ta
 // G column groups per wavefront (see below); bytes from one group's parked activations to the next: 64 more than a
 // tile's 256, so that the groups' reads of the same word fall on different banks
 constexpr int kLaneGroupStride = 320;
-// NB right-hand sides per pass (1 or 4).  Per wavefront: a slot for the parked activations of its tiles (G of them)
+// NB right-hand sides per pass (1, 4 or 8).  Per wavefront: a slot for the parked activations of its tiles (G of them)
 // per sample; with one sample and one group, four more for the tiles it keeps across row blocks.
 template <int NB, int G>
 __host__ __device__ constexpr int lane_x_bytes() {
@@ -83,11 +84,17 @@ __host__ __device__ constexpr int lane_x_bytes() {
 // tables, partial sums, activation slots, and (one sample: the decode step) room for the selectors.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
 // activations are borrowed from the partial sums, which are not in use between the barrier that opens a row block
 // and the stores that close it (its own partial sums of sample 0).
+// Eight samples: their partial sums take the place of the tables, which are done with by then (two barriers more per row
+// block keep two workgroups per compute unit), and activations are re-paired in place.
+template <int NB>
+__host__ __device__ constexpr int lane_red_offset() { return NB == 8 ? 0 : kLaneTableBytes; }
+template <int NB>
+__host__ __device__ constexpr int lane_x_offset() { return NB == 8 ? kLaneTableBytes : kLaneTableBytes + NB * kLaneRedBytes; }
 template <int NB, int G>
 __host__ __device__ constexpr int lane_lds_bytes() {
-  return kLaneTableBytes + NB * kLaneRedBytes + kLaneWaves * lane_x_bytes<NB, G>() + (NB == 1 ? kSelSharedBytes : 0);
+  return lane_x_offset<NB>() + kLaneWaves * lane_x_bytes<NB, G>() + (NB == 1 ? kSelSharedBytes : 0);
 }
-static_assert(lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920 && lane_lds_bytes<1, 2>() <= 81920 &&
+static_assert(8 * kLaneRedBytes <= LaneDecode<3>::table_bytes && lane_lds_bytes<8, 1>() <= 81920 && lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920 && lane_lds_bytes<1, 2>() <= 81920 &&
               lane_lds_bytes<1, 4>() <= 81920, "two workgroups per compute unit");
 
 // x pair held by lane Q of the quad, times the looked-up pair, added to acc
@@ -115,7 +122,8 @@ __device__ __forceinline__ void mfma_chunk(f32x4& acc, uint64_t x, uint32_t w0, 
 }
 
 // The lane's partial sums.  One sample: four fp32 sums that take turns.  Four samples: two sets of four (sum i
-// of a set = sample i) that take turns, so that no matrix instruction waits for the one before it.
+// of a set = sample i) that take turns, so that no matrix instruction waits for the one before it.  Eight: a set for
+// samples 0 .. 3 and one for 4 .. 7.
 template <int NB>
 struct LaneAcc;
 template <>
@@ -129,6 +137,13 @@ struct LaneAcc<4> {
   f32x4 v[2];
   __device__ __forceinline__ void zero() { v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
   __device__ __forceinline__ float sum(int b) const { return v[0][b] + v[1][b]; }
+};
+
+template <>
+struct LaneAcc<8> {
+  f32x4 v[2];
+  __device__ __forceinline__ void zero() { v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ float sum(int b) const { return v[b >> 2][b & 3]; }
 };
 
 // LDS address of entry (byte N of t) in the lane's table column: byte 1 = the entry, byte 0 = lane * 4
@@ -314,7 +329,17 @@ __device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32
 // (four activations, 8 n bytes into the sample's slot) sits in lane quad n mod P of the group, P = 16 / G quads per
 // group, as its operand n / P.
 template <int NB, int G>
-struct LaneX;
+struct LaneX {
+  static constexpr int P = 16 / G;
+  static constexpr int sample = G == 1 ? 256 : G * kLaneGroupStride;   // bytes from one sample's slot to the next
+  uint64_t a[NB / 4][2 * G];   // a[s][h] = chunk P h + (lane / 4) mod P of the tile, of sample 4 s + lane mod 4
+  __device__ __forceinline__ void load(const char* xmine) {
+#pragma unroll
+    for (int s = 0; s < NB / 4; ++s)
+#pragma unroll
+      for (int h = 0; h < 2 * G; ++h) a[s][h] = *reinterpret_cast<const uint64_t*>(xmine + s * 4 * sample + h * P * 8);
+  }
+};
 template <int G>
 struct LaneX<1, G> {
   u32x4 q[4];   // q[j][m] = pair 4 (lane mod 4) + m of word j
@@ -323,19 +348,12 @@ struct LaneX<1, G> {
     for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64);
   }
 };
-template <int G>
-struct LaneX<4, G> {
-  static constexpr int P = 16 / G;
-  uint64_t a[2 * G];   // a[h] = chunk P h + (lane / 4) mod P of the tile, of sample lane mod 4
-  __device__ __forceinline__ void load(const char* xmine) {
-#pragma unroll
-    for (int h = 0; h < 2 * G; ++h) a[h] = *reinterpret_cast<const uint64_t*>(xmine + h * P * 8);
-  }
-};
-// chunk C of the tile for four samples; chunks take turns in the two accumulator sets
-template <int C, int G>
-__device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<4, G>& x, LaneAcc<4>& acc) {
-  mfma_chunk<C % LaneX<4, G>::P, G>(acc.v[C & 1], x.a[C / LaneX<4, G>::P], w0, w1);
+// chunk C of the tile for four samples (chunks take turns in the two accumulator sets) or eight
+template <int C, int NB, int G>
+__device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
+  constexpr int P = LaneX<NB, G>::P;
+  mfma_chunk<C % P, G>(acc.v[NB == 4 ? C & 1 : 0], x.a[0][C / P], w0, w1);
+  if constexpr (NB == 8) mfma_chunk<C % P, G>(acc.v[1], x.a[1][C / P], w0, w1);
 }
 
 // the eight lookups of entry words JA, JA + 1 of word J: chunks 8 J + 2 JA .. + 3
@@ -343,8 +361,8 @@ template <int JA, int J, int G>
 __device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
   lane_consume_pairs<JA>(v, x.q[J], acc.v);
 }
-template <int JA, int J, int G>
-__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<4, G>& x, LaneAcc<4>& acc) {
+template <int JA, int J, int NB, int G>
+__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
   lane_mac_chunk<8 * J + 2 * JA + 3>(v[6], v[7], x, acc);
   lane_mac_chunk<8 * J + 2 * JA + 2>(v[4], v[5], x, acc);
   lane_mac_chunk<8 * J + 2 * JA + 1>(v[2], v[3], x, acc);
@@ -355,8 +373,8 @@ template <int JJ, int J, int G>
 __device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
   lane_consume_singles<JJ>(v, x.q[J], acc.v);
 }
-template <int JJ, int J, int G>
-__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<4, G>& x, LaneAcc<4>& acc) {
+template <int JJ, int J, int NB, int G>
+__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
   lane_mac_chunk<8 * J + 2 * JJ + 1>(v[4] | (v[5] << 16), v[6] | (v[7] << 16), x, acc);
   lane_mac_chunk<8 * J + 2 * JJ + 0>(v[0] | (v[1] << 16), v[2] | (v[3] << 16), x, acc);
 }
@@ -533,12 +551,11 @@ constexpr int kLaneDepth = 2;
 // blocks; past the end of the run the ring is refilled with dummy loads (see lane_load_tile).
 template <int K, int NB>
 __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
-  constexpr int table_bytes = kLaneTableBytes;
   constexpr int D = kLaneDepth;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint32_t lanecol = (uint32_t)lane * 4;  // the lane's column of the interleaved tables
-  float* red = reinterpret_cast<float*>(lds + table_bytes);
-  char* ready = lds + table_bytes + NB * kLaneRedBytes + wave * lane_x_bytes<NB, 1>();   // + 256 b: the parked tile of sample b
+  float* red = reinterpret_cast<float*>(lds + lane_red_offset<NB>());
+  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, 1>();   // + 256 b: the parked tile of sample b
   char* repair = reinterpret_cast<char*>(red) + wave * 256;   // k = 4: room to re-pair a tile's activations (see lane_lds_bytes)
   const int c0 = wave * job.ncc / kLaneWaves, c1 = (wave + 1) * job.ncc / kLaneWaves;
   const int nrb = job.nrq;                     // row blocks of the job
@@ -603,6 +620,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
     lds_barrier();
   };
   auto close_block = [&]() {
+    if constexpr (NB == 8) lds_barrier();   // the tables are done with
 #pragma unroll
     for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = acc.sum(b);
     acc.zero();
@@ -615,6 +633,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
     }
     const int o = rb * 64 + lane;
     if (storer && o < job.out) as_global(job.y)[(size_t)wave * job.out + o] = __builtin_bit_cast(uint16_t, (_Float16)s);
+    if constexpr (NB == 8) lds_barrier();   // the next tables may be built
   };
   open_block();
   if (idle) {
@@ -632,7 +651,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
       const char* xready = kept + (cc - c0) * 256;
       if (!keep) {
 #pragma unroll
-        for (int b = 0; b < NB; ++b) lane_park_x<K>(lane_mask_x(job, cc, lane, ring[s].x[b]), lane, repair, ready + b * 256);
+        for (int b = 0; b < NB; ++b) lane_park_x<K>(lane_mask_x(job, cc, lane, ring[s].x[b]), lane, NB == 8 ? ready + b * 256 : repair, ready + b * 256);
         xready = ready;
       }
       lane_compute<K, NB, 1>(ring[s].w, lanecol, lds, xready + xlane, acc, addr, mask, M, job.ncw - cc * 4, cc * 4 + 4 > job.ncw);
@@ -745,13 +764,14 @@ __device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside,
 // one workgroup: block number `block` of 64 / G rows
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
+  static_assert(NB <= 4, "eight samples are served by launches that fill the chip");
   constexpr int D = kLaneDepth;
   constexpr int rows = 64 / G;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int row = block * rows + lane % rows, group = lane / rows;
   const uint32_t lanecol = (uint32_t)lane * 4;
-  float* red = reinterpret_cast<float*>(lds + kLaneTableBytes);
-  char* ready = lds + kLaneTableBytes + NB * kLaneRedBytes + wave * lane_x_bytes<NB, G>();   // sample b: + G * kLaneGroupStride * b
+  float* red = reinterpret_cast<float*>(lds + lane_red_offset<NB>());
+  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, G>();   // sample b: + G * kLaneGroupStride * b
   const int xlane = group * kLaneGroupStride +
                     (NB == 1 ? (lane & 3) * 16 : (lane & 3) * G * kLaneGroupStride + ((lane >> 2) % (16 / G)) * 8);
   const int nsc = (job.ncc + G - 1) / G;
