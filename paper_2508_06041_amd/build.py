@@ -9,7 +9,7 @@ SOURCES = ["dpllm_api.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the first kernel arguments arrive in scalar registers with the launch instead of being loaded from memory
-         "-mllvm", "-amdgpu-kernarg-preload-count=12"]
+         "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
 def build(verbose: bool = False, extra=()) -> str:

@@ -302,7 +302,10 @@ int pick_groups(long blocks64, int ncc, int nb) {
 }
 
 void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const GemvJob& one, int nrhs) {
-  auto go = [&](auto kernel) { hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, one, nrhs); };
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, one.arena, one.x, one.k_dev, one.plane_stride_u4,
+                       one.k_dev ? 0u : one.lut_off[one.k - 1], one.k, one.out, one.ncw, one.ncc, one.nblocks, nrhs, one);
+  };
   if (nb == 1) {
     switch (groups) {
       case 1: go(gemv_lane_kernel<1, 1>); break;

@@ -678,7 +678,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
 // stored 4.2; another 1.3 around the kernel.  So the loads are asked for in the order they are needed, the activations
 // are parked while the rest is on its way, and one workgroup per compute unit may use all its registers.
 // us per launch, columns split between workgroups -> now: 4096 x 4096 k = 4 10.9 -> 5.5, k = 8 14.6 -> 8.5; 4096 x 11008
-// k = 3 12.2 -> 7.9; 1024 x 4096 k = 3 7.3 -> 3.9.
+// k = 3 12.2 -> 7.9; 1024 x 4096 k = 3 7.3 -> 3.9 (before the arguments came in registers, see gemv_lane_kernel).
 template <int K, int NB, int G>
 struct NarrowTile {
   u32x4 w[K];
@@ -841,30 +841,23 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 template <int NB, int G>
 __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpret_cast<double*>(lds + lane_lds_bytes<NB, G>() - kSelSharedBytes); }
 
-// The bitwidth of the job: its own value, the word a selector left in device memory, or the decision taken here
-// from the partial products that the launch's workgroups left in the slots (every workgroup of the job repeats the same
-// fixed-order sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
-// linear does not serve (outside [max(kmin, 3), p]) is not served: the workgroup returns and y keeps what it held.
-template <int NB, int G>
-__device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* active,
-                                                int polls) {   // active == nullptr: no decisions here
-  if (block * (64 / G) >= job.out) return;   // (no row of the job is this workgroup's)
-  int k = job.k;
-  if (NB == 1 && job.has_fin && active != nullptr) {
-    static_assert(kSelMaxRank * sizeof(double) <= kLaneTableBytes, "room where the tables will be");
-    const SelParams P = load_record(active + job.fin.linear);
-    k = selector_gather(job.fin, P, polls, block, tid, lane_sel_shared<NB, G>(lds), reinterpret_cast<double*>(lds), block == 0);
-    k = __builtin_amdgcn_readfirstlane(k);
-  } else if (job.k_dev != nullptr) {
-    k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
-  }
-  if (k < job.kmin || k > job.p) return;
+// byte offset of the k-bit tables (by constant index: a run-time index would put the job record in scratch memory)
+__device__ __forceinline__ uint32_t lane_lut_off(const GemvJob& job, int k) {
+  uint32_t off = job.lut_off[0];
+#pragma unroll
+  for (int j = 1; j < kKMax; ++j) off = k == j + 1 ? job.lut_off[j] : off;
+  return off;
+}
+
+// lut_off(K as a constant): byte offset of the K-bit tables
+template <int NB, int G, class Off>
+__device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, Off lut_off, int block, int tid, char* lds) {
   auto run = [&](auto kc) {
     constexpr int K = decltype(kc)::value;
-    if constexpr (G == 1) gemv_lane<K, NB>(job, job.lut_off[K - 1], block, tid, lds);
-    else gemv_narrow<K, NB, G>(job, job.lut_off[K - 1], block, tid, lds);
+    if constexpr (G == 1) gemv_lane<K, NB>(job, lut_off(kc), block, tid, lds);
+    else gemv_narrow<K, NB, G>(job, lut_off(kc), block, tid, lds);
   };
-  switch (k) {   // (the table offsets are taken by constant index: a run-time index would put the job record in scratch memory)
+  switch (k) {
     case 1: run(std::integral_constant<int, 1>{}); break;
     case 2: run(std::integral_constant<int, 2>{}); break;
     case 3: run(std::integral_constant<int, 3>{}); break;
@@ -876,18 +869,62 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
   }
 }
 
-// One linear, the job passed by value, for nrhs right-hand sides in groups of NB that share one pass over the planes
-// (group g reads x + g * NB * in and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) * nblocks) serve it).
+// The bitwidth of the job: its own value, the word a selector left in device memory, or the decision taken here
+// from the partial products that the launch's workgroups left in the slots (every workgroup of the job repeats the same
+// fixed-order sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
+// linear does not serve (outside [max(kmin, 3), p]) is not served: the workgroup returns and y keeps what it held.
+template <int G>
+__device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* active,
+                                                int polls) {   // active == nullptr: no decisions here
+  constexpr int NB = 1;
+  if (block * (64 / G) >= job.out) return;   // (no row of the job is this workgroup's)
+  int k = job.k;
+  if (job.has_fin && active != nullptr) {
+    static_assert(kSelMaxRank * sizeof(double) <= kLaneTableBytes, "room where the tables will be");
+    const SelParams P = load_record(active + job.fin.linear);
+    k = selector_gather(job.fin, P, polls, block, tid, lane_sel_shared<NB, G>(lds), reinterpret_cast<double*>(lds), block == 0);
+    k = __builtin_amdgcn_readfirstlane(k);
+  } else if (job.k_dev != nullptr) {
+    k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
+  }
+  if (k < job.kmin || k > job.p) return;
+  gemv_lane_width<NB, G>(job, k, [&](auto kc) { return job.lut_off[decltype(kc)::value - 1]; }, block, tid, lds);
+}
+
+// One linear, for nrhs right-hand sides in groups of NB that share one pass over the planes (group g reads x + g * NB * in
+// and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) * nblocks) serve it).  What a workgroup needs to ask for its
+// first tiles and tables comes as plain arguments, which fit the registers that are set with the launch; a record passed
+// by value is loaded from memory first.  us per call, record -> arguments: 4096 x 4096 k = 4 5.7 -> 5.2, 2500 x 6688 k = 7
+// 9.6 -> 9.2, 4096 x 11008 k = 2 7.3 -> 7.1.
 template <int NB, int G>
-__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(GemvJob one, int nrhs) {
+__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const char* arena, const uint16_t* x, const int32_t* k_dev,
+                                                                                uint32_t plane_stride_u4, uint32_t lut_off, int k, int out,
+                                                                                int ncw, int ncc, int nblocks, int nrhs, GemvJob one) {
   __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB, G>()];
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
-  const int group = blockIdx.x / one.nblocks;
-  one.x += (size_t)group * NB * one.ncw * 32;
-  one.y += (size_t)group * NB * one.out;
-  one.nsamples = min(NB, nrhs - group * NB);
-  gemv_lane_block<NB, G>(one, blockIdx.x - group * one.nblocks, threadIdx.x, lds, nullptr, 0);
+  const int group = NB == 1 ? 0 : blockIdx.x / nblocks;
+  GemvJob job = one;
+  job.arena = arena;
+  job.x = x + (size_t)group * NB * ncw * 32;
+  job.y += (size_t)group * NB * out;
+  job.k_dev = k_dev;
+  job.plane_stride_u4 = plane_stride_u4;
+  job.k = k;
+  job.out = out;
+  job.ncw = ncw;
+  job.ncc = ncc;
+  job.nrq = (out + 63) / 64;
+  job.nblocks = nblocks;
+  job.nsamples = min(NB, nrhs - group * NB);
+  const int block = blockIdx.x - group * nblocks;
+  if (block * (64 / G) >= out) return;
+  if (k_dev != nullptr) {
+    k = load_record(k_dev);
+    if (k < one.kmin || k > one.p) return;
+    lut_off = lane_lut_off(one, k);
+  }
+  gemv_lane_width<NB, G>(job, k, [&](auto) { return lut_off; }, block, threadIdx.x, lds);
 }
 
 // The linears of a dependency level of a decode step: block b < nblocks belongs to job block_jobs[b]; blocks past them
@@ -903,7 +940,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_step_kernel
   selector_tasks(tasks, ntasks, task_groups, b, threadIdx.x, lane_sel_shared<1, G>(lds));
   if (b >= nblocks) return;
   const GemvJob job = load_record(jobs + load_record(block_jobs + b));
-  gemv_lane_block<1, G>(job, b - job.block_start, threadIdx.x, lds, active, polls);
+  gemv_lane_block<G>(job, b - job.block_start, threadIdx.x, lds, active, polls);
 }
 
 }  // namespace dpllm
