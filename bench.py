@@ -451,7 +451,7 @@ def main():
         "chained_step": chained,
         "per_layer": per_layer,
         "batch": batch,
-        "roofline": {"bound": "hbm", "kernel": "gemv_lane_kernel<1>", "achieved": round(roof_achieved, 1),
+        "roofline": {"bound": "hbm", "kernel": "gemv_step_kernel<1>", "achieved": round(roof_achieved, 1),
                      "peak": HBM_PEAK_GBPS, "unit": "GB/s", "frac": round(roof_achieved / HBM_PEAK_GBPS, 4),
                      "us_per_launch": round(ms_gemv * 1e3, 1), "algorithmic_bytes": int(gemv_bytes0),
                      "measured_read_ceiling": round(read_ceiling, 1),
