@@ -79,6 +79,7 @@ struct Phase {
   int blocks = 0;                       // workgroups of that launch
   int block_first = 0;                  // slice of the device workgroup-to-job table
   bool estimators = true;               // under some target a job of the selector launch has an estimator (else the launch is skipped)
+  bool may_estimate = true;             // ... under some pair its linear holds: what a captured step has to be able to follow
   int groups = 1;                       // column groups per wavefront of that launch (see gemv_narrow)
   bool fused = false;                   // a whole step runs the selectors inside the GEMV launch
   int task_first = 0, task_count = 0;   // slice of the device table of selector tasks
@@ -96,6 +97,7 @@ struct StepPlan {
   std::vector<Phase> phases;
   size_t slots = 0;      // partial dot products of all selectors; emptied at the start of a whole step if
   bool fused = false;    //   any of its phases runs selectors inside its GEMV launch
+  bool idle = false;     // some phase has no estimator under any target, though its linears hold pairs with one
 };
 
 // The caller's workspace, carved once by dpllm_set_workspace.  Offsets in bytes, every region 256-byte aligned.
@@ -392,11 +394,16 @@ int upload_params(dpllm_model* m, hipStream_t st) {
   fill_params(m);
   // a selector launch none of whose linears has an estimator under any target has nothing to compute
   const size_t n = m->linears.size();
+  m->plan.idle = false;
   for (Phase& ph : m->plan.phases) {
-    ph.estimators = false;
-    for (int j = ph.sel_first; j < ph.sel_first + ph.sel_count && !ph.estimators; ++j)
+    ph.estimators = ph.may_estimate = false;
+    for (int j = ph.sel_first; j < ph.sel_first + ph.sel_count && !ph.estimators; ++j) {
+      const int linear = m->h_sel_jobs[j].linear;
       for (int t = 0; t < DPLLM_MAX_TARGETS && !ph.estimators; ++t)
-        ph.estimators = m->h_params[(size_t)t * n + m->h_sel_jobs[j].linear].kind != DPLLM_SEL_NONE;
+        ph.estimators = m->h_params[(size_t)t * n + linear].kind != DPLLM_SEL_NONE;
+      for (const Pair& s : m->linears[linear].sel) ph.may_estimate |= s.set && s.kind != DPLLM_SEL_NONE;
+    }
+    m->plan.idle |= ph.may_estimate && !ph.estimators;
   }
   HIP_TRY(m, hipMemcpyAsync(m->ws.at<SelParams>(m->ws.sel_params), m->h_params.data(), sizeof(SelParams) * m->h_params.size(),
                             hipMemcpyHostToDevice, st));
@@ -971,22 +978,24 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   SelParams pnone{};
   const SelParams* active = W.at<SelParams>(W.sel_active);
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
+  // a captured step is replayed under pairs and targets chosen later: it holds the selectors of every pair
+  const bool all = P.idle && capturing(st);
   if (both && P.fused && P.slots > 0)   // the slots the fused launches collect start empty
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((P.slots * 2 + 255) / 256)), dim3(256), 0, st,
                        W.at<uint32_t>(W.sel_ws), P.slots * 2, (uint32_t)kSelEmpty);
   for (const Phase& ph : P.phases) {
-    const bool fused = both && ph.fused;
+    const bool fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
     const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
     const SelPart* sel_parts = W.at<SelPart>(W.sel_parts) + ph.part_first;
     if ((parts & DPLLM_STEP_SELECT) && !fused && ph.sel_count > 0) {
-      if (ph.estimators)
+      if (estimators)
         hipLaunchKernelGGL(selector_part_kernel, dim3(ph.part_count), dim3(kSelPartThreads), 0, st, jobs, sel_parts,
                            (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), active, none, pnone);
       hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, active, none, pnone);
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
     launch_step(ph.groups, ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
-                fused ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && ph.estimators ? ph.task_count : 0);
+                fused ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0);
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;

@@ -102,3 +102,40 @@ def test_selector_on_the_buffer_its_own_linear_writes(dp):
         ref = oracle.gemv(planes, 4, luts[4], synth.lut_np(x))
         assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
     model.close()
+
+
+@pytest.mark.parametrize("own_launch", [True, False])
+def test_step_captured_without_estimators_follows_a_later_pair(dp, own_launch):
+    """A graph captured while no linear has an estimator, replayed after the pair in use has changed to one with a
+    projection: estimates of the vector the replay finds, not of the one an eager step in between left products of.
+    own_launch: the selectors run in front of the GEMV launch (the selector reads what its linear writes)."""
+    model, planes, luts, G = _lone_linear(dp, 256, 32, seed=41, out=256)
+    x = synth.make_x(256, 1, seed=42)[0].cuda()
+    vectors = synth.make_x(256, 3, seed=43)
+    vectors[1] *= 3.0
+    est = [oracle.estimate(synth.lut_np(G), synth.lut_np(v)) for v in vectors]
+    T = synth.nudge_threshold(float(np.median(est)), torch.tensor(est))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=T)
+    model.dpllm_set_selector(0, 4, 4, dp.DPLLM_SEL_NONE)
+    y, sel = torch.zeros(256, dtype=torch.float16, device="cuda"), torch.zeros(256, dtype=torch.float16, device="cuda")
+    read = y if own_launch else sel
+    model.dpllm_set_selector_input(0, read)
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    xp, yp = model.pointers([x]), model.pointers([y])
+    model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+    model.dpllm_set_active_pair(0, 3, 4)
+    for v, e_ref in zip(vectors, est):
+        read.copy_(vectors[0])
+        model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+        read.copy_(v)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert math.isclose(float(e_dev), e_ref, rel_tol=3e-7)
+        k = oracle.decide(e_ref, T, 3, 4)
+        assert int(k_dev) == k
+        ref = oracle.gemv(planes, k, luts[k], synth.lut_np(x))
+        assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
+    model.close()
