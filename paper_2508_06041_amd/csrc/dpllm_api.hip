@@ -423,17 +423,13 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
   P.k_dev = k_dev;
   P.e_dev = e_dev;
   P.phases.clear();
-  P.fused = false;
   std::vector<SelJob>& sel_jobs = m->h_sel_jobs;
   std::vector<SelPart>& sel_parts = m->h_sel_parts;
   std::vector<int32_t>& sel_members = m->h_sel_members;
   std::vector<SelTask>& sel_tasks = m->h_sel_tasks;
-  sel_members.clear();
-  sel_tasks.clear();
   std::vector<GemvJob>& gemv_jobs = m->h_gemv_jobs;
   std::vector<int32_t>& block_jobs = m->h_block_jobs;
-  sel_jobs.clear(); sel_parts.clear(); gemv_jobs.clear(); block_jobs.clear();
-  size_t ws_slots = 0;
+  gemv_jobs.clear(); block_jobs.clear();
   // phases: maximal runs of consecutive linears that do not depend on one another
   std::vector<std::pair<int, int>> bounds;
   std::vector<int> phase_of(n, 0);
@@ -521,92 +517,103 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     }
     P.phases.push_back(ph);
   }
-  // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
-  // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
-  // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
-  // input), so that its own phase starts with the GEMV; without such a phase it stays where it is, and so it does where
-  // the GEMV launch of its own phase does not take the decision (the launch that does serves the selectors of its phase).
-  std::vector<char> has_selectors(bounds.size(), 0);
-  for (int j = 0; j < n; ++j)
-    if (!m->linears[j].sel_input) has_selectors[phase_of[j]] = 1;
-  std::vector<std::vector<int>> sel_of_phase(bounds.size());
-  for (int j = 0; j < n; ++j) {
-    const Linear& lin = m->linears[j];
-    int q = phase_of[j];
-    if (lin.sel_input && P.phases[q].fused) {
-      int first = q;   // earliest phase the selector may run in
-      while (first > 0) {
-        bool written = false;
-        for (int i = bounds[first - 1].first; i < bounds[first - 1].second && !written; ++i)
-          written = overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[i], (size_t)m->linears[i].L.out * 2);
-        if (written) break;
-        --first;
-      }
-      while (q > first && !has_selectors[q]) --q;
-      if (!has_selectors[q]) q = phase_of[j];
-      has_selectors[q] = 1;
-    }
-    sel_of_phase[q].push_back(j);
-  }
-  for (size_t pi = 0; pi < bounds.size(); ++pi) {
-    Phase& ph = P.phases[pi];
-    ph.sel_first = (int)sel_jobs.size();
-    ph.sel_count = (int)sel_of_phase[pi].size();
-    ph.part_first = (int)sel_parts.size();
-    long launch_rowgroups = 0;
-    for (int j : sel_of_phase[pi]) launch_rowgroups += m->linears[j].max_rowgroups();
-    // Selectors inside the GEMV launch: a task is a row of G times a slice of at most 4096 columns (one load per
-    // wavefront), or more where there are more rows than workgroups to share them out to.
-    ph.task_first = (int)sel_tasks.size();
-    const long slices_each = std::max<long>(1, kSelTaskGroups / std::max<long>(1, launch_rowgroups * kSelPartRows));
-    for (size_t local = 0; local < sel_of_phase[pi].size(); ++local) {
-      const int j = sel_of_phase[pi][local];
+  // the selectors of every phase, at most twice: a workspace handed over before the selectors were attached may hold
+  // their parts but not the tasks of the launches that run them
+  for (;;) {
+    // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
+    // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
+    // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
+    // input), so that its own phase starts with the GEMV; without such a phase it stays where it is, and so it does where
+    // the GEMV launch of its own phase does not take the decision (the launch that does serves the selectors of its phase).
+    sel_jobs.clear(); sel_parts.clear(); sel_members.clear(); sel_tasks.clear();
+    size_t ws_slots = 0;
+    P.fused = false;
+    std::vector<char> has_selectors(bounds.size(), 0);
+    for (int j = 0; j < n; ++j)
+      if (!m->linears[j].sel_input) has_selectors[phase_of[j]] = 1;
+    std::vector<std::vector<int>> sel_of_phase(bounds.size());
+    for (int j = 0; j < n; ++j) {
       const Linear& lin = m->linears[j];
-      const int rowgroups = lin.max_rowgroups();
-      SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, launch_rowgroups);
-      for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
-      sj.ws = W.at<double>(W.sel_ws) + ws_slots;
-      SelFinish fin = sel_finish_of(sj);
-      if (ph.fused && rowgroups > 0) {
-        const long slices = std::min<long>(sel_slices(lin.L.in), slices_each);
-        fin.chunk_cols = (int)((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
-        fin.nchunks = (lin.L.in + fin.chunk_cols - 1) / fin.chunk_cols;
-        fin.copies = kSelCopies;
-        for (int row = 0; row < rowgroups * kSelPartRows; ++row)
-          for (int c = 0; c < fin.nchunks; ++c) {
-            const int col0 = c * fin.chunk_cols;
-            sel_tasks.push_back(SelTask{nullptr, fin.x + col0, (uint64_t*)sj.ws + (size_t)c * sj.ws_rows + row,
-                                        fin.nchunks * sj.ws_rows, std::min(fin.chunk_cols, lin.L.in - col0), j, row, col0, lin.L.in});
-          }
+      int q = phase_of[j];
+      if (lin.sel_input && P.phases[q].fused) {
+        int first = q;   // earliest phase the selector may run in
+        while (first > 0) {
+          bool written = false;
+          for (int i = bounds[first - 1].first; i < bounds[first - 1].second && !written; ++i)
+            written = overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[i], (size_t)m->linears[i].L.out * 2);
+          if (written) break;
+          --first;
+        }
+        while (q > first && !has_selectors[q]) --q;
+        if (!has_selectors[q]) q = phase_of[j];
+        has_selectors[q] = 1;
       }
-      ws_slots += (size_t)sj.ws_rows * std::max(sj.nchunks, fin.copies * fin.nchunks);
-      gemv_jobs[j].has_fin = 1;                 // (the jobs of all linears, in their order)
-      gemv_jobs[j].fin = fin;
-      sel_jobs.push_back(sj);
+      sel_of_phase[q].push_back(j);
     }
-    ph.task_count = (int)sel_tasks.size() - ph.task_first;
-    // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
-    // estimator is the linear regression
-    ph.member_first = (int)sel_members.size();
-    for (int a = 0; a < ph.sel_count; ++a) {
-      const SelJob& ja = sel_jobs[ph.sel_first + a];
-      bool head = true;
-      for (int b = 0; b < a && head; ++b) head = sel_jobs[ph.sel_first + b].x != ja.x || sel_jobs[ph.sel_first + b].in != ja.in;
-      if (!head) continue;
-      const int first = (int)sel_members.size() - ph.member_first;
-      for (int b = a; b < ph.sel_count; ++b) {
-        const SelJob& jb = sel_jobs[ph.sel_first + b];
-        if (jb.x == ja.x && jb.in == ja.in) sel_members.push_back(b);
+    for (size_t pi = 0; pi < bounds.size(); ++pi) {
+      Phase& ph = P.phases[pi];
+      ph.sel_first = (int)sel_jobs.size();
+      ph.sel_count = (int)sel_of_phase[pi].size();
+      ph.part_first = (int)sel_parts.size();
+      long launch_rowgroups = 0;
+      for (int j : sel_of_phase[pi]) launch_rowgroups += m->linears[j].max_rowgroups();
+      // Selectors inside the GEMV launch: a task is a row of G times a slice of at most 4096 columns (one load per
+      // wavefront), or more where there are more rows than workgroups to share them out to.
+      ph.task_first = (int)sel_tasks.size();
+      const long slices_each = std::max<long>(1, kSelTaskGroups / std::max<long>(1, launch_rowgroups * kSelPartRows));
+      for (size_t local = 0; local < sel_of_phase[pi].size(); ++local) {
+        const int j = sel_of_phase[pi][local];
+        const Linear& lin = m->linears[j];
+        const int rowgroups = lin.max_rowgroups();
+        SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, launch_rowgroups);
+        for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
+        sj.ws = W.at<double>(W.sel_ws) + ws_slots;
+        SelFinish fin = sel_finish_of(sj);
+        if (ph.fused && rowgroups > 0) {
+          const long slices = std::min<long>(sel_slices(lin.L.in), slices_each);
+          fin.chunk_cols = (int)((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
+          fin.nchunks = (lin.L.in + fin.chunk_cols - 1) / fin.chunk_cols;
+          fin.copies = kSelCopies;
+          for (int row = 0; row < rowgroups * kSelPartRows; ++row)
+            for (int c = 0; c < fin.nchunks; ++c) {
+              const int col0 = c * fin.chunk_cols;
+              sel_tasks.push_back(SelTask{nullptr, fin.x + col0, (uint64_t*)sj.ws + (size_t)c * sj.ws_rows + row,
+                                          fin.nchunks * sj.ws_rows, std::min(fin.chunk_cols, lin.L.in - col0), j, row, col0, lin.L.in});
+            }
+        }
+        ws_slots += (size_t)sj.ws_rows * std::max(sj.nchunks, fin.copies * fin.nchunks);
+        gemv_jobs[j].has_fin = 1;                 // (the jobs of all linears, in their order)
+        gemv_jobs[j].fin = fin;
+        sel_jobs.push_back(sj);
       }
-      sel_parts.push_back(SelPart{a, -1, ja.linear, (int)sel_members.size() - ph.member_first - first, first, 0});
+      ph.task_count = (int)sel_tasks.size() - ph.task_first;
+      // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
+      // estimator is the linear regression
+      ph.member_first = (int)sel_members.size();
+      for (int a = 0; a < ph.sel_count; ++a) {
+        const SelJob& ja = sel_jobs[ph.sel_first + a];
+        bool head = true;
+        for (int b = 0; b < a && head; ++b) head = sel_jobs[ph.sel_first + b].x != ja.x || sel_jobs[ph.sel_first + b].in != ja.in;
+        if (!head) continue;
+        const int first = (int)sel_members.size() - ph.member_first;
+        for (int b = a; b < ph.sel_count; ++b) {
+          const SelJob& jb = sel_jobs[ph.sel_first + b];
+          if (jb.x == ja.x && jb.in == ja.in) sel_members.push_back(b);
+        }
+        sel_parts.push_back(SelPart{a, -1, ja.linear, (int)sel_members.size() - ph.member_first - first, first, 0});
+      }
+      ph.part_count = (int)sel_parts.size() - ph.part_first;
+      if (ph.fused) P.fused = true;
     }
-    ph.part_count = (int)sel_parts.size() - ph.part_first;
-    if (ph.fused) P.fused = true;
+    const bool fits = sel_parts.size() <= W.sel_parts_cap && ws_slots <= W.sel_ws_cap && sel_tasks.size() <= W.sel_tasks_cap &&
+                      block_jobs.size() <= W.block_jobs_cap;
+    P.slots = ws_slots;
+    if (fits) break;
+    if (!P.fused)
+      return fail(m, DPLLM_ESTATE, "workspace too small for this step (set after the model changed?): call dpllm_workspace_bytes and "
+                                   "dpllm_set_workspace again");
+    for (Phase& ph : P.phases) ph.fused = false;
   }
-  P.slots = ws_slots;
-  if (sel_parts.size() > W.sel_parts_cap || ws_slots > W.sel_ws_cap || sel_tasks.size() > W.sel_tasks_cap || block_jobs.size() > W.block_jobs_cap)
-    return fail(m, DPLLM_ESTATE, "workspace too small for this step (set after the model changed?): call dpllm_workspace_bytes and "
-                                 "dpllm_set_workspace again");
   // The tables may still be read by a step enqueued earlier on this stream: the copies are ordered behind it.
   if (!sel_parts.empty())
     HIP_TRY(m, hipMemcpyAsync(W.at<SelPart>(W.sel_parts), sel_parts.data(), sizeof(SelPart) * sel_parts.size(), hipMemcpyHostToDevice, st));

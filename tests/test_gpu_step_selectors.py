@@ -139,3 +139,25 @@ def test_step_captured_without_estimators_follows_a_later_pair(dp, own_launch):
         ref = oracle.gemv(planes, k, luts[k], synth.lut_np(x))
         assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
     model.close()
+
+
+@pytest.mark.parametrize("in_,r", [(4096, 64), (1056, 48)])
+def test_step_with_a_workspace_from_before_its_selectors(dp, in_, r):
+    """A workspace of the size the model asked for when no pair was attached: too small for the tasks of r rows, large
+    enough for the parts of one selector.  The step runs its selectors in launches of their own."""
+    model, planes, luts, G = _lone_linear(dp, in_, r, seed=in_ + 7 * r)
+    model.dpllm_set_workspace()
+    x = synth.make_x(in_, 1, seed=r)[0]
+    e_ref = oracle.estimate(synth.lut_np(G), synth.lut_np(x))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.9 * e_ref)))
+    assert model.workspace.numel() < model.dpllm_workspace_bytes()
+    model._ws_stale = False              # as a caller of the C functions that keeps the workspace it has
+    y = torch.zeros(planes.shape[1], dtype=torch.float16, device="cuda")
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    for _ in range(2):
+        k_dev.zero_(), e_dev.zero_(), y.zero_()
+        model.dpllm_decode_step([x.cuda()], [y], k_dev, e_dev)
+        assert int(k_dev) == 4 and math.isclose(float(e_dev), e_ref, rel_tol=3e-7)
+        ref = oracle.gemv(planes, 4, luts[4], synth.lut_np(x))
+        assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
+    model.close()
