@@ -70,7 +70,8 @@ struct Linear {
 // A decode step is cut into phases: maximal runs of consecutive linears none of which reads or overwrites
 // what an earlier linear of the run writes.  Inside a phase all selectors run in one launch and all GEMVs
 // in another; phases run one after the other on the stream, so the result equals running the linears strictly
-// in order.  Small GEMV launches run the selectors themselves (fused).
+// in order.  Small GEMV launches take the decisions themselves (decides), those with little selector work run the
+// selectors as well (fused).
 struct Phase {
   int sel_first = 0, sel_count = 0;     // slice of the device selector job table
   int part_first = 0, part_count = 0;   // slice of the device selector part table
@@ -81,7 +82,9 @@ struct Phase {
   bool estimators = true;               // under some target a job of the selector launch has an estimator (else the launch is skipped)
   bool may_estimate = true;             // ... under some pair its linear holds: what a captured step has to be able to follow
   int groups = 1;                       // column groups per wavefront of that launch (see gemv_narrow)
-  bool fused = false;                   // a whole step runs the selectors inside the GEMV launch
+  bool may_decide = false;              // the GEMV launch is small enough to take the decisions of its linears
+  bool decides = false;                 // a whole step takes them there
+  bool fused = false;                   // ... and runs the selectors of this slice there too
   int task_first = 0, task_count = 0;   // slice of the device table of selector tasks
 };
 constexpr int kMaxGroups = 8;           // column groups per wavefront, at most
@@ -279,9 +282,23 @@ GemvJob make_gemv_job(const Linear& lin, int k, const int32_t* k_dev, const void
 // end of the launch (measured on the 7B step: 0.25 MiB 496 us, 0.375 MiB 480, 0.75 MiB 471, 1 MiB 468, 2 MiB
 // 477, 4 MiB 546); and a launch wants at least a few workgroups per compute unit.
 constexpr long kLaneGroupBytes = 1048576;
-// GEMV launches below this many workgroups run their selectors themselves; larger ones get launches of their own for
-// the selectors and the decisions (repeating the decision in each of 3094 workgroups: 514 against 509 us for a 7B step)
-constexpr int kFusedMaxBlocks = 1536;
+// Where a whole step takes the decisions of a launch's linears and runs its selectors.  us per level at rank r with
+// launches in front for parts and decisions / a part launch and the decision in the prologue of every workgroup /
+// everything inside the GEMV launch:
+//   7B q, k, v (192 workgroups)       r = 64: 15.8 / 15.1 / 13.0, 256: 17.0 / 16.0 / 15.3, 384: 18.2 / 16.7 / 17.7
+//   7B down (256, 11008 columns)      r = 64: 15.5 / 16.0 / 12.2, 1024: 25.9 / 21.2 / 19.1
+//   7B gate, up (344)                 r = 64: 18.5 / 18.1 / 17.1, 128: 19.0 / 18.5 / 16.7, 192: 19.2 / 18.4 / 18.7, 512: 21.3 / 19.5 / 22.4
+//   70B gate, up (896, 8192 columns)  r = 64: 47.3 / 49.2 / 47.1, 512: 54.3 / 54.5 / 55.3
+//   a 7B block at once (664)          r = 64: 40.5 / 41.6 / 42.2, 256: 45.8 / 45.9 / 52.9, 1024: 59.3 / 57.3 / 617
+//   two of them (1328)                r = 64: 53.0 / 55.8 / 55.6
+// The 256 workgroups that share the selectors inside work their rows off one after the other, the rest of the launch waits,
+// and who has waited too long computes every product of its linear (the 617 us): inside is right up to four rows each, one
+// slice of 4096 columns where there are more than 256 workgroups.  Repeating the decision pays up to 512.  (One 70B block
+// at once with every second linear on the linear regression is the exception seen: 110.5 us in front, 107.3 inside.)
+constexpr int kDecideMaxBlocks = 1024, kPrologueMaxBlocks = 512;
+bool runs_selectors(int blocks, long rows, long slices) {
+  return blocks <= kSelTaskGroups ? rows <= 4L * kSelTaskGroups : slices <= kSelTaskGroups;
+}
 constexpr int kSelPolls = 64;   // polls of about a microsecond before a workgroup computes missing products itself
 int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long group_bytes = kLaneGroupBytes) {
   const long bytes_per_block = 64L * L.in * k / 8;
@@ -509,17 +526,17 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     }
     ph.gemv_count = (int)gemv_jobs.size() - ph.gemv_first;
     ph.blocks = blocks;
-    ph.fused = blocks < kFusedMaxBlocks;
+    ph.may_decide = blocks < kDecideMaxBlocks;
     // a selector that reads what its own linear writes has to be done before the GEMV launch starts
     for (int j = id; j < end; ++j) {
       const Linear& lin = m->linears[j];
-      if (lin.sel_input && overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[j], (size_t)lin.L.out * 2)) ph.fused = false;
+      if (lin.sel_input && overlap(lin.sel_input, (size_t)lin.L.in * 2, ys[j], (size_t)lin.L.out * 2)) ph.may_decide = false;
     }
     P.phases.push_back(ph);
   }
   // the selectors of every phase, at most twice: a workspace handed over before the selectors were attached may hold
   // their parts but not the tasks of the launches that run them
-  for (;;) {
+  for (bool tasks = true;; tasks = false) {
     // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
     // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
     // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
@@ -532,10 +549,11 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     for (int j = 0; j < n; ++j)
       if (!m->linears[j].sel_input) has_selectors[phase_of[j]] = 1;
     std::vector<std::vector<int>> sel_of_phase(bounds.size());
+    std::vector<char> ahead(bounds.size(), 0);   // a selector of the phase runs with an earlier one
     for (int j = 0; j < n; ++j) {
       const Linear& lin = m->linears[j];
       int q = phase_of[j];
-      if (lin.sel_input && P.phases[q].fused) {
+      if (lin.sel_input && P.phases[q].may_decide) {
         int first = q;   // earliest phase the selector may run in
         while (first > 0) {
           bool written = false;
@@ -549,14 +567,21 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         has_selectors[q] = 1;
       }
       sel_of_phase[q].push_back(j);
+      if (q != phase_of[j]) ahead[phase_of[j]] = 1;
     }
     for (size_t pi = 0; pi < bounds.size(); ++pi) {
       Phase& ph = P.phases[pi];
       ph.sel_first = (int)sel_jobs.size();
       ph.sel_count = (int)sel_of_phase[pi].size();
       ph.part_first = (int)sel_parts.size();
-      long launch_rowgroups = 0;
-      for (int j : sel_of_phase[pi]) launch_rowgroups += m->linears[j].max_rowgroups();
+      long launch_rowgroups = 0, launch_slices = 0;
+      for (int j : sel_of_phase[pi]) {
+        launch_rowgroups += m->linears[j].max_rowgroups();
+        launch_slices += (long)m->linears[j].max_rowgroups() * kSelPartRows * sel_slices(m->linears[j].L.in);
+      }
+      const bool small = runs_selectors(ph.blocks, launch_rowgroups * kSelPartRows, launch_slices);
+      ph.fused = tasks && ph.may_decide && small;
+      ph.decides = ph.may_decide && (small || ahead[pi] || ph.blocks <= kPrologueMaxBlocks);
       // Selectors inside the GEMV launch: a task is a row of G times a slice of at most 4096 columns (one load per
       // wavefront), or more where there are more rows than workgroups to share them out to.
       ph.task_first = (int)sel_tasks.size();
@@ -569,11 +594,11 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
         sj.ws = W.at<double>(W.sel_ws) + ws_slots;
         SelFinish fin = sel_finish_of(sj);
+        if (ph.fused) fin.copies = kSelCopies;
         if (ph.fused && rowgroups > 0) {
           const long slices = std::min<long>(sel_slices(lin.L.in), slices_each);
           fin.chunk_cols = (int)((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
           fin.nchunks = (lin.L.in + fin.chunk_cols - 1) / fin.chunk_cols;
-          fin.copies = kSelCopies;
           for (int row = 0; row < rowgroups * kSelPartRows; ++row)
             for (int c = 0; c < fin.nchunks; ++c) {
               const int col0 = c * fin.chunk_cols;
@@ -581,7 +606,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
                                           fin.nchunks * sj.ws_rows, std::min(fin.chunk_cols, lin.L.in - col0), j, row, col0, lin.L.in});
             }
         }
-        ws_slots += (size_t)sj.ws_rows * std::max(sj.nchunks, fin.copies * fin.nchunks);
+        ws_slots += (size_t)sj.ws_rows * (rowgroups > 0 ? std::max(sj.nchunks, fin.copies * fin.nchunks) : 1);
         gemv_jobs[j].has_fin = 1;                 // (the jobs of all linears, in their order)
         gemv_jobs[j].fin = fin;
         sel_jobs.push_back(sj);
@@ -603,7 +628,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         sel_parts.push_back(SelPart{a, -1, ja.linear, (int)sel_members.size() - ph.member_first - first, first, 0});
       }
       ph.part_count = (int)sel_parts.size() - ph.part_first;
-      if (ph.fused) P.fused = true;
+      if (ph.task_count > 0) P.fused = true;
     }
     const bool fits = sel_parts.size() <= W.sel_parts_cap && ws_slots <= W.sel_ws_cap && sel_tasks.size() <= W.sel_tasks_cap &&
                       block_jobs.size() <= W.block_jobs_cap;
@@ -612,7 +637,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     if (!P.fused)
       return fail(m, DPLLM_ESTATE, "workspace too small for this step (set after the model changed?): call dpllm_workspace_bytes and "
                                    "dpllm_set_workspace again");
-    for (Phase& ph : P.phases) ph.fused = false;
   }
   // The tables may still be read by a step enqueued earlier on this stream: the copies are ordered behind it.
   if (!sel_parts.empty())
@@ -991,18 +1015,19 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((P.slots * 2 + 255) / 256)), dim3(256), 0, st,
                        W.at<uint32_t>(W.sel_ws), P.slots * 2, (uint32_t)kSelEmpty);
   for (const Phase& ph : P.phases) {
-    const bool fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
+    const bool decides = both && ph.decides, fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
     const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
     const SelPart* sel_parts = W.at<SelPart>(W.sel_parts) + ph.part_first;
     if ((parts & DPLLM_STEP_SELECT) && !fused && ph.sel_count > 0) {
       if (estimators)
         hipLaunchKernelGGL(selector_part_kernel, dim3(ph.part_count), dim3(kSelPartThreads), 0, st, jobs, sel_parts,
                            (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), active, none, pnone);
-      hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, active, none, pnone);
+      if (!decides)
+        hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, active, none, pnone);
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
     launch_step(ph.groups, ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
-                fused ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0);
+                decides ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0);
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;

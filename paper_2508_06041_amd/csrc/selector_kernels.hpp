@@ -485,6 +485,8 @@ __device__ __forceinline__ int selector_gather(const SelFinish& f, const SelPara
       lds_barrier();
     }
     e = sqrt(sum);
+  } else if (P.kind == 2 && f.copies == 1) {
+    e = (double)P.alpha * sqrt(((const DPLLM_SEL_GLOBAL double*)f.ws)[0]) + (double)P.beta;   // an earlier launch's group part
   } else if (P.kind == 2) {
     // sum x^2 of the linear's own vector: no hand-over; the first kSelPartWaves wavefronts, as selector_group_part does
     if (wave < kSelPartWaves) {
