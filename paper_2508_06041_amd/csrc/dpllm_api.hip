@@ -292,12 +292,15 @@ constexpr long kLaneGroupBytes = 1048576;
 //   a 7B block at once (664)          r = 64: 40.5 / 41.6 / 42.2, 256: 45.8 / 45.9 / 52.9, 1024: 59.3 / 57.3 / 617
 //   two of them (1328)                r = 64: 53.0 / 55.8 / 55.6
 // The 256 workgroups that share the selectors inside work their rows off one after the other, the rest of the launch waits,
-// and who has waited too long computes every product of its linear (the 617 us): inside is right up to four rows each, one
-// slice of 4096 columns where there are more than 256 workgroups.  Repeating the decision pays up to 512.  (One 70B block
-// at once with every second linear on the linear regression is the exception seen: 110.5 us in front, 107.3 inside.)
+// and who has waited too long computes every product of its linear (the 617 us).  A level between others of a chain gains
+// a little more from being one launch: chained 7B / 8B block with the lines at 4, 6, 8 rows each (up to 256 workgroups) and
+// 1, 2, 4 slices of 4096 columns (up to 512), r = 256: 52.5 / 53.7, 51.3 / 53.1, 51.4 / 53.1; r = 512: 61.2 / 64.0, 60.4 /
+// 62.6, 61.2 / 64.3.  Repeating the decision in every workgroup pays up to 512.  (One 70B block at once with every second
+// linear on the linear regression is the exception seen: 110.5 us in front, 107.3 inside.)
 constexpr int kDecideMaxBlocks = 1024, kPrologueMaxBlocks = 512;
 bool runs_selectors(int blocks, long rows, long slices) {
-  return blocks <= kSelTaskGroups ? rows <= 4L * kSelTaskGroups : slices <= kSelTaskGroups;
+  if (blocks <= kSelTaskGroups) return rows <= 6L * kSelTaskGroups;
+  return slices <= (blocks <= kPrologueMaxBlocks ? 2L : 1L) * kSelTaskGroups;
 }
 constexpr int kSelPolls = 64;   // polls of about a microsecond before a workgroup computes missing products itself
 int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long group_bytes = kLaneGroupBytes) {

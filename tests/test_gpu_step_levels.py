@@ -63,12 +63,12 @@ class Net:
             assert err <= 2e-3 * np.linalg.norm(ref), (tag, i)
 
 
-# 96 and 192 blocks of 64 rows (32 and 64 rows per workgroup), 344, 688 and 1064 workgroups; ranks on either side of four
-# rows (256 workgroups) and of one slice (more) per sharing workgroup
+# 96 and 192 blocks of 64 rows (32 and 64 rows per workgroup), 344, 688 and 1064 workgroups; rows of G on either side of six
+# (256 workgroups), two (512) and one (more) per sharing workgroup
 @pytest.mark.parametrize("out,in_,count,r,hybrid", [
-    (2048, 256, 3, 64, True), (2048, 256, 3, 352, False), (4096, 256, 3, 64, True), (4096, 256, 3, 336, False), (4096, 256, 3, 352, False),
-    (11008, 256, 2, 64, True), (11008, 256, 2, 144, False), (11008, 256, 2, 272, True), (11008, 256, 4, 48, False), (11008, 256, 4, 96, True),
-    (17000, 160, 4, 32, False)])
+    (2048, 256, 3, 64, True), (2048, 256, 3, 528, False), (4096, 256, 3, 64, True), (4096, 256, 3, 512, False), (4096, 256, 3, 528, True),
+    (4096, 256, 3, 528, False), (11008, 256, 2, 64, True), (11008, 256, 2, 256, False), (11008, 256, 2, 528, True), (11008, 256, 4, 48, False),
+    (11008, 256, 4, 96, True), (17000, 160, 4, 32, False)])
 def test_level_matches_oracle(dp, out, in_, count, r, hybrid):
     """hybrid: the last linear is on the linear regression."""
     net = Net(dp, [(out, in_)] * count, [r] * (count - 1) + [0 if hybrid else r], seed=out + r)
