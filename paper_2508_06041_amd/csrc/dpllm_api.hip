@@ -108,7 +108,7 @@ struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
   size_t est_ws = 0;                         // dpllm_estimate: kSelOneSlots fp64
-  size_t target = 0;                         // the number of the active target, the number of selector tasks
+  size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
   size_t sel_active = 0;                     // SelParams [n]: the row of the active target
   size_t sel_tasks = 0, sel_tasks_cap = 0;   // SelTask [cap]
@@ -138,8 +138,6 @@ struct dpllm_model {
   std::vector<GemvJob> h_gemv_jobs;
   std::vector<int32_t> h_block_jobs;
   std::vector<SelParams> h_params;
-  std::vector<SelTask> h_sel_tasks;
-  int32_t h_ntasks = 0;
   int device = 0;
 };
 
@@ -201,7 +199,7 @@ Workspace carve_workspace(const dpllm_model* m) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
   w.est_ws = take(sizeof(double) * kSelOneSlots);
-  w.target = take(2 * sizeof(int32_t));
+  w.target = take(sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
   w.sel_active = take(sizeof(SelParams) * n);
   w.sel_tasks_cap = tasks;
@@ -406,8 +404,10 @@ void fill_params(dpllm_model* m) {
 
 void activate(const dpllm_model* m, int target, hipStream_t st) {
   const Workspace& W = m->ws;
-  hipLaunchKernelGGL(selector_activate_kernel, dim3(64), dim3(256), 0, st, (const SelParams*)W.at<SelParams>(W.sel_params), W.at<SelParams>(W.sel_active),
-                     (int)m->linears.size(), W.at<SelTask>(W.sel_tasks), (const int32_t*)(W.at<int32_t>(W.target) + 1), W.at<int32_t>(W.target), target);
+  const int n = (int)m->linears.size();
+  hipLaunchKernelGGL(selector_activate_kernel, dim3(std::min(n, 256)), dim3(256), 0, st, (const SelParams*)W.at<SelParams>(W.sel_params),
+                     W.at<SelParams>(W.sel_active), n, (const GemvJob*)W.at<GemvJob>(W.gemv_jobs), W.at<SelTask>(W.sel_tasks),
+                     W.at<int32_t>(W.target), target);
 }
 
 int upload_params(dpllm_model* m, hipStream_t st) {
@@ -446,7 +446,6 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
   std::vector<SelJob>& sel_jobs = m->h_sel_jobs;
   std::vector<SelPart>& sel_parts = m->h_sel_parts;
   std::vector<int32_t>& sel_members = m->h_sel_members;
-  std::vector<SelTask>& sel_tasks = m->h_sel_tasks;
   std::vector<GemvJob>& gemv_jobs = m->h_gemv_jobs;
   std::vector<int32_t>& block_jobs = m->h_block_jobs;
   gemv_jobs.clear(); block_jobs.clear();
@@ -545,8 +544,8 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
     // input), so that its own phase starts with the GEMV; without such a phase it stays where it is, and so it does where
     // the GEMV launch of its own phase does not take the decision (the launch that does serves the selectors of its phase).
-    sel_jobs.clear(); sel_parts.clear(); sel_members.clear(); sel_tasks.clear();
-    size_t ws_slots = 0;
+    sel_jobs.clear(); sel_parts.clear(); sel_members.clear();
+    size_t ws_slots = 0, ntasks = 0;
     P.fused = false;
     std::vector<char> has_selectors(bounds.size(), 0);
     for (int j = 0; j < n; ++j)
@@ -587,7 +586,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
       ph.decides = ph.may_decide && (small || ahead[pi] || ph.blocks <= kPrologueMaxBlocks);
       // Selectors inside the GEMV launch: a task is a row of G times a slice of at most 4096 columns (one load per
       // wavefront), or more where there are more rows than workgroups to share them out to.
-      ph.task_first = (int)sel_tasks.size();
+      ph.task_first = (int)ntasks;
       const long slices_each = std::max<long>(1, kSelTaskGroups / std::max<long>(1, launch_rowgroups * kSelPartRows));
       for (size_t local = 0; local < sel_of_phase[pi].size(); ++local) {
         const int j = sel_of_phase[pi][local];
@@ -602,19 +601,16 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
           const long slices = std::min<long>(sel_slices(lin.L.in), slices_each);
           fin.chunk_cols = (int)((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
           fin.nchunks = (lin.L.in + fin.chunk_cols - 1) / fin.chunk_cols;
-          for (int row = 0; row < rowgroups * kSelPartRows; ++row)
-            for (int c = 0; c < fin.nchunks; ++c) {
-              const int col0 = c * fin.chunk_cols;
-              sel_tasks.push_back(SelTask{nullptr, fin.x + col0, (uint64_t*)sj.ws + (size_t)c * sj.ws_rows + row,
-                                          fin.nchunks * sj.ws_rows, std::min(fin.chunk_cols, lin.L.in - col0), j, row, col0, lin.L.in});
-            }
+          fin.task_first = (int)ntasks;
+          fin.task_rows = rowgroups * kSelPartRows;
+          ntasks += (size_t)fin.task_rows * fin.nchunks;
         }
         ws_slots += (size_t)sj.ws_rows * (rowgroups > 0 ? std::max(sj.nchunks, fin.copies * fin.nchunks) : 1);
         gemv_jobs[j].has_fin = 1;                 // (the jobs of all linears, in their order)
         gemv_jobs[j].fin = fin;
         sel_jobs.push_back(sj);
       }
-      ph.task_count = (int)sel_tasks.size() - ph.task_first;
+      ph.task_count = (int)ntasks - ph.task_first;
       // groups of jobs that read the same vector: one more part each, which adds up x^2 once for the members whose
       // estimator is the linear regression
       ph.member_first = (int)sel_members.size();
@@ -633,7 +629,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
       ph.part_count = (int)sel_parts.size() - ph.part_first;
       if (ph.task_count > 0) P.fused = true;
     }
-    const bool fits = sel_parts.size() <= W.sel_parts_cap && ws_slots <= W.sel_ws_cap && sel_tasks.size() <= W.sel_tasks_cap &&
+    const bool fits = sel_parts.size() <= W.sel_parts_cap && ws_slots <= W.sel_ws_cap && ntasks <= W.sel_tasks_cap &&
                       block_jobs.size() <= W.block_jobs_cap;
     P.slots = ws_slots;
     if (fits) break;
@@ -646,17 +642,13 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     HIP_TRY(m, hipMemcpyAsync(W.at<SelPart>(W.sel_parts), sel_parts.data(), sizeof(SelPart) * sel_parts.size(), hipMemcpyHostToDevice, st));
   if (!block_jobs.empty())
     HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.block_jobs), block_jobs.data(), sizeof(int32_t) * block_jobs.size(), hipMemcpyHostToDevice, st));
-  m->h_ntasks = (int32_t)sel_tasks.size();
-  if (!sel_tasks.empty())
-    HIP_TRY(m, hipMemcpyAsync(W.at<SelTask>(W.sel_tasks), sel_tasks.data(), sizeof(SelTask) * sel_tasks.size(), hipMemcpyHostToDevice, st));
-  HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.target) + 1, &m->h_ntasks, sizeof(int32_t), hipMemcpyHostToDevice, st));
   HIP_TRY(m, hipMemcpyAsync(W.at<SelJob>(W.sel_jobs), sel_jobs.data(), sizeof(SelJob) * sel_jobs.size(), hipMemcpyHostToDevice, st));
   HIP_TRY(m, hipMemcpyAsync(W.at<int32_t>(W.sel_members), sel_members.data(), sizeof(int32_t) * sel_members.size(), hipMemcpyHostToDevice, st));
   if (!gemv_jobs.empty())
     HIP_TRY(m, hipMemcpyAsync(W.at<GemvJob>(W.gemv_jobs), gemv_jobs.data(), sizeof(GemvJob) * gemv_jobs.size(), hipMemcpyHostToDevice, st));
   P.version = m->version;
   P.valid = true;
-  m->params_dirty = true;   // the phases' estimator flags and the tasks' rows of G are worked out with the parameter table
+  m->params_dirty = true;   // the phases' estimator flags and the tasks are worked out with the parameter table
   return DPLLM_OK;
 }
 
@@ -742,8 +734,10 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   w.base = (char*)ws_dev;
   w.bytes = bytes;
   hipStream_t st = (hipStream_t)stream;
-  // the target and the number of tasks start at zero; everything else is written before it is used
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(64), 0, st, w.at<uint32_t>(w.target), (size_t)2, 0u);
+  // the target starts at zero and the jobs without tasks; everything else is written before it is used
+  struct { size_t off, words; } zero[] = {{w.target, 1}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size()}};
+  for (const auto& z : zero)
+    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, 0u);
   HIP_TRY(m, hipGetLastError());
   m->ws = w;
   m->params_dirty = true;

@@ -47,6 +47,32 @@ struct alignas(64) GemvJob {   // (aligned: few scalar loads)
   int32_t nsamples;           // right-hand sides served together (1..NB): sample s reads x + s * in, writes y + s * out
 };
 
+// Makes a target the active one: copies its row of the parameter table to `active` and writes the table of selector tasks,
+// with the target's G, from the job records (a table made by the host was 64 bytes a task to send with every new plan: one
+// linear of rank 1024 whose buffers move with every step 66 instead of 41 us a step).  target < 0: the one *target_word
+// names; else that word is written too.  Workgroup b serves linears b, b + gridDim.x, ...
+__global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams* __restrict__ table, SelParams* __restrict__ active, int n_linears,
+                                                                const GemvJob* __restrict__ jobs, SelTask* __restrict__ tasks,
+                                                                int32_t* target_word, int target) {
+  if (target < 0) target = *target_word;
+  else if (blockIdx.x == 0 && threadIdx.x == 0) *target_word = target;
+  for (int i = blockIdx.x; i < n_linears; i += gridDim.x) {
+    const SelParams P = table[(size_t)target * n_linears + i];
+    if (threadIdx.x == 0) active[i] = P;
+    const SelFinish f = jobs[i].fin;
+    for (int t = threadIdx.x; t < f.task_rows * f.nchunks; t += 256) {
+      const int row = t / f.nchunks, c = t - row * f.nchunks, col0 = c * f.chunk_cols;
+      SelTask k;
+      k.g = P.kind == 1 && row < P.r ? P.G + (size_t)row * f.in + col0 : nullptr;
+      k.x = f.x + col0;
+      k.slot = (uint64_t*)f.ws + (size_t)c * f.ws_rows + row;
+      k.copy_stride = f.nchunks * f.ws_rows;
+      k.cols = min(f.chunk_cols, f.in - col0);
+      tasks[f.task_first + t] = k;
+    }
+  }
+}
+
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
 
 // v_bfi_b32 with a wavefront-uniform mask (held in a scalar register)

@@ -181,9 +181,10 @@ struct SelFinish {
   const uint16_t* x;
   int32_t in, linear, nchunks, ws_rows, chunk_cols;   // chunk c: columns [chunk_cols c, + chunk_cols) inside the row
   int32_t copies;      // of the slots, [copy][chunk][row] (1 or kSelCopies)
+  int32_t task_first, task_rows;   // the selector's tasks: entries of the table from task_first on, [row][chunk] (0 rows: none)
 };
 __host__ __device__ inline SelFinish sel_finish_of(const SelJob& j) {
-  return SelFinish{j.ws, j.e_out, j.k_out, j.x, j.in, j.linear, j.nchunks, j.ws_rows, j.chunk_cols, 1};
+  return SelFinish{j.ws, j.e_out, j.k_out, j.x, j.in, j.linear, j.nchunks, j.ws_rows, j.chunk_cols, 1, 0, 0};
 }
 
 // The estimate from what the selector launch left in the workspace, and the decision; called by all `nthreads`
@@ -330,7 +331,6 @@ struct alignas(64) SelTask {
   uint64_t* slot;      // where the partial dot product goes, kSelCopies times,
   int32_t copy_stride; //   slots apart
   int32_t cols;        // length of the slice
-  int32_t linear, row, col0, in;
 };
 // Records that no kernel of the launch writes, read at an address that is the same for the whole workgroup: from the
 // constant address space they come with one scalar load (through a generic pointer every field is a vector load of its
@@ -515,23 +515,6 @@ __device__ __forceinline__ int selector_gather(const SelFinish& f, const SelPara
     *f.k_out = k;
   }
   return k;
-}
-
-// Makes a target the active one: copies its row of the parameter table to `active` and gives every task its slice of
-// the target's G.  target < 0: the one *target_word names; else that word is written too.
-__global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams* __restrict__ table, SelParams* __restrict__ active, int n_linears,
-                                                                SelTask* __restrict__ tasks, const int32_t* __restrict__ ntasks,
-                                                                int32_t* target_word, int target) {
-  if (target < 0) target = *target_word;
-  else if (blockIdx.x == 0 && threadIdx.x == 0) *target_word = target;
-  const SelParams* row = table + (size_t)target * n_linears;
-  const int stride = gridDim.x * 256, first = blockIdx.x * 256 + threadIdx.x;
-  for (int i = first; i < n_linears; i += stride) active[i] = row[i];
-  const int n = *ntasks;
-  for (int t = first; t < n; t += stride) {
-    const SelParams* P = row + tasks[t].linear;
-    tasks[t].g = P->kind == 1 && tasks[t].row < P->r ? P->G + (size_t)tasks[t].row * tasks[t].in + tasks[t].col0 : nullptr;
-  }
 }
 
 // parts == nullptr: the single job `one_job` with the parameters `one`; workgroup b is its projection part b, or
