@@ -122,8 +122,8 @@ __device__ __forceinline__ void mfma_chunk(f32x4& acc, uint64_t x, uint32_t w0, 
 }
 
 // The lane's partial sums.  One sample: four fp32 sums that take turns.  Four samples: two sets of four (sum i
-// of a set = sample i) that take turns, so that no matrix instruction waits for the one before it.  Eight: a set for
-// samples 0 .. 3 and one for 4 .. 7.
+// of a set = sample i) that take turns, so that no matrix instruction waits for the one before it and no chain of
+// additions holds more than half of the columns.  Eight: two such sets for samples 0 .. 3 and two for 4 .. 7.
 template <int NB>
 struct LaneAcc;
 template <>
@@ -141,9 +141,9 @@ struct LaneAcc<4> {
 
 template <>
 struct LaneAcc<8> {
-  f32x4 v[2];
-  __device__ __forceinline__ void zero() { v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
-  __device__ __forceinline__ float sum(int b) const { return v[b >> 2][b & 3]; }
+  f32x4 v[4];
+  __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ float sum(int b) const { return v[2 * (b >> 2)][b & 3] + v[2 * (b >> 2) + 1][b & 3]; }
 };
 
 // LDS address of entry (byte N of t) in the lane's table column: byte 1 = the entry, byte 0 = lane * 4
@@ -348,12 +348,12 @@ struct LaneX<1, G> {
     for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64);
   }
 };
-// chunk C of the tile for four samples (chunks take turns in the two accumulator sets) or eight
+// chunk C of the tile for four samples or eight (chunks take turns in the two accumulator sets of four samples)
 template <int C, int NB, int G>
 __device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
   constexpr int P = LaneX<NB, G>::P;
-  mfma_chunk<C % P, G>(acc.v[NB == 4 ? C & 1 : 0], x.a[0][C / P], w0, w1);
-  if constexpr (NB == 8) mfma_chunk<C % P, G>(acc.v[1], x.a[1][C / P], w0, w1);
+  mfma_chunk<C % P, G>(acc.v[C & 1], x.a[0][C / P], w0, w1);
+  if constexpr (NB == 8) mfma_chunk<C % P, G>(acc.v[2 + (C & 1)], x.a[1][C / P], w0, w1);
 }
 
 // the eight lookups of entry words JA, JA + 1 of word J: chunks 8 J + 2 JA .. + 3

@@ -34,3 +34,18 @@ def test_gemv_five_to_eight_samples(out, in_):
             assert (np.abs(y[:B].double().cpu().numpy() - ref[:B]) <= bound[:B]).all(), (k, B)
             assert (y[B] == 7.0).all()
     model.close()
+
+
+def test_eight_samples_add_as_four_do():
+    """The sums of five to eight right-hand sides are no longer chains of additions than those of four: the same bits, where
+    both take one pass of 64 rows per workgroup."""
+    import paper_2508_06041_amd as dp
+    out, in_ = 129 * 64, 4096 + 32
+    lin = synth.make_linear(out, in_, 8, 3, seed=5, device="cuda", keep_codes=False)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, lin["planes"], lin["luts"], 3)
+    X = synth.make_x(in_, 8, seed=6).cuda()
+    for k in range(3, 9):
+        halves = [model.dpllm_gemv(0, k, X[i:i + 4].contiguous()) for i in (0, 4)]
+        assert torch.equal(model.dpllm_gemv(0, k, X), torch.cat(halves)), k
+    model.close()
