@@ -313,11 +313,14 @@ int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long 
 // workgroup per compute unit.  Measured, us per launch in a graph, one linear at k = 4 with 1 / 2 / 4 / 8 groups: 4096 x
 // 4096 8.5 / 6.7 / 5.5 / 8.4, 4096 x 11008 18.0 / 12.0 / 9.2 / 12.7, 8192 x 8192 14.8 / 11.3 / 14.2 / 18.5, 11008 x 4096
 // 9.7 / 12.3 / 12.5 / 21.2, 192 x 28672 38.0 / 20.1 / 12.3 / 9.8.  Eight groups only where every wavefront gets a step
-// (1024 x 4096: 3.9 us with four, 4.1 with eight), and not for a batch (registers).
-int pick_groups(long blocks64, int ncc, int nb) {
+// (1024 x 4096: 3.9 us with four, 4.1 with eight).  A batch of four, four / eight groups: 1000 x 8192 k = 4 9.1 / 8.6, 640 x
+// 14336 k = 3 10.1 / 9.8, 192 x 14336 k = 6 14.0 / 12.7, 419 x 28672 k = 8 24.5 / 21.0 (workgroups that split the columns of
+// 64 rows, with a hand-over through memory that calls would share, take 10.2, 11.4 and 18.0 us for the last three: every
+// workgroup reads all activations here).
+int pick_groups(long blocks64, int ncc) {
   int g = 1;
   while (g < 4 && blocks64 * g * 2 <= 256) g *= 2;
-  if (g == 4 && nb == 1 && blocks64 * 8 <= 256 && ncc >= 8 * kLaneWaves) g = 8;
+  if (g == 4 && blocks64 * 8 <= 256 && ncc >= 8 * kLaneWaves) g = 8;
   return g;
 }
 
@@ -337,7 +340,8 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
     switch (groups) {
       case 1: go(gemv_lane_kernel<4, 1>); break;
       case 2: go(gemv_lane_kernel<4, 2>); break;
-      default: go(gemv_lane_kernel<4, 4>); break;
+      case 4: go(gemv_lane_kernel<4, 4>); break;
+      default: go(gemv_lane_kernel<4, 8>); break;
     }
   } else {
     go(gemv_lane_kernel<8, 1>);
@@ -367,7 +371,7 @@ int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, 
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
   const int nb = B == 1 ? 1 : B <= 4 || lin.L.nrq <= 128 ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
-  const int groups = nb == 8 ? 1 : pick_groups((long)lin.L.nrq * passes, lin.L.ncc, nb);
+  const int groups = nb == 8 ? 1 : pick_groups((long)lin.L.nrq * passes, lin.L.ncc);
   if (groups > 1) {
     j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   } else {
@@ -480,7 +484,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     for (int j = id; j < end; ++j) total_rq += m->linears[j].L.nrq;
     int min_ncc = m->linears[id].L.ncc;
     for (int j = id; j < end; ++j) min_ncc = std::min(min_ncc, m->linears[j].L.ncc);
-    ph.groups = pick_groups(total_rq, min_ncc, 1);
+    ph.groups = pick_groups(total_rq, min_ncc);
     // The chip runs 512 workgroups at a time.  A launch of a few such rounds loses the unfilled part of its last
     // round (2.7 rounds cost 3): the work per workgroup is scaled, between half and one and a half times the
     // usual megabyte, to the value with the smallest estimate of rounds x (start-up + work of a workgroup).

@@ -101,3 +101,27 @@ def test_decode_step_with_a_two_bit_child(dp):
         ref = oracle.gemv(synth.planes_np(lin["planes"]), k, lut, synth.lut_np(x))
         assert (np.abs(y.double().cpu().numpy() - ref) <= bound(ref, lut, synth.lut_np(x), in_)).all()
     model.close()
+
+
+# eight column groups for a batch: the most row blocks and the fewest column tiles that take them, one row, a last step of
+# one tile whose last words lie past the row
+@pytest.mark.parametrize("out,in_", [(2048, 8192), (1, 28672), (1017, 8192 + 32), (500, 9216 + 96)])
+def test_gemv_batch_of_few_rows_on_long_columns(dp, out, in_):
+    lin = synth.make_linear(out, in_, 8, 1, seed=out + in_, device="cuda", keep_codes=False)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, lin["planes"], lin["luts"], 1)
+    planes = synth.planes_np(lin["planes"])
+    X = synth.make_x(in_, 7, seed=out)
+    k_dev = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for k in range(1, 9):
+        lut = synth.lut_np(lin["luts"][k])
+        ref = oracle.gemv(planes, k, lut, synth.lut_np(X))
+        for B in (2, 4, 7):
+            y = torch.full((B + 1, out), 7.0, dtype=torch.float16, device="cuda")     # one row more than may be written
+            k_dev.fill_(k)
+            model.dpllm_gemv(0, -1 if B == 4 else k, X[:B].cuda(), y=y[:B], k_dev=k_dev)
+            got = y.double().cpu().numpy()
+            assert (got[B] == 7.0).all()
+            for b in range(B):
+                assert (np.abs(got[b] - ref[b]) <= bound(ref[b], lut, synth.lut_np(X[b]), in_)).all(), (k, B, b)
+    model.close()
