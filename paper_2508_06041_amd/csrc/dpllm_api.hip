@@ -343,8 +343,10 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
       case 4: go(gemv_lane_kernel<4, 4>); break;
       default: go(gemv_lane_kernel<4, 8>); break;
     }
-  } else {
+  } else if (groups == 1) {
     go(gemv_lane_kernel<8, 1>);
+  } else {
+    go(gemv_lane_kernel<8, 4>);
   }
 }
 
@@ -367,11 +369,16 @@ void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, co
 // more workgroups than there are compute units; below that the second pass runs beside the first one.  us per call of
 // B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 10.5, k = 6 23.1 / 17.5, 11008 x 4096 k = 8 27.5 / 18.5, 28672 x
 // 8192 k = 5 64.1 / 40.8 (B = 4: 35.3); 4096 x 14336 k = 3 12.8 / 13.8, 4096 x 4096 k = 4 8.2 / 8.9.
+// In between, 33 to 64 row blocks: two passes leave 64 / 2 rows to a workgroup, one pass 64 / 4, which is half the lookups
+// for the same sums and pays where lookups are what a step consists of (k >= 5) and every wavefront gets a step: 2120 x
+// 28672 k = 6 36.3 / 29.6, 3000 x 8192 k = 5 13.8 / 13.1, 4096 x 4096 k = 8 11.8 / 10.8; 4096 x 2048 k = 5 6.6 / 7.2, 2120 x
+// 14336 k = 4 17.3 / 20.3.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
-  const int nb = B == 1 ? 1 : B <= 4 || lin.L.nrq <= 128 ? 4 : 8;
+  const bool mid = lin.L.nrq > 32 && lin.L.nrq <= 64 && lin.L.ncc >= 4 * kLaneWaves && (k_dev ? lin.L.p : k) >= 5;
+  const int nb = B == 1 ? 1 : B <= 4 || (lin.L.nrq <= 128 && !mid) ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
-  const int groups = nb == 8 ? 1 : pick_groups((long)lin.L.nrq * passes, lin.L.ncc);
+  const int groups = nb == 8 ? (mid ? 4 : 1) : pick_groups((long)lin.L.nrq * passes, lin.L.ncc);
   if (groups > 1) {
     j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   } else {

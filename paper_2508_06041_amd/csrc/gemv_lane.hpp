@@ -764,7 +764,7 @@ __device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside,
 // one workgroup: block number `block` of 64 / G rows
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
-  static_assert(NB <= 4, "eight samples are served by launches that fill the chip");
+  static_assert(NB <= 4 || G == 4, "LDS and registers");
   constexpr int D = kLaneDepth;
   constexpr int rows = 64 / G;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -826,6 +826,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   }
   // the last step may have fewer than G tiles: a lane without one (it decoded another tile) drops what it added there
   const bool whole = (c1 - 1) * G + group < job.ncc;
+  if constexpr (NB == 8) lds_barrier();   // the tables, which the sums take the place of, are done with
 #pragma unroll
   for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
   lds_barrier();

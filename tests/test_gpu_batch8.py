@@ -49,3 +49,30 @@ def test_eight_samples_add_as_four_do():
         halves = [model.dpllm_gemv(0, k, X[i:i + 4].contiguous()) for i in (0, 4)]
         assert torch.equal(model.dpllm_gemv(0, k, X), torch.cat(halves)), k
     model.close()
+
+
+# one pass with four column groups: 33 and 64 row blocks, the fewest column tiles that take it, a last step of one tile and
+# a ragged last word
+@pytest.mark.parametrize("out,in_", [(2049, 4096), (4096, 4096 - 32), (2600, 9216 + 32)])
+def test_gemv_five_to_eight_samples_of_a_narrow_launch(out, in_):
+    import paper_2508_06041_amd as dp
+    lin = synth.make_linear(out, in_, 8, 3, seed=out + in_, device="cuda", keep_codes=False)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, lin["planes"], lin["luts"], 3)
+    planes = synth.planes_np(lin["planes"])
+    X = synth.make_x(in_, 8, seed=out)
+    xmax = float(X.double().abs().max())
+    k_dev = torch.zeros(1, dtype=torch.int32, device="cuda")
+    for k in range(3, 9):
+        lut = synth.lut_np(lin["luts"][k])
+        ref = oracle.gemv(planes, k, lut, synth.lut_np(X))
+        wmax = np.abs(lut.view(np.float16).astype(np.float64)).max(axis=1)
+        bound = 2.0 ** -10 * np.abs(ref) + 2.0 * np.sqrt(in_) * 2.0 ** -24 * wmax * xmax + 2.0 ** -24
+        for B in (5, 8):
+            for dev in (False, True):        # the bitwidth on the device: every one of them runs in this launch
+                y = torch.full((B + 1, out), 7.0, dtype=torch.float16, device="cuda")     # one row more than may be written
+                k_dev.fill_(k)
+                model.dpllm_gemv(0, -1 if dev else k, X[:B].cuda(), y=y[:B], k_dev=k_dev)
+                assert (np.abs(y[:B].double().cpu().numpy() - ref[:B]) <= bound[:B]).all(), (k, B, dev)
+                assert (y[B] == 7.0).all()
+    model.close()
