@@ -213,6 +213,11 @@ int dpllm_debug_unpack(dpllm_model* m, int id, int k, uint8_t* idx_dev, void* st
  * 32-bit word), *bit inside that word.  Errors: EINVAL, ESHAPE, ERANGE. */
 int dpllm_debug_locate(int out, int in, int p, int kmin, int plane, int row, int col, size_t* byte_offset, int* bit);
 
+/* Parity aid: how often a workgroup of a step looks for products of its linear's selector that other workgroups of the
+ * launch deliver, before it computes them all itself (64 looks of about a microsecond unless set).  0: it looks once;
+ * -1: it looks once and nobody delivers any.  The results are the same bits.  Errors: EINVAL. */
+int dpllm_debug_set_polls(dpllm_model* m, int polls);
+
 /* Measurement aid: a plain 128-bit copy kernel, bytes % 16 == 0, both pointers device and 16-byte
  * aligned.  Its known traffic (bytes read + bytes written) scales the HBM byte counters that the
  * profiles report for the GEMV.  Errors: EINVAL, EHIP. */

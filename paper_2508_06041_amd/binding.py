@@ -23,7 +23,7 @@ SYMBOLS = ["dpllm_model_create", "dpllm_model_destroy", "dpllm_last_error", "dpl
            "dpllm_load_linear", "dpllm_set_selector", "dpllm_set_threshold", "dpllm_set_active_pair",
            "dpllm_set_target_entry", "dpllm_set_target", "dpllm_set_selector_input",
            "dpllm_estimate", "dpllm_estimate_noalloc", "dpllm_gemv", "dpllm_decode_step", "dpllm_decode_step_parts", "dpllm_debug_unpack", "dpllm_debug_locate",
-           "dpllm_debug_copy", "dpllm_debug_read"]
+           "dpllm_debug_set_polls", "dpllm_debug_copy", "dpllm_debug_read"]
 
 
 class DpllmError(RuntimeError):
@@ -60,6 +60,7 @@ def _load():
     L.dpllm_decode_step.argtypes = [vp, C.POINTER(vp), C.POINTER(vp), vp, vp, vp]
     L.dpllm_decode_step_parts.argtypes = [vp, C.POINTER(vp), C.POINTER(vp), vp, vp, i32, vp]
     L.dpllm_debug_unpack.argtypes = [vp, i32, i32, vp, vp]
+    L.dpllm_debug_set_polls.argtypes = [vp, i32]
     L.dpllm_debug_copy.argtypes = [vp, vp, sz, vp]
     L.dpllm_debug_read.argtypes = [vp, sz, vp, vp]
     return L
@@ -253,3 +254,6 @@ class Model:
         idx = torch.empty((out, in_), dtype=torch.uint8, device="cuda")
         _check(self.h, lib.dpllm_debug_unpack(self.h, id, k, _ptr(idx), _stream()))
         return idx
+
+    def dpllm_debug_set_polls(self, polls):
+        _check(self.h, lib.dpllm_debug_set_polls(self.h, polls))

@@ -88,6 +88,7 @@ struct Phase {
   int task_first = 0, task_count = 0;   // slice of the device table of selector tasks
 };
 constexpr int kMaxGroups = 8;           // column groups per wavefront, at most
+constexpr int kSelPolls = 64;           // polls of about a microsecond before a workgroup computes missing products itself
 constexpr size_t kSelOneSlots = (size_t)kSelMaxChunks * kSelMaxRank;
 
 struct StepPlan {
@@ -138,6 +139,7 @@ struct dpllm_model {
   std::vector<GemvJob> h_gemv_jobs;
   std::vector<int32_t> h_block_jobs;
   std::vector<SelParams> h_params;
+  int polls = kSelPolls;           // < 0: the selector tasks are left out of the launches (dpllm_debug_set_polls)
   int device = 0;
 };
 
@@ -300,7 +302,6 @@ bool runs_selectors(int blocks, long rows, long slices) {
   if (blocks <= kSelTaskGroups) return rows <= 6L * kSelTaskGroups;
   return slices <= (blocks <= kPrologueMaxBlocks ? 2L : 1L) * kSelTaskGroups;
 }
-constexpr int kSelPolls = 64;   // polls of about a microsecond before a workgroup computes missing products itself
 int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long group_bytes = kLaneGroupBytes) {
   const long bytes_per_block = 64L * L.in * k / 8;
   long r = std::min<long>(16, std::max<long>(1, group_bytes / std::max<long>(1, bytes_per_block)));
@@ -352,10 +353,11 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
 
 // fewer workgroups than compute units: more of them help with the selectors
 void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, const int32_t* block_jobs, const SelParams* active,
-                 const SelTask* tasks, int ntasks) {
+                 const SelTask* tasks, int ntasks, int polls) {
+  if (polls < 0) ntasks = 0;
   const unsigned grid = (unsigned)std::max(blocks, std::min(ntasks, kSelTaskGroups));
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLaneThreads), 0, st, tasks, jobs, block_jobs, active, ntasks, kSelTaskGroups, blocks, kSelPolls);
+    hipLaunchKernelGGL(kernel, dim3(grid), dim3(kLaneThreads), 0, st, tasks, jobs, block_jobs, active, ntasks, kSelTaskGroups, blocks, polls);
   };
   switch (groups) {
     case 1: go(gemv_step_kernel<1>); break;
@@ -1035,7 +1037,7 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
     launch_step(ph.groups, ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
-                decides ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0);
+                decides ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0, m->polls);
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
@@ -1056,6 +1058,13 @@ int dpllm_debug_unpack(dpllm_model* m, int id, int k, uint8_t* idx_dev, void* st
   hipLaunchKernelGGL(debug_unpack_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, (hipStream_t)stream,
                      (const uint32_t*)lin->arena, lin->L.plane_bytes / 4, lin->L.p, k, lin->L.out, lin->L.ncw, lin->L.ncc, idx_dev);
   HIP_TRY(m, hipGetLastError());
+  return DPLLM_OK;
+}
+
+int dpllm_debug_set_polls(dpllm_model* m, int polls) {
+  if (!m) return DPLLM_EINVAL;
+  if (polls < -1) return fail(m, DPLLM_EINVAL, "polls %d below -1", polls);
+  m->polls = polls;
   return DPLLM_OK;
 }
 

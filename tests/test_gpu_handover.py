@@ -1,9 +1,9 @@
-"""GPU tests of the two places where workgroups hand partial results to one another inside a launch: the parts
-of a projection selector (partial dot products of G x) and the column-split GEMV (partial row sums).  Both
-leave their partial results in workspace slots that the launch plan fixes, so a slot that the last-arriving
-workgroup reads before the writer's value is visible still holds what the PREVIOUS launch left there.  The tests
+"""GPU tests of the places where workgroups leave partial results to one another: the parts of a projection selector, read
+by a later launch, and the selector tasks of a small level, read by the workgroups of the same launch.  Both leave their
+partial dot products of G x in workspace slots that the launch plan fixes, so a slot that is read before the writer's
+value is visible still holds what the PREVIOUS launch left there (or, inside a launch, nothing).  The tests
 therefore alternate two different input sets on successive launches: a stale slot then holds the other input's
-partial result, which changes the estimate (or the output row) by a large factor and fails the bitwise comparison
+partial result, which changes the estimate by a large factor and fails the bitwise comparison
 with a clean run of the same input and the comparison with the oracle.  (Repeating one input would hide exactly
 this failure: a stale slot would hold the right value.)"""
 import numpy as np
@@ -125,8 +125,8 @@ def test_lone_selector_handover_alternating_inputs(dp, in_, r):
 
 @pytest.mark.parametrize("out,in_", [(200, 3072), (64, 8192 + 32), (130, 2080), (1, 16384), (4096, 14336)])
 def test_split_gemv_handover_alternating_inputs(dp, out, in_):
-    """Launches with far fewer blocks of rows than compute units: several workgroups share a block of rows and the
-    last one to finish adds up their partial sums.  Two different right-hand sides alternate on successive calls
+    """Launches with far fewer blocks of 64 rows than compute units: the columns of a row are split between the lanes and
+    wavefronts of a workgroup.  Two different right-hand sides alternate on successive calls
     (single calls with one to three samples, and a decode-step launch of two linears); every call is compared
     with the oracle (norm-wise and row by row) and, bit for bit, with the first call on the same input."""
     lin = synth.make_linear(out, in_, 8, 3, seed=out + in_, device="cuda")
@@ -182,4 +182,89 @@ def test_split_gemv_handover_alternating_inputs(dp, out, in_):
                 g = ys[i].float().cpu().numpy().astype(np.float64)
                 assert rel_l2(g, y_ref) <= REL_L2, (k, rep, i)
                 assert row_ok(g, y_ref, refs[i]["luts"][k], synth.lut_np(X[nm][i])), (k, rep, i)
+    model.close()
+
+
+def test_selector_handover_inside_launches_of_a_chain(dp):
+    """Two Transformer blocks, chained: levels of 192, 128, 344 and 128 workgroups whose selectors run inside the GEMV
+    launches, one selector in each block reading a vector of its own ahead of its level.  Inputs A and B alternate, eager and
+    as replays of one graph, while a second stream copies memory or multiplies matrices.  Estimates, bitwidths and results
+    equal those of a clean run bit for bit; the clean runs match the oracle linear by linear."""
+    shapes = [(4096, 512)] * 3 + [(512, 4096)] + [(11008, 512)] * 2 + [(512, 11008)]
+    shapes, n = shapes * 2, 14
+    rng = np.random.default_rng(3)
+    model, lin = dp.Model(n), []
+    for i, (out, in_) in enumerate(shapes):
+        planes = rng.integers(0, 2 ** 32, size=(4, out, in_ // 32), dtype=np.uint32)
+        luts = {k: (rng.standard_normal((out, 1 << k)) / np.sqrt(in_)).astype(np.float16).view(np.uint16) for k in (3, 4)}
+        G = (rng.standard_normal((64, in_)) * 0.1 / np.sqrt(in_)).astype(np.float16)
+        model.dpllm_load_linear(i, planes, luts, 3)
+        lin.append((planes, luts, G))
+    x0, late = torch.zeros(512, dtype=torch.float16, device="cuda"), torch.zeros(512, dtype=torch.float16, device="cuda")
+    ys = [torch.zeros(out, dtype=torch.float16, device="cuda") for out, _ in shapes]
+    src = [x0] * 3 + [ys[0], ys[3], ys[3], ys[4]] + [ys[6]] * 3 + [ys[7], ys[10], ys[10], ys[11]]
+    sel = list(src)
+    for i in (4, 12):
+        sel[i] = late
+    k_dev, e_dev = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, dtype=torch.float32, device="cuda")
+    xp, yp = model.pointers(src), model.pointers(ys)
+    sets = {"A": synth.make_x(512, 2, seed=1), "B": 3.0 * synth.make_x(512, 2, seed=2)}
+
+    def put(name):
+        x0.copy_(sets[name][0])
+        late.copy_(sets[name][1])
+
+    def step():
+        model.dpllm_decode_step(xp, yp, k_dev, e_dev)
+
+    def select(T):
+        for i, (_, _, G) in enumerate(lin):
+            model.dpllm_set_selector(i, 3, 4, dp.DPLLM_SEL_PROJ, G=torch.from_numpy(G).cuda(), T=float(np.float32(T[i])))
+
+    select([np.inf] * n)
+    for i in (4, 12):
+        model.dpllm_set_selector_input(i, late)
+    est = []
+    for name in sets:
+        put(name)
+        step()
+        est.append(e_dev.tolist())
+    T = [a + 0.5 * (b - a) if i % 3 == 0 else (0.5 if i % 3 == 1 else 2.0) * max(a, b) for i, (a, b) in enumerate(zip(*est))]
+    select(T)
+    clean = {}
+    for name in sets:
+        put(name)
+        step()
+        torch.cuda.synchronize()
+        clean[name] = [t.clone() for t in [k_dev, e_dev] + ys]
+        bits = lambda t: t.cpu().numpy().view(np.uint16)
+        for i, (planes, luts, G) in enumerate(lin):
+            e_ref = oracle.estimate(G.view(np.uint16), bits(sel[i]))
+            assert abs(float(e_dev[i]) - e_ref) <= 3e-7 * e_ref, (name, i)
+            k = oracle.decide(e_ref, float(np.float32(T[i])), 3, 4)
+            assert int(k_dev[i]) == k, (name, i)
+            assert rel_l2(ys[i].float().cpu().numpy(), oracle.gemv(planes, k, luts[k], bits(src[i]))) <= REL_L2, (name, i)
+    assert not torch.equal(clean["A"][0], clean["B"][0])
+    gap = ((clean["A"][1] - clean["B"][1]).abs() / clean["A"][1]).median().item()
+    assert gap > 1e-2, gap
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        step()
+    other = torch.cuda.Stream()
+    big = torch.ones(1 << 26, dtype=torch.int32, device="cuda")
+    mat = torch.randn(2048, 2048, device="cuda").half()
+    for how, go in (("eager", step), ("graph", graph.replay)):
+        for rep in range(40):
+            name = "AB"[rep % 2]
+            with torch.cuda.stream(other):
+                if rep % 4 < 2:
+                    big.add_(1)
+                else:
+                    mat @ mat
+            put(name)
+            k_dev.zero_(), e_dev.zero_()
+            go()
+            torch.cuda.synchronize()
+            for what, got, want in zip(["k", "e"] + ["y%d" % i for i in range(n)], [k_dev, e_dev] + ys, clean[name]):
+                assert torch.equal(got, want), (how, rep, name, what)
     model.close()

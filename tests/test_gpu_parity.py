@@ -694,10 +694,9 @@ def test_gemv_many_rows_several_row_quads_per_wavefront(dp, out, in_):
 
 @pytest.mark.parametrize("out,in_", [(200, 3072), (64, 8192 + 32), (130, 2080), (1, 16384)])
 def test_gemv_few_rows_long_columns(dp, out, in_):
-    """Launches with far fewer blocks of rows than compute units: in the row-per-lane arrangement several
-    workgroups share a block of rows and the last one to finish adds up their partial sums.  Single calls with
-    one to three samples and a decode step; every call twice, which must give the same bits (the arrival counters
-    are back at zero, the order of the additions is fixed)."""
+    """Launches with far fewer blocks of 64 rows than compute units: the columns of a row are split between the lanes and
+    wavefronts of a workgroup.  Single calls with one to three samples and a decode step; every call twice, which must give
+    the same bits (the order of the additions is fixed)."""
     lin = synth.make_linear(out, in_, 8, 3, seed=out + in_)
     other = synth.make_linear(96, in_, 8, 3, seed=out + in_ + 1)
     model = load(dp, [lin, other])

@@ -54,9 +54,8 @@ def test_step_selectors_match_oracle(dp, in_, r):
 
 @pytest.mark.parametrize("in_,r", [(1056, 17), (8224, 64), (4096, 600)])
 def test_step_takes_products_nobody_delivers_itself(dp, in_, r):
-    """A graph captured while no linear has an estimator holds launches that run no selectors.  Replayed after the pair in
-    use has changed to one with a projection, every workgroup finds its slots empty, stops polling and computes the
-    products itself: same bits as an eager step, whose workgroups share the work."""
+    """A graph captured while no linear has an estimator, replayed after the pair in use has changed to one with a
+    projection: same bits as an eager step under that pair."""
     model, planes, luts, G = _lone_linear(dp, in_, r, seed=in_ * 3 + r)
     x = synth.make_x(in_, 1, seed=r)[0].cuda()
     e_ref = oracle.estimate(synth.lut_np(G), synth.lut_np(x))
@@ -160,4 +159,32 @@ def test_step_with_a_workspace_from_before_its_selectors(dp, in_, r):
         assert int(k_dev) == 4 and math.isclose(float(e_dev), e_ref, rel_tol=3e-7)
         ref = oracle.gemv(planes, 4, luts[4], synth.lut_np(x))
         assert np.linalg.norm(y.float().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref)
+    model.close()
+
+
+@pytest.mark.parametrize("in_,r", [(1056, 17), (8224, 64), (4096, 600), (32, 3)])
+def test_step_computes_the_products_nobody_delivers(dp, in_, r):
+    """Workgroups that stop looking for the products of their linear's selector compute them: with no look but the first one,
+    and with the selector work left out of the launch, where every slot is empty.  Same bits as with the work shared."""
+    model, planes, luts, G = _lone_linear(dp, in_, r, seed=in_ * 5 + r)
+    X = synth.make_x(in_, 2, seed=r)
+    X[1] *= 2.0
+    est = [oracle.estimate(synth.lut_np(G), synth.lut_np(x)) for x in X]
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.5 * sum(est))))
+    x, y = torch.zeros(in_, dtype=torch.float16, device="cuda"), torch.zeros(planes.shape[1], dtype=torch.float16, device="cuda")
+    k_dev, e_dev = torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(1, dtype=torch.float32, device="cuda")
+    want = {}
+    for polls in (64, 0, -1, 64):
+        model.dpllm_debug_set_polls(polls)
+        for rep in range(4):
+            which = rep % 2
+            x.copy_(X[which])
+            y.zero_(), k_dev.zero_(), e_dev.zero_()
+            model.dpllm_decode_step([x], [y], k_dev, e_dev)
+            assert math.isclose(float(e_dev), est[which], rel_tol=3e-7) and int(k_dev) == 3 + which, (polls, rep)
+            got = (e_dev.clone(), y.clone())
+            want.setdefault(which, got)
+            assert all(torch.equal(a, b) for a, b in zip(got, want[which])), (polls, rep)
+    with pytest.raises(dp.DpllmError):
+        model.dpllm_debug_set_polls(-2)
     model.close()
