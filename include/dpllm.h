@@ -180,7 +180,8 @@ int dpllm_gemv(dpllm_model* m, int id, int k, const int32_t* k_dev, const void* 
  * synchronisation.  xs, ys: host arrays of n_linears device pointers (fp16 [in_id], fp16
  * [out_id]; xs[id] and ys[id] must not overlap).  k_dev, e_dev: device arrays of n_linears
  * entries receiving every linear's bitwidth and estimate.  Results equal those of running
- * the linears one after another: consecutive linears that do not touch each other's
+ * the linears one after another (the order of additions may differ: fp64 in the estimates,
+ * fp32 in the products): consecutive linears that do not touch each other's
  * inputs and outputs share launches, dependent ones are ordered on the stream.
  * The first call, and a call after the pointers, the linears or the shapes of their pairs
  * changed, rebuilds the launch plan and copies its tables into the workspace; a call after

@@ -21,7 +21,6 @@
 
 namespace dpllm {
 
-typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
@@ -75,13 +74,6 @@ __global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams*
 
 __device__ __forceinline__ uint32_t bfi(uint32_t mask, uint32_t a, uint32_t b) { return (a & mask) | (b & ~mask); }
 
-// v_bfi_b32 with a wavefront-uniform mask (held in a scalar register)
-__device__ __forceinline__ uint32_t bfi_insn(uint32_t mask, uint32_t a, uint32_t b) {
-  uint32_t r;
-  asm("v_bfi_b32 %0, %1, %2, %3" : "=v"(r) : "s"(mask), "v"(a), "v"(b));
-  return r;
-}
-
 // (a & m) | (b & ~m) with all three operands in vector registers: v_bitop3_b32 runs at full rate (a wavefront
 // instruction every two cycles per SIMD) only in that form; with a scalar or literal operand, and v_bfi_b32 /
 // v_and_or_b32 in any form, take four cycles (measured).  The masks of the merge trees are therefore kept in
@@ -89,12 +81,6 @@ __device__ __forceinline__ uint32_t bfi_insn(uint32_t mask, uint32_t a, uint32_t
 __device__ __forceinline__ uint32_t bfi_v(uint32_t m, uint32_t a, uint32_t b) {
   uint32_t r;
   asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xca" : "=v"(r) : "v"(m), "v"(a), "v"(b));
-  return r;
-}
-// (a & m) | b, same form
-__device__ __forceinline__ uint32_t and_or_v(uint32_t a, uint32_t m, uint32_t b) {
-  uint32_t r;
-  asm("v_bitop3_b32 %0, %1, %2, %3 bitop3:0xea" : "=v"(r) : "v"(a), "v"(m), "v"(b));
   return r;
 }
 __device__ __forceinline__ uint32_t vreg_const(uint32_t c) {
@@ -145,23 +131,7 @@ __device__ __forceinline__ void merge_byte_fields(const uint32_t (&w)[K], uint32
   R[7] = bfi(field_mask(8, 7, 4), B[0][3], B[1][3]);
 }
 
-// k = 4: planes of one row -> four words of four bytes 16 a + b.  Word c collects the 4-bit codes whose top
-// bit sits at a position congruent to c (mod 4) and is rotated so that codes fill whole nibbles; the two
-// weights of a byte are four positions apart.
-__device__ __forceinline__ void merge_nibble_pairs(const uint32_t (&w)[4], uint32_t (&T)[4]) {
-  uint32_t A[2][2];
-#pragma unroll
-  for (int i = 0; i < 2; ++i) {
-    A[i][0] = bfi(field_mask(2, 0, 1), w[2 * i], w[2 * i + 1]);
-    A[i][1] = bfi(field_mask(2, 1, 1), w[2 * i], w[2 * i + 1]);
-  }
-  T[0] = __builtin_rotateright32(bfi(field_mask(4, 0, 2), A[0][0], A[1][0]), 1);
-  T[1] = __builtin_rotateright32(bfi(field_mask(4, 1, 2), A[0][1], A[1][1]), 2);
-  T[2] = __builtin_rotateright32(bfi(field_mask(4, 2, 2), A[0][0], A[1][0]), 3);
-  T[3] = bfi(field_mask(4, 3, 2), A[0][1], A[1][1]);
-}
-
-// The same trees with their masks in vector registers (MergeMasks<K>::init, once per workgroup).
+// The tree with its masks in vector registers (MergeMasks<K>::init, once per workgroup).
 template <int K>
 struct MergeMasks {
   static constexpr int count = K == 3 ? 8 : K == 4 ? 6 : 15;   // k >= 5: 14 masks and a zero
@@ -222,6 +192,9 @@ __device__ __forceinline__ void merge_byte_fields_v(const uint32_t (&w)[K], uint
   R[7] = bfi_v(M.m[13], B[0][3], B[1][3]);
 }
 
+// k = 4: planes of one row -> four words of four bytes 16 a + b.  Word c collects the 4-bit codes whose top
+// bit sits at a position congruent to c (mod 4) and is rotated so that codes fill whole nibbles; the two
+// weights of a byte are four positions apart.
 __device__ __forceinline__ void merge_nibble_pairs_v(const uint32_t (&w)[4], uint32_t (&T)[4], const MergeMasks<4>& M) {
   uint32_t A[2][2];
 #pragma unroll
@@ -235,7 +208,7 @@ __device__ __forceinline__ void merge_nibble_pairs_v(const uint32_t (&w)[4], uin
   T[3] = bfi_v(M.m[5], A[0][1], A[1][1]);
 }
 
-// columns of the two weights in byte m of word c of merge_nibble_pairs: upper nibble, lower nibble
+// columns of the two weights in byte m of word c of merge_nibble_pairs_v: upper nibble, lower nibble
 __host__ __device__ constexpr int nibble_pair_col_hi(int c, int m) { return pos_to_col((8 * m + 7 + ((c + 1) & 3)) & 31); }
 __host__ __device__ constexpr int nibble_pair_col_lo(int c, int m) { return pos_to_col((8 * m + 3 + ((c + 1) & 3)) & 31); }
 

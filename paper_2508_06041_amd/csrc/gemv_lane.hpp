@@ -84,8 +84,8 @@ __host__ __device__ constexpr int lane_x_bytes() {
 // tables, partial sums, activation slots, and (one sample: the decode step) room for the selectors.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
 // activations are borrowed from the partial sums, which are not in use between the barrier that opens a row block
 // and the stores that close it (its own partial sums of sample 0).
-// Eight samples: their partial sums take the place of the tables, which are done with by then (two barriers more per row
-// block keep two workgroups per compute unit), and activations are re-paired in place.
+// Eight samples: their partial sums take the place of the tables, which are done with by then (at G = 1 two barriers more
+// per row block keep two workgroups per compute unit), and activations are re-paired in place.
 template <int NB>
 __host__ __device__ constexpr int lane_red_offset() { return NB == 8 ? 0 : kLaneTableBytes; }
 template <int NB>
@@ -94,8 +94,10 @@ template <int NB, int G>
 __host__ __device__ constexpr int lane_lds_bytes() {
   return lane_x_offset<NB>() + kLaneWaves * lane_x_bytes<NB, G>() + (NB == 1 ? kSelSharedBytes : 0);
 }
-static_assert(8 * kLaneRedBytes <= LaneDecode<3>::table_bytes && lane_lds_bytes<8, 1>() <= 81920 && lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920 && lane_lds_bytes<1, 2>() <= 81920 &&
-              lane_lds_bytes<1, 4>() <= 81920, "two workgroups per compute unit");
+static_assert(8 * kLaneRedBytes <= LaneDecode<3>::table_bytes, "room for the sums of eight samples");
+static_assert(lane_lds_bytes<8, 1>() <= 81920 && lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920, "two workgroups per compute unit");
+static_assert(lane_lds_bytes<1, 8>() <= 163840 && lane_lds_bytes<4, 8>() <= 163840 && lane_lds_bytes<8, 4>() <= 163840,
+              "one workgroup per compute unit (the registers of several column groups allow no second one)");
 
 // x pair held by lane Q of the quad, times the looked-up pair, added to acc
 template <int Q>
@@ -871,9 +873,9 @@ __device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, Off l
 }
 
 // The bitwidth of the job: its own value, the word a selector left in device memory, or the decision taken here
-// from the partial products that the launch's workgroups left in the slots (every workgroup of the job repeats the same
-// fixed-order sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value the
-// linear does not serve (outside [max(kmin, 3), p]) is not served: the workgroup returns and y keeps what it held.
+// from the partial products in the slots, left by workgroups of this launch or of an earlier one (every workgroup of the job repeats the same
+// fixed-order sums, so all arrive at the same bits; the job's first workgroup writes bitwidth and estimate out).  A value
+// outside [kmin, p] is not served: the workgroup returns and y keeps what it held.
 template <int G>
 __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, int tid, char* lds, const SelParams* active,
                                                 int polls) {   // active == nullptr: no decisions here
@@ -929,8 +931,8 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
 }
 
 // The linears of a dependency level of a decode step: block b < nblocks belongs to job block_jobs[b]; blocks past them
-// help with the selectors only.  active: the table of selector parameters, for launches that run the selectors of their
-// jobs (tasks, see selector_tasks) and take the decisions here; else nullptr.
+// help with the selectors only.  active: the table of selector parameters, for launches that take the decisions of their
+// jobs here; else nullptr.  ntasks: selector work of the launch (see selector_tasks), 0 if an earlier one did it.
 template <int G>
 __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_step_kernel(const SelTask* tasks, const GemvJob* jobs, const int32_t* block_jobs,
                                                                                 const SelParams* active, int ntasks, int task_groups,

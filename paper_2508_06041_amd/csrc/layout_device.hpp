@@ -42,7 +42,6 @@ __host__ __device__ constexpr uint32_t rotl_c(uint32_t v, int s) {
   s &= 31;
   return s ? (v << s) | (v >> (32 - s)) : v;
 }
-__host__ __device__ constexpr uint32_t rotr_c(uint32_t v, int s) { return rotl_c(v, 32 - (s & 31)); }
 
 // positions q with (c - q) mod period < width: the bits a field of `width` planes occupies when its top
 // bit sits at a position congruent to c

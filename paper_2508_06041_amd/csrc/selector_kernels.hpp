@@ -7,7 +7,7 @@
 // precision the model runs under (Algorithm 1 hands out one threshold list per target; Sec. 5.1 keeps one G per
 // candidate pair): a table on the device holds the parameters of every target, and the kernels read a copy of the
 // active target's row.  A switch of target is one small kernel (selector_activate_kernel) that copies the row and
-// puts the rows of G where the tasks find them; the launches stay what they are, and none of them has to look the
+// writes the tasks of the small launches; the launches stay what they are, and none of them has to look the
 // target up before it can look its parameters up (a round trip to memory of 0.6 us in every launch of a chained step).
 //
 // A projection job reads 0.5 - 3.5 MB of G.  It is cut into parts of 16 rows of G (one workgroup of four
@@ -18,11 +18,14 @@
 // sum x^2 only: the jobs of a launch that read the same input vector form a group with one extra part, which
 // adds up x^2 once and leaves it in the slot of every member that asks for it.
 //
-// Who takes the estimate and the decision:
-//   - selectors alone, and in front of GEMV launches that fill the chip several times over: selector_decide_kernel, in
+// Who takes the estimate and the decision (the choice for a step: runs_selectors and kPrologueMaxBlocks in dpllm_api.hip):
+//   - selectors alone, and in front of large GEMV launches: selector_decide_kernel, in
 //     a launch of its own behind the parts (the end of one launch and the start of the next order the two at device
 //     scope);
-//   - in the small launches of a chained step (selector_tasks, selector_gather): every workgroup of the GEMV launch
+//   - in GEMV launches of up to two rounds of workgroups: every workgroup, before it starts (selector_gather), from the
+//     slots of its own linear;
+//   - in the small launches of a chained step, whose selectors are little work (selector_tasks, selector_gather): every
+//     workgroup of the GEMV launch
 //     first works off its share of the launch's selectors, a row of G times a slice of the columns, and leaves the
 //     partial dot product in its slot; then every workgroup collects the slots of its own linear, adds them up and
 //     decides.  A slot is its own flag: it holds kSelEmpty (a NaN no writer stores) until the value is there, and both
@@ -36,12 +39,12 @@
 //     blocks 1888 -> 1428 us, of 16 8B blocks with selectors ahead 1060 -> 940.  Tried on top of it: asking for the
 //     planes and tables of the level while the selectors work (the traffic delays the hand-over by more than it saves:
 //     1605 us with the first tiles, 1460 with the table rows alone), longer pauses between polls (no change).
-// Either way the partial products of every row are added in chunk order, squared, added over the rows in index order:
-// the order of all additions is fixed, so every workgroup that repeats it gets the same bits.
 //
-// The estimate and the compare are taken in fp64: fp16 x fp16 products are exact in fp32, their sum runs in
-// fp64 in a fixed order, so a decision is reproducible and differs from an ideal-arithmetic decision only
-// when |e - T| is below ~1e-13 relative.
+// The estimate and the compare are taken in fp64: fp16 x fp16 products are exact in fp32, their sums run in fp64.  Every
+// order of additions is fixed, so a decision is reproducible and workgroups that repeat it get the same bits, but the
+// orders differ: the columns of a row are cut differently for parts and tasks, selector_finish adds the squares of the rows
+// in 64 lanes, selector_gather in 512.  Estimates of dpllm_estimate, of DPLLM_STEP_SELECT and of a whole step agree to about
+// 1e-13 relative; a decision differs between them, or from an ideal-arithmetic one, only when |e - T| is below that.
 #pragma once
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
