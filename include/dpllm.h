@@ -99,7 +99,8 @@ int dpllm_load_linear(dpllm_model* m, int id, int out, int in, int p, int kmin,
 int dpllm_workspace_bytes(const dpllm_model* m, size_t* bytes);
 
 /* Hands the model its workspace: ws_dev (device, caller-owned, 256-byte aligned, >= dpllm_workspace_bytes), which
- * the model uses until it is destroyed or given another.  Enqueues the clearing of its target word on `stream`.
+ * the model uses until it is destroyed or given another.  Enqueues the clearing of its target word and of what estimates
+ * hand over on `stream`.
  * dpllm_estimate, dpllm_decode_step(_parts) and dpllm_set_target need a workspace; dpllm_gemv runs without one.
  * Errors: EINVAL, ESTATE (too small), EHIP. */
 int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream);

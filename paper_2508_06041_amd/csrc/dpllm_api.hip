@@ -108,7 +108,8 @@ struct StepPlan {
 struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
-  size_t est_ws = 0;                         // dpllm_estimate: kSelOneSlots fp64
+  size_t est_ws = 0;                         // dpllm_estimate in two launches: kSelOneSlots fp64
+  size_t est_slots = 0, est_slots_cap = 0;   // dpllm_estimate in one: uint64 [kEstRing][cap], empty between calls
   size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
   size_t sel_active = 0;                     // SelParams [n]: the row of the active target
@@ -139,6 +140,10 @@ struct dpllm_model {
   std::vector<GemvJob> h_gemv_jobs;
   std::vector<int32_t> h_block_jobs;
   std::vector<SelParams> h_params;
+  unsigned est_turn = 0;           // estimates take turns in the sets of slots,
+  hipStream_t ws_stream = nullptr; //   which dpllm_set_workspace empties on this stream:
+  hipEvent_t ws_event = nullptr;   //   done for every stream to see once the event has passed
+  bool est_ready = false;
   int polls = kSelPolls;           // < 0: the selector tasks are left out of the launches (dpllm_debug_set_polls)
   int device = 0;
 };
@@ -185,13 +190,19 @@ Linear* get_linear(dpllm_model* m, int id, int* rc) {
 // slices of a row of G, at most
 int sel_slices(int in) { return (in + kSelTaskCols - 1) / kSelTaskCols; }
 
+// slots of an estimate in one launch: 16 rows of G in chunks of 512 columns and more
+size_t est_slots_of(const Linear& lin, int rowgroups) {
+  return (size_t)rowgroups * kSelPartRows * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
+}
+
 // Sized for any launch plan over the linears as they stand (shapes, pairs): the caps are upper bounds.
 Workspace carve_workspace(const dpllm_model* m) {
   Workspace w;
   const size_t n = m->linears.size();
-  size_t parts = 0, slots = 0, blocks = 0, tasks = 0;
+  size_t parts = 0, slots = 0, blocks = 0, tasks = 0, est = 0;
   for (const Linear& lin : m->linears) {
     if (!lin.loaded) continue;
+    if (lin.max_rowgroups() > 0) est = std::max(est, est_slots_of(lin, lin.max_rowgroups()));
     const size_t rg = (size_t)std::max(1, lin.max_rowgroups());
     parts += rg * kSelMaxChunks + 1;
     slots += rg * kSelPartRows * std::max(kSelMaxChunks, kSelCopies * sel_slices(lin.L.in));
@@ -201,6 +212,8 @@ Workspace carve_workspace(const dpllm_model* m) {
   size_t off = 0;
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
   w.est_ws = take(sizeof(double) * kSelOneSlots);
+  w.est_slots_cap = est;
+  w.est_slots = take(sizeof(uint64_t) * kEstRing * est);
   w.target = take(sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
   w.sel_active = take(sizeof(SelParams) * n);
@@ -707,7 +720,10 @@ int dpllm_model_create(dpllm_model** out, int n_linears) {
   return DPLLM_OK;
 }
 
-void dpllm_model_destroy(dpllm_model* m) { delete m; }
+void dpllm_model_destroy(dpllm_model* m) {
+  if (m && m->ws_event) (void)hipEventDestroy(m->ws_event);
+  delete m;
+}
 
 const char* dpllm_last_error(const dpllm_model* m) { return m ? m->err.c_str() : "null model"; }
 
@@ -747,11 +763,18 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   w.base = (char*)ws_dev;
   w.bytes = bytes;
   hipStream_t st = (hipStream_t)stream;
-  // the target starts at zero and the jobs without tasks; everything else is written before it is used
-  struct { size_t off, words; } zero[] = {{w.target, 1}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size()}};
-  for (const auto& z : zero)
-    hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, 0u);
+  if (capturing(st)) w.est_slots_cap = 0;   // (emptied by a replay at some time to come: no estimate relies on it)
+  else if (w.est_slots_cap > 0 && !m->ws_event) HIP_TRY(m, hipEventCreateWithFlags(&m->ws_event, hipEventDisableTiming));
+  // the target starts at zero, the jobs without tasks, the slots of lone estimates empty; everything else is written before it is used
+  struct { size_t off, words; uint32_t value; } start[] = {{w.target, 1, 0u}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size(), 0u},
+                                                           {w.est_slots, w.est_slots_cap * kEstRing * 2, (uint32_t)kSelEmpty}};
+  for (const auto& z : start)
+    if (z.words > 0)
+      hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, z.value);
   HIP_TRY(m, hipGetLastError());
+  if (w.est_slots_cap > 0) HIP_TRY(m, hipEventRecord(m->ws_event, st));
+  m->ws_stream = st;
+  m->est_ready = false;
   m->ws = w;
   m->params_dirty = true;
   m->version++;
@@ -929,6 +952,27 @@ static int launch_estimate(dpllm_model* m, const Linear& lin, int id, const Pair
   return DPLLM_OK;
 }
 
+// one launch, with slots of the workspace; false: a pair attached after the workspace was handed over needs more of them, or they
+// may not be empty yet
+static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, const Pair& sel, const void* x_dev, float* e_dev, int32_t* k_dev,
+                                 hipStream_t st) {
+  const Workspace& W = m->ws;
+  const int rowgroups = sel_rowgroups_of(sel.kind, sel.r);
+  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups);
+  if ((size_t)rowgroups * kSelPartRows * j.nchunks > W.est_slots_cap) return false;
+  if (!m->est_ready && sel.kind == DPLLM_SEL_PROJ) {
+    // the slots are empty for work behind dpllm_set_workspace on its stream, for any other once that has been seen to be done
+    if (!capturing(st) && hipEventQuery(m->ws_event) == hipSuccess) m->est_ready = true;
+    else (void)hipGetLastError();
+    if (!m->est_ready && st != m->ws_stream) return false;
+  }
+  const unsigned turn = sel.kind == DPLLM_SEL_PROJ ? m->est_turn++ % kEstRing : 0;
+  const int parts = sel.kind == DPLLM_SEL_PROJ ? (sel.r + kEstPartRows - 1) / kEstPartRows * j.nchunks : 1;
+  hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, j.x,
+                     W.at<double>(W.est_slots) + turn * W.est_slots_cap, j.in, sel.r, j.nchunks, j.chunk_cols, j.ws_rows, sel.kind, j, make_params(sel, sel.T));
+  return true;
+}
+
 static int check_estimate_args(dpllm_model* m, int id, int l, int h, const void* x_dev, float* e_dev, int32_t* k_dev, Linear** lin,
                                int* slot) {
   int rc = DPLLM_OK;
@@ -948,6 +992,10 @@ int dpllm_estimate(dpllm_model* m, int id, int l, int h, const void* x_dev, floa
   int rc = check_estimate_args(m, id, l, h, x_dev, e_dev, k_dev, &lin, &slot);
   if (rc != DPLLM_OK) return rc;
   if (!m->ws.base) return fail(m, DPLLM_ESTATE, "no workspace set");
+  if (launch_estimate_once(m, *lin, id, lin->sel[slot], x_dev, e_dev, k_dev, (hipStream_t)stream)) {
+    HIP_TRY(m, hipGetLastError());
+    return DPLLM_OK;
+  }
   return launch_estimate(m, *lin, id, lin->sel[slot], x_dev, e_dev, k_dev, m->ws.at<double>(m->ws.est_ws), (hipStream_t)stream);
 }
 

@@ -19,9 +19,10 @@
 // adds up x^2 once and leaves it in the slot of every member that asks for it.
 //
 // Who takes the estimate and the decision (the choice for a step: runs_selectors and kPrologueMaxBlocks in dpllm_api.hip):
-//   - selectors alone, and in front of large GEMV launches: selector_decide_kernel, in
+//   - the selectors of a step alone, and in front of large GEMV launches: selector_decide_kernel, in
 //     a launch of its own behind the parts (the end of one launch and the start of the next order the two at device
 //     scope);
+//   - one estimate (dpllm_estimate): the workgroup of the part launch that started last (selector_estimate_kernel);
 //   - in GEMV launches of up to two rounds of workgroups: every workgroup, before it starts (selector_gather), from the
 //     slots of its own linear;
 //   - in the small launches of a chained step, whose selectors are little work (selector_tasks, selector_gather): every
@@ -138,30 +139,33 @@ __device__ __forceinline__ double wave_sum_f64(double v) {
 
 typedef uint32_t sel_u32x4 __attribute__((ext_vector_type(4)));
 
+template <int ROWS>
 struct SelTile {
-  sel_u32x4 g[kSelRowsPerWave];
+  sel_u32x4 g[ROWS];
   uint4 x;
 };
 
-// columns [c, c + 8) of the wavefront's four rows and of x; c is clamped by the caller, so the loads are
+// columns [c, c + 8) of the wavefront's rows and of x; c is clamped by the caller, so the loads are
 // unconditional and the next tile can be in flight while the current one is accumulated
 // (pointers taken from a job record are generic; global-address-space loads keep them on the vector-memory path)
 #define DPLLM_SEL_GLOBAL __attribute__((address_space(1)))
-__device__ __forceinline__ void sel_load(SelTile& t, const uint16_t* const (&rows)[kSelRowsPerWave], const uint16_t* x, int c) {
+template <int ROWS>
+__device__ __forceinline__ void sel_load(SelTile<ROWS>& t, const uint16_t* const (&rows)[ROWS], const uint16_t* x, int c) {
 #pragma unroll
-  for (int i = 0; i < kSelRowsPerWave; ++i)
+  for (int i = 0; i < ROWS; ++i)
     t.g[i] = __builtin_nontemporal_load((const DPLLM_SEL_GLOBAL sel_u32x4*)(rows[i] + c));
   const sel_u32x4 xv = *(const DPLLM_SEL_GLOBAL sel_u32x4*)(x + c);
   t.x = make_uint4(xv.x, xv.y, xv.z, xv.w);
 }
 
-__device__ __forceinline__ void sel_accumulate(const SelTile& t, bool valid, double (&acc)[kSelRowsPerWave]) {
+template <int ROWS>
+__device__ __forceinline__ void sel_accumulate(const SelTile<ROWS>& t, bool valid, double (&acc)[ROWS]) {
   const __half* xh = reinterpret_cast<const __half*>(&t.x);
   double xd[8];
 #pragma unroll
   for (int i = 0; i < 8; ++i) xd[i] = valid ? (double)__half2float(xh[i]) : 0.0;
 #pragma unroll
-  for (int r = 0; r < kSelRowsPerWave; ++r) {
+  for (int r = 0; r < ROWS; ++r) {
     const __half* gh = reinterpret_cast<const __half*>(&t.g[r]);
     // an fp16 x fp16 product is exact in fp64, so the fused multiply-add rounds once, like an fp64 add of the
     // exact product
@@ -280,21 +284,24 @@ __device__ __forceinline__ void selector_group_part(const SelJob* jobs, const in
   }
 }
 
-// One projection part: wavefront w owns rows 16 rg + 4 w .. + 3 (clamped to r - 1; surplus rows are dropped),
+// One projection part: wavefront w owns ROWS rows (clamped to r - 1; surplus rows are dropped), with four of them 16 rg + 4 w .. + 3,
 // columns [cb, ce) of them
+// HANDED: the products are read inside this launch (selector_estimate_kernel), and slots of surplus rows stay empty
+template <bool HANDED = false, int ROWS = kSelRowsPerWave>
 __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelParams& P, int part, int tid) {
   const int wave = tid >> 6, lane = tid & 63;
   if (P.kind != 1) return;                                    // this target estimates the linear otherwise
   const int rg = part / job.nchunks, ch = part - rg * job.nchunks;
-  if (rg >= sel_rowgroups_of(1, P.r)) return;                 // the pair of this target has fewer rows of G
+  constexpr int part_rows = kSelPartWaves * ROWS;
+  if (rg * part_rows >= P.r) return;                          // the pair of this target has fewer rows of G
   const int cb = ch * job.chunk_cols, ce = min(job.in, cb + job.chunk_cols);
-  const int row0 = rg * kSelPartRows + wave * kSelRowsPerWave;
-  const uint16_t* rows[kSelRowsPerWave];
+  const int row0 = rg * part_rows + wave * ROWS;
+  const uint16_t* rows[ROWS];
 #pragma unroll
-  for (int i = 0; i < kSelRowsPerWave; ++i) rows[i] = P.G + (size_t)min(row0 + i, P.r - 1) * job.in;
-  double acc[kSelRowsPerWave];
+  for (int i = 0; i < ROWS; ++i) rows[i] = P.G + (size_t)min(row0 + i, P.r - 1) * job.in;
+  double acc[ROWS];
 #pragma unroll
-  for (int i = 0; i < kSelRowsPerWave; ++i) acc[i] = 0.0;
+  for (int i = 0; i < ROWS; ++i) acc[i] = 0.0;
   const int last = ce - 8;              // in % 32 == 0 and chunks are multiples of 512, so every 8-column group is whole
   const int nit = (ce - cb + kSelChunkStep - 1) / kSelChunkStep;
   // Rows of G are a power-of-two number of bytes apart in the common shapes, so wavefronts that all walk the
@@ -302,7 +309,7 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
   // (circular) walk at a different 1 KiB column chunk.
   int it = (int)((blockIdx.x * kSelPartWaves + wave) * 5u % (unsigned)nit);   // tile being loaded
   int ca = cb + it * kSelChunkStep + lane * 8;                                // first column of the tile being accumulated
-  SelTile ring[kSelDepth];
+  SelTile<ROWS> ring[kSelDepth];
 #pragma unroll
   for (int d = 0; d < kSelDepth - 1; ++d) {
     sel_load(ring[d], rows, job.x, min(cb + it * kSelChunkStep + lane * 8, last));
@@ -320,9 +327,15 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
   }
   DPLLM_SEL_GLOBAL double* ws = (DPLLM_SEL_GLOBAL double*)job.ws;
 #pragma unroll
-  for (int i = 0; i < kSelRowsPerWave; ++i) {
+  for (int i = 0; i < ROWS; ++i) {
     const double rowsum = wave_sum_f64(acc[i]);
-    if (lane == 0) ws[(size_t)ch * job.ws_rows + row0 + i] = sel_storable(rowsum);
+    const size_t at = (size_t)ch * job.ws_rows + row0 + i;
+    if constexpr (HANDED) {
+      if (lane == 0 && row0 + i < P.r)
+        __hip_atomic_store((DPLLM_SEL_GLOBAL uint64_t*)ws + at, __builtin_bit_cast(uint64_t, sel_storable(rowsum)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      if (lane == 0) ws[at] = sel_storable(rowsum);
+    }
   }
 }
 
@@ -556,6 +569,97 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
   }
   const SelJob job = jobs[blockIdx.x];
   selector_finish(sel_finish_of(job), active + job.linear, threadIdx.x, kSelDecideThreads, sh.sq, true);
+}
+
+// One estimate in one launch.  The workgroups are parts of the projection, four rows of G by a chunk of columns; the last one
+// collects the products of all and decides.  A product travels through a slot that is its own flag (kSelEmpty until it is there,
+// relaxed atomics on that one word on both sides); who has collected it empties the slot again, so that every launch finds the
+// slots empty.  Workgroups start in order, and no more than one per launch ever waits, so those it waits for find a place whatever
+// else the chip is doing: the wait ends.  (It is bounded all the same; a product nobody delivered is the NaN in its slot, and so
+// is the estimate then: l.)  Launches take turns in kEstRing sets of slots.
+// What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection. 
+// us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> now: rank 64 of 4096 columns
+// 4.5 / 7.4 -> 3.3 / 4.2, of 11008 5.7 / 7.3 -> 4.2 / 4.5, rank 1024 of 4096 9.8 / 10.0 -> 9.3 / 9.2, linear regression 3.6 / 7.2 ->
+// 2.0 / 4.5 (eager: the host takes 4.2 for a call).
+constexpr int kEstRing = 16;
+constexpr int kEstRows = 1;             // rows of G of a wavefront (14 linears of 7B with a GEMV each: 164 us; with four, and a counter that says who started last, 178)
+constexpr int kEstPartRows = kSelPartWaves * kEstRows;
+constexpr int kEstPolls = 1 << 20;      // of about a microsecond
+
+// rows t, t + 64, ... of the products in lane t, each the sum of its chunks in order; BATCH chunks are asked for at a time
+template <int BATCH>
+__device__ __forceinline__ void selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, int nchunks, int ws_rows, int r, int tid, double* sq) {
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  int left = kEstPolls;
+  for (int t0 = wave * 64; t0 < r; t0 += kSelPartThreads) {
+    const int t = min(t0 + lane, r - 1);
+    double g = 0.0;
+    for (int c0 = 0; c0 < nchunks; c0 += BATCH) {
+      uint64_t v[BATCH];
+      for (;;) {
+        bool all = true;
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i)
+          v[i] = __hip_atomic_load(slots + (size_t)min(c0 + i, nchunks - 1) * ws_rows + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+        for (int i = 0; i < BATCH; ++i) all = all && v[i] != kSelEmpty;
+        if (__all(all) || --left < 0) break;
+        __builtin_amdgcn_s_sleep(1);
+      }
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) {
+        if (c0 + i >= nchunks) break;
+        g += __builtin_bit_cast(double, v[i]);
+        __hip_atomic_store(slots + (size_t)(c0 + i) * ws_rows + t, kSelEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    if (t0 + lane < r) sq[t] = g * g;
+  }
+}
+
+// G .. kind: what a workgroup needs to ask for its first rows comes as plain arguments (see gemv_lane_kernel)
+__global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, double* ws, int in, int r,
+                                                                           int nchunks, int chunk_cols, int ws_rows, int kind, SelJob job, SelParams P) {
+  __shared__ SelShared sh;
+  const int tid = threadIdx.x;
+  P.G = G; P.r = r; P.kind = kind;
+  job.x = x; job.ws = ws; job.in = in; job.nchunks = nchunks; job.chunk_cols = chunk_cols; job.ws_rows = ws_rows;
+  double e = 0.0;
+  if (kind == 1) {
+    selector_proj_part<true, kEstRows>(job, P, blockIdx.x, tid);
+    if (blockIdx.x + 1 != gridDim.x) return;
+    if (nchunks <= 8) selector_collect<8>((DPLLM_SEL_GLOBAL uint64_t*)ws, nchunks, ws_rows, r, tid, sh.sq);
+    else selector_collect<24>((DPLLM_SEL_GLOBAL uint64_t*)ws, nchunks, ws_rows, r, tid, sh.sq);
+    __syncthreads();
+    if (tid >= 64) return;
+    // as selector_finish does: the same bits
+    double part = 0.0;
+    for (int t = tid; t < r; t += 64) part += sh.sq[t];
+    e = sqrt(wave_sum_f64(part));
+  } else if (kind == 2) {
+    // as selector_group_part does
+    const int wave = tid >> 6, lane = tid & 63;
+    double acc = 0.0;
+    for (int c = tid * 8; c < in; c += kSelPartThreads * 8) {
+      const sel_u32x4 xv = *(const DPLLM_SEL_GLOBAL sel_u32x4*)(x + c);
+      const __half* xh = reinterpret_cast<const __half*>(&xv);
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float v = __half2float(xh[i]);
+        acc += (double)(v * v);  // exact square in fp32
+      }
+    }
+    acc = wave_sum_f64(acc);
+    if (lane == 0) sh.sq[wave] = acc;
+    __syncthreads();
+    double tot = 0.0;
+    for (int w = 0; w < kSelPartWaves; ++w) tot += sh.sq[w];
+    e = (double)P.alpha * sqrt(tot) + (double)P.beta;
+  }
+  if (tid == 0) {
+    *job.e_out = (float)e;
+    *job.k_out = kind != 0 && e > (double)P.T ? P.h : P.l;
+  }
 }
 
 }  // namespace dpllm

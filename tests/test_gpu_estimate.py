@@ -1,0 +1,90 @@
+"""GPU tests of dpllm_estimate in one launch (selector_estimate_kernel): products of four rows of G by a chunk of columns,
+collected by the launch's last workgroup from slots that it empties again."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dp():
+    import paper_2508_06041_amd as dp
+    assert torch.cuda.is_available()
+    return dp
+
+
+def _model(dp, in_, seed):
+    lin = synth.make_linear(8, in_, 4, 3, seed=seed)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, synth.planes_np(lin["planes"]), {k: synth.lut_np(v) for k, v in lin["luts"].items()}, 3)
+    return model
+
+
+def _G(r, in_, seed):
+    return (torch.randn(r, in_, generator=torch.Generator().manual_seed(seed)) / math.sqrt(r)).half()
+
+
+# ranks around the four rows of a workgroup, the 64 lanes and the 256 threads that collect; columns below one chunk of 512, with a
+# ragged last chunk, of 8 chunks (one batch), 9 and 33 (two batches; chunks of 1024)
+@pytest.mark.parametrize("in_,r", [(32, 1), (544, 3), (512, 4), (1056, 5), (4096, 64), (4128, 65), (11008, 64), (16416, 40), (2080, 257), (4096, 1024)])
+def test_estimate_matches_oracle_over_the_ring(dp, in_, r):
+    """More calls than there are sets of slots, two inputs in turn: a slot that was not emptied would show."""
+    model, G = _model(dp, in_, seed=in_ + r), _G(r, in_, in_ + r)
+    X = synth.make_x(in_, 2, seed=r)
+    X[1] *= 3.0
+    est = [oracle.estimate(synth.lut_np(G), synth.lut_np(x)) for x in X]
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.5 * sum(est))))
+    xs, e, k = [x.cuda() for x in X], torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    first = {}
+    for rep in range(36):
+        which = rep % 2 if rep < 20 else rep % 3 % 2
+        e.fill_(-1.0), k.zero_()
+        model.dpllm_estimate(0, 3, 4, xs[which], e_out=e, k_out=k)
+        assert math.isclose(float(e), est[which], rel_tol=3e-7) and int(k) == 3 + which, rep
+        assert first.setdefault(which, float(e)) == float(e), rep
+    model.close()
+
+
+def test_estimates_of_several_ranks_share_the_slots(dp):
+    """Pairs of different ranks and kinds in turn, eager and as replays of a graph that holds more estimates than sets of slots; a
+    pair whose products do not fit the workspace takes two launches and leaves the same bits."""
+    in_ = 2080
+    model = _model(dp, in_, seed=5)
+    small, large = _G(9, in_, 1), _G(96, in_, 2)
+    x = synth.make_x(in_, 1, seed=3)[0]
+    refs = [oracle.estimate(synth.lut_np(G), synth.lut_np(x)) for G in (small, large)] + [oracle.linreg_estimate(synth.lut_np(x), 0.5, 0.25)]
+    model.dpllm_set_selector(0, 3, 3, dp.DPLLM_SEL_PROJ, G=small.cuda(), T=math.inf)
+    model.dpllm_set_selector(0, 4, 4, dp.DPLLM_SEL_LINREG, alpha=0.5, beta=0.25, T=0.0)
+    pairs, x = [(3, 3), (3, 4), (4, 4)], x.cuda()
+    e, k = torch.zeros(3, device="cuda"), torch.zeros(3, dtype=torch.int32, device="cuda")
+
+    def all_three():
+        for i, (l, h) in enumerate(pairs):
+            model.dpllm_estimate(0, l, h, x, e_out=e[i:i + 1], k_out=k[i:i + 1])
+
+    model.dpllm_set_workspace()          # of the size asked for before the pair of rank 96
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=large.cuda(), T=float(np.float32(0.9 * refs[1])))
+    model._ws_stale = False
+    all_three()
+    two = e.clone()
+    model.dpllm_set_workspace()
+    all_three()
+    torch.cuda.synchronize()
+    assert torch.equal(e, two) and k.tolist() == [3, 4, 4]
+    assert all(math.isclose(a, b, rel_tol=3e-7) for a, b in zip(e.tolist(), refs))
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for _ in range(7):
+            all_three()
+    for rep in range(5):
+        e.zero_(), k.zero_()
+        (graph.replay if rep != 2 else all_three)()
+        torch.cuda.synchronize()
+        assert torch.equal(e, two) and k.tolist() == [3, 4, 4], rep
+    model.close()
