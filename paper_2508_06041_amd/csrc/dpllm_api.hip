@@ -13,6 +13,7 @@
 
 #include "../../include/dpllm.h"
 #include "aux_kernels.hpp"
+#include "chain_kernel.hpp"
 #include "gemv_lane.hpp"
 #include "layout.hpp"
 #include "selector_kernels.hpp"
@@ -89,6 +90,7 @@ struct Phase {
 };
 constexpr int kMaxGroups = 8;           // column groups per wavefront, at most
 constexpr int kSelPolls = 64;           // polls of about a microsecond before a workgroup computes missing products itself
+constexpr int kChainPatience = 1 << 21;   // polls of about a microsecond in a whole step before a wavefront of gemv_chain_kernel gives up
 constexpr size_t kSelOneSlots = (size_t)kSelMaxChunks * kSelMaxRank;
 
 struct StepPlan {
@@ -102,6 +104,10 @@ struct StepPlan {
   size_t slots = 0;      // partial dot products of all selectors; emptied at the start of a whole step if
   bool fused = false;    //   any of its phases runs selectors inside its GEMV launch
   bool idle = false;     // some phase has no estimator under any target, though its linears hold pairs with one
+  bool chain = false;    // a whole step is one launch (gemv_chain_kernel)
+  int chain_bits = 0;    //   the largest bitwidth of a pair
+  int chain_grid = 0;
+  size_t chain_slots = 0, chain_mail = 0;   // 64-bit words
 };
 
 // The caller's workspace, carved once by dpllm_set_workspace.  Offsets in bytes, every region 256-byte aligned.
@@ -119,6 +125,9 @@ struct Workspace {
   size_t sel_ws = 0, sel_ws_cap = 0;         // fp64 [cap]
   size_t gemv_jobs = 0;                      // GemvJob [n]
   size_t block_jobs = 0, block_jobs_cap = 0; // int32 [cap]
+  size_t chain_state = 0;                    // uint32 [kChainStateWords]
+  size_t chain_levels = 0, chain_jobs = 0;   // ChainLevel [n + 1], ChainJob [n]
+  size_t chain_mail = 0, chain_mail_cap = 0; // 64-bit words [cap]
   size_t total = 0;
   template <class T>
   T* at(size_t off) const { return reinterpret_cast<T*>(base + off); }
@@ -139,6 +148,8 @@ struct dpllm_model {
   std::vector<int32_t> h_sel_members;
   std::vector<GemvJob> h_gemv_jobs;
   std::vector<int32_t> h_block_jobs;
+  std::vector<ChainLevel> h_chain_levels;
+  std::vector<ChainJob> h_chain_jobs;
   std::vector<SelParams> h_params;
   unsigned est_turn = 0;           // estimates take turns in the sets of slots,
   hipStream_t ws_stream = nullptr; //   which dpllm_set_workspace empties on this stream:
@@ -195,14 +206,18 @@ size_t est_slots_of(const Linear& lin, int rowgroups) {
   return (size_t)rowgroups * kSelPartRows * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
 }
 
+// 64-bit words of one copy of a linear's mailbox (whole lines: no two linears share one)
+size_t mail_words(const LinearLayout& L) { return align_up((size_t)L.rows_padded * 2, kAlign) / 8; }
+
 // Sized for any launch plan over the linears as they stand (shapes, pairs): the caps are upper bounds.
 Workspace carve_workspace(const dpllm_model* m) {
   Workspace w;
   const size_t n = m->linears.size();
-  size_t parts = 0, slots = 0, blocks = 0, tasks = 0, est = 0;
+  size_t parts = 0, slots = 0, blocks = 0, tasks = 0, est = 0, mail = 0;
   for (const Linear& lin : m->linears) {
     if (!lin.loaded) continue;
     if (lin.max_rowgroups() > 0) est = std::max(est, est_slots_of(lin, lin.max_rowgroups()));
+    mail += mail_words(lin.L) * kMailCopies;
     const size_t rg = (size_t)std::max(1, lin.max_rowgroups());
     parts += rg * kSelMaxChunks + 1;
     slots += rg * kSelPartRows * std::max(kSelMaxChunks, kSelCopies * sel_slices(lin.L.in));
@@ -228,6 +243,11 @@ Workspace carve_workspace(const dpllm_model* m) {
   w.gemv_jobs = take(sizeof(GemvJob) * n);
   w.block_jobs_cap = blocks;
   w.block_jobs = take(sizeof(int32_t) * blocks);
+  w.chain_state = take(sizeof(uint32_t) * kChainStateWords);
+  w.chain_levels = take(sizeof(ChainLevel) * (n + 1));
+  w.chain_jobs = take(sizeof(ChainJob) * n);
+  w.chain_mail_cap = mail;
+  w.chain_mail = take(sizeof(uint64_t) * mail);
   w.total = off;
   return w;
 }
@@ -380,6 +400,19 @@ void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, co
   }
 }
 
+void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, hipStream_t st) {
+  uint32_t* state = W.at<uint32_t>(W.chain_state);
+  hipLaunchKernelGGL(chain_reset_kernel, dim3(512), dim3(256), 0, st, W.at<uint64_t>(W.sel_ws), P.chain_slots, W.at<uint64_t>(W.chain_mail), P.chain_mail, state);
+  auto go = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, dim3((unsigned)P.chain_grid), dim3(kLaneThreads), 0, st, (const ChainLevel*)W.at<ChainLevel>(W.chain_levels),
+                       (const ChainJob*)W.at<ChainJob>(W.chain_jobs), (const SelParams*)W.at<SelParams>(W.sel_active), (const SelTask*)W.at<SelTask>(W.sel_tasks),
+                       state, (int)m->h_chain_levels.size() - 1, kChainPatience);
+  };
+  if (P.chain_bits <= 4) go(gemv_chain_kernel<4>);
+  else if (P.chain_bits <= 6) go(gemv_chain_kernel<6>);
+  else go(gemv_chain_kernel<8>);
+}
+
 // One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
 // more workgroups than there are compute units; below that the second pass runs beside the first one.  us per call of
 // B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 10.5, k = 6 23.1 / 17.5, 11008 x 4096 k = 8 27.5 / 18.5, 28672 x
@@ -457,6 +490,155 @@ int upload_params(dpllm_model* m, hipStream_t st) {
   HIP_TRY(m, hipGetLastError());
   m->params_dirty = false;
   return DPLLM_OK;
+}
+
+// A chained step is one launch from 24 levels on, of 56 MB of planes on average at most.  us a step, a launch per level / one in
+// all, without and with selectors a level early: 7B at 3 and 4 bits (22 .. 25 MB a level), 2 blocks 89 / 91 and 83 / 85, 6 blocks
+// 269 / 259 and 255 / 233, 24 blocks 1067 / 994 and 1012 / 884; at 5 and 6 bits 6 blocks 373 / 341 and 358 / 315; 8B at 3 and 4 bits
+// (24 MB), 3 blocks 136 / 139 and 128 / 121, 6 blocks 272 / 266 and 258 / 237; at 5 and 6 bits (41 MB) 16 blocks 979 / 908 and 950 /
+// 827; 70B (94 .. 147 MB), 4 blocks at 3 and 4 bits 404 / 422 and 403 / 402, at 5 and 6 bits 600 / 600 and 597 / 603.
+constexpr int kChainMinLevels = 24;
+constexpr double kChainLevelBytes = 56e6;
+
+// Plans a whole step as one launch of gemv_chain_kernel.  false: the step is none that it serves.  fins: SelFinish of every linear.
+// It serves steps of several levels in which every vector is either never written or, from a multiple of eight elements on,
+// part of the result of one earlier linear, and no two results share memory: what a level reads then comes from mailboxes and
+// from buffers that stay as they are, and it does not matter that the last workgroups of a level may still be at work when the
+// first ones have begun a later one.
+bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const std::vector<std::pair<int, int>>& bounds,
+                const std::vector<int>& phase_of, std::vector<SelFinish>& fins) {
+  const int n = (int)m->linears.size(), levels = (int)bounds.size();
+  const Workspace& W = m->ws;
+  StepPlan& P = m->plan;
+  if (levels < kChainMinLevels || m->polls != kSelPolls) return false;
+  for (const auto& [id, end] : bounds)
+    if (end - id > kChainLevelJobs) return false;
+  double bytes = 0;
+  for (const Linear& lin : m->linears) bytes += (double)lin.L.plane_bytes * lin.part_k();
+  if (bytes > kChainLevelBytes * levels) return false;
+  // the results by address
+  struct Range { uintptr_t at, end; int id; };
+  std::vector<Range> out(n);
+  for (int j = 0; j < n; ++j) out[j] = {(uintptr_t)ys[j], (uintptr_t)ys[j] + (size_t)m->linears[j].L.out * 2, j};
+  std::sort(out.begin(), out.end(), [](const Range& a, const Range& b) { return a.at < b.at; });
+  for (int i = 1; i < n; ++i)
+    if (out[i].at < out[i - 1].end) return false;
+  // the linear that writes a vector (-1: none), and whether the step can be served
+  auto writer = [&](const void* p, int in, int reader, int* from) {
+    const uintptr_t a = (uintptr_t)p, e = a + (size_t)in * 2;
+    auto it = std::upper_bound(out.begin(), out.end(), a, [](uintptr_t v, const Range& r) { return v < r.end; });   // the first that ends behind a
+    *from = -1;
+    if (it == out.end() || it->at >= e) return true;
+    *from = it->id;
+    return it->at <= a && e <= it->end && (a - it->at) % 16 == 0 && it->id < reader;
+  };
+  std::vector<size_t> mail_at(n, 0);
+  std::vector<char> read(n, 0);
+  size_t mail = 0;
+  for (int j = 0; j < n; ++j) {
+    mail_at[j] = mail;
+    mail += mail_words(m->linears[j].L) * kMailCopies;
+  }
+  if (mail > W.chain_mail_cap) return false;
+  std::vector<ChainLevel>& lv = m->h_chain_levels;
+  std::vector<ChainJob>& jobs = m->h_chain_jobs;
+  lv.assign(levels + 1, ChainLevel{});
+  jobs.assign(n, ChainJob{});
+  P.chain_bits = 0;
+  size_t slots = 0, ntasks = 0;
+  for (ChainLevel& l : lv) std::fill(std::begin(l.unit_start), std::end(l.unit_start), 0x7fffffff);
+  std::vector<std::vector<int>> tasks_of(levels);   // linears whose tasks run in a level
+  for (int j = 0; j < n; ++j) {
+    const Linear& lin = m->linears[j];
+    ChainLevel& l = lv[phase_of[j]];
+    const int first = bounds[phase_of[j]].first;
+    l.job_first = first;
+    l.job_count++;
+    const void* sx = lin.sel_input ? lin.sel_input : xs[j];
+    int from, sel_from;
+    if (!writer(xs[j], lin.L.in, j, &from) || !writer(sx, lin.L.in, j, &sel_from)) return false;
+    auto place = [&](int w, const void* p) {
+      return (const uint16_t*)(W.at<uint64_t>(W.chain_mail) + mail_at[w]) + ((const char*)p - (const char*)ys[w]) / 2;
+    };
+    ChainJob& c = jobs[j];
+    c.arena = lin.arena;
+    c.x = from < 0 ? (const uint16_t*)xs[j] : place(from, xs[j]);
+    c.x_copy = from < 0 ? 0 : (int)mail_words(m->linears[from].L);
+    if (from >= 0) read[from] = 1;
+    c.y = (uint16_t*)ys[j];
+    c.e_out = P.e_dev + j;
+    c.k_out = P.k_dev + j;
+    if (lin.L.total_bytes >> 32) return false;   // (32-bit offsets)
+    c.plane_bytes = (uint32_t)lin.L.plane_bytes;
+    c.out = lin.L.out; c.ncw = lin.L.ncw; c.ncc = lin.L.ncc;
+    for (int k = lin.L.kmin; k <= lin.L.p; ++k) c.lut_off[k - 1] = (uint32_t)lin.L.lut_offset[k];
+    bool any = false, linreg = false;
+    for (const Pair& s : lin.sel) {
+      if (!s.set) continue;
+      P.chain_bits = std::max(P.chain_bits, s.h);
+      any |= s.kind != DPLLM_SEL_NONE;
+      linreg |= s.kind == DPLLM_SEL_LINREG;
+    }
+    SelFinish f{};
+    f.e_out = c.e_out; f.k_out = c.k_out;
+    f.x = sel_from < 0 ? (const uint16_t*)sx : place(sel_from, sx);
+    f.x_copy = sel_from < 0 ? 0 : (int)mail_words(m->linears[sel_from].L);
+    if (sel_from >= 0) read[sel_from] = 1;
+    f.in = lin.L.in; f.linear = j; f.copies = kSelCopies; f.squares = linreg;
+    const int slices = sel_slices(lin.L.in);
+    f.chunk_cols = ((lin.L.in + slices - 1) / slices + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
+    f.nchunks = (lin.L.in + f.chunk_cols - 1) / f.chunk_cols;
+    f.task_rows = any ? std::max(1, lin.max_rowgroups() * kSelPartRows) : 0;
+    f.ws_rows = std::max(1, f.task_rows);
+    f.ws = W.at<double>(W.sel_ws) + slots;
+    c.slots = (const uint64_t*)f.ws;
+    c.slot_rows = f.ws_rows; c.nchunks = f.nchunks;
+    slots += align_up((size_t)f.ws_rows * f.nchunks * kSelCopies, 16);
+    fins[j] = f;
+    if (!any) continue;
+    // a selector whose vector is there a level earlier runs in that level
+    const int ready = sel_from < 0 ? 0 : phase_of[sel_from] + 1, q = phase_of[j];
+    tasks_of[ready < q ? q - 1 : q].push_back(j);
+  }
+  for (int l = 0; l < levels; ++l) {
+    lv[l].task_first = (int32_t)ntasks;
+    for (int j : tasks_of[l]) {
+      fins[j].task_first = (int)ntasks;
+      ntasks += (size_t)fins[j].task_rows * fins[j].nchunks;
+    }
+    lv[l].task_count = (int32_t)ntasks - lv[l].task_first;
+  }
+  if (ntasks > W.sel_tasks_cap || slots > W.sel_ws_cap) return false;
+  // rows of a block: the makespan of a level in tiles a wavefront decodes, and about 0.6 of one for every block
+  for (int i = 0; i < levels; ++i) {
+    ChainLevel& l = lv[i];
+    double best = 1e300;
+    for (int lg = 2; lg >= 0; --lg) {
+      int units = 0, widest = 0;
+      for (int j = bounds[i].first; j < bounds[i].second; ++j) {
+        const LinearLayout& L = m->linears[j].L;
+        units += (L.out + (64 >> lg) - 1) / (64 >> lg);
+        widest = std::max(widest, L.in);
+      }
+      const double chunks = (widest + kChainChunk * kLaneWaves - 1) / (kChainChunk * kLaneWaves);
+      const double est = (units + kChainGrid - 1) / kChainGrid * (chunks * (4 >> lg) + 0.6);
+      if (est < best) { best = est; l.log_groups = lg; }
+    }
+    for (int j = bounds[i].first; j < bounds[i].second; ++j) {
+      l.unit_start[j - bounds[i].first] = l.units;
+      l.units += (m->linears[j].L.out + (64 >> l.log_groups) - 1) / (64 >> l.log_groups);
+    }
+  }
+  int grid = 1;
+  for (int j = 0; j < n; ++j) {
+    jobs[j].mail = read[j] ? W.at<uint64_t>(W.chain_mail) + mail_at[j] : nullptr;
+    jobs[j].mail_copy = (int)mail_words(m->linears[j].L);
+  }
+  for (const ChainLevel& l : lv) grid = std::max(grid, std::max(l.units, 0) + l.task_count);
+  P.chain_grid = std::min(grid, kChainGrid);
+  P.chain_slots = slots;
+  P.chain_mail = mail;
+  return true;
 }
 
 int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* k_dev, float* e_dev, hipStream_t st) {
@@ -562,9 +744,11 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     }
     P.phases.push_back(ph);
   }
+  std::vector<SelFinish> fins(n);
+  P.chain = plan_chain(m, xs, ys, bounds, phase_of, fins);
   // the selectors of every phase, at most twice: a workspace handed over before the selectors were attached may hold
   // their parts but not the tasks of the launches that run them
-  for (bool tasks = true;; tasks = false) {
+  for (bool tasks = !P.chain;; tasks = false) {
     // A selector that reads its own input buffer (asynchronous estimation, Sec. 5.2) does not have to run right
     // before its linear: any phase from which on nothing writes that buffer before the linear runs will do.  It
     // joins the latest such phase that launches selectors anyway (for linears that estimate from their immediate
@@ -662,6 +846,11 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
     if (!P.fused)
       return fail(m, DPLLM_ESTATE, "workspace too small for this step (set after the model changed?): call dpllm_workspace_bytes and "
                                    "dpllm_set_workspace again");
+  }
+  if (P.chain) {   // (the launches of a step in parts, the only others of this plan, do not read them)
+    for (int j = 0; j < n; ++j) gemv_jobs[j].fin = fins[j];
+    HIP_TRY(m, hipMemcpyAsync(W.at<ChainLevel>(W.chain_levels), m->h_chain_levels.data(), sizeof(ChainLevel) * m->h_chain_levels.size(), hipMemcpyHostToDevice, st));
+    HIP_TRY(m, hipMemcpyAsync(W.at<ChainJob>(W.chain_jobs), m->h_chain_jobs.data(), sizeof(ChainJob) * n, hipMemcpyHostToDevice, st));
   }
   // The tables may still be read by a step enqueued earlier on this stream: the copies are ordered behind it.
   if (!sel_parts.empty())
@@ -1069,11 +1258,16 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
   // a captured step is replayed under pairs and targets chosen later: it holds the selectors of every pair
   const bool all = P.idle && capturing(st);
+  if (both && P.chain && m->polls == kSelPolls) {
+    launch_chain(m, W, P, st);
+    HIP_TRY(m, hipGetLastError());
+    return DPLLM_OK;
+  }
   if (both && P.fused && P.slots > 0)   // the slots the fused launches collect start empty
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((P.slots * 2 + 255) / 256)), dim3(256), 0, st,
                        W.at<uint32_t>(W.sel_ws), P.slots * 2, (uint32_t)kSelEmpty);
   for (const Phase& ph : P.phases) {
-    const bool decides = both && ph.decides, fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
+    const bool decides = both && ph.decides && !P.chain, fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
     const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
     const SelPart* sel_parts = W.at<SelPart>(W.sel_parts) + ph.part_first;
     if ((parts & DPLLM_STEP_SELECT) && !fused && ph.sel_count > 0) {

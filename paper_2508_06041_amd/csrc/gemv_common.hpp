@@ -62,11 +62,12 @@ __global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams*
     for (int t = threadIdx.x; t < f.task_rows * f.nchunks; t += 256) {
       const int row = t / f.nchunks, c = t - row * f.nchunks, col0 = c * f.chunk_cols;
       SelTask k;
-      k.g = P.kind == 1 && row < P.r ? P.G + (size_t)row * f.in + col0 : nullptr;
+      k.g = P.kind == 1 && row < P.r ? P.G + (size_t)row * f.in + col0 : P.kind == 2 && f.squares && row == 0 ? f.x + col0 : nullptr;
       k.x = f.x + col0;
       k.slot = (uint64_t*)f.ws + (size_t)c * f.ws_rows + row;
       k.copy_stride = f.nchunks * f.ws_rows;
       k.cols = min(f.chunk_cols, f.in - col0);
+      k.x_copy = f.x_copy;
       tasks[f.task_first + t] = k;
     }
   }

@@ -132,12 +132,17 @@ template <>
 struct LaneAcc<1> {
   float v[4];
   __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0.f; }
+  // before sum(): a dot product's result may be read by another kind of vector instruction three wait states later; the compiler
+  // keeps that distance behind instructions it knows, not behind inline asm (in gemv_lane the step to the next tile, a
+  // comparison and a branch lie between)
+  __device__ __forceinline__ void settle() { asm("s_nop 2" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])); }
   __device__ __forceinline__ float sum(int) const { return (v[0] + v[1]) + (v[2] + v[3]); }
 };
 template <>
 struct LaneAcc<4> {
   f32x4 v[2];
   __device__ __forceinline__ void zero() { v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void settle() {}
   __device__ __forceinline__ float sum(int b) const { return v[0][b] + v[1][b]; }
 };
 
@@ -145,13 +150,15 @@ template <>
 struct LaneAcc<8> {
   f32x4 v[4];
   __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void settle() {}
   __device__ __forceinline__ float sum(int b) const { return v[2 * (b >> 2)][b & 3] + v[2 * (b >> 2) + 1][b & 3]; }
 };
 
-// LDS address of entry (byte N of t) in the lane's table column: byte 1 = the entry, byte 0 = lane * 4
+// LDS address of entry (byte N of t) in the lane's table column: byte 2 = which table (lanecol's), byte 1 = the entry,
+// byte 0 = lane * 4
 template <int N>
 __device__ __forceinline__ uint32_t lane_entry_addr(uint32_t t, uint32_t lanecol) {
-  constexpr uint32_t sel = 0x0c0c0000u | ((4u + N) << 8);   // {0, 0, t.byteN, lanecol.byte0}
+  constexpr uint32_t sel = 0x0c020000u | ((4u + N) << 8);   // {0, lanecol.byte2, t.byteN, lanecol.byte0}
   return __builtin_amdgcn_perm(t, lanecol, sel);
 }
 
@@ -341,14 +348,16 @@ struct LaneX {
 #pragma unroll
       for (int h = 0; h < 2 * G; ++h) a[s][h] = *reinterpret_cast<const uint64_t*>(xmine + s * 4 * sample + h * P * 8);
   }
+  __device__ __forceinline__ void load_word(const char*, int) {}   // (one sample only)
 };
 template <int G>
 struct LaneX<1, G> {
   u32x4 q[4];   // q[j][m] = pair 4 (lane mod 4) + m of word j
   __device__ __forceinline__ void load(const char* xmine) {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64);
+    for (int j = 0; j < 4; ++j) load_word(xmine, j);
   }
+  __device__ __forceinline__ void load_word(const char* xmine, int j) { q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64); }
 };
 // chunk C of the tile for four samples or eight (chunks take turns in the two accumulator sets of four samples)
 template <int C, int NB, int G>
@@ -384,9 +393,16 @@ __device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const L
 // words: how many of the lane's four words lie inside the row, ragged: not all four in every lane (wave-uniform).  The
 // activations of the others are zero, but their codes are zero too, and an infinite centroid of that code would make
 // 0 x inf; k <= 2 clears what those lookups return.
-template <int K, int NB, int G>
-__device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lanecol, const char* lds, const char* xmine,
-                                             LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const LaneMasks<K>& M, int words, bool ragged) {
+// LAZY (one sample): the activations are read back a word at a time, which takes 8 registers instead of 16; spent(tw) runs as
+// soon as tw may be asked for anew.
+struct LaneNothing {
+  template <class Planes>
+  __device__ __forceinline__ void operator()(Planes&) const {}
+};
+template <int K, int NB, int G, bool LAZY = false, int H = K, class Spent = LaneNothing>
+__device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, const char* lds, const char* xmine,
+                                             LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const LaneMasks<K>& M, int words, bool ragged,
+                                             Spent spent = LaneNothing{}) {
   auto clear = [&](uint32_t (&v)[8], int j) {
     if constexpr (K <= 2) {
       if (ragged) {
@@ -397,7 +413,8 @@ __device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lane
   };
   uint32_t va[8], vb[8];
   LaneX<NB, G> x;
-  x.load(xmine);
+  if constexpr (LAZY) x.load_word(xmine, 0);
+  else x.load(xmine);
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
   using J2 = std::integral_constant<int, 2>;
@@ -412,9 +429,15 @@ __device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lane
       if constexpr (K <= 3) lane_entries3<K>(w, T[j], M);
       else merge_nibble_pairs_v(w, T[j], M);
     }
+    if constexpr (LAZY) {
+      sched_fence();
+      spent(tw);
+      sched_fence();
+    }
     lane_issue_pairs<0, K <= 3>(T[0], lanecol, lds, va, addr, mask);
     auto word = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
+      if constexpr (LAZY && j + 1 < 4) x.load_word(xmine, j + 1);
       lane_issue_pairs<2, K <= 3>(T[j], lanecol, lds, vb, addr, mask);
       sched_fence();
       clear(va, j);
@@ -429,10 +452,19 @@ __device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lane
     word(J0{}); word(J1{}); word(J2{}); word(J3{});
   } else {
     uint32_t R[2][8];
+    u32x4 mine[K];
+#pragma unroll
+    for (int b = 0; b < K; ++b) mine[b] = tw[b];
+    if constexpr (LAZY) {
+#pragma unroll
+      for (int b = 0; b < K; ++b) asm volatile("" : "+v"(mine[b]));
+      spent(tw);
+      sched_fence();
+    }
     {
       uint32_t w[K];
 #pragma unroll
-      for (int b = 0; b < K; ++b) w[b] = tw[b][0];
+      for (int b = 0; b < K; ++b) w[b] = mine[b][0];
       lane_merge_fields<K>(w, R[0], M);
     }
     lane_issue_singles<K, 0>(R[0], lanecol, lds, va);
@@ -441,9 +473,10 @@ __device__ __forceinline__ void lane_compute(const u32x4 (&tw)[K], uint32_t lane
       if constexpr (j + 1 < 4) {
         uint32_t w[K];
 #pragma unroll
-        for (int b = 0; b < K; ++b) w[b] = tw[b][j + 1];
+        for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
         lane_merge_fields<K>(w, R[(j + 1) & 1], M);
       }
+      if constexpr (LAZY && j + 1 < 4) x.load_word(xmine, j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
       sched_fence();
       lane_mac_singles<0, j>(va, x, acc);
@@ -474,9 +507,10 @@ struct LaneLut {
   uint32_t v[kDwords];
 };
 
+// row: the row's start in the table
 template <int K>
-__device__ __forceinline__ void lane_fetch_lut(LaneLut<K>& L, const DPLLM_GLOBAL uint16_t* lut_base, int row_number, int wave) {
-  const DPLLM_GLOBAL uint32_t* row = reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(lut_base + ((size_t)row_number << K));
+__device__ __forceinline__ void lane_fetch_lut_at(LaneLut<K>& L, const DPLLM_GLOBAL char* row_start, int wave) {
+  const DPLLM_GLOBAL uint32_t* row = reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(row_start);
   const DPLLM_GLOBAL uint32_t* src = K <= 4 ? row : row + wave * LaneLut<K>::kDwords;
   if constexpr (LaneLut<K>::kDwords >= 4) {
 #pragma unroll
@@ -489,6 +523,10 @@ __device__ __forceinline__ void lane_fetch_lut(LaneLut<K>& L, const DPLLM_GLOBAL
     for (int i = 0; i < LaneLut<K>::kDwords; ++i) L.v[i] = src[i];
   }
 }
+template <int K>
+__device__ __forceinline__ void lane_fetch_lut(LaneLut<K>& L, const DPLLM_GLOBAL uint16_t* lut_base, int row_number, int wave) {
+  lane_fetch_lut_at<K>(L, reinterpret_cast<const DPLLM_GLOBAL char*>(lut_base + ((size_t)row_number << K)), wave);
+}
 
 // half h (0 = low) of dword d, for a wavefront-uniform h
 __device__ __forceinline__ uint32_t half_of(uint32_t d, int h) { return h ? d >> 16 : d & 0xffffu; }
@@ -498,7 +536,7 @@ __device__ __forceinline__ void lane_build_table(const LaneLut<K>& L, int wave, 
   if constexpr (K <= 2) {
     // wavefront w < 2^k writes the entries (a = w, b): (LUT[a], LUT[b])
     if (wave < (1 << K)) {
-      const uint32_t la = half_of(K == 2 && wave >= 2 ? L.v[LaneLut<K>::kDwords - 1] : L.v[0], wave & 1);
+      const uint32_t la = half_of(K == 2 && wave >= 2 ? +L.v[LaneLut<K>::kDwords - 1] : +L.v[0], wave & 1);
 #pragma unroll
       for (int b = 0; b < (1 << K); ++b) {
         const uint32_t hb = (b & 1) ? (L.v[b >> 1] & 0xffff0000u) : (L.v[b >> 1] << 16);
@@ -508,7 +546,8 @@ __device__ __forceinline__ void lane_build_table(const LaneLut<K>& L, int wave, 
     }
   } else if constexpr (K == 3) {
     // wavefront w writes the entries (a = w, b = 0..7): (LUT[a], LUT[b])
-    const uint32_t lw = wave < 2 ? L.v[0] : wave < 4 ? L.v[1] : wave < 6 ? L.v[2] : L.v[3];
+    const uint32_t v0 = L.v[0], v1 = L.v[1], v2 = L.v[2], v3 = L.v[3];
+    const uint32_t lw = wave < 2 ? +v0 : wave < 4 ? +v1 : wave < 6 ? +v2 : +v3;
     const uint32_t la = half_of(lw, wave & 1);
 #pragma unroll
     for (int b = 0; b < 8; ++b) {
@@ -519,7 +558,7 @@ __device__ __forceinline__ void lane_build_table(const LaneLut<K>& L, int wave, 
     // wavefront w writes the entries (a = 2 w + s, b = 0..15), s = 0, 1
     uint32_t lw = L.v[0];
 #pragma unroll
-    for (int i = 1; i < 8; ++i) lw = wave == i ? L.v[i] : lw;
+    for (int i = 1; i < 8; ++i) lw = wave == i ? +L.v[i] : +lw;
 #pragma unroll
     for (int s = 0; s < 2; ++s) {
       const uint32_t la = s ? lw >> 16 : lw & 0xffffu;
@@ -817,6 +856,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 #pragma unroll
         for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[s].x[b], inside(cc), lane, ready + b * G * kLaneGroupStride);
       }
+      acc.settle();
 #pragma unroll
       for (int b = 0; b < NB; ++b) done[b] = acc.sum(b);
       lane_compute<K, NB, G>(ring[s].w, lanecol, lds, ready + xlane, acc, addr, mask, M, job.ncw - (cc * G + group) * 4,
@@ -829,6 +869,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   // the last step may have fewer than G tiles: a lane without one (it decoded another tile) drops what it added there
   const bool whole = (c1 - 1) * G + group < job.ncc;
   if constexpr (NB == 8) lds_barrier();   // the tables, which the sums take the place of, are done with
+  acc.settle();
 #pragma unroll
   for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
   lds_barrier();
