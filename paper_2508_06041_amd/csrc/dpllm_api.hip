@@ -890,6 +890,17 @@ bool capturing(hipStream_t st) {
   return s != hipStreamCaptureStatusNone;
 }
 
+// Whether an event has passed.  A query is not allowed, and can spoil the capture, while some stream is captured in the global
+// mode by any thread; this one has nothing to do with a capture.
+bool passed(hipEvent_t event) {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+  const bool done = hipEventQuery(event) == hipSuccess;
+  if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+  (void)hipGetLastError();
+  return done;
+}
+
 }  // namespace
 
 extern "C" {
@@ -1151,8 +1162,7 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
   if ((size_t)rowgroups * kSelPartRows * j.nchunks > W.est_slots_cap) return false;
   if (!m->est_ready && sel.kind == DPLLM_SEL_PROJ) {
     // the slots are empty for work behind dpllm_set_workspace on its stream, for any other once that has been seen to be done
-    if (!capturing(st) && hipEventQuery(m->ws_event) == hipSuccess) m->est_ready = true;
-    else (void)hipGetLastError();
+    if (!capturing(st) && passed(m->ws_event)) m->est_ready = true;
     if (!m->est_ready && st != m->ws_stream) return false;
   }
   const unsigned turn = sel.kind == DPLLM_SEL_PROJ ? m->est_turn++ % kEstRing : 0;

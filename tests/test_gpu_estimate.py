@@ -88,3 +88,28 @@ def test_estimates_of_several_ranks_share_the_slots(dp):
         torch.cuda.synchronize()
         assert torch.equal(e, two) and k.tolist() == [3, 4, 4], rep
     model.close()
+
+
+def test_first_estimate_while_another_stream_is_captured(dp):
+    """The first estimate behind dpllm_set_workspace asks whether the slots are empty by now: that leaves a capture elsewhere alone."""
+    in_ = 1056
+    model, G = _model(dp, in_, seed=7), _G(24, in_, 7)
+    x = synth.make_x(in_, 1, seed=24)[0]
+    ref = oracle.estimate(synth.lut_np(G), synth.lut_np(x))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.5 * ref)))
+    x, e, k, other = x.cuda(), torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda"), torch.zeros(64, device="cuda")
+    side, graph = torch.cuda.Stream(), torch.cuda.CUDAGraph()
+    model.dpllm_set_workspace()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        other.add_(1.0)
+        with torch.cuda.stream(side):
+            model.dpllm_estimate(0, 3, 4, x, e_out=e, k_out=k)
+        other.add_(2.0)
+    torch.cuda.synchronize()
+    assert math.isclose(float(e), ref, rel_tol=3e-7) and int(k) == 4
+    for rep in range(1, 4):
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(other, torch.full_like(other, 3.0 * rep))
+    model.close()
