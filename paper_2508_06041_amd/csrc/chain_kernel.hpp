@@ -426,30 +426,14 @@ __device__ __forceinline__ void chain_run(u32x4 (&T)[H], uint32_t rec, int block
   }
 }
 
-// H: the largest bitwidth of the step's linears, rounded up to 4, 6 or 8 (registers of the planes asked for ahead)
+// The levels of a step.  H: the largest bitwidth of the active pairs, rounded up to 4, 6 or 8 (registers of the planes asked for
+// ahead); number, count: as chain_enrol gives them.
 template <int H>
-__global__ void __launch_bounds__(kLaneThreads, 2) gemv_chain_kernel(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks,
-                                                                     uint32_t* state, int nlevels, int patience) {
-  __shared__ __attribute__((aligned(256))) char lds[kChainLdsBytes];
-  if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
-  int tid = threadIdx.x;
+__device__ __forceinline__ void chain_levels(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks, int nlevels,
+                                             int patience, int number, int count, int tid, char* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63;
   double* sh = reinterpret_cast<double*>(lds + kChainLdsBytes - kSelSharedBytes);
-  int number, count;
-  {
-    int* seat = reinterpret_cast<int*>(sh);
-    if (tid == 0) {
-      chain_enrol(state, gridDim.x, number, count);
-      seat[0] = number;
-      seat[1] = count;
-    }
-    lds_barrier();
-    number = __builtin_amdgcn_readfirstlane(seat[0]);
-    count = __builtin_amdgcn_readfirstlane(seat[1]);
-    lds_barrier();
-    if (number < 0) return;
-  }
   auto load_level = [&](int l) { return as_global(reinterpret_cast<const uint32_t*>(levels + min(l, nlevels)))[lane]; };   // (the one behind the last is empty)
   auto load_job = [&](int j) {
     const uint32_t* p = lane < 32 ? reinterpret_cast<const uint32_t*>(jobs + j) + lane : reinterpret_cast<const uint32_t*>(active + j) + (lane & 15);
@@ -610,6 +594,40 @@ __global__ void __launch_bounds__(kLaneThreads, 2) gemv_chain_kernel(const Chain
     const uint32_t* p = reinterpret_cast<const uint32_t*>(jobs);
     *as_global(reinterpret_cast<int32_t*>((uint64_t)p[DPLLM_CJ(k_out) + 1] << 32 | p[DPLLM_CJ(k_out)])) = -1;
   }
+}
+
+// The active pairs say on the device how many planes are asked for ahead, whatever other pairs a linear holds: every plane beyond
+// those of a step is a load for nothing in each row block.  7B, 32 blocks at 3 and 4 bits, us a step with pairs of up to 8 bits
+// attached as well: 1485 with a kernel for the largest attached pair, 1310 with the active ones' (1338 with a launch per level).
+// The pairs are read while thread 0 enrols the workgroup.  All three variants have the registers and the LDS of the
+// largest; one workgroup fills a compute unit either way.
+__global__ void __launch_bounds__(kLaneThreads, 2) gemv_chain_kernel(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks,
+                                                                     uint32_t* state, int nlevels, int njobs, int patience) {
+  __shared__ __attribute__((aligned(256))) char lds[kChainLdsBytes];
+  if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int* seat = reinterpret_cast<int*>(lds + kChainLdsBytes - kSelSharedBytes);   // number, count, largest bitwidth class of every wavefront
+  int h = 0;
+  for (int j = tid; j < njobs; j += kLaneThreads) h = max(h, *as_global(&active[j].h));
+  if (tid == 0) {
+    int number, count;
+    chain_enrol(state, gridDim.x, number, count);
+    seat[0] = number;
+    seat[1] = count;
+  }
+  const int mine = __any(h > 6) ? 2 : __any(h > 4) ? 1 : 0;
+  if ((tid & 63) == 0) seat[2 + wave] = mine;
+  lds_barrier();
+  const int number = __builtin_amdgcn_readfirstlane(seat[0]), count = __builtin_amdgcn_readfirstlane(seat[1]);
+  int size = 0;
+#pragma unroll
+  for (int w = 0; w < kLaneWaves; ++w) size = max(size, seat[2 + w]);
+  size = __builtin_amdgcn_readfirstlane(size);
+  lds_barrier();
+  if (number < 0) return;
+  if (size == 0) chain_levels<4>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
+  else if (size == 1) chain_levels<6>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
+  else chain_levels<8>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
 }
 
 }  // namespace dpllm

@@ -105,7 +105,6 @@ struct StepPlan {
   bool fused = false;    //   any of its phases runs selectors inside its GEMV launch
   bool idle = false;     // some phase has no estimator under any target, though its linears hold pairs with one
   bool chain = false;    // a whole step is one launch (gemv_chain_kernel)
-  int chain_bits = 0;    //   the largest bitwidth of a pair
   int chain_grid = 0;
   size_t chain_slots = 0, chain_mail = 0;   // 64-bit words
 };
@@ -403,14 +402,9 @@ void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, co
 void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, hipStream_t st) {
   uint32_t* state = W.at<uint32_t>(W.chain_state);
   hipLaunchKernelGGL(chain_reset_kernel, dim3(512), dim3(256), 0, st, W.at<uint64_t>(W.sel_ws), P.chain_slots, W.at<uint64_t>(W.chain_mail), P.chain_mail, state);
-  auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3((unsigned)P.chain_grid), dim3(kLaneThreads), 0, st, (const ChainLevel*)W.at<ChainLevel>(W.chain_levels),
-                       (const ChainJob*)W.at<ChainJob>(W.chain_jobs), (const SelParams*)W.at<SelParams>(W.sel_active), (const SelTask*)W.at<SelTask>(W.sel_tasks),
-                       state, (int)m->h_chain_levels.size() - 1, kChainPatience);
-  };
-  if (P.chain_bits <= 4) go(gemv_chain_kernel<4>);
-  else if (P.chain_bits <= 6) go(gemv_chain_kernel<6>);
-  else go(gemv_chain_kernel<8>);
+  hipLaunchKernelGGL(gemv_chain_kernel, dim3((unsigned)P.chain_grid), dim3(kLaneThreads), 0, st, (const ChainLevel*)W.at<ChainLevel>(W.chain_levels),
+                     (const ChainJob*)W.at<ChainJob>(W.chain_jobs), (const SelParams*)W.at<SelParams>(W.sel_active), (const SelTask*)W.at<SelTask>(W.sel_tasks),
+                     state, (int)m->h_chain_levels.size() - 1, (int)m->h_chain_jobs.size(), kChainPatience);
 }
 
 // One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
@@ -544,7 +538,6 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
   std::vector<ChainJob>& jobs = m->h_chain_jobs;
   lv.assign(levels + 1, ChainLevel{});
   jobs.assign(n, ChainJob{});
-  P.chain_bits = 0;
   size_t slots = 0, ntasks = 0;
   for (ChainLevel& l : lv) std::fill(std::begin(l.unit_start), std::end(l.unit_start), 0x7fffffff);
   std::vector<std::vector<int>> tasks_of(levels);   // linears whose tasks run in a level
@@ -575,7 +568,6 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
     bool any = false, linreg = false;
     for (const Pair& s : lin.sel) {
       if (!s.set) continue;
-      P.chain_bits = std::max(P.chain_bits, s.h);
       any |= s.kind != DPLLM_SEL_NONE;
       linreg |= s.kind == DPLLM_SEL_LINREG;
     }

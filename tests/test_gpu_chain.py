@@ -185,6 +185,23 @@ def test_target_switches_between_replays(dp):
     net.model.close()
 
 
+@pytest.mark.parametrize("pairs,unused", [([(3, 4)], (5, 6)), ([(3, 4)], (7, 8)), ([(5, 6)], (7, 8)), ([(3, 4), (4, 5)], (7, 8))])
+def test_pairs_that_are_not_active_change_nothing(dp, pairs, unused):
+    """How many planes are asked for ahead follows the active pairs; a wider one beside them leaves every bit as it is."""
+    net = Chain(dp, SMALL, 96, 8, pairs, seed=31)
+    net.calibrate((1, 2))
+    net.put(1)
+    net.step()
+    alone = net.state()
+    net.model.dpllm_set_selector(len(net.lin) - 1, *unused, dp.DPLLM_SEL_LINREG, alpha=0.5, beta=0.5, T=0.0)
+    net.model.dpllm_set_active_pair(len(net.lin) - 1, *net.lin[-1]["pair"])
+    net.clear()
+    net.step()
+    assert all(torch.equal(a, b) for a, b in zip(net.state(), alone))
+    net.check(unused)
+    net.model.close()
+
+
 def test_two_chains_beside_one_another(dp):
     """Two models on two streams: each launch works with the workgroups that found a place."""
     nets = [Chain(dp, SMALL, 96, 4, [(3, 4)], seed=s) for s in (21, 22)]
