@@ -490,7 +490,7 @@ int upload_params(dpllm_model* m, hipStream_t st) {
 // all, without and with selectors a level early: 7B at 3 and 4 bits (22 .. 25 MB a level), 2 blocks 89 / 91 and 83 / 85, 6 blocks
 // 269 / 259 and 255 / 233, 24 blocks 1067 / 994 and 1012 / 884; at 5 and 6 bits 6 blocks 373 / 341 and 358 / 315; 8B at 3 and 4 bits
 // (24 MB), 3 blocks 136 / 139 and 128 / 121, 6 blocks 272 / 266 and 258 / 237; at 5 and 6 bits (41 MB) 16 blocks 979 / 908 and 950 /
-// 827; 70B (94 .. 147 MB), 4 blocks at 3 and 4 bits 404 / 422 and 403 / 402, at 5 and 6 bits 600 / 600 and 597 / 603.
+// 827; 7B at 7 and 8 bits (51 MB) 16 blocks 1188 / 1087 without; 70B (94 .. 147 MB), 4 blocks at 3 and 4 bits 404 / 422 and 403 / 402, at 5 and 6 bits 600 / 600 and 597 / 603.
 constexpr int kChainMinLevels = 24;
 constexpr double kChainLevelBytes = 56e6;
 
