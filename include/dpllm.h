@@ -217,8 +217,18 @@ int dpllm_debug_locate(int out, int in, int p, int kmin, int plane, int row, int
 
 /* Parity aid: how often a workgroup of a step looks for products of its linear's selector that other workgroups of the
  * launch deliver, before it computes them all itself (64 looks of about a microsecond unless set).  0: it looks once;
- * -1: it looks once and nobody delivers any.  The results are the same bits.  Errors: EINVAL. */
+ * -1: it looks once and nobody delivers any.  The results are the same bits.  (A step that is one launch in all does not
+ * ask: see dpllm_debug_set_one_launch.)  Errors: EINVAL. */
 int dpllm_debug_set_polls(dpllm_model* m, int polls);
+
+/* Parity aid: whether a step of dependent linears is one launch whose workgroups hand the results over themselves.
+ * 0 (unless set): where that is faster, by the linears' shapes and the ranks of their pairs; 1: wherever the buffers allow
+ * it; -1: never.  The next step rebuilds the launch plan.  Results may differ in the order of additions.  Errors: EINVAL. */
+int dpllm_debug_set_one_launch(dpllm_model* m, int mode);
+
+/* Parity aid: how many kernels the model's last step was made of (one launch for all linears: 2, one of them clears
+ * what the other hands over).  Errors: EINVAL. */
+int dpllm_debug_step_launches(const dpllm_model* m, int* launches);
 
 /* Measurement aid: a plain 128-bit copy kernel, bytes % 16 == 0, both pointers device and 16-byte
  * aligned.  Its known traffic (bytes read + bytes written) scales the HBM byte counters that the

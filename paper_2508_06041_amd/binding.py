@@ -23,7 +23,7 @@ SYMBOLS = ["dpllm_model_create", "dpllm_model_destroy", "dpllm_last_error", "dpl
            "dpllm_load_linear", "dpllm_set_selector", "dpllm_set_threshold", "dpllm_set_active_pair",
            "dpllm_set_target_entry", "dpllm_set_target", "dpllm_set_selector_input",
            "dpllm_estimate", "dpllm_estimate_noalloc", "dpllm_gemv", "dpllm_decode_step", "dpllm_decode_step_parts", "dpllm_debug_unpack", "dpllm_debug_locate",
-           "dpllm_debug_set_polls", "dpllm_debug_copy", "dpllm_debug_read"]
+           "dpllm_debug_set_polls", "dpllm_debug_set_one_launch", "dpllm_debug_step_launches", "dpllm_debug_copy", "dpllm_debug_read"]
 
 
 class DpllmError(RuntimeError):
@@ -61,6 +61,8 @@ def _load():
     L.dpllm_decode_step_parts.argtypes = [vp, C.POINTER(vp), C.POINTER(vp), vp, vp, i32, vp]
     L.dpllm_debug_unpack.argtypes = [vp, i32, i32, vp, vp]
     L.dpllm_debug_set_polls.argtypes = [vp, i32]
+    L.dpllm_debug_set_one_launch.argtypes = [vp, i32]
+    L.dpllm_debug_step_launches.argtypes = [vp, C.POINTER(i32)]
     L.dpllm_debug_copy.argtypes = [vp, vp, sz, vp]
     L.dpllm_debug_read.argtypes = [vp, sz, vp, vp]
     return L
@@ -257,3 +259,11 @@ class Model:
 
     def dpllm_debug_set_polls(self, polls):
         _check(self.h, lib.dpllm_debug_set_polls(self.h, polls))
+
+    def dpllm_debug_set_one_launch(self, mode):
+        _check(self.h, lib.dpllm_debug_set_one_launch(self.h, mode))
+
+    def dpllm_debug_step_launches(self):
+        n = C.c_int(0)
+        _check(self.h, lib.dpllm_debug_step_launches(self.h, C.byref(n)))
+        return n.value

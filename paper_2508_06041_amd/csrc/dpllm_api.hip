@@ -155,6 +155,8 @@ struct dpllm_model {
   hipEvent_t ws_event = nullptr;   //   done for every stream to see once the event has passed
   bool est_ready = false;
   int polls = kSelPolls;           // < 0: the selector tasks are left out of the launches (dpllm_debug_set_polls)
+  int chain_mode = 0;              // 1: one launch wherever gemv_chain_kernel serves the step, -1: nowhere (dpllm_debug_set_one_launch)
+  int launches = 0;                // kernels of the last step
   int device = 0;
 };
 
@@ -486,13 +488,34 @@ int upload_params(dpllm_model* m, hipStream_t st) {
   return DPLLM_OK;
 }
 
-// A chained step is one launch from 24 levels on, of 56 MB of planes on average at most.  us a step, a launch per level / one in
-// all, without and with selectors a level early: 7B at 3 and 4 bits (22 .. 25 MB a level), 2 blocks 89 / 91 and 83 / 85, 6 blocks
-// 269 / 259 and 255 / 233, 24 blocks 1067 / 994 and 1012 / 884; at 5 and 6 bits 6 blocks 373 / 341 and 358 / 315; 8B at 3 and 4 bits
-// (24 MB), 3 blocks 136 / 139 and 128 / 121, 6 blocks 272 / 266 and 258 / 237; at 5 and 6 bits (41 MB) 16 blocks 979 / 908 and 950 /
-// 827; 7B at 7 and 8 bits (51 MB) 16 blocks 1188 / 1087 without; 70B (94 .. 147 MB), 4 blocks at 3 and 4 bits 404 / 422 and 403 / 402, at 5 and 6 bits 600 / 600 and 597 / 603.
+// Which chained steps are one launch.  The rule looks at shapes and at the ranks of all attached pairs, never at the pairs in use:
+// a graph that holds a captured step follows those, and both kinds of step share the table of tasks.  us a step in a graph, a
+// launch per level / one in all (8 blocks of a Transformer with d model and f hidden features, rank 64, at 3 and 4 bits; 7 and 8):
+//   levels: 24 and more.  d = 4096, f = 11008 276 / 257 and 436 / 410 with 24 of them.
+//   weights of a level, on average: 64 million.  4096, 11008 (51) 1420 / 1290 (32 blocks) and 587 / 555; 4096, 14336 with grouped
+//     queries (55) 374 / 353 and 604 / 578; 3584, 18944 (64) 426 / 402 and 669 / 650; 4096, 16384 (67) 384 / 366 and 648 / 656; 4096,
+//     22016 (84) 473 / 441 and 768 / 785; 8192, 8192 (117) 553 / 531 and 946 / 993.  Larger ones the streaming kernel decodes with
+//     twice the wavefronts.
+//   evenness: eight wavefronts share the columns in chunks of 512, so the one with the most may have up to 1.2 times its share (on
+//     average over the rows).  3840, 10240 (1.10) 358 / 334 and 547 / 518; 3584, 18944 (1.13) above; 3072, 8192 (1.26) 295 / 292 and
+//     418 / 447; 4608, 12288 (1.6) 441 / 463 and 690 / 781; 5120, 13824 (1.5) 454 / 530 and 746 / 976; 2560, 6912 (1.5) 287 / 275 and 394 /
+//     393; 1024, 2816 202 / 203 and 266 / 280; 2048, 16384 302 / 323 and 453 / 516.
+//   selectors: a task (row of G times 4096 columns) to a workgroup and level, on average.  4096, 11008 at rank 96 (0.84 of that) 375 / 366, 128
+//     (1.1) 374 / 388, 256 399 / 439, 1024 612 / 786; 4096, 14336 at 96 (0.94) 286 / 287 and 454 / 456.
 constexpr int kChainMinLevels = 24;
-constexpr double kChainLevelBytes = 56e6;
+constexpr double kChainLevelWeights = 64e6, kChainUneven = 1.2;
+bool chain_pays(const dpllm_model* m, int levels) {
+  double weights = 0, even = 0, dealt = 0, tasks = 0;
+  for (const Linear& lin : m->linears) {
+    const LinearLayout& L = lin.L;
+    const int chunks = (L.in + kChainChunk - 1) / kChainChunk;
+    weights += (double)L.out * L.in;
+    even += (double)L.out * L.ncc / kLaneWaves;
+    dealt += (double)L.out * ((chunks + kLaneWaves - 1) / kLaneWaves) * (kChainChunk / 128);
+    tasks += (double)lin.max_rowgroups() * kSelPartRows * sel_slices(L.in);
+  }
+  return levels >= kChainMinLevels && weights <= kChainLevelWeights * levels && dealt <= kChainUneven * even && tasks <= (double)kChainGrid * levels;
+}
 
 // Plans a whole step as one launch of gemv_chain_kernel.  false: the step is none that it serves.  fins: SelFinish of every linear.
 // It serves steps of several levels in which every vector is either never written or, from a multiple of eight elements on,
@@ -504,12 +527,9 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
   const int n = (int)m->linears.size(), levels = (int)bounds.size();
   const Workspace& W = m->ws;
   StepPlan& P = m->plan;
-  if (levels < kChainMinLevels || m->polls != kSelPolls) return false;
+  if (m->chain_mode < 0 || (m->chain_mode == 0 && !chain_pays(m, levels))) return false;
   for (const auto& [id, end] : bounds)
     if (end - id > kChainLevelJobs) return false;
-  double bytes = 0;
-  for (const Linear& lin : m->linears) bytes += (double)lin.L.plane_bytes * lin.part_k();
-  if (bytes > kChainLevelBytes * levels) return false;
   // the results by address
   struct Range { uintptr_t at, end; int id; };
   std::vector<Range> out(n);
@@ -1260,14 +1280,18 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
   // a captured step is replayed under pairs and targets chosen later: it holds the selectors of every pair
   const bool all = P.idle && capturing(st);
-  if (both && P.chain && m->polls == kSelPolls) {
+  m->launches = 0;
+  if (both && P.chain) {
     launch_chain(m, W, P, st);
+    m->launches = 2;
     HIP_TRY(m, hipGetLastError());
     return DPLLM_OK;
   }
-  if (both && P.fused && P.slots > 0)   // the slots the fused launches collect start empty
+  if (both && P.fused && P.slots > 0) {   // the slots the fused launches collect start empty
     hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((P.slots * 2 + 255) / 256)), dim3(256), 0, st,
                        W.at<uint32_t>(W.sel_ws), P.slots * 2, (uint32_t)kSelEmpty);
+    ++m->launches;
+  }
   for (const Phase& ph : P.phases) {
     const bool decides = both && ph.decides && !P.chain, fused = both && ph.fused, estimators = ph.estimators || (all && ph.may_estimate);
     const SelJob* jobs = W.at<SelJob>(W.sel_jobs) + ph.sel_first;
@@ -1278,10 +1302,12 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
                            (const int32_t*)(W.at<int32_t>(W.sel_members) + ph.member_first), active, none, pnone);
       if (!decides)
         hipLaunchKernelGGL(selector_decide_kernel, dim3(ph.sel_count), dim3(kSelDecideThreads), 0, st, jobs, active, none, pnone);
+      m->launches += estimators + !decides;
     }
     if (!(parts & DPLLM_STEP_GEMV)) continue;
     launch_step(ph.groups, ph.blocks, st, W.at<GemvJob>(W.gemv_jobs) + ph.gemv_first, W.at<int32_t>(W.block_jobs) + ph.block_first,
                 decides ? active : nullptr, W.at<SelTask>(W.sel_tasks) + ph.task_first, fused && estimators ? ph.task_count : 0, m->polls);
+    ++m->launches;
   }
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
@@ -1309,6 +1335,20 @@ int dpllm_debug_set_polls(dpllm_model* m, int polls) {
   if (!m) return DPLLM_EINVAL;
   if (polls < -1) return fail(m, DPLLM_EINVAL, "polls %d below -1", polls);
   m->polls = polls;
+  return DPLLM_OK;
+}
+
+int dpllm_debug_set_one_launch(dpllm_model* m, int mode) {
+  if (!m) return DPLLM_EINVAL;
+  if (mode < -1 || mode > 1) return fail(m, DPLLM_EINVAL, "mode %d outside [-1,1]", mode);
+  m->chain_mode = mode;
+  m->version++;
+  return DPLLM_OK;
+}
+
+int dpllm_debug_step_launches(const dpllm_model* m, int* launches) {
+  if (!m || !launches) return DPLLM_EINVAL;
+  *launches = m->launches;
   return DPLLM_OK;
 }
 

@@ -1,6 +1,7 @@
 """GPU tests of steps of many levels that run as one launch (gemv_chain_kernel): results and products of selectors handed over
 inside the launch, rows dealt out in blocks of 64, 32 or 16, vectors longer than the eight wavefronts park at a time.  Against
-the CPU oracle, linear by linear, from the buffers as they are on the device after the step."""
+the CPU oracle, linear by linear, from the buffers as they are on the device after the step.  Shapes this small take a launch per
+level by themselves: the tests ask for the one launch (dpllm_debug_set_one_launch) and see that they get it."""
 import math
 
 import numpy as np
@@ -55,6 +56,7 @@ class Chain:
         for i in range(n):
             if self.sel[i] is not self.src[i]:
                 self.model.dpllm_set_selector_input(i, self.sel[i])
+        self.model.dpllm_debug_set_one_launch(1)
 
     def select(self, T):
         for i, L in enumerate(self.lin):
@@ -71,14 +73,15 @@ class Chain:
         self.x0.copy_(synth.make_x(self.x0.numel(), 1, seed=seed)[0] * (1 + seed % 3))
         self.late.copy_(synth.make_x(self.late.numel() // 32 * 32 + 32, 1, seed=seed + 50)[0][:self.late.numel()])
 
-    def step(self):
+    def step(self, one=True):
         self.model.dpllm_decode_step(self.xp, self.yp, self.k, self.e)
+        assert (self.model.dpllm_debug_step_launches() == 2) == one
 
     def level_by_level(self):
-        """A step with a bound on the polls of a level's launch is made of such launches."""
-        self.model.dpllm_debug_set_polls(63)
-        self.step()
-        self.model.dpllm_debug_set_polls(64)
+        """The same step with a launch per level (it writes the tables anew: replays come behind the next step in one launch)."""
+        self.model.dpllm_debug_set_one_launch(-1)
+        self.step(one=False)
+        self.model.dpllm_debug_set_one_launch(1)
 
     def state(self):
         torch.cuda.synchronize()
@@ -88,13 +91,13 @@ class Chain:
         for t in [self.k, self.e] + self.ys:
             t.zero_()
 
-    def calibrate(self, seeds):
+    def calibrate(self, seeds, one=True):
         """Thresholds between, below and above the estimates of two inputs in turn."""
         self.select([math.inf] * len(self.lin))
         est = []
         for s in seeds:
             self.put(s)
-            self.step()
+            self.step(one)
             est.append(self.e.tolist())
         self.select([0.5 * (a + b) if i % 3 == 0 else (0.4 if i % 3 == 1 else 2.5) * max(a, b) for i, (a, b) in enumerate(zip(*est))])
 
@@ -115,7 +118,7 @@ class Chain:
             assert np.linalg.norm(self.ys[i].double().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref), (tag, i)
 
 
-# 26 levels of small and ragged linears (rows around 16, 32 and 64, columns below one tile, with a ragged last tile and chunk)
+# small and ragged linears (rows around 16, 32 and 64, columns below one tile, with a ragged last tile and chunk)
 SMALL = [[64], [65, 1, 63], [33], [544, 17], [1000], [15, 130], [96, 4, 4, 4, 4, 4, 4], [200]] * 3 + [[512], [77]]
 # levels that are dealt out in blocks of 64 and 32 rows, vectors of more than 4096 elements, with and without a ragged last chunk
 LARGE = [[4128, 8200], [352, 64], [8224], [96], [4096, 4096, 4100], [160], [11008, 11008], [128], [28672], [64], [64]] + [[64]] * 15
@@ -230,7 +233,7 @@ def test_two_chains_beside_one_another(dp):
 def test_steps_it_does_not_serve_run_level_by_level(dp, case):
     """A vector that spans two results, one result buffer for several linears, a vector that starts off the mailbox's words: the
     results of linears one after the other."""
-    net = Chain(dp, [[96]] * 26, 96, 4, [(3, 4)], seed=31, ranks=(17, 64), late=False)
+    net = Chain(dp, [[96]] * 6 + [[112]] + [[96]] * 19, 96, 4, [(3, 4)], seed=31, ranks=(17, 64), late=False)
     both = torch.zeros(400, dtype=torch.float16, device="cuda")
     if case == "overlap":
         net.ys[3], net.ys[4] = both[:96], both[96:192]
@@ -240,13 +243,13 @@ def test_steps_it_does_not_serve_run_level_by_level(dp, case):
         net.ys[10] = net.ys[7]
         net.src[11] = net.sel[11] = net.ys[7]
     else:
-        net.ys[6] = both[1:97]
+        net.ys[6] = both[1:113]
         net.src[7] = net.sel[7] = both[8:104]
     net.xp, net.yp = net.model.pointers(net.src), net.model.pointers(net.ys)
-    net.calibrate((7, 8))
+    net.calibrate((7, 8), one=False)
     net.put(7)
     net.clear()
-    net.step()
+    net.step(one=False)
     ks, es, ys = net.k.tolist(), net.e.tolist(), [y.clone() for y in net.ys]
     net.clear()
     for i in range(len(net.lin)):
@@ -257,3 +260,113 @@ def test_steps_it_does_not_serve_run_level_by_level(dp, case):
         if not (case == "shared" and i == 7):
             assert (a.double() - b.double()).norm() <= 2e-2 * b.double().norm(), i
     net.model.close()
+
+
+def test_more_linears_in_a_level_than_its_record_holds(dp):
+    """57 linears on one vector: a launch per level."""
+    net = Chain(dp, [[64] * 56, [64] * 57], 64, 4, [(3, 4)], seed=41, late=False)
+    net.calibrate((1, 2), one=False)
+    net.put(1)
+    net.step(one=False)
+    net.check("57")
+    net.model.close()
+
+
+@pytest.mark.parametrize("values", [(math.inf,), (-math.inf, 1.0), (math.nan,), (math.inf, math.nan)])
+def test_infinities_and_nan_travel_through_mailboxes(dp, values):
+    """A result that is not finite, all bits set among them, is handed over like any other: the launch ends, and every result is
+    what a launch per level leaves (an infinity, NaN, or a number to the rounding of the sums)."""
+    net = Chain(dp, SMALL, 96, 4, [(3, 4)], seed=51, late=False)
+    net.calibrate((1, 2))
+    net.put(1)
+    bits = net.x0.view(torch.int16)
+    for i, v in enumerate(values):
+        net.x0[7 * i + 3] = v
+        if math.isnan(v):
+            bits[7 * i + 3] = -1                     # 0xffff
+    net.clear()
+    net.step()
+    got = net.state()
+    net.clear()
+    net.level_by_level()
+    want = net.state()
+    assert torch.equal(got[0], want[0]) and int(got[0][0]) > 0
+    for a, b in zip(got[2:], want[2:]):
+        assert torch.equal(torch.isnan(a), torch.isnan(b)) and torch.equal(torch.isinf(a), torch.isinf(b))
+        keep = torch.isfinite(b)
+        assert (a[keep].double() - b[keep].double()).norm() <= 2e-2 * b[keep].double().norm()
+    assert not bool(torch.isfinite(torch.cat(got[2:])).all())
+    net.model.close()
+
+
+def _big(dp, shapes, p, pairs, seed):
+    """One linear per shape, each fed by the one before, with random planes made on the device."""
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    model, lin = dp.Model(len(shapes)), []
+    for i, (out, in_) in enumerate(shapes):
+        planes = torch.randint(-2 ** 31, 2 ** 31, (p, out, in_ // 32), dtype=torch.int32, device="cuda", generator=g)
+        luts = {k: (torch.randn(out, 1 << k, device="cuda", generator=g) / math.sqrt(in_)).half() for k in range(3, p + 1)}
+        model.dpllm_load_linear(i, planes, luts, 3)
+        Gs = [(torch.randn(16, in_, device="cuda", generator=g) * 0.1 / math.sqrt(in_)).half() for _ in pairs]
+        for (l, h), G in zip(pairs, Gs):
+            model.dpllm_set_selector(i, l, h, dp.DPLLM_SEL_PROJ, G=G, T=0.0)
+        keep = i in (0, len(shapes) - 1)             # what the oracle is asked about
+        lin.append({"planes": planes if keep else None, "luts": luts if keep else None, "G": Gs if keep else None})
+    return model, lin
+
+
+# 24 levels either side of the line between the two kinds of step; at 3 or 4 bits a level is 24 .. 42 MB, at 7 or 8 55 .. 84
+@pytest.mark.parametrize("shapes,one", [([(15360, 4096), (4096, 15360)] * 12, True), ([(15360, 5120), (5120, 15360)] * 12, False)])
+def test_a_captured_step_follows_the_pair_in_use(dp, shapes, one):
+    """How a step is launched does not depend on the pairs in use: a graph captured under one pair runs another after
+    dpllm_set_active_pair and an eager step between, in both directions."""
+    pairs = [(3, 4), (7, 8)]
+    model, lin = _big(dp, shapes, 8, pairs, seed=61)
+    n = len(shapes)
+    x0 = synth.make_x(shapes[0][1], 1, seed=62)[0].cuda()
+    ys = [torch.zeros(out, dtype=torch.float16, device="cuda") for out, _ in shapes]
+    xs = [x0] + ys[:-1]
+    k, e = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, dtype=torch.float32, device="cuda")
+
+    def use(pair, T):
+        for i in range(n):
+            model.dpllm_set_active_pair(i, *pair)
+            model.dpllm_set_threshold(i, *pair, T[i])
+
+    def step():
+        model.dpllm_decode_step(xs, ys, k, e)
+        assert (model.dpllm_debug_step_launches() == 2) == one
+
+    want, T = {}, {}
+    for pair in pairs:
+        T[pair] = [math.inf if i % 2 else -math.inf for i in range(n)]
+        use(pair, T[pair])
+        step()
+        torch.cuda.synchronize()
+        want[pair] = [t.clone() for t in [k, e] + ys]
+        assert k.tolist() == [pair[0] if i % 2 else pair[1] for i in range(n)]
+        for i in (0, n - 1):
+            x = xs[i].cpu().numpy().view(np.uint16)
+            got_k = int(k[i])
+            ref = oracle.gemv(lin[i]["planes"].cpu().numpy().view(np.uint32), got_k, lin[i]["luts"][got_k].cpu().numpy().view(np.uint16), x)
+            assert np.linalg.norm(ys[i].double().cpu().numpy() - ref) <= 2e-3 * np.linalg.norm(ref), (pair, i)
+            ref = oracle.estimate(lin[i]["G"][pairs.index(pair)].cpu().numpy().view(np.uint16), x)
+            assert math.isclose(float(e[i]), ref, rel_tol=3e-7)
+    for captured, other in (pairs, pairs[::-1]):
+        use(captured, T[captured])
+        step()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            step()
+        for pair in (other, captured, other):
+            use(pair, T[pair])
+            for t in ys:
+                t.zero_()
+            step()
+            for rep in range(2):
+                for t in [k, e] + ys:
+                    t.zero_()
+                graph.replay()
+                torch.cuda.synchronize()
+                assert all(torch.equal(a, b) for a, b in zip([k, e] + ys, want[pair])), (captured, pair, rep)
+    model.close()
