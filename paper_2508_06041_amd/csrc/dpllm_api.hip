@@ -104,6 +104,7 @@ struct StepPlan {
   size_t slots = 0;      // partial dot products of all selectors; emptied at the start of a whole step if
   bool fused = false;    //   any of its phases runs selectors inside its GEMV launch
   bool idle = false;     // some phase has no estimator under any target, though its linears hold pairs with one
+  bool captured = false; // a graph may hold launches of this plan
   bool chain = false;    // a whole step is one launch (gemv_chain_kernel)
   int chain_grid = 0;
   size_t chain_slots = 0, chain_mail = 0;   // 64-bit words
@@ -188,6 +189,14 @@ int check_shape(int out, int in, int p, int kmin) {
   if (out < 1 || in < 32 || in % 32 != 0) return DPLLM_ESHAPE;
   if (p < 1 || p > DPLLM_MAX_BITS || kmin < 1 || kmin > p) return DPLLM_ERANGE;
   return DPLLM_OK;
+}
+
+// Makes `slot` the linear's pair under target 0.  The work of a step is cut for the h of that pair, so the next step plans anew
+// where it changes; but not while a graph may hold launches of the present plan: they serve every pair, and replayed under
+// another one they have to find their own tables (a plan for another h has another number of workgroups).
+void use_pair(dpllm_model* m, Linear* lin, int slot) {
+  if (lin->active < 0 || (lin->sel[lin->active].h != lin->sel[slot].h && !(m->plan.valid && m->plan.captured))) m->version++;
+  lin->active = slot;
 }
 
 Linear* get_linear(dpllm_model* m, int id, int* rc) {
@@ -657,7 +666,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
   const int n = (int)m->linears.size();
   const Workspace& W = m->ws;
   StepPlan& P = m->plan;
-  P.valid = false;
+  P.valid = P.captured = false;
   P.xs.assign(xs, xs + n);
   P.ys.assign(ys, ys + n);
   P.k_dev = k_dev;
@@ -1078,13 +1087,12 @@ int dpllm_set_selector(dpllm_model* m, int id, int l, int h, int kind, const voi
       if (!lin->sel[i].set) slot = i;
   if (slot < 0) return fail(m, DPLLM_ESTATE, "linear %d already holds %d pairs", id, DPLLM_MAX_PAIRS);
   Pair& s = lin->sel[slot];
-  // the launch plan is sized by the ranks and bitwidths of all pairs of the linear: it survives a change of G,
-  // alpha, beta or T
-  const bool same_shape = s.set && lin->active == slot && s.kind == kind && sel_rowgroups_of(s.kind, s.r) == sel_rowgroups_of(kind, r);
+  // the launch plan is sized by the kinds and ranks of all pairs of the linear: it survives a change of G, alpha, beta or T
+  const bool same_shape = s.set && s.kind == kind && sel_rowgroups_of(s.kind, s.r) == sel_rowgroups_of(kind, r);
   s.set = true; s.l = l; s.h = h; s.kind = kind; s.r = kind == DPLLM_SEL_PROJ ? r : 0; s.G = (const uint16_t*)G_dev;
   s.alpha = alpha; s.beta = beta; s.T = T;
-  lin->active = slot;
   if (!same_shape) m->version++;
+  use_pair(m, lin, slot);
   m->params_dirty = true;
   return DPLLM_OK;
 }
@@ -1107,8 +1115,7 @@ int dpllm_set_active_pair(dpllm_model* m, int id, int l, int h) {
   if (!lin) return rc;
   int slot = lin->find_pair(l, h);
   if (slot < 0) return fail(m, DPLLM_ESTATE, "pair (%d,%d) not set on linear %d", l, h, id);
-  if (lin->active < 0 || lin->sel[lin->active].h != lin->sel[slot].h) m->version++;   // the step's work is cut for h
-  lin->active = slot;
+  use_pair(m, lin, slot);
   m->params_dirty = true;
   return DPLLM_OK;
 }
@@ -1255,7 +1262,8 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   StepPlan& P = m->plan;
   bool reuse = P.valid && P.version == m->version && P.k_dev == k_dev && P.e_dev == e_dev &&
                std::equal(xs, xs + n, P.xs.begin()) && std::equal(ys, ys + n, P.ys.begin());
-  if ((!reuse || m->params_dirty) && capturing(st))
+  const bool in_capture = capturing(st);
+  if ((!reuse || m->params_dirty) && in_capture)
     return fail(m, DPLLM_ESTATE, "the model changed since its last step: run one step outside stream capture first");
   if (!reuse) {
     for (int id = 0; id < n; ++id) {
@@ -1279,7 +1287,8 @@ int dpllm_decode_step_parts(dpllm_model* m, const void* const* xs, void* const* 
   const SelParams* active = W.at<SelParams>(W.sel_active);
   const bool both = parts == (DPLLM_STEP_SELECT | DPLLM_STEP_GEMV);
   // a captured step is replayed under pairs and targets chosen later: it holds the selectors of every pair
-  const bool all = P.idle && capturing(st);
+  const bool all = P.idle && in_capture;
+  P.captured |= in_capture;
   m->launches = 0;
   if (both && P.chain) {
     launch_chain(m, W, P, st);

@@ -315,17 +315,19 @@ def _big(dp, shapes, p, pairs, seed):
     return model, lin
 
 
-# 24 levels either side of the line between the two kinds of step; at 3 or 4 bits a level is 24 .. 42 MB, at 7 or 8 55 .. 84
-@pytest.mark.parametrize("shapes,one", [([(15360, 4096), (4096, 15360)] * 12, True), ([(15360, 5120), (5120, 15360)] * 12, False)])
-def test_a_captured_step_follows_the_pair_in_use(dp, shapes, one):
-    """How a step is launched does not depend on the pairs in use: a graph captured under one pair runs another after
+# 24 levels either side of the line between the two kinds of step; at 3 or 4 bits a level is 24 .. 42 MB, at 7 or 8 55 .. 84.
+# Linears that do not depend on one another, with 1024 workgroups where the work is cut for 3 or 4 bits and 2048 where for 7 or 8
+@pytest.mark.parametrize("shapes,chained,one", [([(15360, 4096), (4096, 15360)] * 12, True, True), ([(15360, 5120), (5120, 15360)] * 12, True, False),
+                                                ([(16384, 16384)] * 8, False, False)])
+def test_a_captured_step_follows_the_pair_in_use(dp, shapes, chained, one):
+    """How a captured step is launched does not depend on the pairs in use: a graph captured under one pair runs another after
     dpllm_set_active_pair and an eager step between, in both directions."""
     pairs = [(3, 4), (7, 8)]
     model, lin = _big(dp, shapes, 8, pairs, seed=61)
     n = len(shapes)
     x0 = synth.make_x(shapes[0][1], 1, seed=62)[0].cuda()
     ys = [torch.zeros(out, dtype=torch.float16, device="cuda") for out, _ in shapes]
-    xs = [x0] + ys[:-1]
+    xs = [x0] + ys[:-1] if chained else [x0] * n
     k, e = torch.zeros(n, dtype=torch.int32, device="cuda"), torch.zeros(n, dtype=torch.float32, device="cuda")
 
     def use(pair, T):
