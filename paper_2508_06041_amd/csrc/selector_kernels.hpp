@@ -308,8 +308,11 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
   const int nit = (ce - cb + kSelChunkStep - 1) / kSelChunkStep;
   // Rows of G are a power-of-two number of bytes apart in the common shapes, so wavefronts that all walk the
   // columns from the start would hit the same few memory channels at any moment: every wavefront starts its
-  // (circular) walk at a different 1 KiB column chunk.
-  int it = (int)((blockIdx.x * kSelPartWaves + wave) * 5u % (unsigned)nit);   // tile being loaded
+  // (circular) walk at a different 1 KiB column chunk.  (A row starts where it does in a launch of parts of four rows a wavefront:
+  // the same order of additions, the same bits.)
+  const unsigned walk = HANDED ? (unsigned)((row0 / kSelPartRows * job.nchunks + ch) * kSelPartWaves + row0 % kSelPartRows / kSelRowsPerWave)
+                               : blockIdx.x * kSelPartWaves + wave;
+  int it = (int)(walk * 5u % (unsigned)nit);   // tile being loaded
   int ca = cb + it * kSelChunkStep + lane * 8;                                // first column of the tile being accumulated
   SelTile<ROWS> ring[kSelDepth];
 #pragma unroll

@@ -113,3 +113,21 @@ def test_first_estimate_while_another_stream_is_captured(dp):
         torch.cuda.synchronize()
         assert torch.equal(other, torch.full_like(other, 3.0 * rep))
     model.close()
+
+
+# more than 32 chunks of 512 columns: a chunk is two tiles of a wavefront, and rows start their walk at different ones
+@pytest.mark.parametrize("in_,r", [(16416, 17), (28672, 64), (28672, 200), (30720, 33)])
+def test_one_launch_and_two_leave_the_same_bits(dp, in_, r):
+    """Products of 2^32 that cancel between small ones: a lane that adds its columns in another order ends at another sum, by all of it."""
+    model = _model(dp, in_, seed=r)
+    G, x = _G(r, in_, r) * 2.0 ** -8, synth.make_x(in_, 1, seed=r)[0] * 2.0 ** -8
+    c = torch.arange(in_)
+    whole = c < in_ // 1024 * 1024
+    for cols, sign in (whole & (c % 1024 < 512) & (c % 8 == 7), 1.0), (whole & (c % 1024 >= 512) & (c % 8 == 0), -1.0):
+        x[cols], G[:, cols] = 60000.0, 60000.0 * sign
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=0.0)
+    x, e, k = x.cuda(), torch.zeros(2, device="cuda"), torch.zeros(2, dtype=torch.int32, device="cuda")
+    model.dpllm_estimate(0, 3, 4, x, e_out=e[:1], k_out=k[:1])
+    model.dpllm_estimate_noalloc(0, 3, 4, x, e[1:], k[1:])
+    assert float(e[0]) == float(e[1]) > 0.0 and k.tolist() == [4, 4]
+    model.close()
