@@ -115,7 +115,8 @@ struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
   size_t est_ws = 0;                         // dpllm_estimate in two launches: kSelOneSlots fp64
-  size_t est_slots = 0, est_slots_cap = 0;   // dpllm_estimate in one: uint64 [kEstRing][cap], empty between calls
+  size_t est_slots = 0, est_slots_cap = 0;   // dpllm_estimate in one: uint64 [kEstRing][cap][2], empty between calls,
+  size_t est_marks = 0;                      //   and uint32 [kEstRing]: slots that are not relied on any more
   size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
   size_t sel_active = 0;                     // SelParams [n]: the row of the active target
@@ -151,7 +152,7 @@ struct dpllm_model {
   std::vector<ChainLevel> h_chain_levels;
   std::vector<ChainJob> h_chain_jobs;
   std::vector<SelParams> h_params;
-  unsigned est_turn = 0;           // estimates take turns in the sets of slots,
+  uint32_t est_turn = 0;           // the number of the last estimate; they take turns in the sets of slots,
   hipStream_t ws_stream = nullptr; //   which dpllm_set_workspace empties on this stream:
   hipEvent_t ws_event = nullptr;   //   done for every stream to see once the event has passed
   bool est_ready = false;
@@ -213,7 +214,7 @@ int sel_slices(int in) { return (in + kSelTaskCols - 1) / kSelTaskCols; }
 
 // slots of an estimate in one launch: 16 rows of G in chunks of 512 columns and more
 size_t est_slots_of(const Linear& lin, int rowgroups) {
-  return (size_t)rowgroups * kSelPartRows * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
+  return (size_t)std::min(rowgroups * kSelPartRows, kEstMaxRank) * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
 }
 
 // 64-bit words of one copy of a linear's mailbox (whole lines: no two linears share one)
@@ -238,7 +239,8 @@ Workspace carve_workspace(const dpllm_model* m) {
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
   w.est_ws = take(sizeof(double) * kSelOneSlots);
   w.est_slots_cap = est;
-  w.est_slots = take(sizeof(uint64_t) * kEstRing * est);
+  w.est_slots = take(2 * sizeof(uint64_t) * kEstRing * est);
+  w.est_marks = take(sizeof(uint32_t) * kEstRing);
   w.target = take(sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
   w.sel_active = take(sizeof(SelParams) * n);
@@ -987,11 +989,10 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   if (capturing(st)) w.est_slots_cap = 0;   // (emptied by a replay at some time to come: no estimate relies on it)
   else if (w.est_slots_cap > 0 && !m->ws_event) HIP_TRY(m, hipEventCreateWithFlags(&m->ws_event, hipEventDisableTiming));
   // the target starts at zero, the jobs without tasks, the slots of lone estimates empty; everything else is written before it is used
-  struct { size_t off, words; uint32_t value; } start[] = {{w.target, 1, 0u}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size(), 0u},
-                                                           {w.est_slots, w.est_slots_cap * kEstRing * 2, (uint32_t)kSelEmpty}};
-  for (const auto& z : start)
+  struct { size_t off, words; } zero[] = {{w.target, 1}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size()}, {w.est_slots, w.est_slots_cap * kEstRing * 4}, {w.est_marks, kEstRing}};
+  for (const auto& z : zero)
     if (z.words > 0)
-      hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, z.value);
+      hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, 0u);
   HIP_TRY(m, hipGetLastError());
   if (w.est_slots_cap > 0) HIP_TRY(m, hipEventRecord(m->ws_event, st));
   m->ws_stream = st;
@@ -1171,23 +1172,26 @@ static int launch_estimate(dpllm_model* m, const Linear& lin, int id, const Pair
   return DPLLM_OK;
 }
 
-// one launch, with slots of the workspace; false: a pair attached after the workspace was handed over needs more of them, or they
-// may not be empty yet
+// one launch, with slots of the workspace; false: the rank is beyond what its last workgroup collects at a time, a pair attached
+// after the workspace was handed over needs more slots, or they may not be empty yet
 static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, const Pair& sel, const void* x_dev, float* e_dev, int32_t* k_dev,
                                  hipStream_t st) {
   const Workspace& W = m->ws;
   const int rowgroups = sel_rowgroups_of(sel.kind, sel.r);
   SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups);
-  if ((size_t)rowgroups * kSelPartRows * j.nchunks > W.est_slots_cap) return false;
+  if (sel.kind == DPLLM_SEL_PROJ && (sel.r > kEstMaxRank || (size_t)j.ws_rows * j.nchunks > W.est_slots_cap)) return false;
   if (!m->est_ready && sel.kind == DPLLM_SEL_PROJ) {
     // the slots are empty for work behind dpllm_set_workspace on its stream, for any other once that has been seen to be done
     if (!capturing(st) && passed(m->ws_event)) m->est_ready = true;
     if (!m->est_ready && st != m->ws_stream) return false;
   }
-  const unsigned turn = sel.kind == DPLLM_SEL_PROJ ? m->est_turn++ % kEstRing : 0;
+  if (sel.kind == DPLLM_SEL_PROJ && ++m->est_turn == 0) m->est_turn = 1;   // (0: an empty slot)
+  const unsigned set = m->est_turn % kEstRing;
+  const int polls = m->polls == kSelPolls ? kEstPolls : std::max(m->polls, 0);
   const int parts = sel.kind == DPLLM_SEL_PROJ ? (sel.r + kEstPartRows - 1) / kEstPartRows * j.nchunks : 1;
   hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, j.x,
-                     W.at<double>(W.est_slots) + turn * W.est_slots_cap, j.in, sel.r, j.nchunks, j.chunk_cols, j.ws_rows, sel.kind, j, make_params(sel, sel.T));
+                     W.at<uint64_t>(W.est_slots) + set * W.est_slots_cap * 2, j.in, sel.r, j.nchunks, j.chunk_cols, j.ws_rows, sel.kind, m->est_turn, j,
+                     make_params(sel, sel.T), W.at<uint32_t>(W.est_marks) + set, polls);
   return true;
 }
 

@@ -286,18 +286,11 @@ __device__ __forceinline__ void selector_group_part(const SelJob* jobs, const in
   }
 }
 
-// One projection part: wavefront w owns ROWS rows (clamped to r - 1; surplus rows are dropped), with four of them 16 rg + 4 w .. + 3,
-// columns [cb, ce) of them
-// HANDED: the products are read inside this launch (selector_estimate_kernel), and slots of surplus rows stay empty
-template <bool HANDED = false, int ROWS = kSelRowsPerWave>
-__device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelParams& P, int part, int tid) {
-  const int wave = tid >> 6, lane = tid & 63;
-  if (P.kind != 1) return;                                    // this target estimates the linear otherwise
-  const int rg = part / job.nchunks, ch = part - rg * job.nchunks;
-  constexpr int part_rows = kSelPartWaves * ROWS;
-  if (rg * part_rows >= P.r) return;                          // the pair of this target has fewer rows of G
+// What a wavefront does of a projection part: the products of ROWS rows from row0 on (clamped to r - 1; surplus rows are dropped)
+// and columns [cb, ce) of x, chunk ch.  ONE: in a launch for one row a wavefront.
+template <bool ONE, int ROWS>
+__device__ __forceinline__ void selector_part_products(const SelJob& job, const SelParams& P, int row0, int ch, int wave, int lane, double (&rowsum)[ROWS]) {
   const int cb = ch * job.chunk_cols, ce = min(job.in, cb + job.chunk_cols);
-  const int row0 = rg * part_rows + wave * ROWS;
   const uint16_t* rows[ROWS];
 #pragma unroll
   for (int i = 0; i < ROWS; ++i) rows[i] = P.G + (size_t)min(row0 + i, P.r - 1) * job.in;
@@ -310,8 +303,8 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
   // columns from the start would hit the same few memory channels at any moment: every wavefront starts its
   // (circular) walk at a different 1 KiB column chunk.  (A row starts where it does in a launch of parts of four rows a wavefront:
   // the same order of additions, the same bits.)
-  const unsigned walk = HANDED ? (unsigned)((row0 / kSelPartRows * job.nchunks + ch) * kSelPartWaves + row0 % kSelPartRows / kSelRowsPerWave)
-                               : blockIdx.x * kSelPartWaves + wave;
+  const unsigned walk = ONE ? (unsigned)((row0 / kSelPartRows * job.nchunks + ch) * kSelPartWaves + row0 % kSelPartRows / kSelRowsPerWave)
+                            : blockIdx.x * kSelPartWaves + wave;
   int it = (int)(walk * 5u % (unsigned)nit);   // tile being loaded
   int ca = cb + it * kSelChunkStep + lane * 8;                                // first column of the tile being accumulated
   SelTile<ROWS> ring[kSelDepth];
@@ -330,18 +323,23 @@ __device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelP
       ca = ca + kSelChunkStep >= cb + nit * kSelChunkStep ? ca + kSelChunkStep - nit * kSelChunkStep : ca + kSelChunkStep;
     }
   }
+#pragma unroll
+  for (int i = 0; i < ROWS; ++i) rowsum[i] = sel_storable(wave_sum_f64(acc[i]));
+}
+
+// One projection part of 16 rows: wavefront w owns rows 16 rg + 4 w .. + 3
+__device__ __forceinline__ void selector_proj_part(const SelJob& job, const SelParams& P, int part, int tid) {
+  const int wave = tid >> 6, lane = tid & 63;
+  if (P.kind != 1) return;                                    // this target estimates the linear otherwise
+  const int rg = part / job.nchunks, ch = part - rg * job.nchunks;
+  if (rg * kSelPartRows >= P.r) return;                       // the pair of this target has fewer rows of G
+  const int row0 = rg * kSelPartRows + wave * kSelRowsPerWave;
+  double rowsum[kSelRowsPerWave];
+  selector_part_products<false>(job, P, row0, ch, wave, lane, rowsum);
   DPLLM_SEL_GLOBAL double* ws = (DPLLM_SEL_GLOBAL double*)job.ws;
 #pragma unroll
-  for (int i = 0; i < ROWS; ++i) {
-    const double rowsum = wave_sum_f64(acc[i]);
-    const size_t at = (size_t)ch * job.ws_rows + row0 + i;
-    if constexpr (HANDED) {
-      if (lane == 0 && row0 + i < P.r)
-        __hip_atomic_store((DPLLM_SEL_GLOBAL uint64_t*)ws + at, __builtin_bit_cast(uint64_t, sel_storable(rowsum)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
-      if (lane == 0) ws[at] = sel_storable(rowsum);
-    }
-  }
+  for (int i = 0; i < kSelRowsPerWave; ++i)
+    if (lane == 0) ws[(size_t)ch * job.ws_rows + row0 + i] = rowsum[i];
 }
 
 // ---- the selectors of a small GEMV launch, worked off by its own workgroups --------------------------------------
@@ -578,65 +576,106 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
 }
 
 // One estimate in one launch.  The workgroups are parts of the projection, four rows of G by a chunk of columns; the last one
-// collects the products of all and decides.  A product travels through a slot that is its own flag (kSelEmpty until it is there,
-// relaxed atomics on that one word on both sides); who has collected it empties the slot again, so that every launch finds the
-// slots empty.  Workgroups start in order, and no more than one per launch ever waits, so those it waits for find a place whatever
-// else the chip is doing: the wait ends.  (It is bounded all the same; a product nobody delivered is the NaN in its slot, and so
-// is the estimate then: l.)  Launches take turns in kEstRing sets of slots.
-// What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection. 
+// collects the products of all and decides.  A product travels in two 64-bit words, half of it and the number of the call (tag) in
+// each: a word says itself whose it is, so no order of memory locations and no fence is needed (relaxed atomics on both sides), and
+// what another call has left is never taken.  Who has collected a product empties its words again, for a graph that replays the
+// call under the same number.  Workgroups start in order, and no more than one per launch ever waits, so those it waits for find a
+// place whatever else the chip is doing: the wait ends.  Nothing rests on that: it is bounded, and who gives up computes all
+// products itself, with the same bits, and marks the set of slots as distrusted, because what it gave up on may still come; whoever
+// finds the mark computes for itself too.  (A wait is given up where calls of one model overlap, which the header rules out: their
+// products overwrite one another.)  Launches take turns in kEstRing sets of slots.
+// What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection.
 // us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> now: rank 64 of 4096 columns
-// 4.5 / 7.4 -> 3.3 / 4.2, of 11008 5.7 / 7.3 -> 4.2 / 4.5, rank 1024 of 4096 9.8 / 10.0 -> 9.3 / 9.2, linear regression 3.6 / 7.2 ->
-// 2.0 / 4.5 (eager: the host takes 4.2 for a call).
+// 4.5 / 7.4 -> 4.5 / 4.9, of 11008 5.3 / 7.6 -> 5.1 / 5.0, rank 256 of 4096 5.2 / 7.5 -> 5.2 / 4.9, of 11008 7.2 / 7.7 -> 7.2 / 7.7, linear
+// regression 3.7 / 7.5 -> 2.0 / 4.9 (eager: the host takes 4.2 for a call); beyond rank 256 two launches are as fast.  14 linears of 7B
+// with a GEMV each: 189 -> 175 (169 with products of one word, which what an overlap left behind could pass for).
 constexpr int kEstRing = 16;
-constexpr int kEstRows = 1;             // rows of G of a wavefront (14 linears of 7B with a GEMV each: 164 us; with four, and a counter that says who started last, 178)
+constexpr int kEstRows = 1;             // rows of G of a wavefront
 constexpr int kEstPartRows = kSelPartWaves * kEstRows;
-constexpr int kEstPolls = 1 << 20;      // of about a microsecond
+constexpr int kEstMaxRank = kSelPartThreads;
+constexpr int kEstPolls = 1 << 16;      // of about a microsecond
 
-// rows t, t + 64, ... of the products in lane t, each the sum of its chunks in order; BATCH chunks are asked for at a time
+// Row t of the products, the sum of its chunks in order; BATCH chunks are asked for at a time.  A chunk's slots are the lower halves
+// of its rows, then the upper ones.  false: given up, or the slots are not relied on.
 template <int BATCH>
-__device__ __forceinline__ void selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, int nchunks, int ws_rows, int r, int tid, double* sq) {
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  int left = kEstPolls;
-  for (int t0 = wave * 64; t0 < r; t0 += kSelPartThreads) {
-    const int t = min(t0 + lane, r - 1);
-    double g = 0.0;
-    for (int c0 = 0; c0 < nchunks; c0 += BATCH) {
-      uint64_t v[BATCH];
-      for (;;) {
-        bool all = true;
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i)
-          v[i] = __hip_atomic_load(slots + (size_t)min(c0 + i, nchunks - 1) * ws_rows + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-#pragma unroll
-        for (int i = 0; i < BATCH; ++i) all = all && v[i] != kSelEmpty;
-        if (__all(all) || --left < 0) break;
-        __builtin_amdgcn_s_sleep(1);
-      }
+__device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, uint32_t tag, int nchunks, int ws_rows, int t, uint32_t marked, int polls, double& g) {
+  g = 0.0;
+  for (int c0 = 0; c0 < nchunks; c0 += BATCH) {
+    uint64_t lo[BATCH], hi[BATCH];
+    for (;;) {
+      bool all = true;
 #pragma unroll
       for (int i = 0; i < BATCH; ++i) {
-        if (c0 + i >= nchunks) break;
-        g += __builtin_bit_cast(double, v[i]);
-        __hip_atomic_store(slots + (size_t)(c0 + i) * ws_rows + t, kSelEmpty, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        DPLLM_SEL_GLOBAL uint64_t* slot = slots + (uint32_t)(min(c0 + i, nchunks - 1) * ws_rows * 2) + t;
+        lo[i] = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        hi[i] = __hip_atomic_load(slot + ws_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       }
+#pragma unroll
+      for (int i = 0; i < BATCH; ++i) all = all && (uint32_t)(lo[i] >> 32) == tag && (uint32_t)(hi[i] >> 32) == tag;
+      if (__all(all)) break;
+      if (marked != 0 || --polls < 0) return false;
+      __builtin_amdgcn_s_sleep(1);
     }
-    if (t0 + lane < r) sq[t] = g * g;
+#pragma unroll
+    for (int i = 0; i < BATCH; ++i) {
+      if (c0 + i >= nchunks) break;
+      g += __builtin_bit_cast(double, hi[i] << 32 | (uint32_t)lo[i]);
+      DPLLM_SEL_GLOBAL uint64_t* slot = slots + (uint32_t)((c0 + i) * ws_rows * 2) + t;
+      __hip_atomic_store(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(slot + ws_rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
+  return marked == 0;
 }
 
 // G .. kind: what a workgroup needs to ask for its first rows comes as plain arguments (see gemv_lane_kernel)
-__global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, double* ws, int in, int r,
-                                                                           int nchunks, int chunk_cols, int ws_rows, int kind, SelJob job, SelParams P) {
+// distrust: the word of the set of slots
+__global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, uint64_t* ws, int in, int r,
+                                                                           int nchunks, int chunk_cols, int ws_rows, int kind, uint32_t tag, SelJob job,
+                                                                           SelParams P, uint32_t* distrust, int polls) {
   __shared__ SelShared sh;
-  const int tid = threadIdx.x;
+  __shared__ int here[kSelPartWaves];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   P.G = G; P.r = r; P.kind = kind;
-  job.x = x; job.ws = ws; job.in = in; job.nchunks = nchunks; job.chunk_cols = chunk_cols; job.ws_rows = ws_rows;
+  job.x = x; job.in = in; job.nchunks = nchunks; job.chunk_cols = chunk_cols;
   double e = 0.0;
   if (kind == 1) {
-    selector_proj_part<true, kEstRows>(job, P, blockIdx.x, tid);
+    static_assert(kEstRows == 1 && kEstMaxRank <= kSelPartThreads, "a product a wavefront, a row a lane");
+    DPLLM_SEL_GLOBAL uint64_t* slots = (DPLLM_SEL_GLOBAL uint64_t*)ws;
+    DPLLM_SEL_GLOBAL uint32_t* mark = (DPLLM_SEL_GLOBAL uint32_t*)distrust;
+    const int rg = blockIdx.x / nchunks, ch = blockIdx.x - rg * nchunks, row = rg * kEstPartRows + wave;
+    double g[1];
+    selector_part_products<true>(job, P, row, ch, wave, lane, g);
+    if (lane == 0 && row < r) {
+      const uint64_t v = __builtin_bit_cast(uint64_t, g[0]);
+      DPLLM_SEL_GLOBAL uint64_t* slot = slots + (size_t)ch * ws_rows * 2 + row;
+      __hip_atomic_store(slot, (uint64_t)tag << 32 | (uint32_t)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      __hip_atomic_store(slot + ws_rows, (uint64_t)tag << 32 | v >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
     if (blockIdx.x + 1 != gridDim.x) return;
-    if (nchunks <= 8) selector_collect<8>((DPLLM_SEL_GLOBAL uint64_t*)ws, nchunks, ws_rows, r, tid, sh.sq);
-    else selector_collect<24>((DPLLM_SEL_GLOBAL uint64_t*)ws, nchunks, ws_rows, r, tid, sh.sq);
+    const uint32_t marked = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    bool all = true;
+    if (wave * 64 < r) {
+      all = nchunks <= 8 ? selector_collect<8>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0])
+                         : selector_collect<12>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0]);
+      sh.sq[tid] = g[0] * g[0];
+    }
+    if (lane == 0) here[wave] = all;
     __syncthreads();
+    if (!(here[0] && here[1] && here[2] && here[3])) {
+      static_assert(kSelPartWaves == 4, "flags");
+      __syncthreads();
+      if (tid == 0) __hip_atomic_store(mark, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int t = wave; t < r; t += kSelPartWaves) {
+        double sum = 0.0;
+        for (int c = 0; c < nchunks; ++c) {
+          selector_part_products<true>(job, P, t, c, wave, lane, g);
+          sum += g[0];
+        }
+        if (lane == 0) sh.sq[t] = sum * sum;
+      }
+      __syncthreads();
+    }
     if (tid >= 64) return;
     // as selector_finish does: the same bits
     double part = 0.0;
@@ -644,7 +683,6 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     e = sqrt(wave_sum_f64(part));
   } else if (kind == 2) {
     // as selector_group_part does
-    const int wave = tid >> 6, lane = tid & 63;
     double acc = 0.0;
     for (int c = tid * 8; c < in; c += kSelPartThreads * 8) {
       const sel_u32x4 xv = *(const DPLLM_SEL_GLOBAL sel_u32x4*)(x + c);

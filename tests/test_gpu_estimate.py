@@ -1,5 +1,5 @@
 """GPU tests of dpllm_estimate in one launch (selector_estimate_kernel): products of four rows of G by a chunk of columns,
-collected by the launch's last workgroup from slots that it empties again."""
+collected by the launch's last workgroup from slots that carry the number of the call and that it empties again."""
 import math
 
 import numpy as np
@@ -130,4 +130,64 @@ def test_one_launch_and_two_leave_the_same_bits(dp, in_, r):
     model.dpllm_estimate(0, 3, 4, x, e_out=e[:1], k_out=k[:1])
     model.dpllm_estimate_noalloc(0, 3, 4, x, e[1:], k[1:])
     assert float(e[0]) == float(e[1]) > 0.0 and k.tolist() == [4, 4]
+    model.close()
+
+
+@pytest.mark.parametrize("in_,r", [(32, 1), (4096, 64), (11008, 65), (16416, 130), (2080, 256)])
+def test_products_left_behind_do_no_harm(dp, in_, r):
+    """Calls that give up their wait at once leave products behind in every set of slots (and, captured, under the number a replay
+    has again); they and the calls that follow leave the bits of two launches."""
+    model, G = _model(dp, in_, seed=in_ + r), _G(r, in_, in_ + r)
+    X = synth.make_x(in_, 2, seed=r)
+    X[1] *= 3.0
+    est = [oracle.estimate(synth.lut_np(G), synth.lut_np(x)) for x in X]
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.5 * sum(est))))
+    x, e, k = X[0].clone().cuda(), torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    xs, want = [v.cuda() for v in X], []
+    for v in xs:
+        model.dpllm_estimate_noalloc(0, 3, 4, v, e, k)
+        want.append(float(e))
+    assert all(math.isclose(a, b, rel_tol=3e-7) for a, b in zip(want, est))
+
+    def look(call, which, tag):
+        x.copy_(xs[which])
+        e.fill_(-1.0), k.zero_()
+        call()
+        assert float(e) == want[which] and int(k) == 3 + which, tag
+
+    one = lambda: model.dpllm_estimate(0, 3, 4, x, e_out=e, k_out=k)
+    model.dpllm_set_workspace()
+    torch.cuda.synchronize()
+    graphs = []
+    for polls in (64, 0):
+        model.dpllm_debug_set_polls(polls)
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            one()
+        for rep in range(40):
+            look(one, rep % 2 if rep < 20 else rep % 3 % 2, (polls, rep))
+            look(graphs[rep % len(graphs)].replay, (rep + 1) % 2, (polls, rep, "replay"))
+    model.dpllm_debug_set_polls(64)
+    for rep in range(40):
+        look(one, rep % 2 if rep < 20 else rep % 3 % 2, ("after", rep))
+        look(graphs[rep % 2].replay, (rep + 1) % 2, ("after", rep, "replay"))
+    model.close()
+
+
+def test_what_a_set_of_slots_holds_is_not_taken_for_a_product(dp):
+    """Products nobody collected, here numbers written over the slots from outside, stay without effect."""
+    in_, r = 2080, 24
+    model, G = _model(dp, in_, seed=9), _G(r, in_, 9)
+    x = synth.make_x(in_, 1, seed=9)[0]
+    ref = oracle.estimate(synth.lut_np(G), synth.lut_np(x))
+    model.dpllm_set_selector(0, 3, 4, dp.DPLLM_SEL_PROJ, G=G.cuda(), T=float(np.float32(0.9 * ref)))
+    x, e, k = x.cuda(), torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
+    model.dpllm_set_workspace()
+    first = 8 * 32 * 1024                                    # behind the products of an estimate in two launches
+    slots = 16 * 2 * 32 * ((in_ + 511) // 512)               # sets, words, rows of the pair in whole parts, chunks
+    model.workspace[first:first + 8 * slots].view(torch.float64).fill_(1.0)
+    for rep in range(36):
+        e.fill_(-1.0), k.zero_()
+        model.dpllm_estimate(0, 3, 4, x, e_out=e, k_out=k)
+        assert math.isclose(float(e), ref, rel_tol=3e-7) and int(k) == 4, rep
     model.close()
