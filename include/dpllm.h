@@ -223,8 +223,10 @@ int dpllm_debug_set_polls(dpllm_model* m, int polls);
 
 /* Parity aid: whether a step of dependent linears is one launch whose workgroups hand the results over themselves.
  * 0 (unless set): where that is faster, by the linears' shapes and the ranks of their pairs; 1: wherever the buffers allow
- * it; -1: never.  The next step rebuilds the launch plan.  Results may differ in the order of additions.  Errors: EINVAL. */
-int dpllm_debug_set_one_launch(dpllm_model* m, int mode);
+ * it; -1: never.  seats > 0: the first linears of such a launch are dealt out to at most so many workgroups, and the others
+ * join later, as they do where the chip is busy with other work (0, unless set: no bound).  The next step rebuilds the launch
+ * plan.  mode changes the order of additions, seats no bit of the results.  Errors: EINVAL. */
+int dpllm_debug_set_one_launch(dpllm_model* m, int mode, int seats);
 
 /* Parity aid: how many kernels the model's last step was made of (one launch for all linears: 2, one of them clears
  * what the other hands over).  Errors: EINVAL. */

@@ -61,7 +61,7 @@ def _load():
     L.dpllm_decode_step_parts.argtypes = [vp, C.POINTER(vp), C.POINTER(vp), vp, vp, i32, vp]
     L.dpllm_debug_unpack.argtypes = [vp, i32, i32, vp, vp]
     L.dpllm_debug_set_polls.argtypes = [vp, i32]
-    L.dpllm_debug_set_one_launch.argtypes = [vp, i32]
+    L.dpllm_debug_set_one_launch.argtypes = [vp, i32, i32]
     L.dpllm_debug_step_launches.argtypes = [vp, C.POINTER(i32)]
     L.dpllm_debug_copy.argtypes = [vp, vp, sz, vp]
     L.dpllm_debug_read.argtypes = [vp, sz, vp, vp]
@@ -260,8 +260,8 @@ class Model:
     def dpllm_debug_set_polls(self, polls):
         _check(self.h, lib.dpllm_debug_set_polls(self.h, polls))
 
-    def dpllm_debug_set_one_launch(self, mode):
-        _check(self.h, lib.dpllm_debug_set_one_launch(self.h, mode))
+    def dpllm_debug_set_one_launch(self, mode, seats=0):
+        _check(self.h, lib.dpllm_debug_set_one_launch(self.h, mode, seats))
 
     def dpllm_debug_step_launches(self):
         n = C.c_int(0)

@@ -23,11 +23,15 @@
 // word, so nothing rests on the order of two memory locations and no fence is needed (a device-scope release writes back the
 // die's whole L2).  chain_reset_kernel empties both before the launch.
 //
-// Who takes part.  Every workgroup that starts takes a number; the last of the grid seals the list, or whoever has waited
-// about 50 us for it (chain_enrol), and only the workgroups on the list work, on rows dealt out by their number among
-// them.  So every wait is for a workgroup that is running and works its levels off in order (tasks, then rows): the lowest
-// level that is not finished is always one that its workgroups can finish, however many workgroups the chip has room for
-// beside other work.
+// Who takes part.  Every workgroup that starts takes a number.  A level is dealt out to the workgroups that have a number by the
+// time somebody settles it (one compare-and-swap per level; everybody else reads how many they are): the first level when the last
+// of the grid has started, or somebody has waited about 50 us for it, and from then on every level while the level before is being
+// worked on, until all of the grid take part.  So every wait is for a workgroup that is running and works its levels off in order
+// (tasks, then rows): the lowest level that is not finished is always one that its workgroups can finish, however many workgroups
+// the chip has room for beside other work; and those that find a place later join at the next level.  us a chained 7B step beside
+// work on another stream, median and worst, a launch per level / this launch with the workgroups of its first level only / now:
+// copies of 1 GiB 2870, 3090 / 2360, 2390 / 2360, 2380; matrix products of 8192^3 (it waits for them to end) / 2600 .. 4700, 9600 / 2870,
+// 3830; of 2048^3 2900, 3250 / 1540 .. 1700, 2060 / 1340, 1420.
 //
 // A workgroup is eight wavefronts, one workgroup to a compute unit (LDS), and up to 256 registers.
 #pragma once
@@ -48,8 +52,7 @@ constexpr int kChainLevelJobs = 56;        // linears of a level, at most
 constexpr int kMailCopies = 1;             // of every result (chained 7B step with 1, 2, 4: 1318, 1330, 1326 us)
 constexpr uint32_t kMailEmpty = 0xffffffffu;   // the low half of a mailbox word nobody has written
 constexpr int kChainEnrolPolls = 64;       // of about a microsecond
-constexpr uint32_t kChainSealed = 1u << 31;
-constexpr int kChainStateWords = 64;       // [0] workgroups that have started, sealed or not; [32] how many take part
+constexpr int kChainLevelCounts = 32;      // state words: [0] workgroups that have started, [32 + l] how many level l is dealt out to
 
 // One level: 64 dwords, which a wavefront holds in one register (lane i = dword i) and reads with v_readlane.
 struct ChainLevel {
@@ -94,46 +97,41 @@ __device__ __forceinline__ uint64_t mail_load(const DPLLM_GLOBAL uint64_t* p) {
   return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Empties slots and mailboxes and opens the list of workgroups.
-__global__ void __launch_bounds__(256) chain_reset_kernel(uint64_t* slots, size_t nslots, uint64_t* mail, size_t nmail, uint32_t* state) {
+// Empties slots and mailboxes; no workgroup has started and no level is settled.
+__global__ void __launch_bounds__(256) chain_reset_kernel(uint64_t* slots, size_t nslots, uint64_t* mail, size_t nmail, uint32_t* state, size_t nstate) {
   const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x, n = (size_t)gridDim.x * 256;
   for (size_t j = i; j < nslots; j += n) slots[j] = kSelEmpty;
   for (size_t j = i; j < nmail; j += n) mail[j] = ~0ull;
-  if (i < kChainStateWords) state[i] = 0;
+  for (size_t j = i; j < nstate; j += n) state[j] = 0;
 }
 
-// Thread 0 of a workgroup: its number among those that take part and how many these are; number < 0: not among them.
-__device__ __forceinline__ void chain_enrol(uint32_t* state, uint32_t grid, int& number, int& count) {
-  DPLLM_GLOBAL uint32_t* started = (DPLLM_GLOBAL uint32_t*)state;
-  DPLLM_GLOBAL uint32_t* sealed = started + 32;
-  auto seal = [&](uint32_t at) {           // true: the list ends at `at`, by this workgroup's hand
-    uint32_t want = at;
-    if (!__hip_atomic_compare_exchange_strong(started, &want, at | kChainSealed, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) return false;
-    __hip_atomic_store(sealed, at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return true;
-  };
-  const uint32_t mine = __hip_atomic_fetch_add(started, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  number = -1;
-  count = 0;
-  if (mine & kChainSealed) return;
-  number = (int)mine;
-  if (mine + 1 == grid && seal(grid)) {
-    count = (int)grid;
-    return;
+// How many workgroups level `level` is dealt out to: as many as have started by now, unless it is settled.  most: 0 for no bound.
+__device__ __forceinline__ int chain_settle(DPLLM_GLOBAL uint32_t* state, int level, int most) {
+  DPLLM_GLOBAL uint32_t* at = state + kChainLevelCounts + level;
+  uint32_t count = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (count != 0) return (int)count;
+  uint32_t started = __hip_atomic_load(state, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (most > 0) started = min(started, (uint32_t)most);
+  return (int)(__hip_atomic_compare_exchange_strong(at, &count, started, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ? started : count);
+}
+
+// Thread 0 of a workgroup: its number, the first level it takes part in and how many that one is dealt out to; number < 0: none.
+__device__ __forceinline__ void chain_enrol(DPLLM_GLOBAL uint32_t* state, int grid, int seats, int nlevels, int patience, int& number, int& level, int& count) {
+  const DPLLM_GLOBAL uint32_t* counts = state + kChainLevelCounts;
+  number = (int)__hip_atomic_fetch_add(state, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  level = 0;
+  count = number + 1 == grid ? chain_settle(state, 0, seats) : 0;
+  for (int left = kChainEnrolPolls; count == 0; --left) {
+    count = left > 0 ? (int)__hip_atomic_load(counts, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : chain_settle(state, 0, seats);
+    if (count == 0) __builtin_amdgcn_s_sleep(2);
   }
-  // ends: the list is sealed by the last workgroup, by another one that has waited, or here (an exchange fails only
-  // because a workgroup has joined or the list is sealed)
-  for (int left = kChainEnrolPolls;; --left) {
-    count = (int)__hip_atomic_load(sealed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (count != 0) return;
-    if (left <= 0) {
-      const uint32_t at = __hip_atomic_load(started, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (!(at & kChainSealed) && seal(at)) {
-        count = (int)at;
-        return;
-      }
+  // not among them: a later level.  While fewer than the grid take part, those that do settle every level, so this ends
+  while (number >= count) {
+    if (++level == nlevels || patience < 0) {
+      number = -1;
+      return;
     }
-    __builtin_amdgcn_s_sleep(2);
+    while ((count = (int)__hip_atomic_load(counts + level, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) == 0 && --patience >= 0) __builtin_amdgcn_s_sleep(8);
   }
 }
 
@@ -426,11 +424,11 @@ __device__ __forceinline__ void chain_run(u32x4 (&T)[H], uint32_t rec, int block
   }
 }
 
-// The levels of a step.  H: the largest bitwidth of the active pairs, rounded up to 4, 6 or 8 (registers of the planes asked for
-// ahead); number, count: as chain_enrol gives them.
+// The levels of a step from `first` on.  H: the largest bitwidth of the active pairs, rounded up to 4, 6 or 8 (registers of the
+// planes asked for ahead); number, first, count: as chain_enrol gives them.
 template <int H>
-__device__ __forceinline__ void chain_levels(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks, int nlevels,
-                                             int patience, int number, int count, int tid, char* lds) {
+__device__ __forceinline__ void chain_levels(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks, DPLLM_GLOBAL uint32_t* state,
+                                             int nlevels, int patience, int number, int first, int count, int tid, char* lds) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   int lane = tid & 63;
   double* sh = reinterpret_cast<double*>(lds + kChainLdsBytes - kSelSharedBytes);
@@ -440,9 +438,11 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
     return *as_global(p);
   };
   auto load_task = [&](int t) { return as_global(reinterpret_cast<const uint32_t*>(tasks + t))[lane & 15]; };
-  // this workgroup's blocks [u0, u1) of a level; units / count as a product: exact for fewer than 2^24 units (count <= 256)
-  const uint32_t per_count = count > 1 ? 0xffffffffu / (uint32_t)count + 1 : 0;
-  auto share = [&](uint32_t lev, int& u0, int& u1) {
+  // this workgroup's blocks [u0, u1) of a level that is dealt out to `count`; units / count as a product: exact for fewer than
+  // 2^24 units (count <= 256)
+  auto inverse = [](int count) { return count > 1 ? 0xffffffffu / (uint32_t)count + 1 : 0; };
+  uint32_t per_count = inverse(count), per_count1 = per_count;   // of this level, of the next one
+  auto share = [&](uint32_t lev, int count, uint32_t per_count, int& u0, int& u1) {
     const int units = (int)rec_u32(lev, DPLLM_CL(units)), base = count > 1 ? (int)__umulhi((uint32_t)units, per_count) : units, extra = units - base * count;
     u0 = number * base + min(number, extra);
     u1 = u0 + base + (number < extra ? 1 : 0);
@@ -459,15 +459,17 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
     c0 = wave * chunks / kLaneWaves;
     c1 = (wave + 1) * chunks / kLaneWaves;
   };
-  const int mirror = count - 1 - number;   // tasks go to the workgroups that have the fewest rows first
-  uint32_t lev = load_level(0), lev1 = load_level(1);
+  uint32_t lev = load_level(first), lev1 = load_level(first + 1);
   uint32_t trec = 0;
   sel_u32x4 tg = {0u, 0u, 0u, 0u};
-  // this workgroup's first task of a level (without one: any, unused)
-  auto task_of = [&](uint32_t lev) { return mirror < (int)rec_u32(lev, DPLLM_CL(task_count)) ? (int)rec_u32(lev, DPLLM_CL(task_first)) + mirror : 0; };
-  bool task_here = mirror < (int)rec_u32(lev, DPLLM_CL(task_count));
+  // tasks go to the workgroups that have the fewest rows first; this workgroup's first one of a level (without one: any, unused)
+  auto task_of = [&](uint32_t lev, int count) {
+    const int mirror = count - 1 - number;
+    return mirror < (int)rec_u32(lev, DPLLM_CL(task_count)) ? (int)rec_u32(lev, DPLLM_CL(task_first)) + mirror : 0;
+  };
+  bool task_here = count - 1 - number < (int)rec_u32(lev, DPLLM_CL(task_count));
   if (task_here) {
-    trec = load_task(task_of(lev));
+    trec = load_task(task_of(lev, count));
     tg = chain_task_g(trec, wave, lane);
   }
   u32x4 T[H];
@@ -482,17 +484,27 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
   };
   {
     int u0, u1;
-    share(lev, u0, u1);
+    share(lev, count, per_count, u0, u1);
     if (u0 < u1) first_rows(lev, u0);
   }
   int turn = 0;
-  for (int l = 0; l < nlevels; ++l) {
+  for (int l = first; l < nlevels; ++l) {
+    // how many the next level is dealt out to (a workgroup that has joined stays: all of the grid do from some level on)
+    int count1 = count;
+    if (count < (int)gridDim.x && l + 1 < nlevels) {
+      int* word = reinterpret_cast<int*>(lds + kChainLdsBytes) - 1;
+      if (tid == 0) *word = chain_settle(state, l + 1, 0);
+      lds_barrier();
+      count1 = __builtin_amdgcn_readfirstlane(*word);
+      lds_barrier();
+      per_count1 = inverse(count1);
+    }
     // records of the levels behind this one
-    uint32_t lev2 = load_level(l + 2), trec1 = load_task(task_of(lev1));
-    const bool task1 = mirror < (int)rec_u32(lev1, DPLLM_CL(task_count));
+    uint32_t lev2 = load_level(l + 2), trec1 = load_task(task_of(lev1, count1));
+    const bool task1 = count1 - 1 - number < (int)rec_u32(lev1, DPLLM_CL(task_count));
     int u0, u1, n0, n1;
-    share(lev, u0, u1);
-    share(lev1, n0, n1);
+    share(lev, count, per_count, u0, u1);
+    share(lev1, count1, per_count1, n0, n1);
     u32x4 task_x = {0u, 0u, 0u, 0u};       // the vector of the workgroup's first task, if it is one slice, and where it lies
     const uint16_t* task_at = nullptr;
     int task_cols = 0;
@@ -500,9 +512,9 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
       chain_task(trec, tg, number, patience, tid, sh, turn, task_x);
       if (rec_ptr<const uint16_t>(trec, DPLLM_CT(g)) != nullptr) task_at = rec_ptr<const uint16_t>(trec, DPLLM_CT(x));
       task_cols = (int)rec_u32(trec, DPLLM_CT(cols));
-      const int tasks_here = (int)rec_u32(lev, DPLLM_CL(task_count)), first = (int)rec_u32(lev, DPLLM_CL(task_first));
-      for (int t = mirror + count; t < tasks_here; t += count) {
-        const uint32_t r = load_task(first + t);
+      const int tasks_here = (int)rec_u32(lev, DPLLM_CL(task_count)), first_task = (int)rec_u32(lev, DPLLM_CL(task_first));
+      for (int t = 2 * count - 1 - number; t < tasks_here; t += count) {
+        const uint32_t r = load_task(first_task + t);
         u32x4 unused = task_x;
         chain_task(r, chain_task_g(r, wave, lane), number, patience, tid, sh, turn, unused);
       }
@@ -588,6 +600,8 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
     if (task1) tg = chain_task_g(trec, wave, lane);
     lev = lev1;
     lev1 = lev2;
+    count = count1;
+    per_count = per_count1;
   }
   // cannot be, by what chain_enrol promises; if it is, a bitwidth says so
   if (patience < 0 && lane == 0) {
@@ -602,32 +616,29 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
 // The pairs are read while thread 0 enrols the workgroup.  All three variants have the registers and the LDS of the
 // largest; one workgroup fills a compute unit either way.
 __global__ void __launch_bounds__(kLaneThreads, 2) gemv_chain_kernel(const ChainLevel* levels, const ChainJob* jobs, const SelParams* active, const SelTask* tasks,
-                                                                     uint32_t* state, int nlevels, int njobs, int patience) {
+                                                                     uint32_t* state, int nlevels, int njobs, int patience, int seats) {
   __shared__ __attribute__((aligned(256))) char lds[kChainLdsBytes];
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  int* seat = reinterpret_cast<int*>(lds + kChainLdsBytes - kSelSharedBytes);   // number, count, largest bitwidth class of every wavefront
+  int* seat = reinterpret_cast<int*>(lds + kChainLdsBytes - kSelSharedBytes);   // number, first level, count, largest bitwidth class of every wavefront
   int h = 0;
   for (int j = tid; j < njobs; j += kLaneThreads) h = max(h, *as_global(&active[j].h));
   if (tid == 0) {
-    int number, count;
-    chain_enrol(state, gridDim.x, number, count);
-    seat[0] = number;
-    seat[1] = count;
+    chain_enrol((DPLLM_GLOBAL uint32_t*)state, (int)gridDim.x, seats, nlevels, patience, seat[0], seat[1], seat[2]);
   }
   const int mine = __any(h > 6) ? 2 : __any(h > 4) ? 1 : 0;
-  if ((tid & 63) == 0) seat[2 + wave] = mine;
+  if ((tid & 63) == 0) seat[3 + wave] = mine;
   lds_barrier();
-  const int number = __builtin_amdgcn_readfirstlane(seat[0]), count = __builtin_amdgcn_readfirstlane(seat[1]);
+  const int number = __builtin_amdgcn_readfirstlane(seat[0]), first = __builtin_amdgcn_readfirstlane(seat[1]), count = __builtin_amdgcn_readfirstlane(seat[2]);
   int size = 0;
 #pragma unroll
-  for (int w = 0; w < kLaneWaves; ++w) size = max(size, seat[2 + w]);
+  for (int w = 0; w < kLaneWaves; ++w) size = max(size, seat[3 + w]);
   size = __builtin_amdgcn_readfirstlane(size);
   lds_barrier();
   if (number < 0) return;
-  if (size == 0) chain_levels<4>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
-  else if (size == 1) chain_levels<6>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
-  else chain_levels<8>(levels, jobs, active, tasks, nlevels, patience, number, count, tid, lds);
+  if (size == 0) chain_levels<4>(levels, jobs, active, tasks, (DPLLM_GLOBAL uint32_t*)state, nlevels, patience, number, first, count, tid, lds);
+  else if (size == 1) chain_levels<6>(levels, jobs, active, tasks, (DPLLM_GLOBAL uint32_t*)state, nlevels, patience, number, first, count, tid, lds);
+  else chain_levels<8>(levels, jobs, active, tasks, (DPLLM_GLOBAL uint32_t*)state, nlevels, patience, number, first, count, tid, lds);
 }
 
 }  // namespace dpllm

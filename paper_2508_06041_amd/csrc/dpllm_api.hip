@@ -126,7 +126,7 @@ struct Workspace {
   size_t sel_ws = 0, sel_ws_cap = 0;         // fp64 [cap]
   size_t gemv_jobs = 0;                      // GemvJob [n]
   size_t block_jobs = 0, block_jobs_cap = 0; // int32 [cap]
-  size_t chain_state = 0;                    // uint32 [kChainStateWords]
+  size_t chain_state = 0;                    // uint32 [kChainLevelCounts + n]
   size_t chain_levels = 0, chain_jobs = 0;   // ChainLevel [n + 1], ChainJob [n]
   size_t chain_mail = 0, chain_mail_cap = 0; // 64-bit words [cap]
   size_t total = 0;
@@ -158,6 +158,7 @@ struct dpllm_model {
   bool est_ready = false;
   int polls = kSelPolls;           // < 0: the selector tasks are left out of the launches (dpllm_debug_set_polls)
   int chain_mode = 0;              // 1: one launch wherever gemv_chain_kernel serves the step, -1: nowhere (dpllm_debug_set_one_launch)
+  int chain_seats = 0;             // of the first level of such a launch, at most (0: all)
   int launches = 0;                // kernels of the last step
   int device = 0;
 };
@@ -255,7 +256,7 @@ Workspace carve_workspace(const dpllm_model* m) {
   w.gemv_jobs = take(sizeof(GemvJob) * n);
   w.block_jobs_cap = blocks;
   w.block_jobs = take(sizeof(int32_t) * blocks);
-  w.chain_state = take(sizeof(uint32_t) * kChainStateWords);
+  w.chain_state = take(sizeof(uint32_t) * (kChainLevelCounts + n));
   w.chain_levels = take(sizeof(ChainLevel) * (n + 1));
   w.chain_jobs = take(sizeof(ChainJob) * n);
   w.chain_mail_cap = mail;
@@ -414,10 +415,11 @@ void launch_step(int groups, int blocks, hipStream_t st, const GemvJob* jobs, co
 
 void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, hipStream_t st) {
   uint32_t* state = W.at<uint32_t>(W.chain_state);
-  hipLaunchKernelGGL(chain_reset_kernel, dim3(512), dim3(256), 0, st, W.at<uint64_t>(W.sel_ws), P.chain_slots, W.at<uint64_t>(W.chain_mail), P.chain_mail, state);
+  hipLaunchKernelGGL(chain_reset_kernel, dim3(512), dim3(256), 0, st, W.at<uint64_t>(W.sel_ws), P.chain_slots, W.at<uint64_t>(W.chain_mail), P.chain_mail, state,
+                     m->h_chain_levels.size() - 1 + kChainLevelCounts);
   hipLaunchKernelGGL(gemv_chain_kernel, dim3((unsigned)P.chain_grid), dim3(kLaneThreads), 0, st, (const ChainLevel*)W.at<ChainLevel>(W.chain_levels),
                      (const ChainJob*)W.at<ChainJob>(W.chain_jobs), (const SelParams*)W.at<SelParams>(W.sel_active), (const SelTask*)W.at<SelTask>(W.sel_tasks),
-                     state, (int)m->h_chain_levels.size() - 1, (int)m->h_chain_jobs.size(), kChainPatience);
+                     state, (int)m->h_chain_levels.size() - 1, (int)m->h_chain_jobs.size(), kChainPatience, m->chain_seats);
 }
 
 // One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
@@ -1351,10 +1353,12 @@ int dpllm_debug_set_polls(dpllm_model* m, int polls) {
   return DPLLM_OK;
 }
 
-int dpllm_debug_set_one_launch(dpllm_model* m, int mode) {
+int dpllm_debug_set_one_launch(dpllm_model* m, int mode, int seats) {
   if (!m) return DPLLM_EINVAL;
   if (mode < -1 || mode > 1) return fail(m, DPLLM_EINVAL, "mode %d outside [-1,1]", mode);
+  if (seats < 0) return fail(m, DPLLM_EINVAL, "seats %d below 0", seats);
   m->chain_mode = mode;
+  m->chain_seats = seats;
   m->version++;
   return DPLLM_OK;
 }

@@ -229,6 +229,53 @@ def test_two_chains_beside_one_another(dp):
         net.model.close()
 
 
+@pytest.mark.parametrize("name,p,pairs", [("small", 4, [(3, 4)]), ("large", 6, [(5, 6), (4, 5)])])
+def test_workgroups_that_join_later(dp, name, p, pairs):
+    """However many workgroups share the first levels, the results are the same bits, eager and replayed."""
+    net = Chain(dp, SMALL if name == "small" else LARGE, 96 if name == "small" else 64, p, pairs, seed=71)
+    net.calibrate((1, 2))
+    net.put(1)
+    net.step()
+    clean = net.state()
+    net.check(name)
+    for seats in (1, 2, 7, 100, 255, 256, 1000, 0):
+        net.model.dpllm_debug_set_one_launch(1, seats)
+        for rep in range(3):
+            net.clear()
+            net.step()
+            assert all(torch.equal(a, b) for a, b in zip(net.state(), clean)), (seats, rep)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            net.step()
+        for rep in range(3):
+            net.clear()
+            graph.replay()
+            assert all(torch.equal(a, b) for a, b in zip(net.state(), clean)), (seats, rep, "replay")
+    net.model.close()
+
+
+def test_a_chain_beside_other_work(dp):
+    """Copies and matrix products on a second stream hold compute units while the step starts and while it runs."""
+    net = Chain(dp, LARGE, 64, 6, [(5, 6), (4, 5)], seed=81)
+    net.calibrate((1, 2))
+    net.put(1)
+    net.step()
+    clean = net.state()
+    a, b = torch.randn(4096, 4096, device="cuda").half(), torch.empty(1 << 27, dtype=torch.float16, device="cuda")
+    work = [lambda: torch.mm(a, a), lambda: b[:1 << 26].copy_(b[1 << 26:])]
+    side = torch.cuda.Stream()
+    for rep in range(8):
+        net.clear()
+        torch.cuda.synchronize()
+        with torch.cuda.stream(side):
+            for i in range(30):
+                work[(i // 3 if rep % 3 == 2 else rep) % 2]()
+        for _ in range(6):
+            net.step()
+        assert all(torch.equal(u, v) for u, v in zip(net.state(), clean)), rep
+    net.model.close()
+
+
 @pytest.mark.parametrize("case", ["overlap", "shared", "offset"])
 def test_steps_it_does_not_serve_run_level_by_level(dp, case):
     """A vector that spans two results, one result buffer for several linears, a vector that starts off the mailbox's words: the
