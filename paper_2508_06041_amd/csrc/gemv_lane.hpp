@@ -663,6 +663,11 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   };
   auto close_block = [&]() {
     if constexpr (NB == 8) lds_barrier();   // the tables are done with
+    if constexpr (NB == 1) {   // the wait of LaneAcc<1>::settle, once a block (7B step 503 us with and without; with settle() 492 for 490)
+      sched_fence();
+      asm volatile("s_nop 2");
+      sched_fence();
+    }
 #pragma unroll
     for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = acc.sum(b);
     acc.zero();
