@@ -49,7 +49,6 @@ constexpr int kChainMaxGroups = 4;         // blocks of 64, 32 or 16 rows
 constexpr int kChainChunk = 512;           // columns: four tiles, what a wavefront parks at a time
 constexpr int kChainGrid = 256;            // one workgroup per compute unit
 constexpr int kChainLevelJobs = 56;        // linears of a level, at most
-constexpr int kMailCopies = 1;             // of every result (chained 7B step with 1, 2, 4: 1318, 1330, 1326 us)
 constexpr uint32_t kMailEmpty = 0xffffffffu;   // the low half of a mailbox word nobody has written
 constexpr int kChainEnrolPolls = 64;       // of about a microsecond
 constexpr int kChainLevelCounts = 32;      // state words: [0] workgroups that have started, [32 + l] how many level l is dealt out to
@@ -60,7 +59,7 @@ struct ChainLevel {
   int32_t units;                           // blocks of 64 >> log_groups rows
   int32_t task_first, task_count;          // selector tasks: of this level's linears, and of the next one's whose vector is there by now
   int32_t log_groups;                      // column groups of a wavefront: 1, 2 or 4
-  int32_t pad[2];
+  int32_t unused[2];                       // (unit_start begins at lane 8)
   int32_t unit_start[kChainLevelJobs];     // first block of every linear; 0x7fffffff past the last one
 };
 static_assert(sizeof(ChainLevel) == 256, "one dword per lane");
@@ -75,8 +74,7 @@ struct alignas(64) ChainJob {
   float* e_out;
   int32_t* k_out;
   uint32_t plane_bytes;
-  int32_t x_copy;                          // 64-bit words from one copy to the next; 0: the caller's buffer, always there
-  int32_t mail_copy;
+  int32_t x_handed;                        // x lies in a mailbox; 0: the caller's buffer, always there
   int32_t out, ncw, ncc;
   int32_t slot_rows, nchunks;
   uint32_t lut_off[kKMax];
@@ -244,19 +242,19 @@ __device__ __forceinline__ sel_u32x4 chain_task_g(uint32_t rec, int wave, int la
     v = __builtin_nontemporal_load((const DPLLM_SEL_GLOBAL sel_u32x4*)(g + min(wave * kSelChunkStep + lane * 8, cols - 8)));
   return v;
 }
-__device__ __forceinline__ void chain_task(uint32_t rec, sel_u32x4 g, int number, int& patience, int tid, double* sh, int& turn, u32x4& v) {
+__device__ __forceinline__ void chain_task(uint32_t rec, sel_u32x4 g, int& patience, int tid, double* sh, int& turn, u32x4& v) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint16_t* gp = rec_ptr<const uint16_t>(rec, DPLLM_CT(g));
   if (gp == nullptr) return;
   const uint16_t* xp = rec_ptr<const uint16_t>(rec, DPLLM_CT(x));
-  const int cols = (int)rec_u32(rec, DPLLM_CT(cols)), copy = (int)rec_u32(rec, DPLLM_CT(x_copy));
+  const int cols = (int)rec_u32(rec, DPLLM_CT(cols)), handed = (int)rec_u32(rec, DPLLM_CT(x_handed));
   double acc = 0.0;
   if (wave * kSelChunkStep < cols) {
-    const DPLLM_GLOBAL uint64_t* x = as_global(reinterpret_cast<const uint64_t*>(xp)) + (size_t)(number & (kMailCopies - 1)) * copy;
+    const DPLLM_GLOBAL uint64_t* x = as_global(reinterpret_cast<const uint64_t*>(xp));
     const int c = wave * kSelChunkStep + lane * 8;
     for (;;) {
       v = chain_load_x(x, c, cols);
-      if (copy == 0 || __all(chain_here(v)) || --patience < 0) break;
+      if (handed == 0 || __all(chain_here(v)) || --patience < 0) break;
       __builtin_amdgcn_s_sleep(1);
     }
     const sel_u32x4 xv = v, gv = gp == xp ? xv : g;
@@ -302,14 +300,12 @@ __device__ __forceinline__ void chain_store(uint32_t rec, int block, int buffer,
   const bool inside = row < (int)rec_u32(rec, DPLLM_CJ(out));
   uint64_t* mail = rec_ptr<uint64_t>(rec, DPLLM_CJ(mail));
   if (mail != nullptr) {
-    // lane rows i + 4 q + j stores rows 4 q .. + 3 in copy 4 i + j
-    static_assert(kMailCopies <= 4, "a lane to a copy");
+    // lane 4 q stores rows 4 q .. + 3
     const int v = !inside ? 0 : bits == 0xffffu ? 0xfe00 : (int)bits;
     const uint32_t r0 = (uint32_t)__builtin_amdgcn_update_dpp(0, v, 0x00, 0xf, 0xf, true), r1 = (uint32_t)__builtin_amdgcn_update_dpp(0, v, 0x55, 0xf, 0xf, true);
     const uint32_t r2 = (uint32_t)__builtin_amdgcn_update_dpp(0, v, 0xaa, 0xf, 0xf, true), r3 = (uint32_t)__builtin_amdgcn_update_dpp(0, v, 0xff, 0xf, 0xf, true);
-    const int copy = (lane / rows) * 4 + (lane & 3);
-    if (copy < kMailCopies)
-      __hip_atomic_store(as_global(mail) + (size_t)copy * rec_u32(rec, DPLLM_CJ(mail_copy)) + row / 4,
+    if (lane < rows && (lane & 3) == 0)
+      __hip_atomic_store(as_global(mail) + row / 4,
                          (uint64_t)(r2 | r3 << 16) << 32 | (r0 | r1 << 16), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   if (lane < rows && inside) as_global(rec_ptr<uint16_t>(rec, DPLLM_CJ(y)))[row] = (uint16_t)bits;
@@ -509,14 +505,14 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
     const uint16_t* task_at = nullptr;
     int task_cols = 0;
     if (task_here) {
-      chain_task(trec, tg, number, patience, tid, sh, turn, task_x);
+      chain_task(trec, tg, patience, tid, sh, turn, task_x);
       if (rec_ptr<const uint16_t>(trec, DPLLM_CT(g)) != nullptr) task_at = rec_ptr<const uint16_t>(trec, DPLLM_CT(x));
       task_cols = (int)rec_u32(trec, DPLLM_CT(cols));
       const int tasks_here = (int)rec_u32(lev, DPLLM_CL(task_count)), first_task = (int)rec_u32(lev, DPLLM_CL(task_first));
       for (int t = 2 * count - 1 - number; t < tasks_here; t += count) {
         const uint32_t r = load_task(first_task + t);
         u32x4 unused = task_x;
-        chain_task(r, chain_task_g(r, wave, lane), number, patience, tid, sh, turn, unused);
+        chain_task(r, chain_task_g(r, wave, lane), patience, tid, sh, turn, unused);
       }
     }
     const int lg = (int)rec_u32(lev, DPLLM_CL(log_groups)), lg1 = (int)rec_u32(lev1, DPLLM_CL(log_groups));
@@ -525,9 +521,9 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
       const int blocks = min(u1, end) - u;
       // a look at the vector and at the products of the selector, the tables of both bitwidths
       const int lo = (int)rec_u32(rec, DPLLM_CP(l)), hi = (int)rec_u32(rec, DPLLM_CP(h)), row = block * (64 >> lg) + (lane & ((64 >> lg) - 1));
-      const int x_copy = (int)rec_u32(rec, DPLLM_CJ(x_copy)), in = (int)rec_u32(rec, DPLLM_CJ(ncw)) * 32;
+      const int x_handed = (int)rec_u32(rec, DPLLM_CJ(x_handed)), in = (int)rec_u32(rec, DPLLM_CJ(ncw)) * 32;
       const uint16_t* xp = rec_ptr<const uint16_t>(rec, DPLLM_CJ(x));
-      const DPLLM_GLOBAL uint64_t* xw = as_global(reinterpret_cast<const uint64_t*>(xp)) + (size_t)(number & (kMailCopies - 1)) * x_copy;
+      const DPLLM_GLOBAL uint64_t* xw = as_global(reinterpret_cast<const uint64_t*>(xp));
       const int c = c0 * kChainChunk + lane * 8;
       const u32x4 x_look = chain_load_x(xw, c, in);
       const ChainSlots slots = chain_slots(rec, number);
@@ -541,15 +537,15 @@ __device__ __forceinline__ void chain_levels(const ChainLevel* levels, const Cha
       // the vector
       const bool have_x = c0 >= c1 || (xp == task_at && task_cols == in && c0 == wave && c1 == wave + 1);
       u32x4 x = have_x ? task_x : x_look;
-      if (!have_x && (c1 - c0 > 1 || (x_copy != 0 && !__all(chain_here(x))))) {
+      if (!have_x && (c1 - c0 > 1 || (x_handed != 0 && !__all(chain_here(x))))) {
         for (;;) {
           x = chain_load_x(xw, c, in);
           bool here = chain_here(x);
-          for (int sc = c0 + 1; sc < c1 && x_copy != 0; sc += 2) {
+          for (int sc = c0 + 1; sc < c1 && x_handed != 0; sc += 2) {
             const u32x4 p = chain_load_x(xw, c + (sc - c0) * kChainChunk, in), q = chain_load_x(xw, c + (min(sc + 1, c1 - 1) - c0) * kChainChunk, in);
             here = here && chain_here(p) && chain_here(q);
           }
-          if (x_copy == 0 || __all(here) || --patience < 0) break;
+          if (x_handed == 0 || __all(here) || --patience < 0) break;
           __builtin_amdgcn_s_sleep(1);
         }
       }

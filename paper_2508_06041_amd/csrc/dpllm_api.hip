@@ -218,7 +218,7 @@ size_t est_slots_of(const Linear& lin, int rowgroups) {
   return (size_t)std::min(rowgroups * kSelPartRows, kEstMaxRank) * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
 }
 
-// 64-bit words of one copy of a linear's mailbox (whole lines: no two linears share one)
+// 64-bit words of a linear's mailbox (whole lines: no two linears share one)
 size_t mail_words(const LinearLayout& L) { return align_up((size_t)L.rows_padded * 2, kAlign) / 8; }
 
 // Sized for any launch plan over the linears as they stand (shapes, pairs): the caps are upper bounds.
@@ -229,7 +229,7 @@ Workspace carve_workspace(const dpllm_model* m) {
   for (const Linear& lin : m->linears) {
     if (!lin.loaded) continue;
     if (lin.max_rowgroups() > 0) est = std::max(est, est_slots_of(lin, lin.max_rowgroups()));
-    mail += mail_words(lin.L) * kMailCopies;
+    mail += mail_words(lin.L);
     const size_t rg = (size_t)std::max(1, lin.max_rowgroups());
     parts += rg * kSelMaxChunks + 1;
     slots += rg * kSelPartRows * std::max(kSelMaxChunks, kSelCopies * sel_slices(lin.L.in));
@@ -564,7 +564,7 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
   size_t mail = 0;
   for (int j = 0; j < n; ++j) {
     mail_at[j] = mail;
-    mail += mail_words(m->linears[j].L) * kMailCopies;
+    mail += mail_words(m->linears[j].L);
   }
   if (mail > W.chain_mail_cap) return false;
   std::vector<ChainLevel>& lv = m->h_chain_levels;
@@ -589,7 +589,7 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
     ChainJob& c = jobs[j];
     c.arena = lin.arena;
     c.x = from < 0 ? (const uint16_t*)xs[j] : place(from, xs[j]);
-    c.x_copy = from < 0 ? 0 : (int)mail_words(m->linears[from].L);
+    c.x_handed = from >= 0;
     if (from >= 0) read[from] = 1;
     c.y = (uint16_t*)ys[j];
     c.e_out = P.e_dev + j;
@@ -607,7 +607,7 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
     SelFinish f{};
     f.e_out = c.e_out; f.k_out = c.k_out;
     f.x = sel_from < 0 ? (const uint16_t*)sx : place(sel_from, sx);
-    f.x_copy = sel_from < 0 ? 0 : (int)mail_words(m->linears[sel_from].L);
+    f.x_handed = sel_from >= 0;
     if (sel_from >= 0) read[sel_from] = 1;
     f.in = lin.L.in; f.linear = j; f.copies = kSelCopies; f.squares = linreg;
     const int slices = sel_slices(lin.L.in);
@@ -655,10 +655,7 @@ bool plan_chain(dpllm_model* m, const void* const* xs, void* const* ys, const st
     }
   }
   int grid = 1;
-  for (int j = 0; j < n; ++j) {
-    jobs[j].mail = read[j] ? W.at<uint64_t>(W.chain_mail) + mail_at[j] : nullptr;
-    jobs[j].mail_copy = (int)mail_words(m->linears[j].L);
-  }
+  for (int j = 0; j < n; ++j) jobs[j].mail = read[j] ? W.at<uint64_t>(W.chain_mail) + mail_at[j] : nullptr;
   for (const ChainLevel& l : lv) grid = std::max(grid, std::max(l.units, 0) + l.task_count);
   P.chain_grid = std::min(grid, kChainGrid);
   P.chain_slots = slots;

@@ -67,7 +67,7 @@ __global__ void __launch_bounds__(256) selector_activate_kernel(const SelParams*
       k.slot = (uint64_t*)f.ws + (size_t)c * f.ws_rows + row;
       k.copy_stride = f.nchunks * f.ws_rows;
       k.cols = min(f.chunk_cols, f.in - col0);
-      k.x_copy = f.x_copy;
+      k.x_handed = f.x_handed;
       tasks[f.task_first + t] = k;
     }
   }

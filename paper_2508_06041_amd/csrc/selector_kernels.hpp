@@ -189,7 +189,7 @@ struct SelFinish {
   int32_t in, linear, nchunks, ws_rows, chunk_cols;   // chunk c: columns [chunk_cols c, + chunk_cols) inside the row
   int32_t copies;      // of the slots, [copy][chunk][row] (1 or kSelCopies)
   int32_t task_first, task_rows;   // the selector's tasks: entries of the table from task_first on, [row][chunk] (0 rows: none)
-  int32_t x_copy;      // SelTask::x_copy of them
+  int32_t x_handed;    // SelTask::x_handed of them
   int32_t squares;     // linear regression: row 0 of the tasks adds up x^2
 };
 __host__ __device__ inline SelFinish sel_finish_of(const SelJob& j) {
@@ -350,7 +350,7 @@ struct alignas(64) SelTask {
   uint64_t* slot;      // where the partial dot product goes, kSelCopies times,
   int32_t copy_stride; //   slots apart
   int32_t cols;        // length of the slice
-  int32_t x_copy;      // gemv_chain_kernel only: x lies in a mailbox whose copies are this many 64-bit words apart; 0: it does not
+  int32_t x_handed;    // gemv_chain_kernel only: x lies in a mailbox
 };
 // Records that no kernel of the launch writes, read at an address that is the same for the whole workgroup: from the
 // constant address space they come with one scalar load (through a generic pointer every field is a vector load of its
