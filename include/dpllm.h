@@ -192,6 +192,10 @@ int dpllm_gemv(dpllm_model* m, int id, int k, const int32_t* k_dev, const void* 
  * A graph that holds captured steps reads these tables when it is replayed: it follows later changes of
  * thresholds, pairs in use, target entries and the target (that is the point of keeping them on the device),
  * and it must not be replayed after a call that rebuilt the launch plan for other pointers or shapes.
+ * Many small linears that depend on one another run as one launch whose workgroups wait for each other's results.
+ * They wait for workgroups that are running only, so the waits end whatever else the GPU does; they are bounded all the
+ * same (some seconds a step).  Should one end at its bound, k_dev[0] is -1 after the step and everything else the step
+ * wrote is undefined; the call itself, which only enqueues, has returned OK.
  * Errors: EINVAL, ESTATE, ESHAPE, EHIP. */
 int dpllm_decode_step(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* k_dev,
                       float* e_dev, void* stream);
