@@ -133,9 +133,7 @@ struct LaneAcc<1> {
   float v[4];
   __device__ __forceinline__ void zero() { v[0] = v[1] = v[2] = v[3] = 0.f; }
   // between a step and sum(): a dot product's result may be read by another kind of vector instruction three wait states later;
-  // the compiler keeps that distance behind instructions it knows, not behind inline asm.  Right behind the step it costs nothing;
-  // in front of the sum, inside the loop, it kept the next step's first reads behind the sum: 2500 x 6688 k = 7, 8 calls, 74.5 us
-  // without a wait, 75.1 there, 74.5 here; 4096 x 4096 k = 4, 16 calls, 81.2, 80.1 and 80.9; 4096 x 11008 k = 2 56.3, 55.8, 55.4.
+  // the compiler keeps that distance behind instructions it knows, not behind inline asm
   __device__ __forceinline__ void settle() { asm("s_nop 2" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])); }
   __device__ __forceinline__ float sum(int) const { return (v[0] + v[1]) + (v[2] + v[3]); }
 };
@@ -846,6 +844,11 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   LaneAcc<NB> acc;
   acc.zero();
   float done[NB];   // the sums before the last step, where lanes may be without a tile
+  // The wait between a step's last dot product and the sum (LaneAcc<1>::settle) stands in front of the sum, at k = 7 behind the step.  us of
+  // a loop of calls without a wait / in front / behind: 2500 x 6688 k = 7 74.4 / 75.0 / 74.5; 4096 x 4096 k = 4 81.2 / 80.2 / 81.0, k = 3 72.6 /
+  // 71.9 / 72.5, k = 8 61.6 / 61.4 / 61.6; 4096 x 11008 k = 4 68.1 / 67.0 / 67.6, k = 2 56.2 / 55.8 / 55.5; 2500 x 6688 k = 5 61.5 / 61.5 / 61.0.
+  // (Behind at every k >= 5 costs k = 3 and 4 what they gain here: how the code of one bitwidth lies moves the others by a per cent.)
+  constexpr bool kSettleBehind = K == 7;
 #pragma unroll
   for (int b = 0; b < NB; ++b) done[b] = 0.f;
   LaneMasks<K> M;
@@ -862,11 +865,12 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 #pragma unroll
         for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[s].x[b], inside(cc), lane, ready + b * G * kLaneGroupStride);
       }
+      if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
       for (int b = 0; b < NB; ++b) done[b] = acc.sum(b);
       lane_compute<K, NB, G>(ring[s].w, lanecol, lds, ready + xlane, acc, addr, mask, M, job.ncw - (cc * G + group) * 4,
                              (cc + 1) * G * 4 > job.ncw);
-      acc.settle();
+      if constexpr (kSettleBehind) acc.settle();
       if (++cc >= c1) break;
       narrow_load_x<K, NB, G>(ring[s], job, cc + D - 1, lane);
       narrow_load_planes<K, NB, G>(ring[s], job, plane_rows, (cc + D - 1) * G + group, cc + D - 1 < c1);
@@ -875,6 +879,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   // the last step may have fewer than G tiles: a lane without one (it decoded another tile) drops what it added there
   const bool whole = (c1 - 1) * G + group < job.ncc;
   if constexpr (NB == 8) lds_barrier();   // the tables, which the sums take the place of, are done with
+  if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
   for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
   lds_barrier();
