@@ -8,11 +8,14 @@
 // bitwidths stand before the decision falls; and the rows of a level are dealt out in blocks of 64, 32 or 16, whichever ends
 // first.  Measured inside (7B, k = 3 / 4, us after the last result of the level before): that result seen 1.2, products of the
 // selector stored 1.9, seen and decided 3.5, first tile decoded 5; a level ends at 5 (o), 10 (q, k, v; down) and 16 (gate, up).
-// us a step, a launch per level -> now: 7B, 32 blocks 1470 -> 1295, 24 blocks at 5 and 6 bits 1483 -> 1300; 8B, 16 blocks with
-// most selectors a level early 945 -> 820.  What is left is decode at two wavefronts per SIMD (an instruction in five cycles,
-// and 30 % of them are not decode) and the chain in front of it.
-// Not served (plan_chain): few levels, whose start (number, list, first records: 8 us) weighs more, and large levels, which the
-// streaming kernel decodes with twice the wavefronts.
+// us a step, a launch per level -> now, eager and in a graph: 7B, 32 blocks at 3 and 4 bits 1419 -> 1281 and 1420 -> 1283, with most
+// selectors a level early 1381 -> 1206 and 1380 -> 1205, at 5 and 6 bits 1987 -> 1696 and 1989 -> 1700; 8B, 16 blocks at 5 and 6 bits,
+// selectors early, 969 -> 842 and 970 -> 845.  Where 0.53 of the linears run at 4 bits and their weights are quantised Gaussians (bench.py's
+// workload, in a graph) 1318 -> 1304, selectors early 1247 -> 1167, none 1060 -> 905: what a level waits for its selector is not less than
+// with a launch per level, but weighs more.  What is left is that wait, and decode at two wavefronts per SIMD (an instruction in five
+// cycles).
+// Not served (chain_pays, plan_chain): few levels, whose start (number, first records: 8 us) weighs more; large levels, which the
+// streaming kernel decodes with twice the wavefronts; columns that eight wavefronts cannot share evenly in chunks; high ranks.
 // Tried and taken back: two workgroups per compute unit with 128 registers (spills; 1790 us), planes asked for two blocks
 // ahead of tables that are built between two barriers (1560), table rows of the next level asked for before its tasks (no
 // change), more copies of the results (no change), longer and shorter pauses between polls (no change).
@@ -45,7 +48,6 @@
 
 namespace dpllm {
 
-constexpr int kChainMaxGroups = 4;         // blocks of 64, 32 or 16 rows
 constexpr int kChainChunk = 512;           // columns: four tiles, what a wavefront parks at a time
 constexpr int kChainGrid = 256;            // one workgroup per compute unit
 constexpr int kChainLevelJobs = 56;        // linears of a level, at most

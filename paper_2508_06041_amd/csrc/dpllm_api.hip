@@ -514,7 +514,8 @@ int upload_params(dpllm_model* m, hipStream_t st) {
 //     418 / 447; 4608, 12288 (1.6) 441 / 463 and 690 / 781; 5120, 13824 (1.5) 454 / 530 and 746 / 976; 2560, 6912 (1.5) 287 / 275 and 394 /
 //     393; 1024, 2816 202 / 203 and 266 / 280; 2048, 16384 302 / 323 and 453 / 516.
 //   selectors: a task (row of G times 4096 columns) to a workgroup and level, on average.  4096, 11008 at rank 96 (0.84 of that) 375 / 366, 128
-//     (1.1) 374 / 388, 256 399 / 439, 1024 612 / 786; 4096, 14336 at 96 (0.94) 286 / 287 and 454 / 456.
+//     (1.1) 374 / 388, 256 399 / 439, 1024 612 / 786; 4096, 14336 at 96 (0.94) 385 / 384,
+//     and 489 / 465 at 5 and 6 bits with selectors a level early; 4096, 4096 at 144 (0.98) 312 / 315, and 383 / 376 at 5 and 6 bits.
 constexpr int kChainMinLevels = 24;
 constexpr double kChainLevelWeights = 64e6, kChainUneven = 1.2;
 bool chain_pays(const dpllm_model* m, int levels) {

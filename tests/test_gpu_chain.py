@@ -346,7 +346,7 @@ def test_infinities_and_nan_travel_through_mailboxes(dp, values):
     net.model.close()
 
 
-def _big(dp, shapes, p, pairs, seed):
+def _big(dp, shapes, p, pairs, seed, rank=16):
     """One linear per shape, each fed by the one before, with random planes made on the device."""
     g = torch.Generator(device="cuda").manual_seed(seed)
     model, lin = dp.Model(len(shapes)), []
@@ -354,7 +354,7 @@ def _big(dp, shapes, p, pairs, seed):
         planes = torch.randint(-2 ** 31, 2 ** 31, (p, out, in_ // 32), dtype=torch.int32, device="cuda", generator=g)
         luts = {k: (torch.randn(out, 1 << k, device="cuda", generator=g) / math.sqrt(in_)).half() for k in range(3, p + 1)}
         model.dpllm_load_linear(i, planes, luts, 3)
-        Gs = [(torch.randn(16, in_, device="cuda", generator=g) * 0.1 / math.sqrt(in_)).half() for _ in pairs]
+        Gs = [(torch.randn(rank, in_, device="cuda", generator=g) * 0.1 / math.sqrt(in_)).half() for _ in pairs]
         for (l, h), G in zip(pairs, Gs):
             model.dpllm_set_selector(i, l, h, dp.DPLLM_SEL_PROJ, G=G, T=0.0)
         keep = i in (0, len(shapes) - 1)             # what the oracle is asked about
@@ -418,4 +418,24 @@ def test_a_captured_step_follows_the_pair_in_use(dp, shapes, chained, one):
                 graph.replay()
                 torch.cuda.synchronize()
                 assert all(torch.equal(a, b) for a, b in zip([k, e] + ys, want[pair])), (captured, pair, rep)
+    model.close()
+
+
+# either side of the lines of the rule: levels, columns that eight wavefronts share evenly or not, rows of G per level, weights
+@pytest.mark.parametrize("shapes,rank,one", [([(4096, 4096)] * 24, 64, True), ([(4096, 4096)] * 23, 64, False), ([(4096, 4096)] * 24, 256, True),
+                                             ([(4096, 4096)] * 24, 272, False), ([(3584, 3584)] * 24, 16, True), ([(3072, 3072)] * 24, 16, False),
+                                             ([(5120, 5120)] * 24, 16, False), ([(8192, 7680)] + [(8192, 8192)] * 23, 16, False)])
+def test_which_steps_are_one_launch(dp, shapes, rank, one):
+    model, _ = _big(dp, shapes, 3, [(3, 3)], seed=91, rank=rank)
+    ys = [torch.zeros(out, dtype=torch.float16, device="cuda") for out, _ in shapes]
+    xs = [synth.make_x(shapes[0][1], 1, seed=92)[0].cuda()] + ys[:-1]
+    k, e = torch.zeros(len(shapes), dtype=torch.int32, device="cuda"), torch.zeros(len(shapes), dtype=torch.float32, device="cuda")
+    model.dpllm_decode_step(xs, ys, k, e)
+    torch.cuda.synchronize()
+    assert (model.dpllm_debug_step_launches() == 2) == one and k.tolist() == [3] * len(shapes)
+    first = [t.clone() for t in ys]
+    for i in range(len(shapes)):                     # linear by linear
+        model.dpllm_gemv(i, 3, xs[i], y=ys[i])
+    for i, (a, b) in enumerate(zip(ys, first)):
+        assert (a.double() - b.double()).norm() <= 2e-2 * a.double().norm() > 0, i
     model.close()
