@@ -221,7 +221,7 @@ int dpllm_debug_locate(int out, int in, int p, int kmin, int plane, int row, int
 
 /* Parity aid: how often a workgroup of a step looks for products of its linear's selector that other workgroups of the
  * launch deliver, before it computes them all itself (64 looks of about a microsecond unless set; dpllm_estimate then
- * looks 65536 times).  0: it looks once; -1: it looks once and, in a step, nobody delivers any.  The results are the same bits.  (A step that is one launch in all does not
+ * looks a million times).  0: it looks once; -1: it looks once and, in a step, nobody delivers any.  The results are the same bits.  (A step that is one launch in all does not
  * ask: see dpllm_debug_set_one_launch.)  Errors: EINVAL. */
 int dpllm_debug_set_polls(dpllm_model* m, int polls);
 

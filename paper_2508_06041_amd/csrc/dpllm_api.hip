@@ -116,7 +116,7 @@ struct Workspace {
   size_t bytes = 0;
   size_t est_ws = 0;                         // dpllm_estimate in two launches: kSelOneSlots fp64
   size_t est_slots = 0, est_slots_cap = 0;   // dpllm_estimate in one: uint64 [kEstRing][cap][2], empty between calls,
-  size_t est_marks = 0;                      //   and uint32 [kEstRing]: slots that are not relied on any more
+  size_t est_marks = 0;                      //   and uint32 [kEstRing]: the captured call that does not rely on its slots any more
   size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
   size_t sel_active = 0;                     // SelParams [n]: the row of the active target
@@ -1185,13 +1185,13 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
     if (!capturing(st) && passed(m->ws_event)) m->est_ready = true;
     if (!m->est_ready && st != m->ws_stream) return false;
   }
-  if (sel.kind == DPLLM_SEL_PROJ && ++m->est_turn == 0) m->est_turn = 1;   // (0: an empty slot)
+  if (sel.kind == DPLLM_SEL_PROJ && (++m->est_turn == kEstAll || m->est_turn == 0)) m->est_turn = 1;   // (0: an empty slot)
   const unsigned set = m->est_turn % kEstRing;
   const int polls = m->polls == kSelPolls ? kEstPolls : std::max(m->polls, 0);
   const int parts = sel.kind == DPLLM_SEL_PROJ ? (sel.r + kEstPartRows - 1) / kEstPartRows * j.nchunks : 1;
   hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, j.x,
                      W.at<uint64_t>(W.est_slots) + set * W.est_slots_cap * 2, j.in, sel.r, j.nchunks, j.chunk_cols, j.ws_rows, sel.kind, m->est_turn, j,
-                     make_params(sel, sel.T), W.at<uint32_t>(W.est_marks) + set, polls);
+                     make_params(sel, sel.T), sel.kind == DPLLM_SEL_PROJ && capturing(st) ? W.at<uint32_t>(W.est_marks) + set : nullptr, polls);
   return true;
 }
 

@@ -581,24 +581,28 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
 // what another call has left is never taken.  Who has collected a product empties its words again, for a graph that replays the
 // call under the same number.  Workgroups start in order, and no more than one per launch ever waits, so those it waits for find a
 // place whatever else the chip is doing: the wait ends.  Nothing rests on that: it is bounded, and who gives up computes all
-// products itself, with the same bits, and marks the set of slots as distrusted, because what it gave up on may still come; whoever
-// finds the mark computes for itself too.  (A wait is given up where calls of one model overlap, which the header rules out: their
-// products overwrite one another.)  Launches take turns in kEstRing sets of slots.
+// products itself, with the same bits.  What it gave up on may still come and stay; that matters to a replay of the same captured
+// call only, which has its number again: a captured call that gives up leaves its number in the mark of the set of slots, and who
+// finds its own there (or that several calls have given up) computes for itself too.  (A wait is given up where calls of one model
+// overlap, which the header rules out: their products overwrite one another.)  Launches take turns in kEstRing sets of slots.
 // What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection.
 // us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> now: rank 64 of 4096 columns
-// 4.5 / 7.4 -> 4.5 / 4.9, of 11008 5.3 / 7.6 -> 5.1 / 5.0, rank 256 of 4096 5.2 / 7.5 -> 5.2 / 4.9, of 11008 7.2 / 7.7 -> 7.2 / 7.7, linear
-// regression 3.7 / 7.5 -> 2.0 / 4.9 (eager: the host takes 4.2 for a call); beyond rank 256 two launches are as fast.  14 linears of 7B
-// with a GEMV each: 189 -> 175 (169 with products of one word, which what an overlap left behind could pass for).
+// 4.5 / 7.4 -> 4.5 / 4.8, of 11008 5.3 / 7.6 -> 5.2 / 5.0, rank 128 of 11008 5.6 / 7.3 -> 5.3 / 5.8, rank 256 of 4096 5.2 / 7.5 -> 5.1 / 4.8, linear
+// regression 3.7 / 7.5 -> 2.0 / 4.9 (eager: the host takes 4.2 for a call).  With more rows the second launch is gained back: rank 256 of
+// 11008 7.1 .. 8.0 / 7.5 .. 8.4 (by where the memory lies) and 8.0 / 7.5, rank 512 of 8192 8.7 / 9.1 and 8.8 / 9.0; beyond the lanes of the
+// workgroup that collects there are two.  14 linears of 7B with a GEMV each: 190 -> 169 (161 with products of one word, which what an
+// overlap left behind could pass for).
 constexpr int kEstRing = 16;
 constexpr int kEstRows = 1;             // rows of G of a wavefront
 constexpr int kEstPartRows = kSelPartWaves * kEstRows;
 constexpr int kEstMaxRank = kSelPartThreads;
-constexpr int kEstPolls = 1 << 16;      // of about a microsecond
+constexpr int kEstPolls = 1 << 20;      // of about a microsecond
+constexpr uint32_t kEstAll = ~0u;       // a mark: several captured calls have given up
 
 // Row t of the products, the sum of its chunks in order; BATCH chunks are asked for at a time.  A chunk's slots are the lower halves
 // of its rows, then the upper ones.  false: given up, or the slots are not relied on.
 template <int BATCH>
-__device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, uint32_t tag, int nchunks, int ws_rows, int t, uint32_t marked, int polls, double& g) {
+__device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, uint32_t tag, int nchunks, int ws_rows, int t, bool marked, int polls, double& g) {
   g = 0.0;
   for (int c0 = 0; c0 < nchunks; c0 += BATCH) {
     uint64_t lo[BATCH], hi[BATCH];
@@ -613,7 +617,7 @@ __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slot
 #pragma unroll
       for (int i = 0; i < BATCH; ++i) all = all && (uint32_t)(lo[i] >> 32) == tag && (uint32_t)(hi[i] >> 32) == tag;
       if (__all(all)) break;
-      if (marked != 0 || --polls < 0) return false;
+      if (marked || --polls < 0) return false;
       __builtin_amdgcn_s_sleep(1);
     }
 #pragma unroll
@@ -625,14 +629,14 @@ __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slot
       __hip_atomic_store(slot + ws_rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
-  return marked == 0;
+  return !marked;
 }
 
 // G .. kind: what a workgroup needs to ask for its first rows comes as plain arguments (see gemv_lane_kernel)
-// distrust: the word of the set of slots
+// mark_of: the mark of the set of slots; nullptr: the call is not captured
 __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, uint64_t* ws, int in, int r,
                                                                            int nchunks, int chunk_cols, int ws_rows, int kind, uint32_t tag, SelJob job,
-                                                                           SelParams P, uint32_t* distrust, int polls) {
+                                                                           SelParams P, uint32_t* mark_of, int polls) {
   __shared__ SelShared sh;
   __shared__ int here[kSelPartWaves];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
@@ -642,7 +646,7 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
   if (kind == 1) {
     static_assert(kEstRows == 1 && kEstMaxRank <= kSelPartThreads, "a product a wavefront, a row a lane");
     DPLLM_SEL_GLOBAL uint64_t* slots = (DPLLM_SEL_GLOBAL uint64_t*)ws;
-    DPLLM_SEL_GLOBAL uint32_t* mark = (DPLLM_SEL_GLOBAL uint32_t*)distrust;
+    DPLLM_SEL_GLOBAL uint32_t* mark = (DPLLM_SEL_GLOBAL uint32_t*)mark_of;
     const int rg = blockIdx.x / nchunks, ch = blockIdx.x - rg * nchunks, row = rg * kEstPartRows + wave;
     double g[1];
     selector_part_products<true>(job, P, row, ch, wave, lane, g);
@@ -653,7 +657,8 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
       __hip_atomic_store(slot + ws_rows, (uint64_t)tag << 32 | v >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (blockIdx.x + 1 != gridDim.x) return;
-    const uint32_t marked = __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t found = mark_of != nullptr ? __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    const bool marked = found == tag || found == kEstAll;
     bool all = true;
     if (wave * 64 < r) {
       all = nchunks <= 8 ? selector_collect<8>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0])
@@ -665,7 +670,11 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     if (!(here[0] && here[1] && here[2] && here[3])) {
       static_assert(kSelPartWaves == 4, "flags");
       __syncthreads();
-      if (tid == 0) __hip_atomic_store(mark, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (tid == 0 && mark_of != nullptr) {
+        uint32_t was = 0u;
+        if (!__hip_atomic_compare_exchange_strong(mark, &was, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && was != tag)
+          __hip_atomic_store(mark, kEstAll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
       for (int t = wave; t < r; t += kSelPartWaves) {
         double sum = 0.0;
         for (int c = 0; c < nchunks; ++c) {

@@ -133,7 +133,7 @@ def test_one_launch_and_two_leave_the_same_bits(dp, in_, r):
     model.close()
 
 
-@pytest.mark.parametrize("in_,r", [(32, 1), (4096, 64), (11008, 65), (16416, 130), (2080, 256)])
+@pytest.mark.parametrize("in_,r", [(32, 1), (4096, 64), (11008, 65), (16416, 130), (2080, 256), (11008, 256)])
 def test_products_left_behind_do_no_harm(dp, in_, r):
     """Calls that give up their wait at once leave products behind in every set of slots (and, captured, under the number a replay
     has again); they and the calls that follow leave the bits of two launches."""
