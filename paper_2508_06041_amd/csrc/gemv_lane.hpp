@@ -9,10 +9,10 @@
 // interleaved in LDS (entry e of row l at byte e * 256 + l * 4), so lane l only ever touches bank l mod 32 and
 // lookups are free of bank conflicts whatever the table size; the two-weight tables of k = 3 and k = 4, which
 // cost 4 - 6 LDS cycles per lookup when a whole wavefront shares one row's table, cost 2.
-// The activations are the same for all lanes.  With every tile a lane fetches one dword of them (256 bytes per
+// The activations are the same for all lanes.
+// One right-hand side (the decode step): with every tile a lane fetches one dword of them (256 bytes per
 // wavefront); before the tile is decoded the wavefront parks them in a private LDS slot.  A wavefront with at
-// most four tiles per row block (rows up to 4096 columns) parks them once for its whole run instead.
-// One right-hand side (the decode step): every lane reads back 16 bytes per word (lane l takes the pairs
+// most four tiles per row block (rows up to 4096 columns) parks them once for its whole run instead.  Every lane reads back 16 bytes per word (lane l takes the pairs
 // 4 (l mod 4) .. + 3) and the multiply-add v_dot2c_f32_f16 reads the pair it needs from the right lane of its quad
 // with a DPP quad broadcast: 16 registers hold the 64 pairs of a tile, fp32 accumulation in the lane.
 // Several right-hand sides (a small dense contraction: 64 rows x up to 4 samples per wavefront) run on the matrix
@@ -22,8 +22,12 @@
 // (Five to eight right-hand sides: two matrix instructions per looked-up chunk, each with its four samples.)
 // B = four looked-up weights of the lane's own row; A = the four activations that go with them, held by the
 // lanes of quad Q: lane 4 Q + i holds sample i's chunk, acc[i] is sample i's sum.  Quad Q of the wavefront holds
-// chunks Q and 16 + Q of the tile's 32 chunks of four activations, so 4 registers carry a tile's activations and
-// every lookup serves four (eight) samples: up to eight right-hand sides share a pass over the planes.
+// two of the tile's 32 chunks of four activations (LaneRawX says which), so 4 registers carry a tile's activations and
+// every lookup serves four (eight) samples: up to eight right-hand sides share a pass over the planes.  They are loaded with the
+// tile in that form.  (Parked in LDS sample by sample and read back, as one right-hand side is, they cost a tile of four samples
+// four LDS writes and two reads per lane, at k = 4 two reads, a write and a wait for each sample more.  us per call, parked -> loaded:
+// 14336 x 4096 B = 4, k = 6 15.6 -> 14.5, B = 2, k = 3 7.9 -> 7.4, B = 8, k = 3 10.4 -> 8.7; 20000 x 4096 B = 3, k = 4 15.7 -> 13.5; 4096 x
+// 14336 B = 8, k = 3 11.8 -> 11.5.)
 // Each lane accumulates its own row: no cross-lane reduction.  A workgroup is eight wavefronts that split the
 // columns of the same 64 rows and share the tables; their eight partial sums per row meet in LDS.
 //
@@ -75,17 +79,17 @@ static_assert(LaneDecode<2>::table_bytes <= kLaneTableBytes && LaneDecode<3>::ta
 // G column groups per wavefront (see below); bytes from one group's parked activations to the next: 64 more than a
 // tile's 256, so that the groups' reads of the same word fall on different banks
 constexpr int kLaneGroupStride = 320;
-// NB right-hand sides per pass (1, 4 or 8).  Per wavefront: a slot for the parked activations of its tiles (G of them)
-// per sample; with one sample and one group, four more for the tiles it keeps across row blocks.
+// One right-hand side: a slot per wavefront for the parked activations of its tiles (G of them); with one group four more
+// for the tiles it keeps across row blocks.  Several right-hand sides read their activations from memory in the form they are used in.
 template <int NB, int G>
 __host__ __device__ constexpr int lane_x_bytes() {
-  return G > 1 ? NB * G * kLaneGroupStride : NB == 1 ? 256 + kLaneKeepTiles * 256 : NB * 256;
+  return NB > 1 ? 0 : G > 1 ? G * kLaneGroupStride : 256 + kLaneKeepTiles * 256;
 }
-// tables, partial sums, activation slots, and (one sample: the decode step) room for the selectors.  At k = 4 and G = 1 the 256 bytes a wavefront needs to re-pair the
-// activations are borrowed from the partial sums, which are not in use between the barrier that opens a row block
-// and the stores that close it (its own partial sums of sample 0).
-// Eight samples: their partial sums take the place of the tables, which are done with by then (at G = 1 two barriers more
-// per row block keep two workgroups per compute unit), and activations are re-paired in place.
+// Tables, partial sums, activation slots, and (one sample: the decode step) room for the selectors.  At k = 4
+// and G = 1 the 256 bytes a wavefront needs to re-pair the activations of one sample are borrowed from the partial sums, which are not in
+// use between the barrier that opens a row block and the stores that close it (its own partial sums).
+// Eight samples: their partial sums take the place of the tables, which are done with by then (at G = 1 two barriers
+// more per row block keep two workgroups per compute unit).
 template <int NB>
 __host__ __device__ constexpr int lane_red_offset() { return NB == 8 ? 0 : kLaneTableBytes; }
 template <int NB>
@@ -175,40 +179,91 @@ __device__ __forceinline__ void lane_entry_addr_masked(uint32_t t, uint32_t mask
 
 __device__ __forceinline__ uint32_t lds_u32(const char* lds, uint32_t addr) { return *reinterpret_cast<const uint32_t*>(lds + addr); }
 
-// ---- a tile: the lane's row, 128 columns, and the lane's dword of the tile's 128 activations -------------------
-template <int K, int NB>
+// ---- a tile: the lane's row, 128 columns, and the lane's part of the activations -------------------------------
+// One sample: a dword of the tile's 128 activations per lane (and group), parked in LDS before the tile is decoded.
+// Several: the operands of the matrix instructions as they lie in memory (see LaneX); nothing is parked.  The 32 chunks of a
+// tile (four activations each, 8 j + 2 q + half: see mfma_chunk) are dealt out to the P = 16 / G quads of a group so that what
+// a lane holds is contiguous: quad n has chunks 2 G n .. 2 G n + 2 G - 1, lane 4 n + i those of sample i: 16 G bytes.
+// At k = 4 a chunk is two pairs of columns (see nibble_pair_col_hi): merged words q = 0 and 3 of word j take the odd and the
+// even ones of its columns 0 .. 7 and 16 .. 23, q = 2 and 1 those of columns 8 .. 15 and 24 .. 31.  A lane loads both eights and
+// picks halves (LaneX::settle).
+template <int K, int NB, int G>
+struct LaneRawX {
+  static constexpr int P = 16 / G;
+  static constexpr int kLoads = K == 4 && G == 1 ? 2 : G;      // 16 bytes each
+  u32x4 v[NB / 4][kLoads];
+  // the column of load r inside the tile, for quad n of the group
+  static __device__ __forceinline__ int column(int n, int r) {
+    if constexpr (K == 4 && G <= 2) {
+      const int j = G == 1 ? n >> 2 : n >> 1, t = G == 1 ? (n ^ n >> 1) & 1 : n & 1;
+      return 32 * j + 8 * t + 16 * r;
+    } else {
+      return 8 * G * n + 8 * r;
+    }
+  }
+};
+template <int K, int G>
+struct LaneRawX<K, 1, G> {
+  uint32_t v[1][G];
+};
+
+template <int K, int NB, int G = 1>
 struct LaneTile {
   u32x4 w[K];
-  uint32_t x[NB];
+  LaneRawX<K, NB, G> x;
 };
 
 // the lane's dword of the 128 activations of tile cc (address clamped to the row).  Columns past the end of a
 // ragged row hold zero codes, whose centroid is not zero: their activations must read as 0, which lane_mask_x
 // sees to when the value is used.  (Masking right after the load would make the wavefront wait for the load,
 // and with it for every tile load issued before it, at the point of issue.)
-__device__ __forceinline__ uint32_t lane_load_x(const GemvJob& job, int cc, int lane, int sample = 0) {
+__device__ __forceinline__ uint32_t lane_load_x(const GemvJob& job, int cc, int lane) {
   const int c = cc * 128 + lane * 2, last = job.ncw * 32 - 2;
-  return *reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(as_global(job.x) + (size_t)sample * job.ncw * 32 + min(c, last));
+  return *reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(as_global(job.x) + min(c, last));
 }
 __device__ __forceinline__ uint32_t lane_mask_x(const GemvJob& job, int cc, int lane, uint32_t v) {
   return cc * 128 + lane * 2 <= job.ncw * 32 - 2 ? v : 0u;
+}
+
+// Several samples: asks for the lane's part of the activations of tile `tile` (clamped to the row).  rows[s]: the vector of
+// sample 4 s + lane mod 4; a group with fewer than NB samples re-reads its last one (the sums are not stored).
+template <int K, int NB, int G>
+__device__ __forceinline__ void lane_load_raw(LaneRawX<K, NB, G>& x, const DPLLM_GLOBAL uint16_t* const (&rows)[NB / 4], int tile, int ncw, int lane) {
+  const int n = (lane >> 2) % LaneRawX<K, NB, G>::P;
+#pragma unroll
+  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
+    const int c = min(tile * 128 + LaneRawX<K, NB, G>::column(n, r), ncw * 32 - 8);
+#pragma unroll
+    for (int s = 0; s < NB / 4; ++s) x.v[s][r] = *reinterpret_cast<const DPLLM_GLOBAL u32x4*>(rows[s] + c);
+  }
+}
+// columns past the end of a ragged row (eight are inside or outside together) read as 0
+template <int K, int NB, int G>
+__device__ __forceinline__ void lane_mask_raw(LaneRawX<K, NB, G>& x, int tile, int ncw, int lane) {
+  const int n = (lane >> 2) % LaneRawX<K, NB, G>::P;
+#pragma unroll
+  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
+    const bool inside = tile * 128 + LaneRawX<K, NB, G>::column(n, r) < ncw * 32;
+#pragma unroll
+    for (int s = 0; s < NB / 4; ++s) x.v[s][r] = inside ? x.v[s][r] : u32x4{0u, 0u, 0u, 0u};
+  }
+}
+template <int NB>
+__device__ __forceinline__ void lane_sample_rows(const GemvJob& job, int lane, const DPLLM_GLOBAL uint16_t* (&rows)[NB / 4]) {
+#pragma unroll
+  for (int s = 0; s < NB / 4; ++s) rows[s] = as_global(job.x) + (size_t)min(4 * s + (lane & 3), job.nsamples - 1) * job.ncw * 32;
 }
 
 // Loads are never predicated, which keeps the compiler's outstanding-load counts exact.  `real` = false (ring
 // slots past the end of the run): the K loads still issue, but all from the first 16 bytes of the activation
 // vector, which is hot in L2, so they cost no HBM traffic; the values are never decoded.
 template <int K, int NB>
-__device__ __forceinline__ void lane_load_tile(LaneTile<K, NB>& t, const GemvJob& job, int rb, int cc, int lane, bool with_x, bool real) {
+__device__ __forceinline__ void lane_load_tile(LaneTile<K, NB>& t, const GemvJob& job, int rb, int cc, int lane, bool real) {
   const DPLLM_GLOBAL u32x4* planes = as_global(reinterpret_cast<const u32x4*>(job.arena)) + ((size_t)rb * job.ncc + cc) * 64 + lane;
   const DPLLM_GLOBAL u32x4* p = real ? planes : as_global(reinterpret_cast<const u32x4*>(job.x));
   const size_t stride = real ? (size_t)job.plane_stride_u4 : 0;
 #pragma unroll
   for (int b = 0; b < K; ++b) t.w[b] = load_stream(p + (size_t)b * stride);
-  if (with_x) {
-    // a group with fewer than NB samples re-reads its last one (the sums are not stored)
-#pragma unroll
-    for (int b = 0; b < NB; ++b) t.x[b] = lane_load_x(job, cc, lane, NB == 1 ? 0 : min(b, job.nsamples - 1));
-  }
 }
 
 // Parks a tile's activations in LDS in the form the lanes read back: 64 dwords, dword 16 j + n = pair n of word
@@ -332,59 +387,112 @@ __device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32
 
 // ---- one tile -------------------------------------------------------------------------------------------------
 // Lookups run in chunks of eight; the next chunk's lookups are issued before the current chunk's multiply-adds.
-// xmine: where this lane finds its part of its tile's parked activations.  One sample: the 16 bytes of its quad
-// lane in word 0 (slot + 16 * (lane mod 4)), those of word j 64 j bytes on.  Four samples: chunk n of the tile's 32
-// (four activations, 8 n bytes into the sample's slot) sits in lane quad n mod P of the group, P = 16 / G quads per
-// group, as its operand n / P.
-template <int NB, int G>
-struct LaneX {
-  static constexpr int P = 16 / G;
-  static constexpr int sample = G == 1 ? 256 : G * kLaneGroupStride;   // bytes from one sample's slot to the next
-  uint64_t a[NB / 4][2 * G];   // a[s][h] = chunk P h + (lane / 4) mod P of the tile, of sample 4 s + lane mod 4
-  __device__ __forceinline__ void load(const char* xmine) {
-#pragma unroll
-    for (int s = 0; s < NB / 4; ++s)
-#pragma unroll
-      for (int h = 0; h < 2 * G; ++h) a[s][h] = *reinterpret_cast<const uint64_t*>(xmine + s * 4 * sample + h * P * 8);
+// One sample: mine is where this lane finds its part of its tile's parked activations, the 16 bytes of its quad
+// lane in word 0 (slot + 16 * (lane mod 4)), those of word j 64 j bytes on.
+template <int K, int NB, int G>
+struct LaneX {   // several samples: operands of the matrix instructions
+  uint64_t a[NB / 4][2 * G];   // a[s][h]: the h-th chunk of the lane's quad (see LaneRawX), of sample 4 s + lane mod 4
+  // which quad of the group and which of its operands holds chunk c
+  static constexpr int quad(int c) {
+    if constexpr (K == 4) {
+      const int j = c >> 3, q = (c >> 1) & 3, t = (q ^ q >> 1) & 1;
+      return G == 1 ? c >> 1 : G == 2 ? 2 * j + t : G == 4 ? j : j >> 1;
+    }
+    return c / (2 * G);
   }
-  __device__ __forceinline__ void load_word(const char*, int) {}   // (one sample only)
+  static constexpr int operand(int c) {
+    if constexpr (K == 4) {
+      const int j = c >> 3, q = (c >> 1) & 3, t = (q ^ q >> 1) & 1, even = q & 1, half = c & 1;
+      return G == 1 ? half : G == 2 ? 2 * even + half : G == 4 ? 4 * t + 2 * even + half : 8 * (j & 1) + 4 * t + 2 * even + half;
+    }
+    return c % (2 * G);
+  }
+  // lo and hi: columns 8 t .. + 7 and 16 + 8 t .. + 7 of a word.  Odd columns: pair m = (hi[2 m + 1], lo[2 m + 1]); even ones: pair m =
+  // (lo[2 m], hi[2 ((m + 3) mod 4)])
+  static __device__ __forceinline__ void odd_pairs(uint64_t (&o)[2], const u32x4& lo, const u32x4& hi) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      o[i] = (uint64_t)__builtin_amdgcn_perm(lo[2 * i + 1], hi[2 * i + 1], 0x07060302u) << 32 | __builtin_amdgcn_perm(lo[2 * i], hi[2 * i], 0x07060302u);
+  }
+  static __device__ __forceinline__ void even_pairs(uint64_t (&o)[2], const u32x4& lo, const u32x4& hi) {
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+      o[i] = (uint64_t)__builtin_amdgcn_perm(hi[2 * i], lo[2 * i + 1], 0x05040100u) << 32 | __builtin_amdgcn_perm(hi[(2 * i + 3) & 3], lo[2 * i], 0x05040100u);
+  }
+  __device__ __forceinline__ void settle(const LaneRawX<K, NB, G>& raw, int lane) {
+#pragma unroll
+    for (int s = 0; s < NB / 4; ++s) {
+      if constexpr (K == 4 && G == 1) {
+        // quad 4 j + q: q = 0, 2 take odd columns, 1, 3 even ones
+        const bool even = (lane >> 2) & 1;
+        const u32x4 &lo = raw.v[s][0], &hi = raw.v[s][1];
+        const uint32_t sel = even ? 0x01000504u : 0x07060302u;   // even: the low half of the pair comes from lo
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+          const uint32_t h0 = even ? +hi[(2 * i + 3) & 3] : +hi[2 * i], h1 = even ? +hi[2 * i] : +hi[2 * i + 1];
+          a[s][i] = (uint64_t)__builtin_amdgcn_perm(lo[2 * i + 1], h1, sel) << 32 | __builtin_amdgcn_perm(lo[2 * i], h0, sel);
+        }
+      } else if constexpr (K == 4) {
+        // G = 2: (odd, even) of one t; G = 4: of t = 0, 1 (loads 0, 2 and 1, 3); G = 8: of two words
+#pragma unroll
+        for (int u = 0; u < G / 2; ++u) {
+          const int at = G == 2 ? 0 : 4 * (u >> 1) + (u & 1);
+          const u32x4 &lo = raw.v[s][at], &hi = raw.v[s][at + (G == 2 ? 1 : 2)];
+          uint64_t o[2], e[2];
+          odd_pairs(o, lo, hi);
+          even_pairs(e, lo, hi);
+          a[s][4 * u] = o[0]; a[s][4 * u + 1] = o[1];
+          a[s][4 * u + 2] = e[0]; a[s][4 * u + 3] = e[1];
+        }
+      } else {
+#pragma unroll
+        for (int r = 0; r < G; ++r) {
+          a[s][2 * r] = (uint64_t)raw.v[s][r].y << 32 | raw.v[s][r].x;
+          a[s][2 * r + 1] = (uint64_t)raw.v[s][r].w << 32 | raw.v[s][r].z;
+        }
+      }
+    }
+  }
+  __device__ __forceinline__ void load() {}
+  __device__ __forceinline__ void load_word(int) {}
 };
-template <int G>
-struct LaneX<1, G> {
+template <int K, int G>
+struct LaneX<K, 1, G> {
   u32x4 q[4];   // q[j][m] = pair 4 (lane mod 4) + m of word j
-  __device__ __forceinline__ void load(const char* xmine) {
+  const char* mine;
+  __device__ __forceinline__ void load() {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) load_word(xmine, j);
+    for (int j = 0; j < 4; ++j) load_word(j);
   }
-  __device__ __forceinline__ void load_word(const char* xmine, int j) { q[j] = *reinterpret_cast<const u32x4*>(xmine + j * 64); }
+  __device__ __forceinline__ void load_word(int j) { q[j] = *reinterpret_cast<const u32x4*>(mine + j * 64); }
 };
 // chunk C of the tile for four samples or eight (chunks take turns in the two accumulator sets of four samples)
-template <int C, int NB, int G>
-__device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
-  constexpr int P = LaneX<NB, G>::P;
-  mfma_chunk<C % P, G>(acc.v[C & 1], x.a[0][C / P], w0, w1);
-  if constexpr (NB == 8) mfma_chunk<C % P, G>(acc.v[2 + (C & 1)], x.a[1][C / P], w0, w1);
+template <int C, int K, int NB, int G>
+__device__ __forceinline__ void lane_mac_chunk(uint32_t w0, uint32_t w1, const LaneX<K, NB, G>& x, LaneAcc<NB>& acc) {
+  constexpr int Q = LaneX<K, NB, G>::quad(C), h = LaneX<K, NB, G>::operand(C);
+  mfma_chunk<Q, G>(acc.v[C & 1], x.a[0][h], w0, w1);
+  if constexpr (NB == 8) mfma_chunk<Q, G>(acc.v[2 + (C & 1)], x.a[1][h], w0, w1);
 }
 
 // the eight lookups of entry words JA, JA + 1 of word J: chunks 8 J + 2 JA .. + 3
-template <int JA, int J, int G>
-__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
+template <int JA, int J, int K, int G>
+__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<K, 1, G>& x, LaneAcc<1>& acc) {
   lane_consume_pairs<JA>(v, x.q[J], acc.v);
 }
-template <int JA, int J, int NB, int G>
-__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
+template <int JA, int J, int K, int NB, int G>
+__device__ __forceinline__ void lane_mac_pairs(const uint32_t (&v)[8], const LaneX<K, NB, G>& x, LaneAcc<NB>& acc) {
   lane_mac_chunk<8 * J + 2 * JA + 3>(v[6], v[7], x, acc);
   lane_mac_chunk<8 * J + 2 * JA + 2>(v[4], v[5], x, acc);
   lane_mac_chunk<8 * J + 2 * JA + 1>(v[2], v[3], x, acc);
   lane_mac_chunk<8 * J + 2 * JA + 0>(v[0], v[1], x, acc);
 }
 // the lookups of columns 8 JJ .. + 7 of word J: chunks 8 J + 2 JJ, + 1
-template <int JJ, int J, int G>
-__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<1, G>& x, LaneAcc<1>& acc) {
+template <int JJ, int J, int K, int G>
+__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<K, 1, G>& x, LaneAcc<1>& acc) {
   lane_consume_singles<JJ>(v, x.q[J], acc.v);
 }
-template <int JJ, int J, int NB, int G>
-__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<NB, G>& x, LaneAcc<NB>& acc) {
+template <int JJ, int J, int K, int NB, int G>
+__device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const LaneX<K, NB, G>& x, LaneAcc<NB>& acc) {
   lane_mac_chunk<8 * J + 2 * JJ + 1>(v[4] | (v[5] << 16), v[6] | (v[7] << 16), x, acc);
   lane_mac_chunk<8 * J + 2 * JJ + 0>(v[0] | (v[1] << 16), v[2] | (v[3] << 16), x, acc);
 }
@@ -399,7 +507,7 @@ struct LaneNothing {
   __device__ __forceinline__ void operator()(Planes&) const {}
 };
 template <int K, int NB, int G, bool LAZY = false, int H = K, class Spent = LaneNothing>
-__device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, const char* lds, const char* xmine,
+__device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, const char* lds, LaneX<K, NB, G>& x,
                                              LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const LaneMasks<K>& M, int words, bool ragged,
                                              Spent spent = LaneNothing{}) {
   auto clear = [&](uint32_t (&v)[8], int j) {
@@ -411,9 +519,8 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     }
   };
   uint32_t va[8], vb[8];
-  LaneX<NB, G> x;
-  if constexpr (LAZY) x.load_word(xmine, 0);
-  else x.load(xmine);
+  if constexpr (LAZY) x.load_word(0);
+  else x.load();
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
   using J2 = std::integral_constant<int, 2>;
@@ -436,7 +543,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     lane_issue_pairs<0, K <= 3>(T[0], lanecol, lds, va, addr, mask);
     auto word = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      if constexpr (LAZY && j + 1 < 4) x.load_word(xmine, j + 1);
+      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_pairs<2, K <= 3>(T[j], lanecol, lds, vb, addr, mask);
       sched_fence();
       clear(va, j);
@@ -475,7 +582,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
         lane_merge_fields<K>(w, R[(j + 1) & 1], M);
       }
-      if constexpr (LAZY && j + 1 < 4) x.load_word(xmine, j + 1);
+      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
       sched_fence();
       lane_mac_singles<0, j>(va, x, acc);
@@ -595,7 +702,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint32_t lanecol = (uint32_t)lane * 4;  // the lane's column of the interleaved tables
   float* red = reinterpret_cast<float*>(lds + lane_red_offset<NB>());
-  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, 1>();   // + 256 b: the parked tile of sample b
+  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, 1>();   // (one sample) the parked tile
   char* repair = reinterpret_cast<char*>(red) + wave * 256;   // k = 4: room to re-pair a tile's activations (see lane_lds_bytes)
   const int c0 = wave * job.ncc / kLaneWaves, c1 = (wave + 1) * job.ncc / kLaneWaves;
   const int nrb = job.nrq;                     // row blocks of the job
@@ -614,8 +721,8 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   constexpr bool kEarlyX = K != 4;
   const bool keep = NB == 1 && c1 - c0 <= kLaneKeepTiles;
   char* kept = ready + 256;
-  // this lane's view of a tile's parked activations (see lane_compute)
-  const int xlane = NB == 1 ? (lane & 3) * 16 : (lane & 3) * 256 + (lane >> 2) * 8;
+  const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
+  if constexpr (NB > 1) lane_sample_rows<NB>(job, lane, xrows);
   uint32_t xkeep[kLaneKeepTiles];
   if (keep) {
     if constexpr (kEarlyX) {
@@ -630,7 +737,11 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   int lrb = block, lcc = c0;                   // load cursor
   bool more = true;                            // the load cursor is still inside the run
   auto load_next = [&](LaneTile<K, NB>& t) {
-    lane_load_tile<K, NB>(t, job, lrb, lcc, lane, !keep, more);
+    if constexpr (NB > 1) lane_load_raw(t.x, xrows, lcc, job.ncw, lane);
+    lane_load_tile<K, NB>(t, job, lrb, lcc, lane, more);
+    if constexpr (NB == 1) {
+      if (!keep) t.x.v[0][0] = lane_load_x(job, lcc, lane);
+    }
     if (++lcc >= c1) {
       lcc = c0;
       if (lrb + step < nrb) lrb += step; else more = false;
@@ -693,13 +804,20 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
 #pragma unroll
     for (int s = 0; s < D; ++s) {
       load_next(ring[(s + D - 1) % D]);
-      const char* xready = kept + (cc - c0) * 256;
-      if (!keep) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) lane_park_x<K>(lane_mask_x(job, cc, lane, ring[s].x[b]), lane, NB == 8 ? ready + b * 256 : repair, ready + b * 256);
-        xready = ready;
+      const bool ragged = cc * 4 + 4 > job.ncw;
+      LaneX<K, NB, 1> x;
+      if constexpr (NB == 1) {
+        x.mine = kept + (cc - c0) * 256;
+        if (!keep) {
+          lane_park_x<K>(lane_mask_x(job, cc, lane, ring[s].x.v[0][0]), lane, repair, ready);
+          x.mine = ready;
+        }
+        x.mine += (lane & 3) * 16;
+      } else {
+        if (ragged) lane_mask_raw(ring[s].x, cc, job.ncw, lane);
+        x.settle(ring[s].x, lane);
       }
-      lane_compute<K, NB, 1>(ring[s].w, lanecol, lds, xready + xlane, acc, addr, mask, M, job.ncw - cc * 4, cc * 4 + 4 > job.ncw);
+      lane_compute<K, NB, 1>(ring[s].w, lanecol, lds, x, acc, addr, mask, M, job.ncw - cc * 4, ragged);
       if (++cc >= c1) {
         close_block();
         rb += step;
@@ -724,12 +842,6 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
 // are parked while the rest is on its way, and one workgroup per compute unit may use all its registers.
 // us per launch, columns split between workgroups -> now: 4096 x 4096 k = 4 10.9 -> 5.5, k = 8 14.6 -> 8.5; 4096 x 11008
 // k = 3 12.2 -> 7.9; 1024 x 4096 k = 3 7.3 -> 3.9 (before the arguments came in registers, see gemv_lane_kernel).
-template <int K, int NB, int G>
-struct NarrowTile {
-  u32x4 w[K];
-  uint32_t x[NB][G];   // the lane's G dwords of the G tiles' activations: dwords G lane .. + G - 1
-};
-
 template <int N>
 __device__ __forceinline__ void load_dwords(uint32_t (&v)[N], const DPLLM_GLOBAL uint32_t* p) {
   if constexpr (N == 2) {
@@ -746,23 +858,19 @@ __device__ __forceinline__ void load_dwords(uint32_t (&v)[N], const DPLLM_GLOBAL
 
 // the planes of the lane's tile (number `tile`, clamped to the row); real as in lane_load_tile
 template <int K, int NB, int G>
-__device__ __forceinline__ void narrow_load_planes(NarrowTile<K, NB, G>& t, const GemvJob& job, const DPLLM_GLOBAL u32x4* rows, int tile, bool real) {
+__device__ __forceinline__ void narrow_load_planes(LaneTile<K, NB, G>& t, const GemvJob& job, const DPLLM_GLOBAL u32x4* rows, int tile, bool real) {
   const DPLLM_GLOBAL u32x4* p = real ? rows + (size_t)min(tile, job.ncc - 1) * 64 : as_global(reinterpret_cast<const u32x4*>(job.x));
   const size_t stride = real ? (size_t)job.plane_stride_u4 : 0;
 #pragma unroll
   for (int b = 0; b < K; ++b) t.w[b] = load_stream(p + (size_t)b * stride);
 }
 
-// the lane's part of the activations of step sc (G tiles).  A lane's 4 G bytes are 2 G columns; rows are whole
-// 32-column words, so they are all inside the row or all past it.
-template <int K, int NB, int G>
-__device__ __forceinline__ void narrow_load_x(NarrowTile<K, NB, G>& t, const GemvJob& job, int sc, int lane) {
+// One sample: the lane's dwords G lane .. + G - 1 of the activations of step sc (G tiles).  They are 2 G columns; rows are
+// whole 32-column words, so they are all inside the row or all past it.
+template <int K, int G>
+__device__ __forceinline__ void narrow_load_x(LaneTile<K, 1, G>& t, const GemvJob& job, int sc, int lane) {
   const int c = min(sc * G * 128 + lane * 2 * G, job.ncw * 32 - 2 * G);
-#pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    const uint16_t* xs = job.x + (size_t)(NB == 1 ? 0 : min(b, job.nsamples - 1)) * job.ncw * 32;
-    load_dwords<G>(t.x[b], reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(as_global(xs) + c));
-  }
+  load_dwords<G>(t.x.v[0], reinterpret_cast<const DPLLM_GLOBAL uint32_t*>(as_global(job.x) + c));
 }
 
 // The sum over the G lanes of a row (64 / G lanes apart), in every one of them.  The swaps exchange two registers,
@@ -809,37 +917,41 @@ __device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside,
 // one workgroup: block number `block` of 64 / G rows
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
-  static_assert(NB <= 4 || G == 4, "LDS and registers");
   constexpr int D = kLaneDepth;
   constexpr int rows = 64 / G;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int row = block * rows + lane % rows, group = lane / rows;
   const uint32_t lanecol = (uint32_t)lane * 4;
   float* red = reinterpret_cast<float*>(lds + lane_red_offset<NB>());
-  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, G>();   // sample b: + G * kLaneGroupStride * b
-  const int xlane = group * kLaneGroupStride +
-                    (NB == 1 ? (lane & 3) * 16 : (lane & 3) * G * kLaneGroupStride + ((lane >> 2) % (16 / G)) * 8);
+  char* ready = lds + lane_x_offset<NB>() + wave * lane_x_bytes<NB, G>();   // (one sample)
   const int nsc = (job.ncc + G - 1) / G;
   const int c0 = wave * nsc / kLaneWaves, c1 = (wave + 1) * nsc / kLaneWaves;
   const DPLLM_GLOBAL u32x4* plane_rows = as_global(reinterpret_cast<const u32x4*>(job.arena)) + (size_t)(row / 64) * job.ncc * 64 + row % 64;
+  const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
+  if constexpr (NB > 1) lane_sample_rows<NB>(job, lane, xrows);
+  auto load_x = [&](LaneTile<K, NB, G>& t, int sc) {
+    if constexpr (NB > 1) lane_load_raw(t.x, xrows, sc * G + group, job.ncw, lane);
+    else narrow_load_x(t, job, sc, lane);
+  };
   // first the activations of the first step (hot in L2: parked while the rest is on its way), then the table rows and
   // the planes of the first D steps
   LaneLut<K> L;
-  NarrowTile<K, NB, G> ring[D];
+  LaneTile<K, NB, G> ring[D];
   const bool some = c0 < c1;                   // fewer steps than wavefronts: some only help with the tables
-  auto inside = [&](int sc) { return sc * G * 128 + lane * 2 * G < job.ncw * 32; };
-  if (some) narrow_load_x<K, NB, G>(ring[0], job, c0, lane);
+  auto park = [&](const LaneTile<K, NB, G>& t, int sc) {
+    if constexpr (NB == 1) narrow_park<K, G>(t.x.v[0], sc * G * 128 + lane * 2 * G < job.ncw * 32, lane, ready);
+  };
+  if (some) load_x(ring[0], c0);
   lane_fetch_lut<K>(L, as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off)), row, wave);
   if (some) {
     narrow_load_planes<K, NB, G>(ring[0], job, plane_rows, c0 * G + group, true);
 #pragma unroll
     for (int i = 1; i < D; ++i) {
-      narrow_load_x<K, NB, G>(ring[i], job, c0 + i, lane);
+      load_x(ring[i], c0 + i);
       narrow_load_planes<K, NB, G>(ring[i], job, plane_rows, (c0 + i) * G + group, c0 + i < c1);
     }
     sched_fence();
-#pragma unroll
-    for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[0].x[b], inside(c0), lane, ready + b * G * kLaneGroupStride);
+    park(ring[0], c0);
   }
   LaneAcc<NB> acc;
   acc.zero();
@@ -861,18 +973,23 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   for (int cc = c0; cc < c1;) {
 #pragma unroll
     for (int s = 0; s < D; ++s) {
-      if (cc != c0) {
-#pragma unroll
-        for (int b = 0; b < NB; ++b) narrow_park<K, G>(ring[s].x[b], inside(cc), lane, ready + b * G * kLaneGroupStride);
-      }
+      if (cc != c0) park(ring[s], cc);
       if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
       for (int b = 0; b < NB; ++b) done[b] = acc.sum(b);
-      lane_compute<K, NB, G>(ring[s].w, lanecol, lds, ready + xlane, acc, addr, mask, M, job.ncw - (cc * G + group) * 4,
-                             (cc + 1) * G * 4 > job.ncw);
+      const int tile = cc * G + group;
+      const bool ragged = (cc + 1) * G * 4 > job.ncw;
+      LaneX<K, NB, G> x;
+      if constexpr (NB == 1) {
+        x.mine = ready + group * kLaneGroupStride + (lane & 3) * 16;
+      } else {
+        if (ragged) lane_mask_raw(ring[s].x, tile, job.ncw, lane);
+        x.settle(ring[s].x, lane);
+      }
+      lane_compute<K, NB, G>(ring[s].w, lanecol, lds, x, acc, addr, mask, M, job.ncw - tile * 4, ragged);
       if constexpr (kSettleBehind) acc.settle();
       if (++cc >= c1) break;
-      narrow_load_x<K, NB, G>(ring[s], job, cc + D - 1, lane);
+      load_x(ring[s], cc + D - 1);
       narrow_load_planes<K, NB, G>(ring[s], job, plane_rows, (cc + D - 1) * G + group, cc + D - 1 < c1);
     }
   }
