@@ -377,11 +377,13 @@ __device__ __forceinline__ void lane_consume_singles(const uint32_t (&v)[8], con
 template <int K>
 using LaneMasks = MergeMasks<(K < 3 ? 3 : K)>;
 
-// k = 5, 6: the merge tree with its masks in vector registers (full-rate instructions); k = 7, 8 have no registers
-// to spare for fifteen masks at two workgroups per compute unit and keep them in the instructions
-template <int K>
+// The merge tree with its masks in vector registers (full-rate instructions).  Two workgroups per compute unit (ROOM: one) leave k = 7, 8
+// no registers to spare for fifteen masks; they keep them in the instructions there.  us per call with one workgroup, masks in the
+// instructions -> in registers: 2500 x 6688 k = 7 9.3 -> 8.7, 4096 x 4096 k = 7 7.2 -> 6.9, 4096 x 11008 k = 7 13.6 -> 12.6, k = 8 14.1 ->
+// 13.8, 8192 x 8192 k = 7 16.4 -> 15.7.
+template <int K, bool ROOM>
 __device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32_t (&R)[8], const LaneMasks<K>& M) {
-  if constexpr (K <= 6) merge_byte_fields_v<K, LaneDecode<K>::d>(w, R, M);
+  if constexpr (K <= 6 || ROOM) merge_byte_fields_v<K, LaneDecode<K>::d>(w, R, M);
   else merge_byte_fields<K, LaneDecode<K>::d>(w, R);
 }
 
@@ -571,7 +573,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
       uint32_t w[K];
 #pragma unroll
       for (int b = 0; b < K; ++b) w[b] = mine[b][0];
-      lane_merge_fields<K>(w, R[0], M);
+      lane_merge_fields<K, (G > 1 && !LAZY)>(w, R[0], M);
     }
     lane_issue_singles<K, 0>(R[0], lanecol, lds, va);
     auto word = [&](auto jc) {
@@ -580,7 +582,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         uint32_t w[K];
 #pragma unroll
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
-        lane_merge_fields<K>(w, R[(j + 1) & 1], M);
+        lane_merge_fields<K, (G > 1 && !LAZY)>(w, R[(j + 1) & 1], M);
       }
       if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
@@ -964,7 +966,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 #pragma unroll
   for (int b = 0; b < NB; ++b) done[b] = 0.f;
   LaneMasks<K> M;
-  if constexpr (K <= 6) M.init();
+  M.init();
   uint32_t addr[8], mask = LaneDecode<K>::pair ? LaneDecode<K>::pair_mask : 0;   // k <= 3 (see lane_issue_pairs)
 #pragma unroll
   for (int i = 0; i < 8; ++i) addr[i] = lanecol;
