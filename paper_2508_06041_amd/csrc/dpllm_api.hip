@@ -390,10 +390,12 @@ void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const Gemv
       case 4: go(gemv_lane_kernel<4, 4>); break;
       default: go(gemv_lane_kernel<4, 8>); break;
     }
-  } else if (groups == 1) {
-    go(gemv_lane_kernel<8, 1>);
   } else {
-    go(gemv_lane_kernel<8, 4>);
+    switch (groups) {
+      case 1: go(gemv_lane_kernel<8, 1>); break;
+      case 2: go(gemv_lane_kernel<8, 2>); break;
+      default: go(gemv_lane_kernel<8, 4>); break;
+    }
   }
 }
 
@@ -424,18 +426,22 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 
 // One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
 // more workgroups than there are compute units; below that the second pass runs beside the first one.  us per call of
-// B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 10.5, k = 6 23.1 / 17.5, 11008 x 4096 k = 8 27.5 / 18.5, 28672 x
-// 8192 k = 5 64.1 / 40.8 (B = 4: 35.3); 4096 x 14336 k = 3 12.8 / 13.8, 4096 x 4096 k = 4 8.2 / 8.9.
-// In between, 33 to 64 row blocks: two passes leave 64 / 2 rows to a workgroup, one pass 64 / 4, which is half the lookups
-// for the same sums and pays where lookups are what a step consists of (k >= 5) and every wavefront gets a step: 2120 x
-// 28672 k = 6 36.3 / 29.6, 3000 x 8192 k = 5 13.8 / 13.1, 4096 x 4096 k = 8 11.8 / 10.8; 4096 x 2048 k = 5 6.6 / 7.2, 2120 x
-// 14336 k = 4 17.3 / 20.3.
+// B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 8.7, 11008 x 4096 k = 3 11.1 / 8.3, k = 5 19.5 / 13.0, k = 8 27.5 / 17.5.
+// Up to 128 row blocks both passes fit, with twice the rows to a workgroup that one pass takes (64 / 1 and 64 / 2; up to 64 blocks
+// 64 / 2 and 64 / 4): twice the lookups in a workgroup for the same sums.  One pass pays where lookups are what a step consists of
+// (k >= 5) and where every wavefront has a step or several.  65 to 128 blocks: 8192 x 8192 k = 3 11.1 / 10.6, k = 4 12.3 / 12.0, k = 5 19.1 / 15.4,
+// k = 8 22.8 / 19.7; 6000 x 28672 k = 2 30.1 / 24.3, k = 5 55.4 / 37.6; 6000 x 4096 k = 3 7.7 / 7.5; 5000 x 2048 k = 2 5.3 / 5.4, k = 4 6.0 / 6.0,
+// k = 5 7.8 / 6.8, k = 8 10.1 / 8.3; 8192 x 1024 k = 3 4.2 / 4.7, k = 5 5.8 / 5.8, k = 8 7.7 / 7.1.  33 to 64: 4096 x 14336 k = 3 11.5 / 12.9, k = 5 18.9 /
+// 17.0, k = 8 22.0 / 21.3; 4096 x 4096 k = 3 6.2 / 6.5, k = 4 7.0 / 8.2, k = 5 8.8 / 7.9; 4096 x 28672 k = 3 19.1 / 18.9, k = 4 21.4 / 25.9, k = 6 33.8 /
+// 27.1; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.3 / 6.3.  Fewer: 1000 x 4096 k = 5 6.5 / 7.4, 1500 x 14336 k = 3 9.9 / 12.4.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
-  const bool mid = lin.L.nrq > 32 && lin.L.nrq <= 64 && lin.L.ncc >= 4 * kLaneWaves && (k_dev ? lin.L.p : k) >= 5;
-  const int nb = B == 1 ? 1 : B <= 4 || (lin.L.nrq <= 128 && !mid) ? 4 : 8;
+  const int blocks = lin.L.nrq;
+  const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= 4 * kLaneWaves;
+  const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
+  const int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
-  const int groups = nb == 8 ? (mid ? 4 : 1) : pick_groups((long)lin.L.nrq * passes, lin.L.ncc);
+  const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc);
   if (groups > 1) {
     j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   } else {

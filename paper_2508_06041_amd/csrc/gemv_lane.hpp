@@ -26,8 +26,8 @@
 // every lookup serves four (eight) samples: up to eight right-hand sides share a pass over the planes.  They are loaded with the
 // tile in that form.  (Parked in LDS sample by sample and read back, as one right-hand side is, they cost a tile of four samples
 // four LDS writes and two reads per lane, at k = 4 two reads, a write and a wait for each sample more.  us per call, parked -> loaded:
-// 14336 x 4096 B = 4, k = 6 15.6 -> 14.5, B = 2, k = 3 7.9 -> 7.4, B = 8, k = 3 10.4 -> 8.7; 20000 x 4096 B = 3, k = 4 15.7 -> 13.5; 4096 x
-// 14336 B = 8, k = 3 11.8 -> 11.5.)
+// 14336 x 4096 B = 4, k = 6 15.6 -> 14.5, B = 2, k = 3 7.9 -> 7.4, B = 8, k = 3 10.4 -> 8.4; 20000 x 4096 B = 3, k = 4 15.7 -> 13.5; 4096 x
+// 14336 B = 8, k = 3 11.8 -> 11.3.)
 // Each lane accumulates its own row: no cross-lane reduction.  A workgroup is eight wavefronts that split the
 // columns of the same 64 rows and share the tables; their eight partial sums per row meet in LDS.
 //
@@ -181,26 +181,29 @@ __device__ __forceinline__ uint32_t lds_u32(const char* lds, uint32_t addr) { re
 
 // ---- a tile: the lane's row, 128 columns, and the lane's part of the activations -------------------------------
 // One sample: a dword of the tile's 128 activations per lane (and group), parked in LDS before the tile is decoded.
-// Several: the operands of the matrix instructions as they lie in memory (see LaneX); nothing is parked.  The 32 chunks of a
-// tile (four activations each, 8 j + 2 q + half: see mfma_chunk) are dealt out to the P = 16 / G quads of a group so that what
-// a lane holds is contiguous: quad n has chunks 2 G n .. 2 G n + 2 G - 1, lane 4 n + i those of sample i: 16 G bytes.
+// Several: sixteen bytes per lane, group and four samples, which the lanes exchange for the operands of the matrix instructions
+// (LaneX::settle); nothing is parked.  The 32 chunks of a tile (four activations each, 8 j + 2 q + half: see mfma_chunk) go in twos,
+// an eight of columns each, to the P = 16 / G quads of a group: quad n has the eights n, n + P, ..; its lane 4 n + i needs those of sample i.
+// They are loaded by lane i P + n of the group instead, so that neighbouring lanes read neighbouring memory: four lanes of a quad
+// in four vectors cost the vector cache about 90 cycles a load (3400 x 14336 k = 5, four column groups, eight samples that way 20.6 us, five,
+// with four lanes in one vector in every second load, 16.6).
 // At k = 4 a chunk is two pairs of columns (see nibble_pair_col_hi): merged words q = 0 and 3 of word j take the odd and the
-// even ones of its columns 0 .. 7 and 16 .. 23, q = 2 and 1 those of columns 8 .. 15 and 24 .. 31.  A lane loads both eights and
-// picks halves (LaneX::settle).
+// even ones of its columns 0 .. 7 and 16 .. 23, q = 2 and 1 those of columns 8 .. 15 and 24 .. 31.  A lane gets both eights and
+// picks halves.
 template <int K, int NB, int G>
 struct LaneRawX {
   static constexpr int P = 16 / G;
-  static constexpr int kLoads = K == 4 && G == 1 ? 2 : G;      // 16 bytes each
-  u32x4 v[NB / 4][kLoads];
-  // the column of load r inside the tile, for quad n of the group
-  static __device__ __forceinline__ int column(int n, int r) {
-    if constexpr (K == 4 && G <= 2) {
-      const int j = G == 1 ? n >> 2 : n >> 1, t = G == 1 ? (n ^ n >> 1) & 1 : n & 1;
-      return 32 * j + 8 * t + 16 * r;
-    } else {
-      return 8 * G * n + 8 * r;
-    }
+  u32x4 v[NB / 4][G];
+  // what lane `lane` loads: of which sample (of four), and the column of load r inside the tile
+  static __device__ __forceinline__ int sample(int lane) { return lane % (4 * P) / P; }
+  static __device__ __forceinline__ int column(int lane, int r) {
+    const int n = lane % P;
+    if constexpr (K == 4 && G == 2) return 32 * (n >> 1) + 8 * (n & 1) + 16 * r;
+    if constexpr (K == 4 && G > 2) return 8 * G * n + 8 * r;
+    return 8 * (r * P + n);
   }
+  // the lane whose loads quad n of the lane's group needs for its own sample (as the address of a bpermute)
+  static __device__ __forceinline__ int source(int lane, int n) { return 4 * ((lane & -(4 * P)) + (lane & 3) * P + n); }
 };
 template <int K, int G>
 struct LaneRawX<K, 1, G> {
@@ -226,13 +229,12 @@ __device__ __forceinline__ uint32_t lane_mask_x(const GemvJob& job, int cc, int 
 }
 
 // Several samples: asks for the lane's part of the activations of tile `tile` (clamped to the row).  rows[s]: the vector of
-// sample 4 s + lane mod 4; a group with fewer than NB samples re-reads its last one (the sums are not stored).
+// the lane's sample among 4 s .. 4 s + 3; a group with fewer than NB samples re-reads its last one (the sums are not stored).
 template <int K, int NB, int G>
 __device__ __forceinline__ void lane_load_raw(LaneRawX<K, NB, G>& x, const DPLLM_GLOBAL uint16_t* const (&rows)[NB / 4], int tile, int ncw, int lane) {
-  const int n = (lane >> 2) % LaneRawX<K, NB, G>::P;
 #pragma unroll
-  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
-    const int c = min(tile * 128 + LaneRawX<K, NB, G>::column(n, r), ncw * 32 - 8);
+  for (int r = 0; r < G; ++r) {
+    const int c = min(tile * 128 + LaneRawX<K, NB, G>::column(lane, r), ncw * 32 - 8);
 #pragma unroll
     for (int s = 0; s < NB / 4; ++s) x.v[s][r] = *reinterpret_cast<const DPLLM_GLOBAL u32x4*>(rows[s] + c);
   }
@@ -240,18 +242,18 @@ __device__ __forceinline__ void lane_load_raw(LaneRawX<K, NB, G>& x, const DPLLM
 // columns past the end of a ragged row (eight are inside or outside together) read as 0
 template <int K, int NB, int G>
 __device__ __forceinline__ void lane_mask_raw(LaneRawX<K, NB, G>& x, int tile, int ncw, int lane) {
-  const int n = (lane >> 2) % LaneRawX<K, NB, G>::P;
 #pragma unroll
-  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
-    const bool inside = tile * 128 + LaneRawX<K, NB, G>::column(n, r) < ncw * 32;
+  for (int r = 0; r < G; ++r) {
+    const bool inside = tile * 128 + LaneRawX<K, NB, G>::column(lane, r) < ncw * 32;
 #pragma unroll
     for (int s = 0; s < NB / 4; ++s) x.v[s][r] = inside ? x.v[s][r] : u32x4{0u, 0u, 0u, 0u};
   }
 }
-template <int NB>
+template <int K, int NB, int G>
 __device__ __forceinline__ void lane_sample_rows(const GemvJob& job, int lane, const DPLLM_GLOBAL uint16_t* (&rows)[NB / 4]) {
 #pragma unroll
-  for (int s = 0; s < NB / 4; ++s) rows[s] = as_global(job.x) + (size_t)min(4 * s + (lane & 3), job.nsamples - 1) * job.ncw * 32;
+  for (int s = 0; s < NB / 4; ++s)
+    rows[s] = as_global(job.x) + (size_t)min(4 * s + LaneRawX<K, NB, G>::sample(lane), job.nsamples - 1) * job.ncw * 32;
 }
 
 // Loads are never predicated, which keeps the compiler's outstanding-load counts exact.  `real` = false (ring
@@ -400,14 +402,14 @@ struct LaneX {   // several samples: operands of the matrix instructions
       const int j = c >> 3, q = (c >> 1) & 3, t = (q ^ q >> 1) & 1;
       return G == 1 ? c >> 1 : G == 2 ? 2 * j + t : G == 4 ? j : j >> 1;
     }
-    return c / (2 * G);
+    return (c >> 1) % (16 / G);
   }
   static constexpr int operand(int c) {
     if constexpr (K == 4) {
       const int j = c >> 3, q = (c >> 1) & 3, t = (q ^ q >> 1) & 1, even = q & 1, half = c & 1;
       return G == 1 ? half : G == 2 ? 2 * even + half : G == 4 ? 4 * t + 2 * even + half : 8 * (j & 1) + 4 * t + 2 * even + half;
     }
-    return c % (2 * G);
+    return 2 * ((c >> 1) / (16 / G)) + (c & 1);
   }
   // lo and hi: columns 8 t .. + 7 and 16 + 8 t .. + 7 of a word.  Odd columns: pair m = (hi[2 m + 1], lo[2 m + 1]); even ones: pair m =
   // (lo[2 m], hi[2 ((m + 3) mod 4)])
@@ -421,36 +423,48 @@ struct LaneX {   // several samples: operands of the matrix instructions
     for (int i = 0; i < 2; ++i)
       o[i] = (uint64_t)__builtin_amdgcn_perm(hi[2 * i], lo[2 * i + 1], 0x05040100u) << 32 | __builtin_amdgcn_perm(hi[(2 * i + 3) & 3], lo[2 * i], 0x05040100u);
   }
+  static __device__ __forceinline__ u32x4 pull(int from, const u32x4& v) {
+    return u32x4{(uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.x), (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.y),
+                 (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.z), (uint32_t)__builtin_amdgcn_ds_bpermute(from, (int)v.w)};
+  }
   __device__ __forceinline__ void settle(const LaneRawX<K, NB, G>& raw, int lane) {
+    using Raw = LaneRawX<K, NB, G>;
+    const int n = (lane >> 2) % Raw::P;          // the lane's quad in its group
 #pragma unroll
     for (int s = 0; s < NB / 4; ++s) {
       if constexpr (K == 4 && G == 1) {
         // quad 4 j + q: q = 0, 2 take odd columns, 1, 3 even ones
-        const bool even = (lane >> 2) & 1;
-        const u32x4 &lo = raw.v[s][0], &hi = raw.v[s][1];
+        const bool even = n & 1;
+        const int at = Raw::source(lane, (n & ~3) + ((n ^ n >> 1) & 1));
+        const u32x4 lo = pull(at, raw.v[s][0]), hi = pull(at + 8, raw.v[s][0]);
         const uint32_t sel = even ? 0x01000504u : 0x07060302u;   // even: the low half of the pair comes from lo
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
           const uint32_t h0 = even ? +hi[(2 * i + 3) & 3] : +hi[2 * i], h1 = even ? +hi[2 * i] : +hi[2 * i + 1];
           a[s][i] = (uint64_t)__builtin_amdgcn_perm(lo[2 * i + 1], h1, sel) << 32 | __builtin_amdgcn_perm(lo[2 * i], h0, sel);
         }
-      } else if constexpr (K == 4) {
-        // G = 2: (odd, even) of one t; G = 4: of t = 0, 1 (loads 0, 2 and 1, 3); G = 8: of two words
-#pragma unroll
-        for (int u = 0; u < G / 2; ++u) {
-          const int at = G == 2 ? 0 : 4 * (u >> 1) + (u & 1);
-          const u32x4 &lo = raw.v[s][at], &hi = raw.v[s][at + (G == 2 ? 1 : 2)];
-          uint64_t o[2], e[2];
-          odd_pairs(o, lo, hi);
-          even_pairs(e, lo, hi);
-          a[s][4 * u] = o[0]; a[s][4 * u + 1] = o[1];
-          a[s][4 * u + 2] = e[0]; a[s][4 * u + 3] = e[1];
-        }
       } else {
+        u32x4 v[G];
 #pragma unroll
-        for (int r = 0; r < G; ++r) {
-          a[s][2 * r] = (uint64_t)raw.v[s][r].y << 32 | raw.v[s][r].x;
-          a[s][2 * r + 1] = (uint64_t)raw.v[s][r].w << 32 | raw.v[s][r].z;
+        for (int r = 0; r < G; ++r) v[r] = pull(Raw::source(lane, n), raw.v[s][r]);
+        if constexpr (K == 4) {
+          // G = 2: (odd, even) of one t; G = 4: of t = 0, 1 (loads 0, 2 and 1, 3); G = 8: of two words
+#pragma unroll
+          for (int u = 0; u < G / 2; ++u) {
+            const int at = G == 2 ? 0 : 4 * (u >> 1) + (u & 1);
+            const u32x4 &lo = v[at], &hi = v[at + (G == 2 ? 1 : 2)];
+            uint64_t o[2], e[2];
+            odd_pairs(o, lo, hi);
+            even_pairs(e, lo, hi);
+            a[s][4 * u] = o[0]; a[s][4 * u + 1] = o[1];
+            a[s][4 * u + 2] = e[0]; a[s][4 * u + 3] = e[1];
+          }
+        } else {
+#pragma unroll
+          for (int r = 0; r < G; ++r) {
+            a[s][2 * r] = (uint64_t)v[r].y << 32 | v[r].x;
+            a[s][2 * r + 1] = (uint64_t)v[r].w << 32 | v[r].z;
+          }
         }
       }
     }
@@ -724,7 +738,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   const bool keep = NB == 1 && c1 - c0 <= kLaneKeepTiles;
   char* kept = ready + 256;
   const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
-  if constexpr (NB > 1) lane_sample_rows<NB>(job, lane, xrows);
+  if constexpr (NB > 1) lane_sample_rows<K, NB, 1>(job, lane, xrows);
   uint32_t xkeep[kLaneKeepTiles];
   if (keep) {
     if constexpr (kEarlyX) {
@@ -930,7 +944,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   const int c0 = wave * nsc / kLaneWaves, c1 = (wave + 1) * nsc / kLaneWaves;
   const DPLLM_GLOBAL u32x4* plane_rows = as_global(reinterpret_cast<const u32x4*>(job.arena)) + (size_t)(row / 64) * job.ncc * 64 + row % 64;
   const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
-  if constexpr (NB > 1) lane_sample_rows<NB>(job, lane, xrows);
+  if constexpr (NB > 1) lane_sample_rows<K, NB, G>(job, lane, xrows);
   auto load_x = [&](LaneTile<K, NB, G>& t, int sc) {
     if constexpr (NB > 1) lane_load_raw(t.x, xrows, sc * G + group, job.ncw, lane);
     else narrow_load_x(t, job, sc, lane);
