@@ -70,6 +70,14 @@ def _load():
 
 lib = _load()
 
+try:
+    from . import _calls
+except ImportError as e:
+    raise ImportError("_calls.so is not built: run `python -c 'import __graft_entry__ as g; g.build()'` "
+                      "(there is no fallback path)") from e
+_calls.bind(C.cast(lib.dpllm_gemv, C.c_void_p).value, C.cast(lib.dpllm_estimate, C.c_void_p).value,
+            torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+
 
 def _stream():
     """The current stream's handle.  torch.cuda.current_stream() builds a Stream object for it (2.9 us of a call of
@@ -120,6 +128,7 @@ class Model:
         if rc != 0:
             raise DpllmError(rc, "dpllm_model_create")
         self.h = h
+        self._address = h.value
         self.n = n_linears
         self.arenas = {}
         self.keep = {}
@@ -155,6 +164,7 @@ class Model:
         if self.h:
             lib.dpllm_model_destroy(self.h)
             self.h = None
+            self._address = 0
 
     def __del__(self):
         self.close()
@@ -212,6 +222,11 @@ class Model:
         _check(self.h, lib.dpllm_set_selector_input(self.h, id, _ptr(x_sel)))
 
     def dpllm_estimate(self, id, l, h, x, e_out=None, k_out=None):
+        if e_out is not None and k_out is not None and not self._ws_stale:
+            rc = _calls.estimate(self._address, id, l, h, x, e_out, k_out)
+            if rc != _calls.ELSEWHERE:
+                _check(self.h, rc)
+                return e_out, k_out
         e_out = torch.empty(1, dtype=torch.float32, device="cuda") if e_out is None else e_out
         k_out = torch.empty(1, dtype=torch.int32, device="cuda") if k_out is None else k_out
         self._need_workspace()
@@ -225,6 +240,11 @@ class Model:
 
     def dpllm_gemv(self, id, k, x, y=None, k_dev=None):
         """k >= 0: fixed bitwidth.  k < 0: read the bitwidth from k_dev on the device."""
+        if y is not None and not self._ws_stale:
+            rc = _calls.gemv(self._address, id, k, x, y, k_dev)
+            if rc != _calls.ELSEWHERE:
+                _check(self.h, rc)
+                return y
         out = self.shapes.get(id, (1,))[0]   # an unknown id is reported by the library
         B = 1 if x.dim() == 1 else x.shape[0]
         if y is None:
