@@ -115,8 +115,9 @@ struct Workspace {
   char* base = nullptr;
   size_t bytes = 0;
   size_t est_ws = 0;                         // dpllm_estimate in two launches: kSelOneSlots fp64
-  size_t est_slots = 0, est_slots_cap = 0;   // dpllm_estimate in one: uint64 [kEstRing][cap][2], empty between calls,
-  size_t est_marks = 0;                      //   and uint32 [kEstRing]: the captured call that does not rely on its slots any more
+  size_t est_sets = 0, est_slots_cap = 0;    // dpllm_estimate in one: [kEstRing] of a header, whose first dword is the captured call
+                                             //   that does not rely on its slots any more, and uint64 [cap][2], empty between calls
+  size_t est_set_words() const { return kEstHeader + 2 * est_slots_cap; }
   size_t target = 0;                         // the number of the active target
   size_t sel_params = 0;                     // SelParams [DPLLM_MAX_TARGETS][n]
   size_t sel_active = 0;                     // SelParams [n]: the row of the active target
@@ -240,8 +241,7 @@ Workspace carve_workspace(const dpllm_model* m) {
   auto take = [&](size_t bytes) { size_t o = off; off = align_up(off + bytes, kAlign); return o; };
   w.est_ws = take(sizeof(double) * kSelOneSlots);
   w.est_slots_cap = est;
-  w.est_slots = take(2 * sizeof(uint64_t) * kEstRing * est);
-  w.est_marks = take(sizeof(uint32_t) * kEstRing);
+  w.est_sets = take(sizeof(uint64_t) * kEstRing * w.est_set_words());
   w.target = take(sizeof(int32_t));
   w.sel_params = take(sizeof(SelParams) * DPLLM_MAX_TARGETS * n);
   w.sel_active = take(sizeof(SelParams) * n);
@@ -371,10 +371,13 @@ int pick_groups(long blocks64, int ncc) {
   return g;
 }
 
-void launch_lane(int groups, int nb, unsigned blocks, hipStream_t st, const GemvJob& one, int nrhs) {
+void launch_lane(const LinearLayout& L, const char* arena, int groups, int nb, int nblocks, int passes, hipStream_t st, int k, const int32_t* k_dev,
+                 const void* x, void* y, int nrhs) {
+  const uint32_t bits = LaneBits{k, L.kmin, L.p, nrhs}.pack();
+  const uint32_t lut = k_dev ? (uint32_t)L.lut_offset[L.kmin] - ((uint32_t)L.rows_padded << (L.kmin + 1)) : (uint32_t)L.lut_offset[k];
   auto go = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kLaneThreads), 0, st, one.arena, one.x, one.k_dev, one.plane_stride_u4,
-                       one.k_dev ? 0u : one.lut_off[one.k - 1], one.k, one.out, one.ncw, one.ncc, one.nblocks, nrhs, one);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(nblocks * passes)), dim3(kLaneThreads), 0, st, arena, (const uint16_t*)x, (uint16_t*)y, k_dev,
+                       (uint32_t)(L.plane_bytes / 16), lut, bits, L.out, L.ncw, nblocks);
   };
   if (nb == 1) {
     switch (groups) {
@@ -435,20 +438,18 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 // 17.0, k = 8 22.0 / 21.3; 4096 x 4096 k = 3 6.2 / 6.5, k = 4 7.0 / 8.2, k = 5 8.8 / 7.9; 4096 x 28672 k = 3 19.1 / 18.9, k = 4 21.4 / 25.9, k = 6 33.8 /
 // 27.1; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.3 / 6.3.  Fewer: 1000 x 4096 k = 5 6.5 / 7.4, 1500 x 14336 k = 3 9.9 / 12.4.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
-  GemvJob j = make_gemv_job(lin, k, k_dev, x, y);
   const int blocks = lin.L.nrq;
   const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= 4 * kLaneWaves;
   const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
   const int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
   const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc);
-  if (groups > 1) {
-    j.nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
-  } else {
+  int nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
+  if (groups == 1) {
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
-    j.nblocks = (lin.L.nrq + rpb - 1) / rpb;
+    nblocks = (lin.L.nrq + rpb - 1) / rpb;
   }
-  launch_lane(groups, nb, (unsigned)(j.nblocks * passes), st, j, B);
+  launch_lane(lin.L, lin.arena, groups, nb, nblocks, passes, st, k, k_dev, x, y, B);
   HIP_TRY(m, hipGetLastError());
   return DPLLM_OK;
 }
@@ -995,7 +996,7 @@ int dpllm_set_workspace(dpllm_model* m, void* ws_dev, size_t bytes, void* stream
   if (capturing(st)) w.est_slots_cap = 0;   // (emptied by a replay at some time to come: no estimate relies on it)
   else if (w.est_slots_cap > 0 && !m->ws_event) HIP_TRY(m, hipEventCreateWithFlags(&m->ws_event, hipEventDisableTiming));
   // the target starts at zero, the jobs without tasks, the slots of lone estimates empty; everything else is written before it is used
-  struct { size_t off, words; } zero[] = {{w.target, 1}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size()}, {w.est_slots, w.est_slots_cap * kEstRing * 4}, {w.est_marks, kEstRing}};
+  struct { size_t off, words; } zero[] = {{w.target, 1}, {w.gemv_jobs, sizeof(GemvJob) / 4 * m->linears.size()}, {w.est_sets, w.est_slots_cap > 0 ? w.est_set_words() * kEstRing * 2 : 0}};
   for (const auto& z : zero)
     if (z.words > 0)
       hipLaunchKernelGGL(fill_u32_kernel, dim3((unsigned)((z.words + 255) / 256)), dim3(256), 0, st, w.at<uint32_t>(z.off), z.words, 0u);
@@ -1185,7 +1186,7 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
   const Workspace& W = m->ws;
   const int rowgroups = sel_rowgroups_of(sel.kind, sel.r);
   SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups);
-  if (sel.kind == DPLLM_SEL_PROJ && (sel.r > kEstMaxRank || (size_t)j.ws_rows * j.nchunks > W.est_slots_cap)) return false;
+  if (lin.L.ncw > kEstMaxWords || (sel.kind == DPLLM_SEL_PROJ && (sel.r > kEstMaxRank || (size_t)j.ws_rows * j.nchunks > W.est_slots_cap))) return false;
   if (!m->est_ready && sel.kind == DPLLM_SEL_PROJ) {
     // the slots are empty for work behind dpllm_set_workspace on its stream, for any other once that has been seen to be done
     if (!capturing(st) && passed(m->ws_event)) m->est_ready = true;
@@ -1195,9 +1196,12 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
   const unsigned set = m->est_turn % kEstRing;
   const int polls = m->polls == kSelPolls ? kEstPolls : std::max(m->polls, 0);
   const int parts = sel.kind == DPLLM_SEL_PROJ ? (sel.r + kEstPartRows - 1) / kEstPartRows * j.nchunks : 1;
-  hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, j.x,
-                     W.at<uint64_t>(W.est_slots) + set * W.est_slots_cap * 2, j.in, sel.r, j.nchunks, j.chunk_cols, j.ws_rows, sel.kind, m->est_turn, j,
-                     make_params(sel, sel.T), sel.kind == DPLLM_SEL_PROJ && capturing(st) ? W.at<uint32_t>(W.est_marks) + set : nullptr, polls);
+  const bool proj = sel.kind == DPLLM_SEL_PROJ;
+  const EstShape shape{lin.L.ncw, proj ? j.nchunks : 0, proj ? j.ws_rows : 0};
+  const EstPair pair{proj ? j.chunk_cols : 0, proj ? sel.r : 0, sel.kind, proj && capturing(st), sel.l, sel.h};
+  hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, (const uint16_t*)x_dev,
+                     W.at<uint64_t>(W.est_sets) + set * W.est_set_words() + kEstHeader, e_dev, k_dev, shape.pack(), pair.pack(), m->est_turn, polls, sel.T, sel.alpha,
+                     sel.beta);
   return true;
 }
 

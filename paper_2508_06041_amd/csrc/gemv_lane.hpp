@@ -1028,14 +1028,6 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 template <int NB, int G>
 __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpret_cast<double*>(lds + lane_lds_bytes<NB, G>() - kSelSharedBytes); }
 
-// byte offset of the k-bit tables (by constant index: a run-time index would put the job record in scratch memory)
-__device__ __forceinline__ uint32_t lane_lut_off(const GemvJob& job, int k) {
-  uint32_t off = job.lut_off[0];
-#pragma unroll
-  for (int j = 1; j < kKMax; ++j) off = k == j + 1 ? job.lut_off[j] : off;
-  return off;
-}
-
 // lut_off(K as a constant): byte offset of the K-bit tables
 template <int NB, int G, class Off>
 __device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, Off lut_off, int block, int tid, char* lds) {
@@ -1078,40 +1070,46 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
   gemv_lane_width<NB, G>(job, k, [&](auto kc) { return job.lut_off[decltype(kc)::value - 1]; }, block, tid, lds);
 }
 
-// One linear, for nrhs right-hand sides in groups of NB that share one pass over the planes (group g reads x + g * NB * in
-// and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) * nblocks) serve it).  What a workgroup needs to ask for its
-// first tiles and tables comes as plain arguments, which fit the registers that are set with the launch; a record passed
-// by value is loaded from memory first.  us per call, record -> arguments: 4096 x 4096 k = 4 5.7 -> 5.2, 2500 x 6688 k = 7
-// 9.6 -> 9.2, 4096 x 11008 k = 2 7.3 -> 7.1.
+// One linear, for several right-hand sides in groups of NB that share one pass over the planes (group g reads x + g * NB * in
+// and writes y + g * NB * out; workgroups [g * nblocks, (g + 1) * nblocks) serve it).  All that a workgroup needs comes as plain arguments,
+// fourteen dwords, which fit the registers that are set with the launch: nothing is loaded from the argument memory, and the host writes
+// 56 bytes instead of 320.  us per call of a loop in Python, with a record by value for what is not needed first -> now: 1024 x 4096 k = 3
+// 4.4 -> 4.05, 11008 x 4096 k = 4 8.8 -> 8.7; an estimate and a GEMV of 4096 x 4096, both so, 10.2 -> 9.7, in a graph 9.7 -> 9.6.
+// bits: LaneBits; lut: byte offset of the tables in the arena, less (rows << (k + 1)) where k_dev says the bitwidth (rows padded to 64).
+struct LaneBits {
+  int k, kmin, p, nrhs;                      // the bitwidth unless k_dev says it; those the linear serves; right-hand sides
+  __host__ __device__ uint32_t pack() const { return (uint32_t)(k | kmin << 4 | p << 8 | nrhs << 12); }
+  static __host__ __device__ LaneBits unpack(uint32_t v) { return {(int)(v & 15), (int)(v >> 4 & 15), (int)(v >> 8 & 15), (int)(v >> 12)}; }
+};
 template <int NB, int G>
-__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const char* arena, const uint16_t* x, const int32_t* k_dev,
-                                                                                uint32_t plane_stride_u4, uint32_t lut_off, int k, int out,
-                                                                                int ncw, int ncc, int nblocks, int nrhs, GemvJob one) {
+__global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const char* arena, const uint16_t* x, uint16_t* y, const int32_t* k_dev,
+                                                                                uint32_t plane_stride_u4, uint32_t lut, uint32_t bits, int out,
+                                                                                int ncw, int nblocks) {
   __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB, G>()];
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
+  const LaneBits b = LaneBits::unpack(bits);
   const int group = NB == 1 ? 0 : blockIdx.x / nblocks;
-  GemvJob job = one;
+  GemvJob job{};
   job.arena = arena;
   job.x = x + (size_t)group * NB * ncw * 32;
-  job.y += (size_t)group * NB * out;
-  job.k_dev = k_dev;
+  job.y = y + (size_t)group * NB * out;
   job.plane_stride_u4 = plane_stride_u4;
-  job.k = k;
   job.out = out;
   job.ncw = ncw;
-  job.ncc = ncc;
+  job.ncc = (ncw + 3) / 4;
   job.nrq = (out + 63) / 64;
   job.nblocks = nblocks;
-  job.nsamples = min(NB, nrhs - group * NB);
+  job.nsamples = min(NB, b.nrhs - group * NB);
   const int block = blockIdx.x - group * nblocks;
   if (block * (64 / G) >= out) return;
+  int k = b.k;
   if (k_dev != nullptr) {
     k = load_record(k_dev);
-    if (k < one.kmin || k > one.p) return;
-    lut_off = lane_lut_off(one, k);
+    if (k < b.kmin || k > b.p) return;
+    lut += (uint32_t)job.nrq << (k + 7);
   }
-  gemv_lane_width<NB, G>(job, k, [&](auto) { return lut_off; }, block, threadIdx.x, lds);
+  gemv_lane_width<NB, G>(job, k, [&](auto) { return lut; }, block, threadIdx.x, lds);
 }
 
 // The linears of a dependency level of a decode step: block b < nblocks belongs to job block_jobs[b]; blocks past them

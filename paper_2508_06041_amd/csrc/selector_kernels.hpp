@@ -586,7 +586,7 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
 // finds its own there (or that several calls have given up) computes for itself too.  (A wait is given up where calls of one model
 // overlap, which the header rules out: their products overwrite one another.)  Launches take turns in kEstRing sets of slots.
 // What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection.
-// us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> now: rank 64 of 4096 columns
+// us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> one: rank 64 of 4096 columns
 // 4.5 / 7.4 -> 4.5 / 4.8, of 11008 5.3 / 7.6 -> 5.2 / 5.0, rank 128 of 11008 5.6 / 7.3 -> 5.3 / 5.8, rank 256 of 4096 5.2 / 7.5 -> 5.1 / 4.8, linear
 // regression 3.7 / 7.5 -> 2.0 / 4.9 (eager: the host takes 4.2 for a call).  With more rows the second launch is gained back: rank 256 of
 // 11008 7.1 .. 8.0 / 7.5 .. 8.4 (by where the memory lies) and 8.0 / 7.5, rank 512 of 8192 8.7 / 9.1 and 8.8 / 9.0; beyond the lanes of the
@@ -632,21 +632,45 @@ __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slot
   return !marked;
 }
 
-// G .. kind: what a workgroup needs to ask for its first rows comes as plain arguments (see gemv_lane_kernel)
-// mark_of: the mark of the set of slots; nullptr: the call is not captured
-__global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, uint64_t* ws, int in, int r,
-                                                                           int nchunks, int chunk_cols, int ws_rows, int kind, uint32_t tag, SelJob job,
-                                                                           SelParams P, uint32_t* mark_of, int polls) {
+// What all workgroups need, and what the last one does where it is on its way, comes as plain arguments that are set in registers with the
+// launch (see gemv_lane_kernel): fourteen dwords, so the small ones are packed.  Threshold and constants are loaded from the argument
+// memory: by the last wavefront of a projection, which has nothing else to do then, through LDS.
+struct EstShape {
+  int words, nchunks, ws_rows;               // 32-column words of the vector (16 bits); chunks; rows of a chunk's slots (a multiple of 16, up to 496)
+  __host__ __device__ uint32_t pack() const { return (uint32_t)(words | nchunks << 16 | ws_rows / kSelPartRows << 22); }
+  static __host__ __device__ EstShape unpack(uint32_t v) { return {(int)(v & 0xffff), (int)(v >> 16 & 63), (int)(v >> 22 & 31) * kSelPartRows}; }
+};
+constexpr int kEstMaxWords = 65535 / 16 * 16;   // (whole chunks of 512 columns in 12 bits)
+struct EstPair {
+  int chunk_cols, r, kind, captured, l, h;   // a multiple of 512; up to kEstMaxRank; SelParams; whether a graph holds the call
+  __host__ __device__ uint32_t pack() const {
+    return (uint32_t)(chunk_cols / kSelChunkStep | r << 12 | kind << 21 | captured << 23) | (uint32_t)l << 24 | (uint32_t)h << 28;
+  }
+  static __host__ __device__ EstPair unpack(uint32_t v) {
+    return {(int)(v & 0xfff) * kSelChunkStep, (int)(v >> 12 & 0x1ff), (int)(v >> 21 & 3), (int)(v >> 23 & 1), (int)(v >> 24 & 15), (int)(v >> 28)};
+  }
+};
+// A set of slots is a header of kEstHeader 64-bit words, whose first dword is its mark, and the slots (ws).
+constexpr int kEstHeader = 16;
+__global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, uint64_t* ws, float* e_out, int32_t* k_out,
+                                                                           uint32_t shape, uint32_t pair, uint32_t tag, int polls, float T, float alpha,
+                                                                           float beta) {
   __shared__ SelShared sh;
   __shared__ int here[kSelPartWaves];
+  __shared__ float threshold;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const EstShape S = EstShape::unpack(shape);
+  const EstPair Q = EstPair::unpack(pair);
+  const int in = S.words * 32, nchunks = S.nchunks, ws_rows = S.ws_rows, r = Q.r, kind = Q.kind;
+  SelParams P{};
   P.G = G; P.r = r; P.kind = kind;
-  job.x = x; job.in = in; job.nchunks = nchunks; job.chunk_cols = chunk_cols;
+  SelJob job{};
+  job.x = x; job.in = in; job.nchunks = nchunks; job.chunk_cols = Q.chunk_cols;
   double e = 0.0;
   if (kind == 1) {
     static_assert(kEstRows == 1 && kEstMaxRank <= kSelPartThreads, "a product a wavefront, a row a lane");
     DPLLM_SEL_GLOBAL uint64_t* slots = (DPLLM_SEL_GLOBAL uint64_t*)ws;
-    DPLLM_SEL_GLOBAL uint32_t* mark = (DPLLM_SEL_GLOBAL uint32_t*)mark_of;
+    DPLLM_SEL_GLOBAL uint32_t* mark = (DPLLM_SEL_GLOBAL uint32_t*)(slots - kEstHeader);
     const int rg = blockIdx.x / nchunks, ch = blockIdx.x - rg * nchunks, row = rg * kEstPartRows + wave;
     double g[1];
     selector_part_products<true>(job, P, row, ch, wave, lane, g);
@@ -657,7 +681,8 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
       __hip_atomic_store(slot + ws_rows, (uint64_t)tag << 32 | v >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (blockIdx.x + 1 != gridDim.x) return;
-    const uint32_t found = mark_of != nullptr ? __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+    if (wave == kSelPartWaves - 1 && lane == 0) threshold = T;
+    const uint32_t found = Q.captured ? __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     const bool marked = found == tag || found == kEstAll;
     bool all = true;
     if (wave * 64 < r) {
@@ -670,7 +695,7 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     if (!(here[0] && here[1] && here[2] && here[3])) {
       static_assert(kSelPartWaves == 4, "flags");
       __syncthreads();
-      if (tid == 0 && mark_of != nullptr) {
+      if (tid == 0 && Q.captured) {
         uint32_t was = 0u;
         if (!__hip_atomic_compare_exchange_strong(mark, &was, tag, __ATOMIC_RELAXED, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) && was != tag)
           __hip_atomic_store(mark, kEstAll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -690,6 +715,7 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     double part = 0.0;
     for (int t = tid; t < r; t += 64) part += sh.sq[t];
     e = sqrt(wave_sum_f64(part));
+    T = threshold;
   } else if (kind == 2) {
     // as selector_group_part does
     double acc = 0.0;
@@ -707,11 +733,11 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     __syncthreads();
     double tot = 0.0;
     for (int w = 0; w < kSelPartWaves; ++w) tot += sh.sq[w];
-    e = (double)P.alpha * sqrt(tot) + (double)P.beta;
+    e = (double)alpha * sqrt(tot) + (double)beta;
   }
   if (tid == 0) {
-    *job.e_out = (float)e;
-    *job.k_out = kind != 0 && e > (double)P.T ? P.h : P.l;
+    *e_out = (float)e;
+    *k_out = kind != 0 && e > (double)T ? Q.h : Q.l;
   }
 }
 
