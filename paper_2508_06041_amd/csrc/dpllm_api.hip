@@ -63,6 +63,12 @@ struct Linear {
       if (s.set) g = std::max(g, sel_rowgroups_of(s.kind, s.r));
     return g;
   }
+  int least_k() const {   // the smallest bitwidth its selectors choose; without selectors the largest there is
+    int k = L.p;
+    for (const Pair& s : sel)
+      if (s.set) k = std::min(k, s.l);
+    return k;
+  }
   int part_k() const {   // the bitwidth the work of a step launch is cut for: the larger one of the pair of target 0
     return active >= 0 ? sel[active].h : L.p;
   }
@@ -386,6 +392,8 @@ void launch_lane(const LinearLayout& L, const char* arena, int groups, int nb, i
       case 4: go(gemv_lane_kernel<1, 4>); break;
       default: go(gemv_lane_kernel<1, 8>); break;
     }
+  } else if (nb == 2) {
+    go(gemv_lane_kernel<2, 1>);
   } else if (nb == 4) {
     switch (groups) {
       case 1: go(gemv_lane_kernel<4, 1>); break;
@@ -437,13 +445,20 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 // k = 5 7.8 / 6.8, k = 8 10.1 / 8.3; 8192 x 1024 k = 3 4.2 / 4.7, k = 5 5.8 / 5.8, k = 8 7.7 / 7.1.  33 to 64: 4096 x 14336 k = 3 11.5 / 12.9, k = 5 18.9 /
 // 17.0, k = 8 22.0 / 21.3; 4096 x 4096 k = 3 6.2 / 6.5, k = 4 7.0 / 8.2, k = 5 8.8 / 7.9; 4096 x 28672 k = 3 19.1 / 18.9, k = 4 21.4 / 25.9, k = 6 33.8 /
 // 27.1; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.3 / 6.3.  Fewer: 1000 x 4096 k = 5 6.5 / 7.4, 1500 x 14336 k = 3 9.9 / 12.4.
+// One right-hand side, blocks of 64 rows: on the matrix pipe, four equal sums a lane, which spares parking the activations and a fifth of the
+// vector instructions.  us per call, vector / matrix pipe: 9000 x 4096 k = 3 7.0 / 6.5, k = 4 8.8 / 7.7, k = 5 10.9 / 11.0, k = 7 13.8 / 14.2; 11008 x
+// 4096 k = 2 7.1 / 6.5, k = 4 9.0 / 8.0, k = 6 12.1 / 12.6; 28672 x 4096 k = 4 12.7 / 11.9, k = 5 17.9 / 18.0; more tiles than a wavefront keeps
+// the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth: 14336 x 14336 k = 2 21.9 / 16.0, k = 4 22.0 /
+// 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0, k = 8 43.0 / 41.4.  With several
+// column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   const int blocks = lin.L.nrq;
   const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= 4 * kLaneWaves;
   const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
-  const int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
+  int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
   const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc);
+  if (B == 1 && groups == 1 && ((k_dev ? lin.least_k() : k) <= 4 || lin.L.ncc > kLaneWaves * kLaneKeepTiles)) nb = 2;
   int nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   if (groups == 1) {
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);

@@ -79,6 +79,9 @@ static_assert(LaneDecode<2>::table_bytes <= kLaneTableBytes && LaneDecode<3>::ta
 // G column groups per wavefront (see below); bytes from one group's parked activations to the next: 64 more than a
 // tile's 256, so that the groups' reads of the same word fall on different banks
 constexpr int kLaneGroupStride = 320;
+// NB: 1 right-hand side per pass on the vector pipe, 4 or 8 on the matrix pipe, 2: one on the matrix pipe.
+__host__ __device__ constexpr int lane_samples(int nb) { return nb == 2 ? 1 : nb; }
+__host__ __device__ constexpr int lane_sets(int nb) { return nb == 8 ? 2 : 1; }   // of four samples
 // One right-hand side: a slot per wavefront for the parked activations of its tiles (G of them); with one group four more
 // for the tiles it keeps across row blocks.  Several right-hand sides read their activations from memory in the form they are used in.
 template <int NB, int G>
@@ -93,7 +96,7 @@ __host__ __device__ constexpr int lane_x_bytes() {
 template <int NB>
 __host__ __device__ constexpr int lane_red_offset() { return NB == 8 ? 0 : kLaneTableBytes; }
 template <int NB>
-__host__ __device__ constexpr int lane_x_offset() { return NB == 8 ? kLaneTableBytes : kLaneTableBytes + NB * kLaneRedBytes; }
+__host__ __device__ constexpr int lane_x_offset() { return NB == 8 ? kLaneTableBytes : kLaneTableBytes + lane_samples(NB) * kLaneRedBytes; }
 template <int NB, int G>
 __host__ __device__ constexpr int lane_lds_bytes() {
   return lane_x_offset<NB>() + kLaneWaves * lane_x_bytes<NB, G>() + (NB == 1 ? kSelSharedBytes : 0);
@@ -140,6 +143,13 @@ struct LaneAcc<1> {
   // the compiler keeps that distance behind instructions it knows, not behind inline asm
   __device__ __forceinline__ void settle() { asm("s_nop 2" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]), "+v"(v[3])); }
   __device__ __forceinline__ float sum(int) const { return (v[0] + v[1]) + (v[2] + v[3]); }
+};
+template <>
+struct LaneAcc<2> {
+  f32x4 v[2];
+  __device__ __forceinline__ void zero() { v[0] = v[1] = f32x4{0.f, 0.f, 0.f, 0.f}; }
+  __device__ __forceinline__ void settle() {}
+  __device__ __forceinline__ float sum(int) const { return v[0][0] + v[1][0]; }   // (four times the same)
 };
 template <>
 struct LaneAcc<4> {
@@ -193,7 +203,8 @@ __device__ __forceinline__ uint32_t lds_u32(const char* lds, uint32_t addr) { re
 template <int K, int NB, int G>
 struct LaneRawX {
   static constexpr int P = 16 / G;
-  u32x4 v[NB / 4][G];
+  static constexpr int kLoads = G;
+  u32x4 v[lane_sets(NB)][kLoads];
   // what lane `lane` loads: of which sample (of four), and the column of load r inside the tile
   static __device__ __forceinline__ int sample(int lane) { return lane % (4 * P) / P; }
   static __device__ __forceinline__ int column(int lane, int r) {
@@ -204,6 +215,18 @@ struct LaneRawX {
   }
   // the lane whose loads quad n of the lane's group needs for its own sample (as the address of a bpermute)
   static __device__ __forceinline__ int source(int lane, int n) { return 4 * ((lane & -(4 * P)) + (lane & 3) * P + n); }
+};
+// One sample on the matrix pipe: every lane loads the eights of its own quad (four lanes the same).
+template <int K>
+struct LaneRawX<K, 2, 1> {
+  static constexpr int P = 16;
+  static constexpr int kLoads = K == 4 ? 2 : 1;
+  u32x4 v[1][kLoads];
+  static __device__ __forceinline__ int sample(int) { return 0; }
+  static __device__ __forceinline__ int column(int lane, int r) {
+    const int n = lane >> 2;
+    return K == 4 ? 32 * (n >> 2) + 8 * ((n ^ n >> 1) & 1) + 16 * r : 8 * n;
+  }
 };
 template <int K, int G>
 struct LaneRawX<K, 1, G> {
@@ -231,28 +254,28 @@ __device__ __forceinline__ uint32_t lane_mask_x(const GemvJob& job, int cc, int 
 // Several samples: asks for the lane's part of the activations of tile `tile` (clamped to the row).  rows[s]: the vector of
 // the lane's sample among 4 s .. 4 s + 3; a group with fewer than NB samples re-reads its last one (the sums are not stored).
 template <int K, int NB, int G>
-__device__ __forceinline__ void lane_load_raw(LaneRawX<K, NB, G>& x, const DPLLM_GLOBAL uint16_t* const (&rows)[NB / 4], int tile, int ncw, int lane) {
+__device__ __forceinline__ void lane_load_raw(LaneRawX<K, NB, G>& x, const DPLLM_GLOBAL uint16_t* const (&rows)[lane_sets(NB)], int tile, int ncw, int lane) {
 #pragma unroll
-  for (int r = 0; r < G; ++r) {
+  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
     const int c = min(tile * 128 + LaneRawX<K, NB, G>::column(lane, r), ncw * 32 - 8);
 #pragma unroll
-    for (int s = 0; s < NB / 4; ++s) x.v[s][r] = *reinterpret_cast<const DPLLM_GLOBAL u32x4*>(rows[s] + c);
+    for (int s = 0; s < lane_sets(NB); ++s) x.v[s][r] = *reinterpret_cast<const DPLLM_GLOBAL u32x4*>(rows[s] + c);
   }
 }
 // columns past the end of a ragged row (eight are inside or outside together) read as 0
 template <int K, int NB, int G>
 __device__ __forceinline__ void lane_mask_raw(LaneRawX<K, NB, G>& x, int tile, int ncw, int lane) {
 #pragma unroll
-  for (int r = 0; r < G; ++r) {
+  for (int r = 0; r < LaneRawX<K, NB, G>::kLoads; ++r) {
     const bool inside = tile * 128 + LaneRawX<K, NB, G>::column(lane, r) < ncw * 32;
 #pragma unroll
-    for (int s = 0; s < NB / 4; ++s) x.v[s][r] = inside ? x.v[s][r] : u32x4{0u, 0u, 0u, 0u};
+    for (int s = 0; s < lane_sets(NB); ++s) x.v[s][r] = inside ? x.v[s][r] : u32x4{0u, 0u, 0u, 0u};
   }
 }
 template <int K, int NB, int G>
-__device__ __forceinline__ void lane_sample_rows(const GemvJob& job, int lane, const DPLLM_GLOBAL uint16_t* (&rows)[NB / 4]) {
+__device__ __forceinline__ void lane_sample_rows(const GemvJob& job, int lane, const DPLLM_GLOBAL uint16_t* (&rows)[lane_sets(NB)]) {
 #pragma unroll
-  for (int s = 0; s < NB / 4; ++s)
+  for (int s = 0; s < lane_sets(NB); ++s)
     rows[s] = as_global(job.x) + (size_t)min(4 * s + LaneRawX<K, NB, G>::sample(lane), job.nsamples - 1) * job.ncw * 32;
 }
 
@@ -395,7 +418,7 @@ __device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32
 // lane in word 0 (slot + 16 * (lane mod 4)), those of word j 64 j bytes on.
 template <int K, int NB, int G>
 struct LaneX {   // several samples: operands of the matrix instructions
-  uint64_t a[NB / 4][2 * G];   // a[s][h]: the h-th chunk of the lane's quad (see LaneRawX), of sample 4 s + lane mod 4
+  uint64_t a[lane_sets(NB)][2 * G];   // a[s][h]: the h-th chunk of the lane's quad (see LaneRawX), of sample 4 s + lane mod 4
   // which quad of the group and which of its operands holds chunk c
   static constexpr int quad(int c) {
     if constexpr (K == 4) {
@@ -431,12 +454,16 @@ struct LaneX {   // several samples: operands of the matrix instructions
     using Raw = LaneRawX<K, NB, G>;
     const int n = (lane >> 2) % Raw::P;          // the lane's quad in its group
 #pragma unroll
-    for (int s = 0; s < NB / 4; ++s) {
+    for (int s = 0; s < lane_sets(NB); ++s) {
       if constexpr (K == 4 && G == 1) {
         // quad 4 j + q: q = 0, 2 take odd columns, 1, 3 even ones
         const bool even = n & 1;
-        const int at = Raw::source(lane, (n & ~3) + ((n ^ n >> 1) & 1));
-        const u32x4 lo = pull(at, raw.v[s][0]), hi = pull(at + 8, raw.v[s][0]);
+        u32x4 lo = raw.v[s][0], hi = raw.v[s][Raw::kLoads - 1];
+        if constexpr (NB > 2) {
+          const int at = Raw::source(lane, (n & ~3) + ((n ^ n >> 1) & 1));
+          lo = pull(at, raw.v[s][0]);
+          hi = pull(at + 8, raw.v[s][0]);
+        }
         const uint32_t sel = even ? 0x01000504u : 0x07060302u;   // even: the low half of the pair comes from lo
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
@@ -446,7 +473,10 @@ struct LaneX {   // several samples: operands of the matrix instructions
       } else {
         u32x4 v[G];
 #pragma unroll
-        for (int r = 0; r < G; ++r) v[r] = pull(Raw::source(lane, n), raw.v[s][r]);
+        for (int r = 0; r < G; ++r) {
+          if constexpr (NB > 2) v[r] = pull(Raw::source(lane, n), raw.v[s][r]);
+          else v[r] = raw.v[s][r];
+        }
         if constexpr (K == 4) {
           // G = 2: (odd, even) of one t; G = 4: of t = 0, 1 (loads 0, 2 and 1, 3); G = 8: of two words
 #pragma unroll
@@ -737,7 +767,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   constexpr bool kEarlyX = K != 4;
   const bool keep = NB == 1 && c1 - c0 <= kLaneKeepTiles;
   char* kept = ready + 256;
-  const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
+  const DPLLM_GLOBAL uint16_t* xrows[lane_sets(NB)];
   if constexpr (NB > 1) lane_sample_rows<K, NB, 1>(job, lane, xrows);
   uint32_t xkeep[kLaneKeepTiles];
   if (keep) {
@@ -794,10 +824,10 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
       sched_fence();
     }
 #pragma unroll
-    for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = acc.sum(b);
+    for (int b = 0; b < lane_samples(NB); ++b) red[(b * kLaneWaves + wave) * 64 + lane] = acc.sum(b);
     acc.zero();
     lds_barrier();
-    const bool storer = wave < NB && (NB == 1 || wave < job.nsamples);   // wavefront b stores sample b
+    const bool storer = wave < lane_samples(NB) && (lane_samples(NB) == 1 || wave < job.nsamples);   // wavefront b stores sample b
     float s = 0.f;
     if (storer) {
 #pragma unroll
@@ -943,7 +973,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   const int nsc = (job.ncc + G - 1) / G;
   const int c0 = wave * nsc / kLaneWaves, c1 = (wave + 1) * nsc / kLaneWaves;
   const DPLLM_GLOBAL u32x4* plane_rows = as_global(reinterpret_cast<const u32x4*>(job.arena)) + (size_t)(row / 64) * job.ncc * 64 + row % 64;
-  const DPLLM_GLOBAL uint16_t* xrows[NB > 1 ? NB / 4 : 1];
+  const DPLLM_GLOBAL uint16_t* xrows[lane_sets(NB)];
   if constexpr (NB > 1) lane_sample_rows<K, NB, G>(job, lane, xrows);
   auto load_x = [&](LaneTile<K, NB, G>& t, int sc) {
     if constexpr (NB > 1) lane_load_raw(t.x, xrows, sc * G + group, job.ncw, lane);
@@ -971,14 +1001,14 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   }
   LaneAcc<NB> acc;
   acc.zero();
-  float done[NB];   // the sums before the last step, where lanes may be without a tile
+  float done[lane_samples(NB)];   // the sums before the last step, where lanes may be without a tile
   // The wait between a step's last dot product and the sum (LaneAcc<1>::settle) stands in front of the sum, at k = 7 behind the step.  us of
   // a loop of calls without a wait / in front / behind: 2500 x 6688 k = 7 74.4 / 75.0 / 74.5; 4096 x 4096 k = 4 81.2 / 80.2 / 81.0, k = 3 72.6 /
   // 71.9 / 72.5, k = 8 61.6 / 61.4 / 61.6; 4096 x 11008 k = 4 68.1 / 67.0 / 67.6, k = 2 56.2 / 55.8 / 55.5; 2500 x 6688 k = 5 61.5 / 61.5 / 61.0.
   // (Behind at every k >= 5 costs k = 3 and 4 what they gain here: how the code of one bitwidth lies moves the others by a per cent.)
   constexpr bool kSettleBehind = K == 7;
 #pragma unroll
-  for (int b = 0; b < NB; ++b) done[b] = 0.f;
+  for (int b = 0; b < lane_samples(NB); ++b) done[b] = 0.f;
   LaneMasks<K> M;
   M.init();
   uint32_t addr[8], mask = LaneDecode<K>::pair ? LaneDecode<K>::pair_mask : 0;   // k <= 3 (see lane_issue_pairs)
@@ -992,7 +1022,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
       if (cc != c0) park(ring[s], cc);
       if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
-      for (int b = 0; b < NB; ++b) done[b] = acc.sum(b);
+      for (int b = 0; b < lane_samples(NB); ++b) done[b] = acc.sum(b);
       const int tile = cc * G + group;
       const bool ragged = (cc + 1) * G * 4 > job.ncw;
       LaneX<K, NB, G> x;
@@ -1014,9 +1044,9 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   if constexpr (NB == 8) lds_barrier();   // the tables, which the sums take the place of, are done with
   if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
-  for (int b = 0; b < NB; ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
+  for (int b = 0; b < lane_samples(NB); ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
   lds_barrier();
-  if (wave < NB && (NB == 1 || wave < job.nsamples)) {   // wavefront b stores sample b
+  if (wave < lane_samples(NB) && (lane_samples(NB) == 1 || wave < job.nsamples)) {   // wavefront b stores sample b
     float s = 0.f;
 #pragma unroll
     for (int w = 0; w < kLaneWaves; ++w) s += red[(wave * kLaneWaves + w) * 64 + lane];
@@ -1089,7 +1119,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
   const LaneBits b = LaneBits::unpack(bits);
-  const int group = NB == 1 ? 0 : blockIdx.x / nblocks;
+  const int group = lane_samples(NB) == 1 ? 0 : blockIdx.x / nblocks;
   GemvJob job{};
   job.arena = arena;
   job.x = x + (size_t)group * NB * ncw * 32;
@@ -1100,7 +1130,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   job.ncc = (ncw + 3) / 4;
   job.nrq = (out + 63) / 64;
   job.nblocks = nblocks;
-  job.nsamples = min(NB, b.nrhs - group * NB);
+  job.nsamples = min(lane_samples(NB), b.nrhs - group * NB);
   const int block = blockIdx.x - group * nblocks;
   if (block * (64 / G) >= out) return;
   int k = b.k;

@@ -9,9 +9,11 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-# four samples with 1, 2, 4 and 8 column groups per wavefront; eight with 1 and 4.  The columns: every place of a word, in the
+# four samples with 1, 2, 4 and 8 column groups per wavefront; eight with 1 and 4; one on the matrix pipe, rows of few and of many
+# tiles (5 bits and more: the second only).  The columns: every place of a word, in the
 # first tile, one in the middle and the ragged last one
-@pytest.mark.parametrize("out,in_,B", [(8200, 288, 4), (4200, 288, 3), (2100, 800, 2), (100, 8192 + 96, 4), (8200, 288, 8), (2049, 4096 + 96, 5)])
+@pytest.mark.parametrize("out,in_,B", [(8200, 288, 4), (4200, 288, 3), (2100, 800, 2), (100, 8192 + 96, 4), (8200, 288, 8), (2049, 4096 + 96, 5), (8200, 288, 1),
+                                      (8200, 4096 + 96, 1)])
 def test_one_column_at_a_time(out, in_, B):
     import paper_2508_06041_amd as dp
     lin = synth.make_linear(out, in_, 6, 1, seed=out + in_, device="cuda", keep_codes=False)
