@@ -222,7 +222,7 @@ int sel_slices(int in) { return (in + kSelTaskCols - 1) / kSelTaskCols; }
 
 // slots of an estimate in one launch: 16 rows of G in chunks of 512 columns and more
 size_t est_slots_of(const Linear& lin, int rowgroups) {
-  return (size_t)std::min(rowgroups * kSelPartRows, kEstMaxRank) * std::min(kSelMaxChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
+  return (size_t)std::min(rowgroups * kSelPartRows, kEstMaxRank) * std::min(kEstChunks, (lin.L.in + kSelChunkStep - 1) / kSelChunkStep);
 }
 
 // 64-bit words of a linear's mailbox (whole lines: no two linears share one)
@@ -281,8 +281,8 @@ SelParams make_params(const Pair& s, float T) {
 }
 
 // launch_rowgroups: groups of 16 rows of G over all jobs of the launch.  A launch with fewer of them than
-// would fill the chip cuts the columns into chunks (multiples of 512 columns) as well.
-SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x, float* e_dev, int32_t* k_dev, long launch_rowgroups) {
+// would fill the chip cuts the columns into chunks (multiples of 512 columns) as well, at most `most` of them.
+SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x, float* e_dev, int32_t* k_dev, long launch_rowgroups, long most = kSelMaxChunks) {
   SelJob j;
   j.x = (const uint16_t*)x;
   j.e_out = e_dev;
@@ -297,13 +297,14 @@ SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x,
     constexpr long max_cols = 4096;
     long want = std::min<long>(kSelMaxChunks, 1152 / std::max<long>(1, launch_rowgroups));   // 1280 parts run at once
     want = std::max<long>(want, std::min<long>(kSelMaxChunks, (lin.L.in + max_cols - 1) / max_cols));
+    want = std::min(want, most);
     if (want > 1) {
       j.chunk_cols = (int)((lin.L.in + want - 1) / want + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;   // <= want chunks
       j.nchunks = (lin.L.in + j.chunk_cols - 1) / j.chunk_cols;
     }
   }
   j.ws_rows = std::max(1, rowgroups) * kSelPartRows;
-  j.pad = 0;
+  j.row_each = 0;
   return j;
 }
 
@@ -1177,14 +1178,26 @@ int dpllm_set_selector_input(dpllm_model* m, int id, const void* xsel_dev) {
   return DPLLM_OK;
 }
 
+// The job of a lone estimate.  Up to the ranks that one launch serves, the columns are cut into no more chunks than its last workgroup
+// collects at a time; the ways an estimate may take share the cut, and with it the bits.  us of a dpllm_estimate in a graph, up to 32 chunks /
+// 12: rank 64 of 8192 columns 4.9 / 4.5, 11008 5.3 / 4.8, 14336 6.3 / 5.2, 28672 6.9 / 6.2; rank 256 of 8192 6.9 / 5.3, 28672 11.3 / 7.8 (8 chunks: rank 64 of
+// 5120 4.4 where 12 take 4.1, of 28672 6.7).
+static SelJob lone_job(const Linear& lin, int id, int rowgroups, const void* x_dev, float* e_dev, int32_t* k_dev) {
+  const bool few = rowgroups * kSelPartRows <= kEstMaxRank;
+  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups, few ? kEstChunks : kSelMaxChunks);
+  j.row_each = few;
+  return j;
+}
+
 // the two launches of a lone estimate: the parts leave their partial results in `slots`, the decide kernel finishes
 static int launch_estimate(dpllm_model* m, const Linear& lin, int id, const Pair& sel, const void* x_dev, float* e_dev, int32_t* k_dev,
                            double* slots, hipStream_t st) {
   const int rowgroups = sel_rowgroups_of(sel.kind, sel.r);
-  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups);
+  SelJob j = lone_job(lin, id, rowgroups, x_dev, e_dev, k_dev);
   j.ws = slots;
   const SelParams P = make_params(sel, sel.T);
-  const int blocks = sel.kind == DPLLM_SEL_PROJ ? rowgroups * j.nchunks : sel.kind == DPLLM_SEL_LINREG ? 1 : 0;
+  const int parts = j.row_each ? (sel.r + kSelPartWaves - 1) / kSelPartWaves : rowgroups;
+  const int blocks = sel.kind == DPLLM_SEL_PROJ ? parts * j.nchunks : sel.kind == DPLLM_SEL_LINREG ? 1 : 0;
   if (blocks > 0)
     hipLaunchKernelGGL(selector_part_kernel, dim3(blocks), dim3(kSelPartThreads), 0, st, (const SelJob*)nullptr,
                        (const SelPart*)nullptr, (const int32_t*)nullptr, (const SelParams*)nullptr, j, P);
@@ -1200,7 +1213,7 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
                                  hipStream_t st) {
   const Workspace& W = m->ws;
   const int rowgroups = sel_rowgroups_of(sel.kind, sel.r);
-  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups);
+  SelJob j = lone_job(lin, id, rowgroups, x_dev, e_dev, k_dev);
   if (lin.L.ncw > kEstMaxWords || (sel.kind == DPLLM_SEL_PROJ && (sel.r > kEstMaxRank || (size_t)j.ws_rows * j.nchunks > W.est_slots_cap))) return false;
   if (!m->est_ready && sel.kind == DPLLM_SEL_PROJ) {
     // the slots are empty for work behind dpllm_set_workspace on its stream, for any other once that has been seen to be done
@@ -1215,7 +1228,7 @@ static bool launch_estimate_once(dpllm_model* m, const Linear& lin, int id, cons
   const EstShape shape{lin.L.ncw, proj ? j.nchunks : 0, proj ? j.ws_rows : 0};
   const EstPair pair{proj ? j.chunk_cols : 0, proj ? sel.r : 0, sel.kind, proj && capturing(st), sel.l, sel.h};
   hipLaunchKernelGGL(selector_estimate_kernel, dim3(parts), dim3(kSelPartThreads), 0, st, sel.G, (const uint16_t*)x_dev,
-                     W.at<uint64_t>(W.est_sets) + set * W.est_set_words() + kEstHeader, e_dev, k_dev, shape.pack(), pair.pack(), m->est_turn, polls, sel.T, sel.alpha,
+                     W.at<uint64_t>(W.est_sets) + set * W.est_set_words() + kEstHeader, e_dev, k_dev, shape.pack(), pair.pack(), m->est_turn, sel.T, polls, sel.alpha,
                      sel.beta);
   return true;
 }

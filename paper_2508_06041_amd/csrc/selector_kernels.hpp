@@ -80,7 +80,7 @@ struct SelJob {
   int32_t linear;      // row of the job's linear in the parameter table
   int32_t nchunks, chunk_cols;  // projection part p covers rows [16 (p / nchunks), + 16), columns [chunk_cols (p % nchunks), + chunk_cols)
   int32_t ws_rows;     // rows of one chunk's slots in ws (the largest rank of the linear's pairs, rounded up to 16)
-  int32_t pad;
+  int32_t row_each;    // a lone estimate: parts of four rows, one to a wavefront (see selector_estimate_kernel)
 };
 struct SelPart {
   int32_t job;     // index into the job table of the launch
@@ -546,7 +546,13 @@ __global__ void __launch_bounds__(kSelPartThreads) __attribute__((amdgpu_waves_p
                                                                          SelJob one_job, SelParams one) {
   __shared__ SelShared sh;
   if (parts == nullptr) {
-    if (one.kind == 1) selector_proj_part(one_job, one, blockIdx.x, threadIdx.x);
+    if (one.kind == 1 && one_job.row_each) {
+      const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, rg = blockIdx.x / one_job.nchunks, ch = blockIdx.x - rg * one_job.nchunks;
+      const int row = rg * kSelPartWaves + wave;
+      double sum[1];
+      selector_part_products<true>(one_job, one, row, ch, wave, lane, sum);
+      if (lane == 0 && row < one.r) ((DPLLM_SEL_GLOBAL double*)one_job.ws)[(size_t)ch * one_job.ws_rows + row] = sum[0];
+    } else if (one.kind == 1) selector_proj_part(one_job, one, blockIdx.x, threadIdx.x);
     else selector_group_part(nullptr, nullptr, 1, nullptr, one_job, one, threadIdx.x, sh);
     return;
   }
@@ -586,16 +592,15 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
 // finds its own there (or that several calls have given up) computes for itself too.  (A wait is given up where calls of one model
 // overlap, which the header rules out: their products overwrite one another.)  Launches take turns in kEstRing sets of slots.
 // What bounds it is a chain of latencies: launch, rows of G and x, the sum over a wavefront, store and collection.
-// us of a dpllm_estimate, graph / eager, with a launch for the parts and one for the decision -> one: rank 64 of 4096 columns
-// 4.5 / 7.4 -> 4.5 / 4.8, of 11008 5.3 / 7.6 -> 5.2 / 5.0, rank 128 of 11008 5.6 / 7.3 -> 5.3 / 5.8, rank 256 of 4096 5.2 / 7.5 -> 5.1 / 4.8, linear
-// regression 3.7 / 7.5 -> 2.0 / 4.9 (eager: the host takes 4.2 for a call).  With more rows the second launch is gained back: rank 256 of
-// 11008 7.1 .. 8.0 / 7.5 .. 8.4 (by where the memory lies) and 8.0 / 7.5, rank 512 of 8192 8.7 / 9.1 and 8.8 / 9.0; beyond the lanes of the
-// workgroup that collects there are two.  14 linears of 7B with a GEMV each: 190 -> 169 (161 with products of one word, which what an
-// overlap left behind could pass for).
+// us of a dpllm_estimate in a graph, with a launch for the parts and one for the decision / one for both: rank 64 of 4096 columns 4.6 / 3.9, of 8192
+// 5.1 / 4.5, of 11008 5.7 / 4.7, rank 256 of 4096 5.4 / 4.8, of 11008 7.2 / 5.8, linear regression 3.7 / 2.0; rank 512 of 8192, where rows go four to a
+// wavefront, 8.7 / 9.1: beyond the lanes of the workgroup that collects there are two.  14 linears of 7B with a GEMV each: 190 -> 169 (161 with
+// products of one word, which what an overlap left behind could pass for).
 constexpr int kEstRing = 16;
 constexpr int kEstRows = 1;             // rows of G of a wavefront
 constexpr int kEstPartRows = kSelPartWaves * kEstRows;
 constexpr int kEstMaxRank = kSelPartThreads;
+constexpr int kEstChunks = 12;          // column chunks of an estimate, at most
 constexpr int kEstPolls = 1 << 20;      // of about a microsecond
 constexpr uint32_t kEstAll = ~0u;       // a mark: several captured calls have given up
 
@@ -633,8 +638,8 @@ __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slot
 }
 
 // What all workgroups need, and what the last one does where it is on its way, comes as plain arguments that are set in registers with the
-// launch (see gemv_lane_kernel): fourteen dwords, so the small ones are packed.  Threshold and constants are loaded from the argument
-// memory: by the last wavefront of a projection, which has nothing else to do then, through LDS.
+// launch (see gemv_lane_kernel): fourteen dwords, so the small ones are packed.  The bound of the wait is loaded from the argument memory while
+// the first look at the products is on its way.
 struct EstShape {
   int words, nchunks, ws_rows;               // 32-column words of the vector (16 bits); chunks; rows of a chunk's slots (a multiple of 16, up to 496)
   __host__ __device__ uint32_t pack() const { return (uint32_t)(words | nchunks << 16 | ws_rows / kSelPartRows << 22); }
@@ -653,11 +658,10 @@ struct EstPair {
 // A set of slots is a header of kEstHeader 64-bit words, whose first dword is its mark, and the slots (ws).
 constexpr int kEstHeader = 16;
 __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(const uint16_t* G, const uint16_t* x, uint64_t* ws, float* e_out, int32_t* k_out,
-                                                                           uint32_t shape, uint32_t pair, uint32_t tag, int polls, float T, float alpha,
+                                                                           uint32_t shape, uint32_t pair, uint32_t tag, float T, int polls, float alpha,
                                                                            float beta) {
   __shared__ SelShared sh;
   __shared__ int here[kSelPartWaves];
-  __shared__ float threshold;
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const EstShape S = EstShape::unpack(shape);
   const EstPair Q = EstPair::unpack(pair);
@@ -681,13 +685,12 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
       __hip_atomic_store(slot + ws_rows, (uint64_t)tag << 32 | v >> 32, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
     if (blockIdx.x + 1 != gridDim.x) return;
-    if (wave == kSelPartWaves - 1 && lane == 0) threshold = T;
     const uint32_t found = Q.captured ? __hip_atomic_load(mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
     const bool marked = found == tag || found == kEstAll;
     bool all = true;
     if (wave * 64 < r) {
       all = nchunks <= 8 ? selector_collect<8>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0])
-                         : selector_collect<12>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0]);
+                         : selector_collect<kEstChunks>(slots, tag, nchunks, ws_rows, min(tid, r - 1), marked, polls, g[0]);
       sh.sq[tid] = g[0] * g[0];
     }
     if (lane == 0) here[wave] = all;
@@ -715,7 +718,6 @@ __global__ void __launch_bounds__(kSelPartThreads) selector_estimate_kernel(cons
     double part = 0.0;
     for (int t = tid; t < r; t += 64) part += sh.sq[t];
     e = sqrt(wave_sum_f64(part));
-    T = threshold;
   } else if (kind == 2) {
     // as selector_group_part does
     double acc = 0.0;
