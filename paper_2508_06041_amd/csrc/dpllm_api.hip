@@ -280,9 +280,9 @@ SelParams make_params(const Pair& s, float T) {
   return P;
 }
 
-// launch_rowgroups: groups of 16 rows of G over all jobs of the launch.  A launch with fewer of them than
-// would fill the chip cuts the columns into chunks (multiples of 512 columns) as well, at most `most` of them.
-SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x, float* e_dev, int32_t* k_dev, long launch_rowgroups, long most = kSelMaxChunks) {
+// cols: columns of a chunk (a multiple of 512), more where the columns would be cut into more than `most` of them
+constexpr int kSelParts = 1152;   // parts of a lone estimate with many rows, about
+SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x, float* e_dev, int32_t* k_dev, int cols, int most = kSelMaxChunks) {
   SelJob j;
   j.x = (const uint16_t*)x;
   j.e_out = e_dev;
@@ -293,15 +293,9 @@ SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x,
   j.nchunks = 1;
   j.chunk_cols = lin.L.in;
   if (rowgroups > 0) {
-    // long rows are cut as well, so that the parts of a launch are of similar size (7B step: 32.5 -> 30.7 us)
-    constexpr long max_cols = 4096;
-    long want = std::min<long>(kSelMaxChunks, 1152 / std::max<long>(1, launch_rowgroups));   // 1280 parts run at once
-    want = std::max<long>(want, std::min<long>(kSelMaxChunks, (lin.L.in + max_cols - 1) / max_cols));
-    want = std::min(want, most);
-    if (want > 1) {
-      j.chunk_cols = (int)((lin.L.in + want - 1) / want + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;   // <= want chunks
-      j.nchunks = (lin.L.in + j.chunk_cols - 1) / j.chunk_cols;
-    }
+    const int least = ((lin.L.in + most - 1) / most + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
+    j.chunk_cols = std::min(std::max(cols, least), (lin.L.in + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep);
+    j.nchunks = (lin.L.in + j.chunk_cols - 1) / j.chunk_cols;
   }
   j.ws_rows = std::max(1, rowgroups) * kSelPartRows;
   j.row_each = 0;
@@ -837,6 +831,17 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         launch_rowgroups += m->linears[j].max_rowgroups();
         launch_slices += (long)m->linears[j].max_rowgroups() * kSelPartRows * sel_slices(m->linears[j].L.in);
       }
+      // Parts of a launch are of one size, the smallest that lets all of them run at once (1280: five wavefronts per SIMD): rows of different
+      // lengths cut into the same number of chunks, as they were, leave the long parts to the end.  us of the selectors of 8 blocks of 70B,
+      // then -> now: 25.7 -> 21.1, every second linear on the linear regression 18.6 -> 15.2; 32 blocks of 7B 29.6 with parts of 4096 columns (1152 of
+      // them), 31.6 of 2048, 33.9 of 1024.
+      int chunk_cols = kSelChunkStep;
+      for (; chunk_cols < kSelTaskCols; chunk_cols += kSelChunkStep) {
+        long parts = 0;
+        for (int j : sel_of_phase[pi])
+          parts += (long)m->linears[j].max_rowgroups() * std::min(kSelMaxChunks, (m->linears[j].L.in + chunk_cols - 1) / chunk_cols);
+        if (parts <= 1280) break;
+      }
       const bool small = runs_selectors(ph.blocks, launch_rowgroups * kSelPartRows, launch_slices);
       ph.fused = tasks && ph.may_decide && small;
       ph.decides = ph.may_decide && (small || ahead[pi] || ph.blocks <= kPrologueMaxBlocks);
@@ -848,7 +853,7 @@ int build_plan(dpllm_model* m, const void* const* xs, void* const* ys, int32_t* 
         const int j = sel_of_phase[pi][local];
         const Linear& lin = m->linears[j];
         const int rowgroups = lin.max_rowgroups();
-        SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, launch_rowgroups);
+        SelJob sj = make_sel_job(lin, j, rowgroups, lin.sel_input ? lin.sel_input : xs[j], e_dev + j, k_dev + j, chunk_cols);
         for (int part = 0; part < rowgroups * sj.nchunks; ++part) sel_parts.push_back(SelPart{(int)local, part, j, 0, 0, 0});
         sj.ws = W.at<double>(W.sel_ws) + ws_slots;
         SelFinish fin = sel_finish_of(sj);
@@ -1184,7 +1189,9 @@ int dpllm_set_selector_input(dpllm_model* m, int id, const void* xsel_dev) {
 // 5120 4.4 where 12 take 4.1, of 28672 6.7).
 static SelJob lone_job(const Linear& lin, int id, int rowgroups, const void* x_dev, float* e_dev, int32_t* k_dev) {
   const bool few = rowgroups * kSelPartRows <= kEstMaxRank;
-  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, rowgroups, few ? kEstChunks : kSelMaxChunks);
+  const long want = std::min<long>(few ? kEstChunks : kSelMaxChunks, kSelParts / std::max(1, rowgroups));
+  const int cols = (int)((lin.L.in + want - 1) / want + kSelChunkStep - 1) / kSelChunkStep * kSelChunkStep;
+  SelJob j = make_sel_job(lin, id, rowgroups, x_dev, e_dev, k_dev, std::min(cols, kSelTaskCols), few ? kEstChunks : kSelMaxChunks);
   j.row_each = few;
   return j;
 }
