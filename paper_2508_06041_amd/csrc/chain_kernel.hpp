@@ -411,7 +411,7 @@ __device__ __forceinline__ void chain_run(u32x4 (&T)[H], uint32_t rec, int block
       const int tile = 4 * c0 + q * G;
       LaneX<K, 1, G> xs;
       xs.mine = xmine + q % S * G * kLaneGroupStride;
-      lane_compute<K, 1, G, true>(T, lanecol, lds, xs, acc, addr, mask, M, ncw - (tile + group) * 4, (tile + G) * 4 > ncw,
+      lane_compute<K, 1, G, true, false>(T, lanecol, lds, xs, acc, addr, mask, M, ncw - (tile + group) * 4, (tile + G) * 4 > ncw,
                                   [&](u32x4 (&t)[H]) { ask(t, b, q); });
       acc.settle();
       if (short_row && tile + group < ncc) sum = acc.sum(0);

@@ -546,13 +546,13 @@ __device__ __forceinline__ void lane_mac_singles(const uint32_t (&v)[8], const L
 // words: how many of the lane's four words lie inside the row, ragged: not all four in every lane (wave-uniform).  The
 // activations of the others are zero, but their codes are zero too, and an infinite centroid of that code would make
 // 0 x inf; k <= 2 clears what those lookups return.
-// LAZY (one sample): the activations are read back a word at a time, which takes 8 registers instead of 16; spent(tw) runs as
-// soon as tw may be asked for anew.
+// LAZY: spent(tw) runs as soon as the planes tw (and what the activations were loaded into) may be asked for anew; one sample's
+// activations are read back a word at a time, which takes 8 registers instead of 16.  ROOM as in lane_merge_fields.
 struct LaneNothing {
   template <class Planes>
   __device__ __forceinline__ void operator()(Planes&) const {}
 };
-template <int K, int NB, int G, bool LAZY = false, int H = K, class Spent = LaneNothing>
+template <int K, int NB, int G, bool LAZY = false, bool ROOM = (G > 1), int H = K, class Spent = LaneNothing>
 __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, const char* lds, LaneX<K, NB, G>& x,
                                              LaneAcc<NB>& acc, uint32_t (&addr)[8], uint32_t mask, const LaneMasks<K>& M, int words, bool ragged,
                                              Spent spent = LaneNothing{}) {
@@ -617,7 +617,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
       uint32_t w[K];
 #pragma unroll
       for (int b = 0; b < K; ++b) w[b] = mine[b][0];
-      lane_merge_fields<K, (G > 1 && !LAZY)>(w, R[0], M);
+      lane_merge_fields<K, ROOM>(w, R[0], M);
     }
     lane_issue_singles<K, 0>(R[0], lanecol, lds, va);
     auto word = [&](auto jc) {
@@ -626,7 +626,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         uint32_t w[K];
 #pragma unroll
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
-        lane_merge_fields<K, (G > 1 && !LAZY)>(w, R[(j + 1) & 1], M);
+        lane_merge_fields<K, ROOM>(w, R[(j + 1) & 1], M);
       }
       if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
@@ -886,8 +886,13 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
 // workgroup's entry: table rows here 1.4 - 1.7, tables built 2.0, first tile here 2.5, its 128 columns decoded 3.4,
 // stored 4.2; another 1.3 around the kernel.  So the loads are asked for in the order they are needed, the activations
 // are parked while the rest is on its way, and one workgroup per compute unit may use all its registers.
-// us per launch, columns split between workgroups -> now: 4096 x 4096 k = 4 10.9 -> 5.5, k = 8 14.6 -> 8.5; 4096 x 11008
-// k = 3 12.2 -> 7.9; 1024 x 4096 k = 3 7.3 -> 3.9 (before the arguments came in registers, see gemv_lane_kernel).
+// One set of planes: a step's planes are merged first, and the next step's are asked for into the same registers before the lookups.
+// Two sets in turns ask earlier but make the loop two bodies of code, which a launch this short runs through a few times at most: us per
+// launch in a graph, two sets -> one: 1024 x 4096 k = 3 3.64 -> 3.56; 4096 x 4096 k = 4 B = 4 6.1 -> 5.6; 2500 x 6688 k = 7 9.0 -> 8.5; 4096 x
+// 11008 k = 2 7.5 -> 6.9; 8192 x 8192 k = 4 9.8 -> 8.6, k = 8 17.5 -> 16.3; 4096 x 14336 B = 8 k = 3 12.2 -> 11.1.  (Two sets, each asked for
+// anew as soon as it is merged: 5.4 where one takes 5.2, 9.4 for 8.5, 17.6 for 16.0.)
+// us per launch, columns split between workgroups -> now: 4096 x 4096 k = 4 10.9 -> 5.1, k = 8 14.6 -> 8.0; 4096 x 11008
+// k = 3 12.2 -> 7.3; 1024 x 4096 k = 3 7.3 -> 3.5.
 template <int N>
 __device__ __forceinline__ void load_dwords(uint32_t (&v)[N], const DPLLM_GLOBAL uint32_t* p) {
   if constexpr (N == 2) {
@@ -963,7 +968,6 @@ __device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside,
 // one workgroup: block number `block` of 64 / G rows
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
-  constexpr int D = kLaneDepth;
   constexpr int rows = 64 / G;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int row = block * rows + lane % rows, group = lane / rows;
@@ -980,33 +984,23 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
     else narrow_load_x(t, job, sc, lane);
   };
   // first the activations of the first step (hot in L2: parked while the rest is on its way), then the table rows and
-  // the planes of the first D steps
+  // the planes
   LaneLut<K> L;
-  LaneTile<K, NB, G> ring[D];
+  LaneTile<K, NB, G> tile;
   const bool some = c0 < c1;                   // fewer steps than wavefronts: some only help with the tables
   auto park = [&](const LaneTile<K, NB, G>& t, int sc) {
     if constexpr (NB == 1) narrow_park<K, G>(t.x.v[0], sc * G * 128 + lane * 2 * G < job.ncw * 32, lane, ready);
   };
-  if (some) load_x(ring[0], c0);
+  if (some) load_x(tile, c0);
   lane_fetch_lut<K>(L, as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off)), row, wave);
   if (some) {
-    narrow_load_planes<K, NB, G>(ring[0], job, plane_rows, c0 * G + group, true);
-#pragma unroll
-    for (int i = 1; i < D; ++i) {
-      load_x(ring[i], c0 + i);
-      narrow_load_planes<K, NB, G>(ring[i], job, plane_rows, (c0 + i) * G + group, c0 + i < c1);
-    }
+    narrow_load_planes<K, NB, G>(tile, job, plane_rows, c0 * G + group, true);
     sched_fence();
-    park(ring[0], c0);
+    park(tile, c0);
   }
   LaneAcc<NB> acc;
   acc.zero();
   float done[lane_samples(NB)];   // the sums before the last step, where lanes may be without a tile
-  // The wait between a step's last dot product and the sum (LaneAcc<1>::settle) stands in front of the sum, at k = 7 behind the step.  us of
-  // a loop of calls without a wait / in front / behind: 2500 x 6688 k = 7 74.4 / 75.0 / 74.5; 4096 x 4096 k = 4 81.2 / 80.2 / 81.0, k = 3 72.6 /
-  // 71.9 / 72.5, k = 8 61.6 / 61.4 / 61.6; 4096 x 11008 k = 4 68.1 / 67.0 / 67.6, k = 2 56.2 / 55.8 / 55.5; 2500 x 6688 k = 5 61.5 / 61.5 / 61.0.
-  // (Behind at every k >= 5 costs k = 3 and 4 what they gain here: how the code of one bitwidth lies moves the others by a per cent.)
-  constexpr bool kSettleBehind = K == 7;
 #pragma unroll
   for (int b = 0; b < lane_samples(NB); ++b) done[b] = 0.f;
   LaneMasks<K> M;
@@ -1016,33 +1010,29 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
   for (int i = 0; i < 8; ++i) addr[i] = lanecol;
   lane_build_table<K>(L, wave, lanecol, lds);
   lds_barrier();
-  for (int cc = c0; cc < c1;) {
+#pragma unroll 1
+  for (int cc = c0; cc < c1; ++cc) {
+    if (cc != c0) park(tile, cc);
 #pragma unroll
-    for (int s = 0; s < D; ++s) {
-      if (cc != c0) park(ring[s], cc);
-      if constexpr (!kSettleBehind) acc.settle();
-#pragma unroll
-      for (int b = 0; b < lane_samples(NB); ++b) done[b] = acc.sum(b);
-      const int tile = cc * G + group;
-      const bool ragged = (cc + 1) * G * 4 > job.ncw;
-      LaneX<K, NB, G> x;
-      if constexpr (NB == 1) {
-        x.mine = ready + group * kLaneGroupStride + (lane & 3) * 16;
-      } else {
-        if (ragged) lane_mask_raw(ring[s].x, tile, job.ncw, lane);
-        x.settle(ring[s].x, lane);
-      }
-      lane_compute<K, NB, G>(ring[s].w, lanecol, lds, x, acc, addr, mask, M, job.ncw - tile * 4, ragged);
-      if constexpr (kSettleBehind) acc.settle();
-      if (++cc >= c1) break;
-      load_x(ring[s], cc + D - 1);
-      narrow_load_planes<K, NB, G>(ring[s], job, plane_rows, (cc + D - 1) * G + group, cc + D - 1 < c1);
+    for (int b = 0; b < lane_samples(NB); ++b) done[b] = acc.sum(b);
+    const int at = cc * G + group;
+    const bool ragged = (cc + 1) * G * 4 > job.ncw;
+    LaneX<K, NB, G> x;
+    if constexpr (NB == 1) {
+      x.mine = ready + group * kLaneGroupStride + (lane & 3) * 16;
+    } else {
+      if (ragged) lane_mask_raw(tile.x, at, job.ncw, lane);
+      x.settle(tile.x, lane);
     }
+    lane_compute<K, NB, G, true>(tile.w, lanecol, lds, x, acc, addr, mask, M, job.ncw - at * 4, ragged, [&](u32x4 (&)[K]) {
+      load_x(tile, cc + 1);
+      narrow_load_planes<K, NB, G>(tile, job, plane_rows, (cc + 1) * G + group, cc + 1 < c1);
+    });
+    acc.settle();
   }
   // the last step may have fewer than G tiles: a lane without one (it decoded another tile) drops what it added there
   const bool whole = (c1 - 1) * G + group < job.ncc;
   if constexpr (NB == 8) lds_barrier();   // the tables, which the sums take the place of, are done with
-  if constexpr (!kSettleBehind) acc.settle();
 #pragma unroll
   for (int b = 0; b < lane_samples(NB); ++b) red[(b * kLaneWaves + wave) * 64 + lane] = whole ? acc.sum(b) : done[b];
   lds_barrier();

@@ -42,6 +42,25 @@ def test_gemv_every_bitwidth_and_batch(dp, out, in_):
     model.close()
 
 
+# two, four and eight column groups, wavefronts of several steps (the tile of the next step is asked for while this one is
+# decoded), the last step with a tile for some of the groups only
+@pytest.mark.parametrize("out,in_", [(300, 32 * 1035), (2500, 6688), (4200, 12320)])
+def test_gemv_several_steps(dp, out, in_):
+    lin = synth.make_linear(out, in_, 8, 1, seed=out + in_, device="cuda", keep_codes=False)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, lin["planes"], lin["luts"], 1)
+    planes = synth.planes_np(lin["planes"])
+    X = synth.make_x(in_, 7, seed=out)
+    for k in (1, 3, 4, 5, 8):
+        lut = synth.lut_np(lin["luts"][k])
+        ref = oracle.gemv(planes, k, lut, synth.lut_np(X))
+        for B in (1, 4, 7):
+            got = model.dpllm_gemv(0, k, (X[:B] if B > 1 else X[0]).cuda()).double().cpu().numpy().reshape(B, out)
+            for b in range(B):
+                assert (np.abs(got[b] - ref[b]) <= bound(ref[b], lut, synth.lut_np(X[b]), in_)).all(), (k, B, b)
+    model.close()
+
+
 @pytest.mark.parametrize("out,in_", [(40, 160), (20000, 96)])
 def test_two_bits_unused_infinite_centroid(dp, out, in_):
     """Columns past the end of a row carry code 0; an infinite centroid of that code must not reach the sum."""
