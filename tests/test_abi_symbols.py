@@ -119,3 +119,28 @@ def test_bench_refuses_more_than_one_gpu():
     r = subprocess.run([sys.executable, os.path.join(ROOT, "bench.py"), "--gpus", "2"], capture_output=True, text=True, timeout=120)
     assert r.returncode != 0
     assert "one GPU" in (r.stdout + r.stderr)
+
+
+@pytest.mark.parametrize("out,in_,p", [(448, 1120, 8), (512, 1024, 8), (500, 1056, 3), (4096, 4096, 8)])
+def test_planes_lie_apart_and_inside_the_arena(lib, out, in_, p):
+    """Planes below 64 KiB lie side by side, larger ones with a gap of a multiple of 256 bytes; the first and the last word of every plane
+    and the tables after them are inside what the arena has room for."""
+    f, g = lib.dpllm_debug_locate, lib.dpllm_linear_device_bytes
+    f.argtypes = [C.c_int] * 7 + [C.POINTER(C.c_size_t), C.POINTER(C.c_int)]
+    g.argtypes = [C.c_int] * 4 + [C.POINTER(C.c_size_t)]
+    n, bit = C.c_size_t(0), C.c_int(0)
+    assert g(out, in_, p, 2, C.byref(n)) == 0
+    nrq, ncc = (out + 63) // 64, (in_ // 32 + 3) // 4
+    size = nrq * ncc * 1024
+
+    def where(plane, row, col):
+        off = C.c_size_t(0)
+        assert f(out, in_, p, 2, plane, row, col, C.byref(off), C.byref(bit)) == 0
+        return off.value
+
+    for plane in range(1, p):
+        stride = where(plane, 0, 0) - where(plane - 1, 0, 0)
+        assert stride == size if size < 65536 else size < stride < size + 65536 and stride % 256 == 0
+        assert where(plane - 1, out - 1, in_ - 1) < where(plane, 0, 0)
+    tables = sum(nrq * 64 * 2 ** k * 2 for k in range(2, p + 1))
+    assert where(p - 1, out - 1, in_ - 1) + tables < n.value
