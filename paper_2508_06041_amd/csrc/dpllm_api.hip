@@ -359,16 +359,19 @@ int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long 
 // Column groups per wavefront (rows per workgroup = 64 / groups) of a launch whose linears have `blocks64` blocks of 64
 // rows in all (times the passes of a batch), the shortest row ncc column tiles: the most that leave at most one
 // workgroup per compute unit.  Measured, us per launch in a graph, one linear at k = 4 with 1 / 2 / 4 / 8 groups: 4096 x
-// 4096 8.5 / 6.7 / 5.5 / 8.4, 4096 x 11008 18.0 / 12.0 / 9.2 / 12.7, 8192 x 8192 14.8 / 11.3 / 14.2 / 18.5, 11008 x 4096
-// 9.7 / 12.3 / 12.5 / 21.2, 192 x 28672 38.0 / 20.1 / 12.3 / 9.8.  Eight groups only where every wavefront gets a step
-// (1024 x 4096: 3.9 us with four, 4.1 with eight).  A batch of four, four / eight groups: 1000 x 8192 k = 4 9.1 / 8.6, 640 x
-// 14336 k = 3 10.1 / 9.8, 192 x 14336 k = 6 14.0 / 12.7, 419 x 28672 k = 8 24.5 / 21.0 (workgroups that split the columns of
-// 64 rows, with a hand-over through memory that calls would share, take 10.2, 11.4 and 18.0 us for the last three: every
-// workgroup reads all activations here).
-int pick_groups(long blocks64, int ncc) {
+// 4096 8.5 / 5.8 / 5.1 / 7.7, 4096 x 11008 17.8 / 10.2 / 8.3 / 10.8, 8192 x 8192 13.8 / 9.0 / 8.9 / 16.1, 11008 x 4096
+// 7.7 / 8.0 / 8.6 / 18.9, 192 x 28672 - / 18.3 / 10.6 / 8.2.  Eight groups only where every wavefront gets a step
+// (1024 x 4096: 4.4 us with four, 4.3 with eight; a batch of four 5.2, 5.6).  A batch of four, four / eight groups: 640 x
+// 14336 k = 3 7.9 / 7.5, 192 x 14336 k = 6 12.2 / 9.9, 419 x 28672 k = 8 20.1 / 17.3 (workgroups that split the columns of
+// 64 rows, with a hand-over through memory that calls would share, take 11.4 and 18.0 us for the last two: every
+// workgroup reads all activations here).  A batch at k = 4 takes four at most (`most`): what a lane holds of a sample comes from two places
+// there, and with 8 rows to a workgroup each wavefront fetches, sorts and exchanges that for eight tiles a step.  k = 4, B = 2, 4, four / eight:
+// 500 x 8192 6.3 / 6.3, 6.5 / 7.9; 1000 x 11008 7.4 / 7.7, 7.6 / 9.8; 2048 x 14336 8.6 / 8.6, 8.9 / 11.1; 1024 x 28672 11.9 / 12.1, 12.6 / 16.2; at
+// k = 2, 3 eight are 0 to 10 per cent ahead, at k >= 5 9 to 20.
+int pick_groups(long blocks64, int ncc, int most = 8) {
   int g = 1;
   while (g < 4 && blocks64 * g * 2 <= 256) g *= 2;
-  if (g == 4 && blocks64 * 8 <= 256 && ncc >= 8 * kLaneWaves) g = 8;
+  if (g == 4 && most == 8 && blocks64 * 8 <= 256 && ncc >= 8 * kLaneWaves) g = 8;
   return g;
 }
 
@@ -432,19 +435,19 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 
 // One linear, B right-hand sides.  Five to eight of them share one pass over the planes where two passes of four would be
 // more workgroups than there are compute units; below that the second pass runs beside the first one.  us per call of
-// B = 8, two passes / one: 14336 x 4096 k = 3 12.4 / 8.7, 11008 x 4096 k = 3 11.1 / 8.3, k = 5 19.5 / 13.0, k = 8 27.5 / 17.5.
+// B = 8, two passes / one: 14336 x 4096 k = 3 10.9 / 8.8, 11008 x 4096 k = 3 11.3 / 8.4, k = 5 18.7 / 12.5, k = 8 25.0 / 15.3.
 // Up to 128 row blocks both passes fit, with twice the rows to a workgroup that one pass takes (64 / 1 and 64 / 2; up to 64 blocks
 // 64 / 2 and 64 / 4): twice the lookups in a workgroup for the same sums.  One pass pays where lookups are what a step consists of
-// (k >= 5) and where every wavefront has a step or several.  65 to 128 blocks: 8192 x 8192 k = 3 11.1 / 10.6, k = 4 12.3 / 12.0, k = 5 19.1 / 15.4,
-// k = 8 22.8 / 19.7; 6000 x 28672 k = 2 30.1 / 24.3, k = 5 55.4 / 37.6; 6000 x 4096 k = 3 7.7 / 7.5; 5000 x 2048 k = 2 5.3 / 5.4, k = 4 6.0 / 6.0,
-// k = 5 7.8 / 6.8, k = 8 10.1 / 8.3; 8192 x 1024 k = 3 4.2 / 4.7, k = 5 5.8 / 5.8, k = 8 7.7 / 7.1.  33 to 64: 4096 x 14336 k = 3 11.5 / 12.9, k = 5 18.9 /
-// 17.0, k = 8 22.0 / 21.3; 4096 x 4096 k = 3 6.2 / 6.5, k = 4 7.0 / 8.2, k = 5 8.8 / 7.9; 4096 x 28672 k = 3 19.1 / 18.9, k = 4 21.4 / 25.9, k = 6 33.8 /
-// 27.1; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.3 / 6.3.  Fewer: 1000 x 4096 k = 5 6.5 / 7.4, 1500 x 14336 k = 3 9.9 / 12.4.
+// (k >= 5) and where every wavefront has a step or several.  65 to 128 blocks: 8192 x 8192 k = 3 11.2 / 9.6, k = 4 12.3 / 11.0, k = 5 19.0 / 13.9,
+// k = 8 22.4 / 17.5; 6000 x 4096 k = 3 7.2 / 6.6, k = 4 8.1 / 7.3; 5000 x 2048 k = 2 5.2 / 5.2, k = 4 5.9 / 5.6,
+// k = 5 7.8 / 6.5, k = 8 9.9 / 7.9; 8192 x 1024 k = 3 4.3 / 5.0, k = 5 5.7 / 6.0, k = 8 7.4 / 7.1.  33 to 64: 4096 x 14336 k = 3 10.9 / 11.5, k = 5 17.4 /
+// 16.0, k = 8 20.5 / 18.8; 4096 x 4096 k = 3 5.8 / 6.2, k = 4 6.2 / 7.6, k = 5 7.9 / 7.5; 4096 x 28672 k = 3 18.2 / 17.4, k = 4 19.4 / 23.3, k = 6 31.8 /
+// 25.0; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.1 / 6.2.  Fewer: 1000 x 4096 k = 5 6.2 / 7.1, 1500 x 14336 k = 3 8.6 / 11.1.
 // One right-hand side, blocks of 64 rows: on the matrix pipe, four equal sums a lane, which spares parking the activations and a fifth of the
-// vector instructions.  us per call, vector / matrix pipe: 9000 x 4096 k = 3 7.0 / 6.5, k = 4 8.8 / 7.7, k = 5 10.9 / 11.0, k = 7 13.8 / 14.2; 11008 x
-// 4096 k = 2 7.1 / 6.5, k = 4 9.0 / 8.0, k = 6 12.1 / 12.6; 28672 x 4096 k = 4 12.7 / 11.9, k = 5 17.9 / 18.0; more tiles than a wavefront keeps
-// the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth: 14336 x 14336 k = 2 21.9 / 16.0, k = 4 22.0 /
-// 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0, k = 8 43.0 / 41.4.  With several
+// vector instructions.  us per call, vector / matrix pipe: 9000 x 4096 k = 2 7.3 / 6.8, k = 4 8.8 / 7.8, k = 5 10.8 / 10.9, k = 7 12.9 / 13.2; 14336 x
+// 4096 k = 4 9.0 / 8.3, k = 5 11.2 / 11.1, k = 8 14.9 / 15.0; 28672 x 4096 k = 4 13.4 / 12.9, k = 8 23.5 / 23.6; more tiles than a wavefront keeps
+// the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth (planes side by side): 14336 x 14336 k = 2 21.9 /
+// 16.0, k = 4 22.0 / 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0.  With several
 // column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   const int blocks = lin.L.nrq;
@@ -452,7 +455,7 @@ int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, 
   const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
   int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
-  const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc);
+  const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc, B > 1 && !k_dev && k == 4 ? 4 : 8);
   if (B == 1 && groups == 1 && ((k_dev ? lin.least_k() : k) <= 4 || lin.L.ncc > kLaneWaves * kLaneKeepTiles)) nb = 2;
   int nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   if (groups == 1) {

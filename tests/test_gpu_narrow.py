@@ -61,6 +61,23 @@ def test_gemv_several_steps(dp, out, in_):
     model.close()
 
 
+# few rows of 64 column tiles and more: a batch at k = 4 takes four column groups where the call names the bitwidth, eight where the device does
+@pytest.mark.parametrize("out,in_,B", [(1, 8192, 2), (500, 8192 + 32, 4), (1100, 11008, 3), (300, 32 * 513, 7)])
+def test_four_bit_batch_on_few_rows(dp, out, in_, B):
+    lin = synth.make_linear(out, in_, 5, 3, seed=out + in_, device="cuda", keep_codes=False)
+    model = dp.Model(1)
+    model.dpllm_load_linear(0, lin["planes"], lin["luts"], 3)
+    lut = synth.lut_np(lin["luts"][4])
+    X = synth.make_x(in_, B, seed=out)
+    ref = oracle.gemv(synth.planes_np(lin["planes"]), 4, lut, synth.lut_np(X))
+    k_dev = torch.full((1,), 4, dtype=torch.int32, device="cuda")
+    for got in (model.dpllm_gemv(0, 4, X.cuda()), model.dpllm_gemv(0, -1, X.cuda(), k_dev=k_dev)):
+        got = got.double().cpu().numpy()
+        for b in range(B):
+            assert (np.abs(got[b] - ref[b]) <= bound(ref[b], lut, synth.lut_np(X[b]), in_)).all(), b
+    model.close()
+
+
 @pytest.mark.parametrize("out,in_", [(40, 160), (20000, 96)])
 def test_two_bits_unused_infinite_centroid(dp, out, in_):
     """Columns past the end of a row carry code 0; an infinite centroid of that code must not reach the sum."""
