@@ -313,7 +313,7 @@ GemvJob make_gemv_job(const Linear& lin, int k, const int32_t* k_dev, const void
   j.fin = SelFinish{};
   j.plane_stride_u4 = (uint32_t)(lin.L.plane_bytes / 16);
   for (int kk = 1; kk <= kKMax; ++kk)
-    j.lut_off[kk - 1] = (kk >= lin.L.kmin && kk <= lin.L.p) ? (uint32_t)lin.L.lut_offset[kk] : 0u;
+    j.lut_at[kk - 1] = (kk >= lin.L.kmin && kk <= lin.L.p) ? lin.L.lut_at(kk) : 0u;
   j.k = k;
   j.kmin = lin.L.kmin; j.p = lin.L.p;
   j.out = lin.L.out; j.ncw = lin.L.ncw; j.nrq = lin.L.nrq; j.ncc = lin.L.ncc;
@@ -378,7 +378,7 @@ int pick_groups(long blocks64, int ncc, int most = 8) {
 void launch_lane(const LinearLayout& L, const char* arena, int groups, int nb, int nblocks, int passes, hipStream_t st, int k, const int32_t* k_dev,
                  const void* x, void* y, int nrhs) {
   const uint32_t bits = LaneBits{k, L.kmin, L.p, nrhs}.pack();
-  const uint32_t lut = k_dev ? (uint32_t)L.lut_offset[L.kmin] - ((uint32_t)L.rows_padded << (L.kmin + 1)) : (uint32_t)L.lut_offset[k];
+  const uint32_t lut = k_dev ? L.lut_at(L.kmin) - ((uint32_t)L.nrq << (L.kmin - 1)) : L.lut_at(k);
   auto go = [&](auto kernel) {
     hipLaunchKernelGGL(kernel, dim3((unsigned)(nblocks * passes)), dim3(kLaneThreads), 0, st, arena, (const uint16_t*)x, (uint16_t*)y, k_dev,
                        (uint32_t)(L.plane_bytes / 16), lut, bits, L.out, L.ncw, nblocks);

@@ -36,7 +36,7 @@ struct alignas(64) GemvJob {   // (aligned: few scalar loads)
   int32_t has_fin;
   SelFinish fin;
   uint32_t plane_stride_u4;
-  uint32_t lut_off[kKMax];    // [k - 1]: byte offset of the k-bit table inside the arena, k = kmin..p
+  uint32_t lut_at[kKMax];     // [k - 1]: where the k-bit table starts in the arena, in units of kAlign bytes, k = kmin..p
   int32_t k;                  // the bitwidth when k_dev == nullptr
   int32_t kmin, p;            // bitwidths the linear serves: a value read from k_dev outside them is not served
   int32_t out, ncw;           // rows; 32-column words per row

@@ -47,6 +47,7 @@
 #include <type_traits>
 
 #include "gemv_common.hpp"
+#include "layout.hpp"
 #include "layout_device.hpp"
 
 namespace dpllm {
@@ -743,7 +744,7 @@ constexpr int kLaneDepth = 2;
 // [w ncc / 8, (w + 1) ncc / 8) in every row block.  Tile loads run kLaneDepth - 1 tiles ahead, also across row
 // blocks; past the end of the run the ring is refilled with dummy loads (see lane_load_tile).
 template <int K, int NB>
-__device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
+__device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
   constexpr int D = kLaneDepth;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const uint32_t lanecol = (uint32_t)lane * 4;  // the lane's column of the interleaved tables
@@ -753,7 +754,7 @@ __device__ __forceinline__ void gemv_lane(const GemvJob& job, uint32_t lut_off, 
   const int c0 = wave * job.ncc / kLaneWaves, c1 = (wave + 1) * job.ncc / kLaneWaves;
   const int nrb = job.nrq;                     // row blocks of the job
   const int step = job.nblocks;
-  const DPLLM_GLOBAL uint16_t* lut_base = as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off));
+  const DPLLM_GLOBAL uint16_t* lut_base = as_global(reinterpret_cast<const uint16_t*>(job.arena + (size_t)lut_at * kAlign));
   const bool idle = c0 >= c1;                  // fewer tiles than wavefronts: this one only helps with the tables
   // the table rows of the next row block travel one block ahead, except at k >= 7, where their 8 - 16 registers
   // would cost the second workgroup per compute unit
@@ -967,7 +968,7 @@ __device__ __forceinline__ void narrow_park(const uint32_t (&x)[G], bool inside,
 
 // one workgroup: block number `block` of 64 / G rows
 template <int K, int NB, int G>
-__device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off, int block, int tid, char* lds) {
+__device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
   constexpr int rows = 64 / G;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int row = block * rows + lane % rows, group = lane / rows;
@@ -992,7 +993,7 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
     if constexpr (NB == 1) narrow_park<K, G>(t.x.v[0], sc * G * 128 + lane * 2 * G < job.ncw * 32, lane, ready);
   };
   if (some) load_x(tile, c0);
-  lane_fetch_lut<K>(L, as_global(reinterpret_cast<const uint16_t*>(job.arena + lut_off)), row, wave);
+  lane_fetch_lut<K>(L, as_global(reinterpret_cast<const uint16_t*>(job.arena + (size_t)lut_at * kAlign)), row, wave);
   if (some) {
     narrow_load_planes<K, NB, G>(tile, job, plane_rows, c0 * G + group, true);
     sched_fence();
@@ -1048,13 +1049,13 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_off
 template <int NB, int G>
 __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpret_cast<double*>(lds + lane_lds_bytes<NB, G>() - kSelSharedBytes); }
 
-// lut_off(K as a constant): byte offset of the K-bit tables
-template <int NB, int G, class Off>
-__device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, Off lut_off, int block, int tid, char* lds) {
+// lut_at(K as a constant): where the K-bit tables start in the arena, in units of kAlign bytes
+template <int NB, int G, class At>
+__device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, At lut_at, int block, int tid, char* lds) {
   auto run = [&](auto kc) {
     constexpr int K = decltype(kc)::value;
-    if constexpr (G == 1) gemv_lane<K, NB>(job, lut_off(kc), block, tid, lds);
-    else gemv_narrow<K, NB, G>(job, lut_off(kc), block, tid, lds);
+    if constexpr (G == 1) gemv_lane<K, NB>(job, lut_at(kc), block, tid, lds);
+    else gemv_narrow<K, NB, G>(job, lut_at(kc), block, tid, lds);
   };
   switch (k) {
     case 1: run(std::integral_constant<int, 1>{}); break;
@@ -1087,7 +1088,7 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
     k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
   }
   if (k < job.kmin || k > job.p) return;
-  gemv_lane_width<NB, G>(job, k, [&](auto kc) { return job.lut_off[decltype(kc)::value - 1]; }, block, tid, lds);
+  gemv_lane_width<NB, G>(job, k, [&](auto kc) { return job.lut_at[decltype(kc)::value - 1]; }, block, tid, lds);
 }
 
 // One linear, for several right-hand sides in groups of NB that share one pass over the planes (group g reads x + g * NB * in
@@ -1095,7 +1096,8 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
 // fourteen dwords, which fit the registers that are set with the launch: nothing is loaded from the argument memory, and the host writes
 // 56 bytes instead of 320.  us per call of a loop in Python, with a record by value for what is not needed first -> now: 1024 x 4096 k = 3
 // 4.4 -> 4.05, 11008 x 4096 k = 4 8.8 -> 8.7; an estimate and a GEMV of 4096 x 4096, both so, 10.2 -> 9.7, in a graph 9.7 -> 9.6.
-// bits: LaneBits; lut: byte offset of the tables in the arena, less (rows << (k + 1)) where k_dev says the bitwidth (rows padded to 64).
+// bits: LaneBits; lut: where the tables start in the arena, in units of kAlign bytes, less row blocks << (k - 1) where k_dev says the bitwidth (a
+// block's tables of k bits are so many units, and those of fewer bits lie in front).
 struct LaneBits {
   int k, kmin, p, nrhs;                      // the bitwidth unless k_dev says it; those the linear serves; right-hand sides
   __host__ __device__ uint32_t pack() const { return (uint32_t)(k | kmin << 4 | p << 8 | nrhs << 12); }
@@ -1127,7 +1129,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   if (k_dev != nullptr) {
     k = load_record(k_dev);
     if (k < b.kmin || k > b.p) return;
-    lut += (uint32_t)job.nrq << (k + 7);
+    lut += (uint32_t)job.nrq << (k - 1);
   }
   gemv_lane_width<NB, G>(job, k, [&](auto) { return lut; }, block, threadIdx.x, lds);
 }

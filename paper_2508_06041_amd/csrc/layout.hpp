@@ -35,8 +35,10 @@ struct LinearLayout {
   int ncc = 0;               // 128-column tiles per row
   int rows_padded = 0;       // rows of the tables (zero rows appended)
   size_t plane_bytes = 0;    // stride between plane regions
-  size_t lut_offset[9] = {}; // byte offset of the k-bit table, k = kmin..p
+  size_t lut_offset[9] = {}; // byte offset of the k-bit table, k = kmin..p (a multiple of kAlign)
   size_t total_bytes = 0;
+
+  uint32_t lut_at(int k) const { return (uint32_t)(lut_offset[k] / kAlign); }   // in 32 bits for arenas up to 1 TiB
 
   static LinearLayout make(int out, int in, int p, int kmin) {
     LinearLayout L;
