@@ -63,12 +63,6 @@ struct Linear {
       if (s.set) g = std::max(g, sel_rowgroups_of(s.kind, s.r));
     return g;
   }
-  int least_k() const {   // the smallest bitwidth its selectors choose; without selectors the largest there is
-    int k = L.p;
-    for (const Pair& s : sel)
-      if (s.set) k = std::min(k, s.l);
-    return k;
-  }
   int part_k() const {   // the bitwidth the work of a step launch is cut for: the larger one of the pair of target 0
     return active >= 0 ? sel[active].h : L.p;
   }
@@ -390,8 +384,6 @@ void launch_lane(const LinearLayout& L, const char* arena, int groups, int nb, i
       case 4: go(gemv_lane_kernel<1, 4>); break;
       default: go(gemv_lane_kernel<1, 8>); break;
     }
-  } else if (nb == 2) {
-    go(gemv_lane_kernel<2, 1>);
   } else if (nb == 4) {
     switch (groups) {
       case 1: go(gemv_lane_kernel<4, 1>); break;
@@ -443,20 +435,13 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 // k = 5 7.8 / 6.5, k = 8 9.9 / 7.9; 8192 x 1024 k = 3 4.3 / 5.0, k = 5 5.7 / 6.0, k = 8 7.4 / 7.1.  33 to 64: 4096 x 14336 k = 3 10.9 / 11.5, k = 5 17.4 /
 // 16.0, k = 8 20.5 / 18.8; 4096 x 4096 k = 3 5.8 / 6.2, k = 4 6.2 / 7.6, k = 5 7.9 / 7.5; 4096 x 28672 k = 3 18.2 / 17.4, k = 4 19.4 / 23.3, k = 6 31.8 /
 // 25.0; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.1 / 6.2.  Fewer: 1000 x 4096 k = 5 6.2 / 7.1, 1500 x 14336 k = 3 8.6 / 11.1.
-// One right-hand side, blocks of 64 rows: on the matrix pipe, four equal sums a lane, which spares parking the activations and a fifth of the
-// vector instructions.  us per call, vector / matrix pipe: 9000 x 4096 k = 2 7.3 / 6.8, k = 4 8.8 / 7.8, k = 5 10.8 / 10.9, k = 7 12.9 / 13.2; 14336 x
-// 4096 k = 4 9.0 / 8.3, k = 5 11.2 / 11.1, k = 8 14.9 / 15.0; 28672 x 4096 k = 4 13.4 / 12.9, k = 8 23.5 / 23.6; more tiles than a wavefront keeps
-// the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth (planes side by side): 14336 x 14336 k = 2 21.9 /
-// 16.0, k = 4 22.0 / 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0.  With several
-// column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   const int blocks = lin.L.nrq;
   const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= 4 * kLaneWaves;
   const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
-  int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
+  const int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
   const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc, B > 1 && !k_dev && k == 4 ? 4 : 8);
-  if (B == 1 && groups == 1 && ((k_dev ? lin.least_k() : k) <= 4 || lin.L.ncc > kLaneWaves * kLaneKeepTiles)) nb = 2;
   int nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
   if (groups == 1) {
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);

@@ -1049,12 +1049,36 @@ __device__ __forceinline__ void gemv_narrow(const GemvJob& job, uint32_t lut_at,
 template <int NB, int G>
 __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpret_cast<double*>(lds + lane_lds_bytes<NB, G>() - kSelSharedBytes); }
 
-// lut_at(K as a constant): where the K-bit tables start in the arena, in units of kAlign bytes
-template <int NB, int G, class At>
+// One workgroup of a launch of its own.  Which code a bitwidth runs is settled here and not by the host, so that a call leaves the same
+// bits whether it names the bitwidth or the device does, and whichever pairs are attached.
+// One right-hand side, blocks of 64 rows: on the matrix pipe, four equal sums a lane, which spares parking the activations and a fifth of the
+// vector instructions.  us per call, vector / matrix pipe: 9000 x 4096 k = 2 7.3 / 6.8, k = 4 8.8 / 7.8, k = 5 10.8 / 10.9, k = 7 12.9 / 13.2; 14336 x
+// 4096 k = 4 9.0 / 8.3, k = 5 11.2 / 11.1, k = 8 14.9 / 15.0; 28672 x 4096 k = 4 13.4 / 12.9, k = 8 23.5 / 23.6; more tiles than a wavefront keeps
+// the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth (planes side by side): 14336 x 14336 k = 2 21.9 /
+// 16.0, k = 4 22.0 / 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0.  With several
+// column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
+template <int K, int NB, int G>
+__device__ __forceinline__ void gemv_lone(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
+  if constexpr (NB == 1 && G == 1) {
+    static_assert(lane_lds_bytes<2, 1>() <= lane_lds_bytes<1, 1>(), "room for either");
+    if constexpr (K >= 5) {
+      if (job.ncc <= kLaneWaves * kLaneKeepTiles) return gemv_lane<K, 1>(job, lut_at, block, tid, lds);
+    }
+    gemv_lane<K, 2>(job, lut_at, block, tid, lds);
+  } else if constexpr (G == 1) {
+    gemv_lane<K, NB>(job, lut_at, block, tid, lds);
+  } else {
+    gemv_narrow<K, NB, G>(job, lut_at, block, tid, lds);
+  }
+}
+
+// lut_at(K as a constant): where the K-bit tables start in the arena, in units of kAlign bytes.  LONE: a launch of its own.
+template <int NB, int G, bool LONE, class At>
 __device__ __forceinline__ void gemv_lane_width(const GemvJob& job, int k, At lut_at, int block, int tid, char* lds) {
   auto run = [&](auto kc) {
     constexpr int K = decltype(kc)::value;
-    if constexpr (G == 1) gemv_lane<K, NB>(job, lut_at(kc), block, tid, lds);
+    if constexpr (LONE) gemv_lone<K, NB, G>(job, lut_at(kc), block, tid, lds);
+    else if constexpr (G == 1) gemv_lane<K, NB>(job, lut_at(kc), block, tid, lds);
     else gemv_narrow<K, NB, G>(job, lut_at(kc), block, tid, lds);
   };
   switch (k) {
@@ -1088,7 +1112,7 @@ __device__ __forceinline__ void gemv_lane_block(const GemvJob& job, int block, i
     k = __builtin_amdgcn_readfirstlane(*as_global(job.k_dev));
   }
   if (k < job.kmin || k > job.p) return;
-  gemv_lane_width<NB, G>(job, k, [&](auto kc) { return job.lut_at[decltype(kc)::value - 1]; }, block, tid, lds);
+  gemv_lane_width<NB, G, false>(job, k, [&](auto kc) { return job.lut_at[decltype(kc)::value - 1]; }, block, tid, lds);
 }
 
 // One linear, for several right-hand sides in groups of NB that share one pass over the planes (group g reads x + g * NB * in
@@ -1111,7 +1135,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
   const LaneBits b = LaneBits::unpack(bits);
-  const int group = lane_samples(NB) == 1 ? 0 : blockIdx.x / nblocks;
+  const int group = NB == 1 ? 0 : blockIdx.x / nblocks;
   GemvJob job{};
   job.arena = arena;
   job.x = x + (size_t)group * NB * ncw * 32;
@@ -1122,7 +1146,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   job.ncc = (ncw + 3) / 4;
   job.nrq = (out + 63) / 64;
   job.nblocks = nblocks;
-  job.nsamples = min(lane_samples(NB), b.nrhs - group * NB);
+  job.nsamples = min(NB, b.nrhs - group * NB);
   const int block = blockIdx.x - group * nblocks;
   if (block * (64 / G) >= out) return;
   int k = b.k;
@@ -1131,7 +1155,7 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
     if (k < b.kmin || k > b.p) return;
     lut += (uint32_t)job.nrq << (k - 1);
   }
-  gemv_lane_width<NB, G>(job, k, [&](auto) { return lut; }, block, threadIdx.x, lds);
+  gemv_lane_width<NB, G, true>(job, k, [&](auto) { return lut; }, block, threadIdx.x, lds);
 }
 
 // The linears of a dependency level of a decode step: block b < nblocks belongs to job block_jobs[b]; blocks past them
