@@ -358,7 +358,7 @@ int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long 
 // (1024 x 4096: 4.4 us with four, 4.3 with eight; a batch of four 5.2, 5.6).  A batch of four, four / eight groups: 640 x
 // 14336 k = 3 7.9 / 7.5, 192 x 14336 k = 6 12.2 / 9.9, 419 x 28672 k = 8 20.1 / 17.3 (workgroups that split the columns of
 // 64 rows, with a hand-over through memory that calls would share, take 11.4 and 18.0 us for the last two: every
-// workgroup reads all activations here).  A batch at k = 4 takes four at most (`most`): what a lane holds of a sample comes from two places
+// workgroup reads all activations here).  A batch at k = 4 takes four at most (`most`; gemv_lone where the device says k): what a lane holds of a sample comes from two places
 // there, and with 8 rows to a workgroup each wavefront fetches, sorts and exchanges that for eight tiles a step.  k = 4, B = 2, 4, four / eight:
 // 500 x 8192 6.3 / 6.3, 6.5 / 7.9; 1000 x 11008 7.4 / 7.7, 7.6 / 9.8; 2048 x 14336 8.6 / 8.6, 8.9 / 11.1; 1024 x 28672 11.9 / 12.1, 12.6 / 16.2; at
 // k = 2, 3 eight are 0 to 10 per cent ahead, at k >= 5 9 to 20.

@@ -1057,6 +1057,7 @@ __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpr
 // the activations of (4096 columns) parks them for every row block, so there it pays at every bitwidth (planes side by side): 14336 x 14336 k = 2 21.9 /
 // 16.0, k = 4 22.0 / 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0.  With several
 // column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
+// A batch at k = 4 in a launch for eight column groups: four of them, in the first half of the workgroups (see pick_groups).
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_lone(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
   if constexpr (NB == 1 && G == 1) {
@@ -1067,6 +1068,8 @@ __device__ __forceinline__ void gemv_lone(const GemvJob& job, uint32_t lut_at, i
     gemv_lane<K, 2>(job, lut_at, block, tid, lds);
   } else if constexpr (G == 1) {
     gemv_lane<K, NB>(job, lut_at, block, tid, lds);
+  } else if constexpr (NB == 4 && G == 8 && K == 4) {
+    if (block * 16 < job.out) gemv_narrow<K, NB, 4>(job, lut_at, block, tid, lds);
   } else {
     gemv_narrow<K, NB, G>(job, lut_at, block, tid, lds);
   }

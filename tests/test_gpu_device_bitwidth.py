@@ -33,3 +33,9 @@ def check(out, in_, batches, p=8, kmin=2):
 @pytest.mark.parametrize("out,in_", [(8256, 4096), (9000, 544), (8200, 4096 + 32), (16390, 96), (4127, 288), (2049, 1056), (300, 8192 + 32)])
 def test_one_right_hand_side(out, in_):
     check(out, in_, (1,))
+
+
+# few rows of 64 column tiles and more, where four bits take four column groups and the other bitwidths eight: one pass and two
+@pytest.mark.parametrize("out,in_", [(1, 8192), (500, 8192 + 32), (1100, 11008), (300, 32 * 513)])
+def test_batch_on_few_rows(out, in_):
+    check(out, in_, (2, 3, 4, 7))

@@ -61,7 +61,7 @@ def test_gemv_several_steps(dp, out, in_):
     model.close()
 
 
-# few rows of 64 column tiles and more: a batch at k = 4 takes four column groups where the call names the bitwidth, eight where the device does
+# few rows of 64 column tiles and more: a batch at k = 4 takes four column groups, in a launch for four or, where the device says k, for eight
 @pytest.mark.parametrize("out,in_,B", [(1, 8192, 2), (500, 8192 + 32, 4), (1100, 11008, 3), (300, 32 * 513, 7)])
 def test_four_bit_batch_on_few_rows(dp, out, in_, B):
     lin = synth.make_linear(out, in_, 5, 3, seed=out + in_, device="cuda", keep_codes=False)
