@@ -437,12 +437,13 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 // 25.0; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.1 / 6.2.  Fewer: 1000 x 4096 k = 5 6.2 / 7.1, 1500 x 14336 k = 3 8.6 / 11.1.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   const int blocks = lin.L.nrq;
-  const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= 4 * kLaneWaves;
+  const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= kLaneWideTiles;
   const bool one_pass = blocks > 128 || (blocks > 64 && (deep || wide)) || (blocks > 32 && deep && wide);
   const int nb = B == 1 ? 1 : B <= 4 || !one_pass ? 4 : 8;
   const int passes = (B + nb - 1) / nb;
   const int groups = nb == 8 ? (blocks > 128 ? 1 : blocks > 64 ? 2 : 4) : pick_groups((long)blocks * passes, lin.L.ncc, B > 1 && !k_dev && k == 4 ? 4 : 8);
   int nblocks = (lin.L.out + 64 / groups - 1) / (64 / groups);
+  if (nb == 8 && k_dev) nblocks = (lin.L.out + 128 / groups - 1) / (128 / groups) * 2;   // (whole halves: gemv_two_passes)
   if (groups == 1) {
     const int rpb = pick_blocks_per_group(lin.L, k_dev ? lin.L.p : k, lin.L.nrq);
     nblocks = (lin.L.nrq + rpb - 1) / rpb;

@@ -1058,6 +1058,26 @@ __device__ __forceinline__ double* lane_sel_shared(char* lds) { return reinterpr
 // 16.0, k = 4 22.0 / 18.3, k = 5 30.5 / 28.6, k = 8 37.2 / 35.5; 16384 x 8192 k = 3 11.7 / 10.2, k = 6 20.9 / 19.6; 28672 x 8192 k = 6 34.8 / 34.0.  With several
 // column groups it costs a per cent more than it saves; in a step, whose wavefronts are four to a SIMD, 2 % more (7B, 3 and 4 bits).
 // A batch at k = 4 in a launch for eight column groups: four of them, in the first half of the workgroups (see pick_groups).
+// Five to eight samples in a launch for one pass with four or two column groups: up to k = 4 two passes of four, each in half of the workgroups,
+// which take half of the groups (see launch_gemv; with two groups on rows of many tiles one pass all the same).
+constexpr int kLaneWideTiles = 4 * kLaneWaves;
+template <int NB, int G>
+__host__ __device__ constexpr int lane_lone_lds_bytes() {
+  return NB == 8 && G > 1 && lane_lds_bytes<4, G / 2>() > lane_lds_bytes<NB, G>() ? lane_lds_bytes<4, G / 2>() : lane_lds_bytes<NB, G>();
+}
+template <int K, int G>
+__device__ __forceinline__ void gemv_two_passes(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
+  GemvJob half = job;
+  half.nblocks = (job.out + 64 / G - 1) / (64 / G);
+  const int pass = block >= half.nblocks;
+  half.x += (size_t)pass * 4 * job.ncw * 32;
+  half.y += (size_t)pass * 4 * job.out;
+  half.nsamples = pass ? job.nsamples - 4 : 4;
+  block -= pass * half.nblocks;
+  if (block >= half.nblocks) return;
+  if constexpr (G == 1) gemv_lane<K, 4>(half, lut_at, block, tid, lds);
+  else gemv_narrow<K, 4, G>(half, lut_at, block, tid, lds);
+}
 template <int K, int NB, int G>
 __device__ __forceinline__ void gemv_lone(const GemvJob& job, uint32_t lut_at, int block, int tid, char* lds) {
   if constexpr (NB == 1 && G == 1) {
@@ -1070,8 +1090,13 @@ __device__ __forceinline__ void gemv_lone(const GemvJob& job, uint32_t lut_at, i
     gemv_lane<K, NB>(job, lut_at, block, tid, lds);
   } else if constexpr (NB == 4 && G == 8 && K == 4) {
     if (block * 16 < job.out) gemv_narrow<K, NB, 4>(job, lut_at, block, tid, lds);
+  } else if constexpr (NB == 8 && G == 4 && K <= 4) {
+    gemv_two_passes<K, 2>(job, lut_at, block, tid, lds);
   } else {
-    gemv_narrow<K, NB, G>(job, lut_at, block, tid, lds);
+    if constexpr (NB == 8 && G == 2 && K <= 4) {
+      if (job.ncc < kLaneWideTiles) return gemv_two_passes<K, 1>(job, lut_at, block, tid, lds);
+    }
+    if (block * (64 / G) < job.out) gemv_narrow<K, NB, G>(job, lut_at, block, tid, lds);
   }
 }
 
@@ -1134,7 +1159,7 @@ template <int NB, int G>
 __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel(const char* arena, const uint16_t* x, uint16_t* y, const int32_t* k_dev,
                                                                                 uint32_t plane_stride_u4, uint32_t lut, uint32_t bits, int out,
                                                                                 int ncw, int nblocks) {
-  __shared__ __attribute__((aligned(256))) char lds[lane_lds_bytes<NB, G>()];
+  __shared__ __attribute__((aligned(256))) char lds[lane_lone_lds_bytes<NB, G>()];
   // the lookup addresses are formed as (entry << 8) | (lane << 2): the tables must start at LDS address 0
   if ((uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)lds != 0u) return;
   const LaneBits b = LaneBits::unpack(bits);
@@ -1151,7 +1176,6 @@ __global__ void __launch_bounds__(kLaneThreads, G == 1 ? 4 : 2) gemv_lane_kernel
   job.nblocks = nblocks;
   job.nsamples = min(NB, b.nrhs - group * NB);
   const int block = blockIdx.x - group * nblocks;
-  if (block * (64 / G) >= out) return;
   int k = b.k;
   if (k_dev != nullptr) {
     k = load_record(k_dev);

@@ -39,3 +39,11 @@ def test_one_right_hand_side(out, in_):
 @pytest.mark.parametrize("out,in_", [(1, 8192), (500, 8192 + 32), (1100, 11008), (300, 32 * 513)])
 def test_batch_on_few_rows(out, in_):
     check(out, in_, (2, 3, 4, 7))
+
+
+# five to eight samples, one pass or two by the bitwidth: 33 and 64 row blocks (an odd number of blocks of 16 rows, the fewest column tiles), 65
+# and 128 on few column tiles and on many; a linear of four bits, whose launch is the one for two passes
+@pytest.mark.parametrize("out,in_,p", [(2049, 4096, 8), (4096, 4096 - 32, 8), (2600, 9216 + 32, 6), (4097, 1056, 8), (8192, 1024, 5), (6000, 32, 8),
+                                      (4097, 4096 - 32, 8), (8192, 4096 + 160, 6), (2049, 4096, 4), (6000, 1056, 4), (4096, 2048, 8), (8256, 544, 8)])
+def test_five_to_eight_samples(out, in_, p):
+    check(out, in_, (5, 8), p)
