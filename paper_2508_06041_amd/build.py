@@ -1,6 +1,8 @@
 """Compile the HIP library for gfx950 into paper_2508_06041_amd/libdpllm.so and the binding's native part into _calls.so (in-tree)."""
 import os
+import re
 import subprocess
+import sys
 import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -14,14 +16,29 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared", "-Wal
          "-mllvm", "-amdgpu-kernarg-preload-count=14"]
 
 
+def spilled(report: str) -> list:
+    """The kernels that keep vector registers in scratch memory, from what the compiler says about the resources of each: their code is
+    written for the registers there are, and one that does not fit makes every launch of it slower without any other sign."""
+    kernels = []
+    for part in report.split("Function Name: ")[1:]:
+        used = {k: int(v) for k, v in re.findall(r"(ScratchSize|VGPRs Spill)[^:\n]*: (\d+)", part)}
+        if any(used.values()):
+            kernels.append(part.split()[0])
+    return kernels
+
+
 def build(verbose: bool = False, extra=()) -> str:
     cmd = ["/opt/rocm/bin/hipcc", *FLAGS, *extra, "-o", LIB] + [os.path.join(CSRC, s) for s in SOURCES]
     calls = ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-Wextra", "-I" + sysconfig.get_paths()["include"], "-o", CALLS,
              os.path.join(CSRC, "py_calls.cpp")]
-    for c in (calls, cmd):
+    for c in (calls, cmd + ["-Rpass-analysis=kernel-resource-usage", "-fno-caret-diagnostics"]):
         if verbose:
             print(" ".join(c))
-        subprocess.run(c, check=True)
+        done = subprocess.run(c, stderr=subprocess.PIPE, text=True)
+        sys.stderr.write("".join(line for line in done.stderr.splitlines(True) if "[-Rpass-analysis" not in line and not line.startswith("In file included")))
+        done.check_returncode()
+    if spilled(done.stderr):
+        raise RuntimeError("vector registers spilled: " + ", ".join(spilled(done.stderr)))
     return LIB
 
 

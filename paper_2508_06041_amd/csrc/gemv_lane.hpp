@@ -406,10 +406,12 @@ using LaneMasks = MergeMasks<(K < 3 ? 3 : K)>;
 // The merge tree with its masks in vector registers (full-rate instructions).  Two workgroups per compute unit (ROOM: one) leave k = 7, 8
 // no registers to spare for fifteen masks; they keep them in the instructions there.  us per call with one workgroup, masks in the
 // instructions -> in registers: 2500 x 6688 k = 7 9.3 -> 8.7, 4096 x 4096 k = 7 7.2 -> 6.9, 4096 x 11008 k = 7 13.6 -> 12.6, k = 8 14.1 ->
-// 13.8, 8192 x 8192 k = 7 16.4 -> 15.7.
-template <int K, bool ROOM>
+// 13.8, 8192 x 8192 k = 7 16.4 -> 15.7.  Nor do they leave any at k = 6 with eight samples, whose operands take sixteen more: with masks in
+// registers that code spilled three, and every launch of its kernel came with scratch memory (us per call of eight, then -> now: 9000 x 11008
+// k = 6 31.2 -> 29.3, 14336 x 4096 k = 6 16.0 -> 15.2, k = 3 9.7 -> 9.5).
+template <int K, int NB, bool ROOM>
 __device__ __forceinline__ void lane_merge_fields(const uint32_t (&w)[K], uint32_t (&R)[8], const LaneMasks<K>& M) {
-  if constexpr (K <= 6 || ROOM) merge_byte_fields_v<K, LaneDecode<K>::d>(w, R, M);
+  if constexpr (K <= (NB == 8 ? 5 : 6) || ROOM) merge_byte_fields_v<K, LaneDecode<K>::d>(w, R, M);
   else merge_byte_fields<K, LaneDecode<K>::d>(w, R);
 }
 
@@ -618,7 +620,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
       uint32_t w[K];
 #pragma unroll
       for (int b = 0; b < K; ++b) w[b] = mine[b][0];
-      lane_merge_fields<K, ROOM>(w, R[0], M);
+      lane_merge_fields<K, NB, ROOM>(w, R[0], M);
     }
     lane_issue_singles<K, 0>(R[0], lanecol, lds, va);
     auto word = [&](auto jc) {
@@ -627,7 +629,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         uint32_t w[K];
 #pragma unroll
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
-        lane_merge_fields<K, ROOM>(w, R[(j + 1) & 1], M);
+        lane_merge_fields<K, NB, ROOM>(w, R[(j + 1) & 1], M);
       }
       if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
