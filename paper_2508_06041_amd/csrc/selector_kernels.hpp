@@ -600,39 +600,35 @@ constexpr int kEstRing = 16;
 constexpr int kEstRows = 1;             // rows of G of a wavefront
 constexpr int kEstPartRows = kSelPartWaves * kEstRows;
 constexpr int kEstMaxRank = kSelPartThreads;
-constexpr int kEstChunks = 12;          // column chunks of an estimate, at most
+constexpr int kEstChunks = 12;          // column chunks of an estimate, at most: as many as are collected at a time
 constexpr int kEstPolls = 1 << 20;      // of about a microsecond
 constexpr uint32_t kEstAll = ~0u;       // a mark: several captured calls have given up
 
-// Row t of the products, the sum of its chunks in order; BATCH chunks are asked for at a time.  A chunk's slots are the lower halves
+// Row t of the products, the sum of its chunks (at most CHUNKS, all asked for at once) in order.  A chunk's slots are the lower halves
 // of its rows, then the upper ones.  false: given up, or the slots are not relied on.
-template <int BATCH>
+template <int CHUNKS>
 __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, uint32_t tag, int nchunks, int ws_rows, int t, bool marked, int polls, double& g) {
+  uint64_t lo[CHUNKS], hi[CHUNKS];
+  auto slot = [&](int i) { return slots + (uint32_t)(min(i, nchunks - 1) * ws_rows * 2) + t; };   // (those past the last: it again)
+  for (;;) {
+    bool all = true;
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) {
+      lo[i] = __hip_atomic_load(slot(i), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      hi[i] = __hip_atomic_load(slot(i) + ws_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+#pragma unroll
+    for (int i = 0; i < CHUNKS; ++i) all = all && (uint32_t)(lo[i] >> 32) == tag && (uint32_t)(hi[i] >> 32) == tag;
+    if (__all(all)) break;
+    if (marked || --polls < 0) return false;
+    __builtin_amdgcn_s_sleep(1);
+  }
   g = 0.0;
-  for (int c0 = 0; c0 < nchunks; c0 += BATCH) {
-    uint64_t lo[BATCH], hi[BATCH];
-    for (;;) {
-      bool all = true;
 #pragma unroll
-      for (int i = 0; i < BATCH; ++i) {
-        DPLLM_SEL_GLOBAL uint64_t* slot = slots + (uint32_t)(min(c0 + i, nchunks - 1) * ws_rows * 2) + t;
-        lo[i] = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        hi[i] = __hip_atomic_load(slot + ws_rows, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-#pragma unroll
-      for (int i = 0; i < BATCH; ++i) all = all && (uint32_t)(lo[i] >> 32) == tag && (uint32_t)(hi[i] >> 32) == tag;
-      if (__all(all)) break;
-      if (marked || --polls < 0) return false;
-      __builtin_amdgcn_s_sleep(1);
-    }
-#pragma unroll
-    for (int i = 0; i < BATCH; ++i) {
-      if (c0 + i >= nchunks) break;
-      g += __builtin_bit_cast(double, hi[i] << 32 | (uint32_t)lo[i]);
-      DPLLM_SEL_GLOBAL uint64_t* slot = slots + (uint32_t)((c0 + i) * ws_rows * 2) + t;
-      __hip_atomic_store(slot, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(slot + ws_rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+  for (int i = 0; i < CHUNKS; ++i) {
+    g += i < nchunks ? __builtin_bit_cast(double, hi[i] << 32 | (uint32_t)lo[i]) : 0.0;
+    __hip_atomic_store(slot(i), 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(slot(i) + ws_rows, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
   return !marked;
 }

@@ -31,8 +31,9 @@ def _G(r, in_, seed):
 
 
 # ranks around the four rows of a workgroup, the 64 lanes and the 256 threads that collect; columns below one chunk of 512, with a
-# ragged last chunk, of 8 chunks (one batch), 9 and 33 (two batches; chunks of 1024)
-@pytest.mark.parametrize("in_,r", [(32, 1), (544, 3), (512, 4), (1056, 5), (4096, 64), (4128, 65), (11008, 64), (16416, 40), (2080, 257), (4096, 1024)])
+# ragged last chunk; 8 chunks of 512 and 9 (the two ways to collect them), 12, the most there are, 7 of 1024 one column word further, 12 of 2560
+@pytest.mark.parametrize("in_,r", [(32, 1), (544, 3), (512, 4), (1056, 5), (4096, 64), (4128, 65), (6144, 70), (6176, 9), (11008, 64), (16416, 40), (28672, 33),
+                                   (2080, 257), (4096, 1024)])
 def test_estimate_matches_oracle_over_the_ring(dp, in_, r):
     """More calls than there are sets of slots, two inputs in turn: a slot that was not emptied would show."""
     model, G = _model(dp, in_, seed=in_ + r), _G(r, in_, in_ + r)
@@ -115,8 +116,8 @@ def test_first_estimate_while_another_stream_is_captured(dp):
     model.close()
 
 
-# more than 32 chunks of 512 columns: a chunk is two tiles of a wavefront, and rows start their walk at different ones
-@pytest.mark.parametrize("in_,r", [(16416, 17), (28672, 64), (28672, 200), (30720, 33)])
+# 12 chunks of one tile of a wavefront, 7 of two, 11 of three, 12 of five: rows start their walk over the tiles of a chunk at different ones
+@pytest.mark.parametrize("in_,r", [(6144, 18), (6176, 21), (16416, 17), (28672, 64), (28672, 200), (30720, 33)])
 def test_one_launch_and_two_leave_the_same_bits(dp, in_, r):
     """Products of 2^32 that cancel between small ones: a lane that adds its columns in another order ends at another sum, by all of it."""
     model = _model(dp, in_, seed=r)
@@ -185,7 +186,7 @@ def test_what_a_set_of_slots_holds_is_not_taken_for_a_product(dp):
     x, e, k = x.cuda(), torch.zeros(1, device="cuda"), torch.zeros(1, dtype=torch.int32, device="cuda")
     model.dpllm_set_workspace()
     first = 8 * 32 * 1024                                    # behind the products of an estimate in two launches
-    slots = 16 * 2 * 32 * ((in_ + 511) // 512)               # sets, words, rows of the pair in whole parts, chunks
+    slots = 16 * (16 + 2 * 32 * ((in_ + 511) // 512))        # sets: words in front, words, rows of the pair in whole parts, chunks
     model.workspace[first:first + 8 * slots].view(torch.float64).fill_(1.0)
     for rep in range(36):
         e.fill_(-1.0), k.zero_()
