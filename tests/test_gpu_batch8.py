@@ -9,7 +9,7 @@ import synth
 pytestmark = pytest.mark.gpu
 
 
-# two passes of four or one pass; fewer column tiles than wavefronts; several row blocks per workgroup (65604 rows);
+# two passes of four or one pass; fewer column tiles than wavefronts; more than a thousand row blocks (65604 rows);
 # rows and tiles that no block or group divides
 @pytest.mark.parametrize("out,in_", [(1, 32), (130, 4096 + 160), (1000, 1056), (4127, 288), (8200, 544), (16390, 96), (65604, 1184)])
 def test_gemv_five_to_eight_samples(out, in_):
@@ -51,8 +51,8 @@ def test_eight_samples_add_as_four_do():
     model.close()
 
 
-# one pass with four column groups: 33 and 64 row blocks, the fewest column tiles that take it, a last step of one tile and
-# a ragged last word
+# 33 and 64 row blocks, where 5 bits and more take one pass with four column groups and fewer bits two passes with two: the fewest column tiles
+# that take it, a last step of one tile and a ragged last word
 @pytest.mark.parametrize("out,in_", [(2049, 4096), (4096, 4096 - 32), (2600, 9216 + 32)])
 def test_gemv_five_to_eight_samples_of_a_narrow_launch(out, in_):
     import paper_2508_06041_amd as dp
@@ -69,7 +69,7 @@ def test_gemv_five_to_eight_samples_of_a_narrow_launch(out, in_):
         wmax = np.abs(lut.view(np.float16).astype(np.float64)).max(axis=1)
         bound = 2.0 ** -10 * np.abs(ref) + 2.0 * np.sqrt(in_) * 2.0 ** -24 * wmax * xmax + 2.0 ** -24
         for B in (5, 8):
-            for dev in (False, True):        # the bitwidth on the device: every one of them runs in this launch
+            for dev in (False, True):        # the bitwidth on the device: the launch is the one for one pass, whichever it is
                 y = torch.full((B + 1, out), 7.0, dtype=torch.float16, device="cuda")     # one row more than may be written
                 k_dev.fill_(k)
                 model.dpllm_gemv(0, -1 if dev else k, X[:B].cuda(), y=y[:B], k_dev=k_dev)
@@ -78,7 +78,7 @@ def test_gemv_five_to_eight_samples_of_a_narrow_launch(out, in_):
     model.close()
 
 
-# one pass with two column groups: 65, 94 and 128 row blocks, few columns (5 bits and more only) and many, an odd last step of one tile
+# 65, 94 and 128 row blocks, one pass with two column groups: few columns (5 bits and more only) and many, an odd last step of one tile
 @pytest.mark.parametrize("out,in_", [(65 * 64 - 63, 4096 - 32), (6000, 1056), (8192, 4096 + 160)])
 def test_gemv_five_to_eight_samples_with_two_column_groups(out, in_):
     import paper_2508_06041_amd as dp

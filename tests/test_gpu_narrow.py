@@ -139,7 +139,7 @@ def test_decode_step_with_a_two_bit_child(dp):
     model.close()
 
 
-# eight column groups for a batch: the most row blocks and the fewest column tiles that take them, one row, a last step of
+# eight column groups for a batch (4 bits: four): the most row blocks and the fewest column tiles that take them, one row, a last step of
 # one tile whose last words lie past the row
 @pytest.mark.parametrize("out,in_", [(2048, 8192), (1, 28672), (1017, 8192 + 32), (500, 9216 + 96)])
 def test_gemv_batch_of_few_rows_on_long_columns(dp, out, in_):
