@@ -275,7 +275,6 @@ SelParams make_params(const Pair& s, float T) {
 }
 
 // cols: columns of a chunk (a multiple of 512), more where the columns would be cut into more than `most` of them
-constexpr int kSelParts = 1152;   // parts of a lone estimate with many rows, about
 SelJob make_sel_job(const Linear& lin, int linear, int rowgroups, const void* x, float* e_dev, int32_t* k_dev, int cols, int most = kSelMaxChunks) {
   SelJob j;
   j.x = (const uint16_t*)x;
@@ -1171,6 +1170,8 @@ int dpllm_set_selector_input(dpllm_model* m, int id, const void* xsel_dev) {
   m->version++;
   return DPLLM_OK;
 }
+
+constexpr int kSelParts = 1152;   // parts of a lone estimate with many rows, about
 
 // The job of a lone estimate.  Up to the ranks that one launch serves, the columns are cut into no more chunks than its last workgroup
 // collects at a time; the ways an estimate may take share the cut, and with it the bits.  us of a dpllm_estimate in a graph, up to 32 chunks /

@@ -12,11 +12,12 @@
 // The activations are the same for all lanes.
 // One right-hand side (the decode step): with every tile a lane fetches one dword of them (256 bytes per
 // wavefront); before the tile is decoded the wavefront parks them in a private LDS slot.  A wavefront with at
-// most four tiles per row block (rows up to 4096 columns) parks them once for its whole run instead.  Every lane reads back 16 bytes per word (lane l takes the pairs
-// 4 (l mod 4) .. + 3) and the multiply-add v_dot2c_f32_f16 reads the pair it needs from the right lane of its quad
-// with a DPP quad broadcast: 16 registers hold the 64 pairs of a tile, fp32 accumulation in the lane.
-// Several right-hand sides (a small dense contraction: 64 rows x up to 4 samples per wavefront) run on the matrix
-// pipe instead: v_mfma_f32_4x4x4_16b_f16 works on 16 blocks of four lanes; with the A operand of one block
+// most four tiles per row block (rows up to 4096 columns) parks them once for its whole run instead.
+// Every lane reads back 16 bytes per word (lane l takes the pairs 4 (l mod 4) .. + 3) and the multiply-add
+// v_dot2c_f32_f16 reads the pair it needs from the right lane of its quad with a DPP quad broadcast: 16 registers
+// hold the 64 pairs of a tile, fp32 accumulation in the lane.
+// Several right-hand sides (a small dense contraction: 64 rows x up to 4 samples per wavefront), and one in some launches
+// of its own (gemv_lone), run on the matrix pipe instead: v_mfma_f32_4x4x4_16b_f16 works on 16 blocks of four lanes; with the A operand of one block
 // broadcast to all blocks (cbsz = 4, abid = Q) lane L gets
 //     acc[i] += sum_n A(lane 4 Q + i)[n] * B(lane L)[n],  n = 0 .. 3,  i = 0 .. 3.
 // (Five to eight right-hand sides: two matrix instructions per looked-up chunk, each with its four samples.)
@@ -36,9 +37,10 @@
 //   k >= 5   : one weight per lookup (table of 2^k entries per row, 8 .. 64 KiB), two results packed into one
 //              register of the B operand
 // One kernel serves every bitwidth from 1 to 8: a workgroup reads the bitwidth of its job (a value, or the word a
-// selector wrote in device memory) and branches to the code of that bitwidth.  Every branch of the kernel for large
-// launches (G = 1) stays below 128 vector registers and the workgroup's LDS is sized for the largest tables (64 KiB), so
-// two workgroups share a compute unit whatever the bitwidth; which bitwidth runs is never a matter for the host.
+// selector wrote in device memory) and branches to the code of that bitwidth.  Every branch of the kernels for large
+// launches (G = 1) stays within 128 vector registers and the workgroup's LDS is sized for the largest tables (64 KiB), so
+// two workgroups share a compute unit whatever the bitwidth.  The host looks at a bitwidth that a call names to choose the
+// launch; what a workgroup then runs, and with it the order of the additions, is the same if the device says it.
 // Small launches give a workgroup 64 / G rows, G = 2, 4, 8 (gemv_narrow).
 #pragma once
 #include <hip/hip_runtime.h>
@@ -105,7 +107,7 @@ __host__ __device__ constexpr int lane_lds_bytes() {
 static_assert(8 * kLaneRedBytes <= LaneDecode<3>::table_bytes, "room for the sums of eight samples");
 static_assert(lane_lds_bytes<8, 1>() <= 81920 && lane_lds_bytes<4, 1>() <= 81920 && lane_lds_bytes<1, 1>() <= 81920, "two workgroups per compute unit");
 static_assert(lane_lds_bytes<1, 8>() <= 163840 && lane_lds_bytes<4, 8>() <= 163840 && lane_lds_bytes<8, 4>() <= 163840,
-              "one workgroup per compute unit (the registers of several column groups allow no second one)");
+              "one workgroup per compute unit (such a launch has no more of them)");
 
 // x pair held by lane Q of the quad, times the looked-up pair, added to acc
 template <int Q>
@@ -502,8 +504,6 @@ struct LaneX {   // several samples: operands of the matrix instructions
       }
     }
   }
-  __device__ __forceinline__ void load() {}
-  __device__ __forceinline__ void load_word(int) {}
 };
 template <int K, int G>
 struct LaneX<K, 1, G> {
@@ -568,8 +568,9 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     }
   };
   uint32_t va[8], vb[8];
-  if constexpr (LAZY) x.load_word(0);
-  else x.load();
+  constexpr bool read_back = LAZY && NB == 1;
+  if constexpr (NB == 1 && !LAZY) x.load();
+  if constexpr (read_back) x.load_word(0);
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
   using J2 = std::integral_constant<int, 2>;
@@ -592,7 +593,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     lane_issue_pairs<0, K <= 3>(T[0], lanecol, lds, va, addr, mask);
     auto word = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
+      if constexpr (read_back && j + 1 < 4) x.load_word(j + 1);
       lane_issue_pairs<2, K <= 3>(T[j], lanecol, lds, vb, addr, mask);
       sched_fence();
       clear(va, j);
@@ -631,7 +632,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
         lane_merge_fields<K, NB, ROOM>(w, R[(j + 1) & 1], M);
       }
-      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
+      if constexpr (read_back && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
       sched_fence();
       lane_mac_singles<0, j>(va, x, acc);
