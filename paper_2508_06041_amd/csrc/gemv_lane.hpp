@@ -504,6 +504,8 @@ struct LaneX {   // several samples: operands of the matrix instructions
       }
     }
   }
+  __device__ __forceinline__ void load() {}   // (nothing is read back)
+  __device__ __forceinline__ void load_word(int) {}
 };
 template <int K, int G>
 struct LaneX<K, 1, G> {
@@ -568,9 +570,8 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     }
   };
   uint32_t va[8], vb[8];
-  constexpr bool read_back = LAZY && NB == 1;
-  if constexpr (NB == 1 && !LAZY) x.load();
-  if constexpr (read_back) x.load_word(0);
+  if constexpr (LAZY) x.load_word(0);
+  else x.load();
   using J0 = std::integral_constant<int, 0>;
   using J1 = std::integral_constant<int, 1>;
   using J2 = std::integral_constant<int, 2>;
@@ -593,7 +594,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
     lane_issue_pairs<0, K <= 3>(T[0], lanecol, lds, va, addr, mask);
     auto word = [&](auto jc) {
       constexpr int j = decltype(jc)::value;
-      if constexpr (read_back && j + 1 < 4) x.load_word(j + 1);
+      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_pairs<2, K <= 3>(T[j], lanecol, lds, vb, addr, mask);
       sched_fence();
       clear(va, j);
@@ -632,7 +633,7 @@ __device__ __forceinline__ void lane_compute(u32x4 (&tw)[H], uint32_t lanecol, c
         for (int b = 0; b < K; ++b) w[b] = mine[b][j + 1];
         lane_merge_fields<K, NB, ROOM>(w, R[(j + 1) & 1], M);
       }
-      if constexpr (read_back && j + 1 < 4) x.load_word(j + 1);
+      if constexpr (LAZY && j + 1 < 4) x.load_word(j + 1);
       lane_issue_singles<K, 1>(R[j & 1], lanecol, lds, vb);
       sched_fence();
       lane_mac_singles<0, j>(va, x, acc);
