@@ -167,7 +167,8 @@ int dpllm_estimate_noalloc(dpllm_model* m, int id, int l, int h, const void* x_d
 /* "Run the GEMV at bitwidth k": y[b][o] = sum_c LUT_k[o][code_k(o,c)] * x[b][c], fp32
  * accumulation, fp16 result.  k >= 0: that bitwidth.  k < 0: the bitwidth is read on the
  * device from k_dev[0] (the hand-over from dpllm_estimate without a host round trip); a
- * value there that the linear does not serve (outside [kmin, p]) leaves y_dev untouched.
+ * value there that the linear does not serve (outside [kmin, p]) leaves y_dev untouched.  Either way, and whichever pairs
+ * are attached, the same linear, B and bitwidth give the same bits.
  * x_dev: device fp16 [B][in]; y_dev: device fp16 [B][out], not overlapping x_dev;
  * 1 <= B <= DPLLM_MAX_BATCH; one bitwidth serves the whole batch.
  * Errors: EINVAL, ESHAPE, ERANGE, ESTATE, EHIP. */

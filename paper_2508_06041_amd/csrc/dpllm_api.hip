@@ -351,16 +351,23 @@ int pick_blocks_per_group(const LinearLayout& L, int k, long total_blocks, long 
 
 // Column groups per wavefront (rows per workgroup = 64 / groups) of a launch whose linears have `blocks64` blocks of 64
 // rows in all (times the passes of a batch), the shortest row ncc column tiles: the most that leave at most one
-// workgroup per compute unit.  Measured, us per launch in a graph, one linear at k = 4 with 1 / 2 / 4 / 8 groups: 4096 x
-// 4096 8.5 / 5.8 / 5.1 / 7.7, 4096 x 11008 17.8 / 10.2 / 8.3 / 10.8, 8192 x 8192 13.8 / 9.0 / 8.9 / 16.1, 11008 x 4096
-// 7.7 / 8.0 / 8.6 / 18.9, 192 x 28672 - / 18.3 / 10.6 / 8.2.  Eight groups only where every wavefront gets a step
-// (1024 x 4096: 4.4 us with four, 4.3 with eight; a batch of four 5.2, 5.6).  A batch of four, four / eight groups: 640 x
-// 14336 k = 3 7.9 / 7.5, 192 x 14336 k = 6 12.2 / 9.9, 419 x 28672 k = 8 20.1 / 17.3 (workgroups that split the columns of
+// workgroup per compute unit.  The bitwidth is not looked at: it moves no line by much.  us per launch in a graph, one linear, k = 3 / 4 / 6 / 8,
+// with one, two, four and eight groups:
+//   4096 x 4096     6.2 / 7.2 / 11.2 / 12.8,   4.9 / 5.6 / 7.6 / 8.8,     4.6 / 4.9 / 6.3 / 7.4,     6.9 / 7.5 / 9.3 / 11.0
+//   4096 x 11008    12.6 / 14.5 / 24.3 / 26.9, 9.2 / 10.5 / 15.2 / 16.5,  7.5 / 8.6 / 11.7 / 13.3,   9.7 / 11.2 / 14.4 / 16.9
+//   8192 x 8192     11.1 / 12.4 / 19.6 / 22.2, 9.0 / 10.1 / 14.4 / 16.5,  9.4 / 10.3 / 14.6 / 16.6,  14.9 / 17.1 / 22.0 / 26.7
+//   11008 x 4096    7.2 / 8.3 / 12.3 / 14.4,   7.5 / 8.6 / 12.8 / 15.1,   8.3 / 9.1 / 12.1 / 14.6,   17.5 / 19.2 / 23.7 / 28.8
+//   16384 x 4096    8.5 / 10.0 / 14.2 / 17.4,  9.2 / 10.2 / 14.7 / 17.3,  10.6 / 11.9 / 15.9 / 19.5, 23.5 / 25.7 / 31.5 / 38.5
+//   1024 x 8192     9.3 / 10.9 / 18.0 / 20.2,  6.6 / 7.6 / 10.9 / 12.1,   5.1 / 5.4 / 7.3 / 8.4,     4.2 / 4.7 / 5.7 / 6.8
+// (129 to 172 blocks at k = 5, 6, 7 would gain 2 to 4 per cent with four.)  Eight groups only where every wavefront gets a step
+// (1024 x 4096: 4.4 us with four, 4.3 with eight; a batch of four 5.2, 5.6).  A batch of four, one / two / four / eight groups: 8192 x 8192 k = 3 11.3 /
+// 9.3 / 11.8 / 20.4, k = 6 20.0 / 15.0 / 18.2 / 27.3; 14336 x 4096 k = 3 8.2 / 10.6 / 14.8 / 25.8, k = 6 13.6 / 16.8 / 22.0 / 35.0; 4096 x 4096 k = 6 11.3 / 8.1 /
+// 6.9 / 11.1; four / eight: 640 x 14336 k = 3 7.9 / 7.5, 192 x 14336 k = 6 12.2 / 9.9, 419 x 28672 k = 8 20.1 / 17.3 (workgroups that split the columns of
 // 64 rows, with a hand-over through memory that calls would share, take 11.4 and 18.0 us for the last two: every
-// workgroup reads all activations here).  A batch at k = 4 takes four at most (`most`; gemv_lone where the device says k): what a lane holds of a sample comes from two places
-// there, and with 8 rows to a workgroup each wavefront fetches, sorts and exchanges that for eight tiles a step.  k = 4, B = 2, 4, four / eight:
-// 500 x 8192 6.3 / 6.3, 6.5 / 7.9; 1000 x 11008 7.4 / 7.7, 7.6 / 9.8; 2048 x 14336 8.6 / 8.6, 8.9 / 11.1; 1024 x 28672 11.9 / 12.1, 12.6 / 16.2; at
-// k = 2, 3 eight are 0 to 10 per cent ahead, at k >= 5 9 to 20.
+// workgroup reads all activations here).  A batch at k = 4 takes four at most (`most`; gemv_lone where the device says k): what a lane holds of a sample
+// comes from two places there, and with 8 rows to a workgroup each wavefront fetches, sorts and exchanges that for eight tiles a step.  k = 4, B = 2,
+// 4, four / eight: 500 x 8192 6.1 / 6.3, 6.3 / 7.9; 1000 x 11008 7.3 / 7.7, 7.5 / 9.8; 2048 x 14336 8.7 / 8.6, 9.0 / 11.1; 1024 x 28672 11.9 / 12.1, 12.6 /
+// 16.2; at k = 2, 3 eight are 0 to 10 per cent ahead, at k >= 5 9 to 20.
 int pick_groups(long blocks64, int ncc, int most = 8) {
   int g = 1;
   while (g < 4 && blocks64 * g * 2 <= 256) g *= 2;
@@ -434,6 +441,8 @@ void launch_chain(const dpllm_model* m, const Workspace& W, const StepPlan& P, h
 // k = 5 7.8 / 6.5, k = 8 9.9 / 7.9; 8192 x 1024 k = 3 4.3 / 5.0, k = 5 5.7 / 6.0, k = 8 7.4 / 7.1.  33 to 64: 4096 x 14336 k = 3 10.9 / 11.5, k = 5 17.4 /
 // 16.0, k = 8 20.5 / 18.8; 4096 x 4096 k = 3 5.8 / 6.2, k = 4 6.2 / 7.6, k = 5 7.9 / 7.5; 4096 x 28672 k = 3 18.2 / 17.4, k = 4 19.4 / 23.3, k = 6 31.8 /
 // 25.0; 3000 x 2048 k = 3 4.9 / 5.4, k = 5 6.1 / 6.2.  Fewer: 1000 x 4096 k = 5 6.2 / 7.1, 1500 x 14336 k = 3 8.6 / 11.1.
+// Where the device says k the launch is the one for the widest bitwidth, and up to k = 4 its workgroups run the two passes (gemv_two_passes): B = 8,
+// named / device / one pass, 4096 x 14336 k = 3 10.6 / 11.1 / 11.5, 4096 x 4096 k = 4 6.0 / 6.2 / 7.6, 8192 x 2048 k = 3 5.2 / 5.2 / 5.7.
 int launch_gemv(dpllm_model* m, const Linear& lin, int k, const int32_t* k_dev, const void* x, void* y, int B, hipStream_t st) {
   const int blocks = lin.L.nrq;
   const bool deep = (k_dev ? lin.L.p : k) >= 5, wide = lin.L.ncc >= kLaneWideTiles;

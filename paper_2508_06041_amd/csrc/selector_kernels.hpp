@@ -595,7 +595,7 @@ __global__ void __launch_bounds__(kSelDecideThreads) selector_decide_kernel(cons
 // us of a dpllm_estimate in a graph, with a launch for the parts and one for the decision / one for both: rank 64 of 4096 columns 4.6 / 3.9, of 8192
 // 5.1 / 4.5, of 11008 5.7 / 4.7, rank 256 of 4096 5.4 / 4.8, of 11008 7.2 / 5.8, linear regression 3.7 / 2.0; rank 512 of 8192, where rows go four to a
 // wavefront, 8.7 / 9.1: beyond the lanes of the workgroup that collects there are two.  14 linears of 7B with a GEMV each: 190 -> 169 (161 with
-// products of one word, which what an overlap left behind could pass for).
+// products of one word, which what an overlap left behind could pass for), 157 now.
 constexpr int kEstRing = 16;
 constexpr int kEstRows = 1;             // rows of G of a wavefront
 constexpr int kEstPartRows = kSelPartWaves * kEstRows;
@@ -605,7 +605,8 @@ constexpr int kEstPolls = 1 << 20;      // of about a microsecond
 constexpr uint32_t kEstAll = ~0u;       // a mark: several captured calls have given up
 
 // Row t of the products, the sum of its chunks (at most CHUNKS, all asked for at once) in order.  A chunk's slots are the lower halves
-// of its rows, then the upper ones.  false: given up, or the slots are not relied on.
+// of its rows, then the upper ones.  false: given up, or the slots are not relied on.  What lies past the last chunk adds nothing and empties the
+// last one's slots again: a branch for each chunk costs more (rank 64 of 4096 columns 4.20 us with, 4.13 without, 11008 5.18 / 5.06, 28672 6.54 / 6.38).
 template <int CHUNKS>
 __device__ __forceinline__ bool selector_collect(DPLLM_SEL_GLOBAL uint64_t* slots, uint32_t tag, int nchunks, int ws_rows, int t, bool marked, int polls, double& g) {
   uint64_t lo[CHUNKS], hi[CHUNKS];
